@@ -149,14 +149,13 @@ int64_t decode_slots_bound(int64_t N, int64_t a, int64_t b)
 }
 
 struct MineCarve {
-    size_t assign, best, psum, pcnt, total;
+    size_t best, psum, pcnt, total;
 };
 MineCarve mine_carve(int64_t S, int64_t T, int P, int d)
 {
     MineCarve m;
     const int ts = mine_tsplit((int)T, (int)S, P);
-    m.assign = 0;
-    m.best = round_up(m.assign + (uint64_t)S * T * 4, 256);
+    m.best = 0;
     m.psum = round_up(m.best + (uint64_t)S * T * 4, 256);
     m.pcnt = round_up(m.psum + (uint64_t)S * ts * P * d * 4, 256);
     m.total = round_up(m.pcnt + (uint64_t)S * ts * P * 4, 256);
@@ -272,7 +271,6 @@ pk_status pk_mine_patterns(const pk_config *cfg, const void *x, int64_t set_stri
     a.init_given = init_given;
     a.d = hd;
     a.patterns = static_cast<__half *>(patterns);
-    a.assign_ws = reinterpret_cast<int32_t *>(ws + mc.assign);
     a.assign = assign;   // optional: written by the last step only
     a.best = reinterpret_cast<float *>(ws + mc.best);
     a.psum = reinterpret_cast<float *>(ws + mc.psum);

@@ -2,7 +2,7 @@
 // step; Sec. 3.2 Eq. 6 argmin in L2 mode).
 //
 // Ranking uses e = x.m - ||m||^2/2 - ||x||^2/2 = -||x - m||^2 / 2 from v_mfma_f32_16x16x32_f16: the
-// accumulator starts at -(||m||^2 + ||x||^2)/2 and the four K-steps add x.m (fp16 products are exact in
+// accumulator starts at -(||m||^2 + ||x||^2)/2 and the D/32 K-steps add x.m (fp16 products are exact in
 // fp32; only the accumulation rounds).  The best and second best value are tracked; a token whose gap
 // between the two is not safely above the rounding error of that form is re-evaluated exactly,
 // sum_c (x_c - m_c)^2 in binary32 over all patterns, lowest index on ties.  A token that is not
@@ -10,7 +10,7 @@
 // exact argmin.
 //
 // Operand layout (lane = 16*kb + n):  A = patterns, row n of the 16-pattern tile, K-step s covers
-// channels 32*s + 8*kb + j;  B = vectors, column n = token n of the 16-token tile, same channels;
+// channels 32*s + 8*kb + j, KS = D/32 steps (3, 4 or 8 at head dimension 96, 128 or 256);  B = vectors, column n = token n of the 16-token tile, same channels;
 // D: column n = token, rows 4*kb + i = patterns 16*tile + 4*kb + i.
 #pragma once
 
@@ -22,12 +22,16 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kTabStride = kD + 16;   // halves per pattern row in LDS: 288 B = 72 words, the row skew at which 16-byte reads of 16 rows x 4 column groups run at full rate
+// Halves per pattern row in LDS: D + 16, i.e. 8 words modulo 16 at D = 96, 128 and 256 (56, 72, 136 words), the row skew at
+// which 16-byte reads of 16 rows x 4 column groups run at full rate.
+template <int D>
+constexpr int kTabStrideOf = D + 16;
+constexpr int kTabStride = kTabStrideOf<kD>;
 
 __host__ __device__ constexpr int pad16(int p) { return (p + 15) & ~15; }
 
 struct PatternTable {
-    const __half *lds_rows;   // LDS copy, pad16(P) rows of stride kTabStride, rows past P are zero
+    const __half *lds_rows;   // LDS copy, pad16(P) rows of stride kTabStrideOf<D>, rows past P are zero
     const float *nh;          // LDS [pad16(P)]: -||m_p||^2 / 2, -inf past P
     float norm2_max;          // max_p ||m_p||^2
     int P;
@@ -38,27 +42,30 @@ __device__ __forceinline__ floatx4_t mfma_f16(const uint4 &a, const uint4 &b, fl
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
 }
 
-// Stage a pattern table into LDS (nthr threads, a multiple of 64 dividing pad16(P)*16... or not: the loop is
-// guarded) and compute the row norms; red_s gets one maximum per wave.  Ends with a barrier.
-// Work item i = (row i/16, 16-byte piece i%16): the 16 lanes of a row sum their squares.
+// Stage a pattern table into LDS (nthr threads, a multiple of 64; the loop is guarded) and compute the row norms; red_s
+// gets one maximum per wave.  Ends with a barrier.
+// Work item i = (row, 16-byte piece): the kLanes lanes of a row (16, or 32 at D = 256; lanes past the row's D / 8 pieces
+// idle at D = 96) sum their squares.
+template <int D = kD>
 __device__ __forceinline__ void stage_patterns(const __half *Mg, int P, __half *tab_s, float *nh_s, float *red_s,
                                                int nthr = 256)
 {
+    constexpr int kLanes = D <= 128 ? 16 : 32, kPieces = D / 8, kStride = kTabStrideOf<D>;
     const int tid = threadIdx.x;
     float mx = 0.f;
-    // pad16(P) * 16 is a multiple of 256, and every 16 consecutive work items sit in one wave: the row sums
+    // pad16(P) * kLanes is a multiple of 256, and every kLanes consecutive work items sit in one wave: the row sums
     // below see whole rows (a trailing half round of a 512-thread group has whole waves idle)
-    for (int i = tid; i < pad16(P) * kRowChunks; i += nthr) {
-        const int r = i >> 4, ch = i & 15;
+    for (int i = tid; i < pad16(P) * kLanes; i += nthr) {
+        const int r = i / kLanes, ch = i % kLanes;
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r < P) v = *reinterpret_cast<const uint4 *>(Mg + (int64_t)r * kD + ch * 8);
-        *reinterpret_cast<uint4 *>(tab_s + r * kTabStride + ch * 8) = v;   // rows past P are zero
+        if (r < P && (kPieces == kLanes || ch < kPieces)) v = *reinterpret_cast<const uint4 *>(Mg + (int64_t)r * D + ch * 8);
+        if (kPieces == kLanes || ch < kPieces) *reinterpret_cast<uint4 *>(tab_s + r * kStride + ch * 8) = v;   // rows past P are zero
         const half2_t *h = reinterpret_cast<const half2_t *>(&v);
         float acc = 0.f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1) acc += __shfl_xor(acc, off);
+        for (int off = 1; off < kLanes; off <<= 1) acc += __shfl_xor(acc, off);
         if (ch == 0) nh_s[r] = r < P ? -0.5f * acc : -INFINITY;   // rows past the table never win
         mx = fmaxf(mx, acc);
     }
@@ -69,16 +76,18 @@ __device__ __forceinline__ void stage_patterns(const __half *Mg, int P, __half *
 }
 
 // A operand and accumulator start of one 16-pattern tile.
+template <int KS>
 struct PatternTile {
-    uint4 a[4];
+    uint4 a[KS];
     float4 nh;
 };
 
-__device__ __forceinline__ void load_pattern_tile(const PatternTable &tb, int p0, int n, int kb, PatternTile &t)
+template <int KS>
+__device__ __forceinline__ void load_pattern_tile(const PatternTable &tb, int p0, int n, int kb, PatternTile<KS> &t)
 {
-    const __half *arow = tb.lds_rows + (p0 + n) * kTabStride + 8 * kb;
+    const __half *arow = tb.lds_rows + (p0 + n) * kTabStrideOf<32 * KS> + 8 * kb;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) t.a[s] = *reinterpret_cast<const uint4 *>(arow + 32 * s);
+    for (int s = 0; s < KS; ++s) t.a[s] = *reinterpret_cast<const uint4 *>(arow + 32 * s);
     t.nh = *reinterpret_cast<const float4 *>(tb.nh + p0 + 4 * kb);
 }
 
@@ -87,12 +96,13 @@ __device__ __forceinline__ void load_pattern_tile(const PatternTable &tb, int p0
 // patterns is the order of decreasing value, so the smallest key is the nearest pattern.  An e that
 // rounding made slightly positive ranks below every negative one, which is right, and can only be
 // mis-ordered against another such e: both are then inside the re-evaluation band.
-__device__ __forceinline__ void rank_pattern_tile(const uint4 (&xb)[4], const PatternTile &t, float hx, int p0, uint32_t &k1,
+template <int KS>
+__device__ __forceinline__ void rank_pattern_tile(const uint4 (&xb)[KS], const PatternTile<KS> &t, float hx, int p0, uint32_t &k1,
                                                   uint32_t &k2)
 {
     floatx4_t d = {t.nh.x - hx, t.nh.y - hx, t.nh.z - hx, t.nh.w - hx};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) d = mfma_f16(t.a[s], xb[s], d);
+    for (int s = 0; s < KS; ++s) d = mfma_f16(t.a[s], xb[s], d);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         // bytes 3..1 of e, byte 0 = index (one byte permute)
@@ -102,11 +112,11 @@ __device__ __forceinline__ void rank_pattern_tile(const uint4 (&xb)[4], const Pa
     }
 }
 
-// NT 16-token tiles held as B operands xb[j][4] (K-step s in xb[j][s]); every pattern tile read from the table
+// NT 16-token tiles of 32 * KS channels held as B operands xb[j][KS] (K-step s in xb[j][s]); every pattern tile read from the table
 // serves all NT of them.  Returns, in every lane of column n, per tile: best index, best squared distance (from
 // the expanded form, low 8 mantissa bits dropped), ||x||^2 and whether the token needs the exact re-evaluation.
-template <int NT>
-__device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][4], const PatternTable &tb, int lane, int (&best_i)[NT],
+template <int NT, int KS>
+__device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], const PatternTable &tb, int lane, int (&best_i)[NT],
                                                   float (&best_v)[NT], float (&x2)[NT], bool (&flag)[NT])
 {
     const int n = lane & 15, kb = lane >> 4;
@@ -115,7 +125,7 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][4], cons
     for (int j = 0; j < NT; ++j) {
         float acc = 0.f;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < KS; ++s) {
             const half2_t *h = reinterpret_cast<const half2_t *>(&xb[j][s]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
@@ -131,17 +141,26 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][4], cons
 #pragma unroll
     for (int j = 0; j < NT; ++j) k1[j] = k2[j] = 0xffffffffu;   // above every key
     const int Pp = pad16(tb.P);
-    PatternTile ta, tc;
-    load_pattern_tile(tb, 0, n, kb, ta);
-    for (int p0 = 0;;) {   // two tiles per round, the next one in flight while the current is ranked
-        if (p0 + 16 < Pp) load_pattern_tile(tb, p0 + 16, n, kb, tc);
+    if constexpr (KS <= 4) {
+        PatternTile<KS> ta, tc;
+        load_pattern_tile(tb, 0, n, kb, ta);
+        for (int p0 = 0;;) {   // two tiles per round, the next one in flight while the current is ranked
+            if (p0 + 16 < Pp) load_pattern_tile(tb, p0 + 16, n, kb, tc);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], ta, hx[j], p0, k1[j], k2[j]);
-        if ((p0 += 16) >= Pp) break;
-        if (p0 + 16 < Pp) load_pattern_tile(tb, p0 + 16, n, kb, ta);
+            for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], ta, hx[j], p0, k1[j], k2[j]);
+            if ((p0 += 16) >= Pp) break;
+            if (p0 + 16 < Pp) load_pattern_tile(tb, p0 + 16, n, kb, ta);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], tc, hx[j], p0, k1[j], k2[j]);
-        if ((p0 += 16) >= Pp) break;
+            for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], tc, hx[j], p0, k1[j], k2[j]);
+            if ((p0 += 16) >= Pp) break;
+        }
+    } else {   // 256 channels: a tile is 36 registers, held once
+        for (int p0 = 0; p0 < Pp; p0 += 16) {
+            PatternTile<KS> ta;
+            load_pattern_tile(tb, p0, n, kb, ta);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], ta, hx[j], p0, k1[j], k2[j]);
+        }
     }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -157,28 +176,31 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][4], cons
         best_v[j] = -2.f * __uint_as_float(a1 & 0xffffff00u);
         const float second = -2.f * __uint_as_float(a2 & 0xffffff00u);
         x2[j] = xx[j];
-        // accumulation error of e is far below 2^-21 (|x|^2 + |m|^2), the keys drop 8 mantissa bits:
-        // flag with a wide margin.  A single pattern has nothing to be confused with.
-        flag[j] = tb.P > 1 && !(second - best_v[j] > 7.62939453125e-06f * (xx[j] + tb.norm2_max) + 6.103515625e-05f * second);
+        // accumulation error of e is far below 2^-21 (|x|^2 + |m|^2) per chain of four matrix instructions, the keys
+        // drop 8 mantissa bits: flag with a wide margin.  A single pattern has nothing to be confused with.
+        constexpr float kBand = KS > 4 ? 1.52587890625e-05f : 7.62939453125e-06f;
+        flag[j] = tb.P > 1 && !(second - best_v[j] > kBand * (xx[j] + tb.norm2_max) + 6.103515625e-05f * second);
     }
 }
 
 // One 16-token tile.
-__device__ __forceinline__ void assign_tile_mfma(const uint4 (&xb)[4], const PatternTable &tb, int lane, int &best_i,
+template <int KS>
+__device__ __forceinline__ void assign_tile_mfma(const uint4 (&xb)[KS], const PatternTable &tb, int lane, int &best_i,
                                                  float &best_v, float &x2, bool &flag)
 {
     int bi[1];
     float bv[1], xx[1];
     bool fl[1];
-    assign_tiles_mfma<1>(reinterpret_cast<const uint4 (&)[1][4]>(xb), tb, lane, bi, bv, xx, fl);
+    assign_tiles_mfma<1, KS>(reinterpret_cast<const uint4 (&)[1][KS]>(xb), tb, lane, bi, bv, xx, fl);
     best_i = bi[0];
     best_v = bv[0];
     x2 = xx[0];
     flag = fl[0];
 }
 
-// Exact re-evaluation of one token by a whole wave: xrow_s = its 128 channels (fp16) in LDS.
+// Exact re-evaluation of one token by a whole wave: xrow_s = its D channels (fp16) in LDS.
 // Every lane returns the exact argmin (lowest index on ties) and its distance.
+template <int D>
 __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const PatternTable &tb, int lane, int &best_i,
                                                   float &best_d)
 {
@@ -187,10 +209,10 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
     for (int p = lane; p < tb.P; p += 64) {
         // the pattern rows come from the LDS copy of the table (the same fp16 values): read from global memory they
         // missed L2 often enough to add a fifth to the HBM traffic of a mining step on a large job
-        const __half *m = tb.lds_rows + p * kTabStride;
+        const __half *m = tb.lds_rows + p * kTabStrideOf<D>;
         float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll 4
-        for (int ch = 0; ch < kRowChunks; ++ch) {   // several row pieces in flight
+        for (int ch = 0; ch < D / 8; ++ch) {   // several row pieces in flight
             const uint4 mv = *reinterpret_cast<const uint4 *>(m + ch * 8);
             const uint4 xv = *reinterpret_cast<const uint4 *>(xrow_s + ch * 8);
             // (one v_fma_mix_f32 per difference instead of two conversions and a subtraction: the same value)
@@ -218,8 +240,9 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
     best_d = bd;
 }
 
-// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of kD halves.
-__device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[4], bool flag, __half *xrow_s, const PatternTable &tb,
+// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.
+template <int KS>
+__device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag, __half *xrow_s, const PatternTable &tb,
                                                 int lane, int &best_i, float &best_d)
 {
     const int n = lane & 15, kb = lane >> 4;
@@ -229,13 +252,13 @@ __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[4], bool flag,
         todo &= todo - 1;
         if (n == col) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) *reinterpret_cast<uint4 *>(xrow_s + 32 * s + 8 * kb) = xb[s];
+            for (int s = 0; s < KS; ++s) *reinterpret_cast<uint4 *>(xrow_s + 32 * s + 8 * kb) = xb[s];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         int bi;
         float bd;
-        exact_argmin_wave(xrow_s, tb, lane, bi, bd);
+        exact_argmin_wave<32 * KS>(xrow_s, tb, lane, bi, bd);
         if (n == col) {
             best_i = bi;
             best_d = bd;

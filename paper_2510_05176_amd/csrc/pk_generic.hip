@@ -6,8 +6,8 @@
 // same parity bars; they are kept simple rather than tuned, and the tuned kernels of the other files keep their
 // fixed head dimension.  The decode kernels here also serve head dimension 128 for head counts that the matrix-core
 // decode does not take.
-// Uniform and ragged appends, decode (with shared prefix and with per-sequence fill states), mining, the window
-// pattern and dequantize are covered, on contiguous and on paged caches.
+// Uniform and ragged appends, decode (with shared prefix and with per-sequence fill states), the window
+// pattern and dequantize are covered (mining is in pk_mine.hip for every head dimension), on contiguous and on paged caches.
 #pragma clang fp contract(off)
 
 #include "pk_assign_mfma.h"
@@ -263,31 +263,6 @@ __global__ __launch_bounds__(256) void gen_assign_mfma_kernel(QuantArgs a, int t
     }
 }
 
-// The assignment step of mining (Sec. 3.1 Eq. 4), the same search over the vectors of a set.
-template <int D>
-__global__ __launch_bounds__(256) void gen_mine_assign_mfma_kernel(MineArgs a, int last, int tiles_per_wg)
-{
-    extern __shared__ __align__(16) unsigned char gen_search_smem[];
-    const GenSearchLds<D> sh(gen_search_smem, a.P);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, s = blockIdx.y;
-    const int n_tiles = (a.T + 15) / 16;
-    const int tile0 = blockIdx.x * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
-    if (tile0 >= n_tiles) return;
-    const float norm2_max = gen_search_stage<D>(a.patterns + (int64_t)s * a.P * D, a.P, sh);
-    for (int tile = tile0 + wave; tile < tile1; tile += 4) {
-        const int t = tile * 16 + (lane & 15);   // a vector past the set's end repeats the last one; nothing is stored for it
-        int best;
-        float bd;
-        gen_search_tile<D>(a.x + (int64_t)s * a.set_stride + (int64_t)min(t, a.T - 1) * D, sh, norm2_max, a.P, sh.xrow + wave * D, lane,
-                           best, bd);
-        if (lane < 16 && t < a.T) {
-            a.assign_ws[(int64_t)s * a.T + t] = best;
-            if (last && a.assign) a.assign[(int64_t)s * a.T + t] = best;
-            a.best[(int64_t)s * a.T + t] = bd;
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------------------------- quantize-append
 // Pattern index of every vector to quantize: a workgroup takes 256 consecutive vectors of a stream.
 template <int D, int METRIC>
@@ -491,110 +466,7 @@ __global__ __launch_bounds__(256) void gen_tail_copy_kernel(TailCopyArgs a)
     *reinterpret_cast<uint4 *>(ring + ((int64_t)n * a.ring_len + slot) * a.d + ch * 8) = v;
 }
 
-// ---------------------------------------------------------------------------------------------- mining
-__global__ __launch_bounds__(256) void gen_mine_init_kernel(MineArgs a)
-{
-    const int s = blockIdx.y;
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= (int64_t)a.P * a.d) return;
-    a.patterns[(int64_t)s * a.P * a.d + w] = a.x[(int64_t)s * a.set_stride + w];   // the first P vectors
-}
-
-// cluster sums of one chunk of one set for a block of patterns (blockIdx.z).  The chunk is cut into
-// pieces of 1024 vectors whose assignments are staged in LDS, and every piece into kGenThreads / d consecutive slices
-// (two at d = 96, one at d = 256); thread <-> (slice, channel) adds the slice's vectors in order into the slice's
-// [patterns][d] accumulators in LDS (only this thread ever touches its column), the slices are added in order at the
-// end: the order of all additions is fixed.  The members are counted by all threads with integer atomics.
-// At the end the block goes to the chunk's own [P][d] part of the workspace.  A workgroup reads the assignment of
-// every vector of the chunk and the vectors of its own patterns only.
-constexpr int kSumsLdsFloats = 12288;   // accumulators per workgroup: floor(12288 / (slices * d)) - 1 patterns per block
-__global__ __launch_bounds__(kGenThreads) void gen_mine_sums_kernel(MineArgs a, int chunk, int pblock)
-{
-    constexpr int kAsg = 1024;             // assignments staged in LDS at a time
-    __shared__ float acc[kSumsLdsFloats];
-    __shared__ int32_t cnt[kGenThreads];   // pblock <= 64
-    __shared__ int32_t rel_s[kAsg];        // pattern of a vector relative to the block, -1 outside it
-    const int tid = threadIdx.x, ck = blockIdx.x, s = blockIdx.y, d = a.d;
-    const int n_slices = kGenThreads / d, slice = tid / d, c = tid - slice * d;
-    const int p0 = blockIdx.z * pblock, np = min(pblock, a.P - p0);
-    const int t0 = ck * chunk, t1 = min(a.T, t0 + chunk);
-    for (int i = tid; i < n_slices * (np + 1) * d; i += kGenThreads) acc[i] = 0.f;
-    cnt[tid] = 0;
-    __syncthreads();
-    const int32_t *asg = a.assign_ws + (int64_t)s * a.T;
-    const __half *x = a.x + (int64_t)s * a.set_stride;
-    float *mine = acc + (slice < n_slices ? slice : 0) * (np + 1) * d;   // np rows and the spare one
-    for (int b0 = t0; b0 < t1; b0 += kAsg) {   // the chunk in pieces of kAsg vectors
-        const int b1 = min(t1, b0 + kAsg);
-        __syncthreads();   // the previous piece's assignments have been used
-        for (int t = b0 + tid; t < b1; t += kGenThreads) {
-            int rel = asg[t] - p0;
-            if (rel < 0 || rel >= np) rel = -1;
-            rel_s[t - b0] = rel;
-            if (rel >= 0) atomicAdd(&cnt[rel], 1);
-        }
-        __syncthreads();
-        if (slice < n_slices) {
-            const int len = (b1 - b0 + n_slices - 1) / n_slices;
-            const int s0 = b0 + slice * len, s1 = min(b1, s0 + len);
-            for (int t = s0; t < s1; t += 16) {
-                // the vectors of sixteen steps are requested together, then added in order
-                // (no branches: a vector outside the block, or past the slice, goes to a spare row nobody reads)
-                int rowi[16];
-                float v[16];
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const int tk = min(t + k, s1 - 1);
-                    const int rel = t + k < s1 ? rel_s[tk - b0] : -1;
-                    rowi[k] = (rel < 0 ? np : rel) * d + c;
-                    v[k] = h2f(x[(int64_t)tk * d + c]);
-                }
-#pragma unroll
-                for (int k = 0; k < 16; ++k) mine[rowi[k]] += v[k];
-            }
-        }
-    }
-    __syncthreads();
-    float *ps = a.psum + (((int64_t)s * a.tsplit + ck) * a.P + p0) * d;
-    int32_t *pc = a.pcnt + ((int64_t)s * a.tsplit + ck) * a.P + p0;
-    for (int i = tid; i < np * d; i += kGenThreads) {
-        float v = acc[i];
-        for (int k = 1; k < n_slices; ++k) v += acc[k * (np + 1) * d + i];
-        ps[i] = v;
-    }
-    if (tid < np) pc[tid] = cnt[tid];
-}
-
-// update: chunks in increasing order, mean in binary32, fp16 nearest even; an empty cluster keeps its centroid
-__global__ __launch_bounds__(kGenThreads) void gen_mine_update_kernel(MineArgs a)
-{
-    const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x, d = a.d;
-    if (c >= d) return;
-    float sum = 0.f;
-    int cnt = 0;
-    for (int ts = 0; ts < a.tsplit; ++ts) {
-        sum += a.psum[(((int64_t)s * a.tsplit + ts) * a.P + p) * d + c];
-        cnt += a.pcnt[((int64_t)s * a.tsplit + ts) * a.P + p];
-    }
-    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * d + c] = __float2half_rn(sum / (float)cnt);
-}
-
-__global__ __launch_bounds__(256) void gen_mine_inertia_kernel(MineArgs a, int it)
-{
-    __shared__ float red[256];
-    const int s = blockIdx.x, tid = threadIdx.x;
-    const float *b = a.best + (int64_t)s * a.T;
-    float acc = 0.f;
-    for (int t = tid; t < a.T; t += 256) acc += b[t];
-    red[tid] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-    }
-    if (tid == 0) a.inertia[(int64_t)s * a.iters + it] = red[0];
-}
-
+// ---------------------------------------------------------------------------------------------- window pattern
 __global__ __launch_bounds__(kGenThreads) void gen_window_pattern_kernel(const __half *x, int64_t set_stride, int n, int d,
                                                                         __half *out, int64_t out_stride)
 {
@@ -1074,48 +946,6 @@ hipError_t launch_generic_tail_copy(const TailCopyArgs &a, hipStream_t s)
     if (work <= 0) return hipSuccess;
     hipLaunchKernelGGL(gen_tail_copy_kernel, dim3((unsigned)((work + 255) / 256), a.n_streams, 2), dim3(256), 0, s, a);
     return hipGetLastError();
-}
-
-template <int D>
-static hipError_t launch_gen_mine_assign(const MineArgs &a, int last, hipStream_t s)
-{
-    static LdsOptIn opt_in;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&gen_mine_assign_mfma_kernel<D>), opt_in, GenSearchLds<D>::bytes(256));
-    if (e != hipSuccess) return e;
-    const int n_tiles = (a.T + 15) / 16;
-    const int64_t total = (int64_t)n_tiles * a.n_sets;
-    int tpw = (int)((total + 2047) / 2048);
-    tpw = tpw < 16 ? 16 : tpw > 256 ? 256 : tpw;
-    hipLaunchKernelGGL(gen_mine_assign_mfma_kernel<D>, dim3((n_tiles + tpw - 1) / tpw, a.n_sets), dim3(256), GenSearchLds<D>::bytes(a.P), s,
-                       a, last, tpw);
-    return hipGetLastError();
-}
-
-hipError_t launch_generic_mine(const MineArgs &a, hipStream_t s)
-{
-    hipError_t e;
-    const int chunk = (a.T + a.tsplit - 1) / a.tsplit;
-    if (!a.init_given) {
-        hipLaunchKernelGGL(gen_mine_init_kernel, dim3((a.P * a.d + 255) / 256, a.n_sets), dim3(256), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    for (int it = 0; it < a.iters; ++it) {
-        if ((e = a.d == 96 ? launch_gen_mine_assign<96>(a, it == a.iters - 1 ? 1 : 0, s)
-                           : launch_gen_mine_assign<256>(a, it == a.iters - 1 ? 1 : 0, s)) != hipSuccess)
-            return e;
-        if (a.inertia) {
-            hipLaunchKernelGGL(gen_mine_inertia_kernel, dim3(a.n_sets), dim3(256), 0, s, a, it);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        const int per = kSumsLdsFloats / ((kGenThreads / a.d) * a.d) - 1;   // 47 patterns at d = 256, 63 at d = 96 (two slices); a spare row
-        const int pblock = a.P < per ? a.P : per;
-        hipLaunchKernelGGL(gen_mine_sums_kernel, dim3(a.tsplit, a.n_sets, (a.P + pblock - 1) / pblock), dim3(kGenThreads), 0,
-                           s, a, chunk, pblock);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(gen_mine_update_kernel, dim3(a.P, a.n_sets), dim3(kGenThreads), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 hipError_t launch_generic_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, int d, __half *out,

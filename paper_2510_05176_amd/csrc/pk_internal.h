@@ -218,23 +218,21 @@ struct MineArgs {
     int32_t n_sets, T, P, iters, init_given;
     int32_t d;             // head dimension
     __half *patterns;
-    int32_t *assign_ws;    // [n_sets][T] workspace (the generic path keeps every step's assignment there)
     int32_t *assign;       // [n_sets][T] caller's, or null
     float *best;           // [n_sets][T] workspace (written when inertia is asked for)
-    float *psum;           // [n_sets][tsplit][P][kD]
+    float *psum;           // [n_sets][tsplit][P][d]
     int32_t *pcnt;         // [n_sets][tsplit][P]
     float *inertia;        // optional [n_sets][iters]
     int32_t tsplit;
 };
 hipError_t launch_mine(const MineArgs &a, hipStream_t s);
-int mine_tsplit(int T, int n_sets, int P);
+int mine_tsplit(int T, int n_sets, int P);   // the most chunks per set launch_mine uses at any head dimension
 hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, __half *out, int64_t out_stride,
                                  hipStream_t s);
 
 // Head dimensions other than kD (pk_generic.hip): plain kernels, thread <-> channel, same results to the same bars.
 hipError_t launch_generic_quantize(const QuantArgs &a, bool v_side, hipStream_t s);
 hipError_t launch_generic_tail_copy(const TailCopyArgs &a, hipStream_t s);
-hipError_t launch_generic_mine(const MineArgs &a, hipStream_t s);
 hipError_t launch_generic_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, int d, __half *out,
                                          int64_t out_stride, hipStream_t s);
 

@@ -16,10 +16,9 @@ __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 {
     const int s = blockIdx.y;
     const int w = blockIdx.x * 256 + threadIdx.x;
-    if (w >= a.P * kRowChunks) return;
-    const int p = w >> 4, ch = w & 15;
-    const uint4 v = *reinterpret_cast<const uint4 *>(a.x + (int64_t)s * a.set_stride + (int64_t)p * kD + ch * 8);
-    *reinterpret_cast<uint4 *>(a.patterns + ((int64_t)s * a.P + p) * kD + ch * 8) = v;
+    if (w >= a.P * a.d / 8) return;   // 16-byte pieces; a set's vectors are dense rows, like the patterns
+    const uint4 v = *reinterpret_cast<const uint4 *>(a.x + (int64_t)s * a.set_stride + (int64_t)w * 8);
+    *reinterpret_cast<uint4 *>(a.patterns + (int64_t)s * a.P * a.d + (int64_t)w * 8) = v;
 }
 
 // Assignment step + partial cluster sums of one chunk of one set.  64*NW threads.
@@ -34,48 +33,59 @@ __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 // group's lanes address four to a row.  The one-hot operand is formed in packed fp16 as
 // clamp(1 - (idx_t - p)^2, 0, 1), which is exactly 1 or 0 for integers below 256; products are exact and the
 // accumulation order is fixed by the instruction sequence, so the sums are reproducible.
-// Dynamic LDS: [table pad16(P) rows] [-norm2/2 pad16(P)] [cnt pad16(P)] [xs 16 NT NW rows]
-//              [idx 16 NT NW halves] [xrow NW*kD halves]
-constexpr int kMineXs = kD + 16;   // halves per row of the vector tile: 72 words, so the eight rows that 32 lanes
-                                   // of a transposing read touch (8 words each) fall on 64 distinct banks
+// All three head dimensions take this kernel: a search and a cluster-sum kernel of their own, which head dimensions 96 and
+// 256 used to have, read the vectors twice and summed them on the vector ALUs; 2 x 10 iterations on 256 sets x 8191
+// vectors of 96 channels at 64 patterns 9.40 -> 2.14 ms (step 103 us), of 256 channels (8192 vectors) 19.9 -> 5.0 ms; 64
+// sets of 256 channels at 200 patterns 14.0 -> 3.4 ms.  Bound by instruction issue and LDS reads, not by the vectors (39 us
+// of traffic in a step at 96 channels).
+// With XC < D (256 channels and more than 128 patterns: the table alone takes 139 KB) the vectors pass through the LDS tile
+// XC channels at a time, the sums of those channels being formed between two barriers each; a wave's own rows of that tile
+// then serve as its re-evaluation row.
+// Dynamic LDS: [table pad16(P) rows] [-norm2/2 pad16(P)] [cnt pad16(P)] [xs 16 NT NW rows of XC]
+//              [idx 16 NT NW halves] [xrow NW*D halves, unless XC < D]
+template <int XC>
+constexpr int kMineXsOf = XC + 16;   // halves per row of the vector tile: 8 words modulo 16, so the eight rows that 32
+                                     // lanes of a transposing read touch (8 words each) fall on 64 distinct banks
 
 typedef _Float16 half2m __attribute__((ext_vector_type(2)));
 typedef short short4m __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4m *lds_short4_ptr;
 
-template <int NPT, int NW, int NT>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && NPT <= 4 ? 4 : 2))) void mine_step_kernel(MineArgs a, int chunk, int outputs)
+template <int D, int NPT, int NW, int NT, int XC>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && NPT <= 4 && D <= 128 ? 4 : 2))) void mine_step_kernel(MineArgs a, int chunk, int outputs)
 {
+    constexpr int KS = D / 32, kXs = kMineXsOf<XC>;
     extern __shared__ __align__(16) unsigned char smem[];
     const int P = a.P;
     __half *tab_s = reinterpret_cast<__half *>(smem);
-    float *norm_s = reinterpret_cast<float *>(smem + (size_t)pad16(P) * kTabStride * 2);
+    float *norm_s = reinterpret_cast<float *>(smem + (size_t)pad16(P) * kTabStrideOf<D> * 2);
     int *cnt = reinterpret_cast<int *>(norm_s + pad16(P));
     __half *xs = reinterpret_cast<__half *>(cnt + pad16(P));
     constexpr int ST = 16 * NT * NW;     // vectors per sub-tile: NT 16-vector tiles per wave
-    __half *idx_s = xs + ST * kMineXs;   // pattern index of every vector of the sub-tile, as an fp16 number
-    __half *xrow_s = idx_s + ST;
+    __half *idx_s = xs + ST * kXs;       // pattern index of every vector of the sub-tile, as an fp16 number
     __shared__ float red_s[NW];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
+    static_assert(XC == D || 16 * NT * kXs >= D, "a wave's rows of the vector tile hold one vector");
+    __half *xrow_s = XC == D ? idx_s + ST + wave * D : xs + wave * NT * 16 * kXs;
     const int ck = blockIdx.x, s = blockIdx.y;
     const int t_begin = ck * chunk, n_tok = min(chunk, a.T - t_begin);
-    const __half *xg = a.x + (int64_t)s * a.set_stride + (int64_t)t_begin * kD;
-    const __half *Mg = a.patterns + (int64_t)s * P * kD;
+    const __half *xg = a.x + (int64_t)s * a.set_stride + (int64_t)t_begin * D;
+    const __half *Mg = a.patterns + (int64_t)s * P * D;
 
-    auto load_tile = [&](int sub, uint4 (&xb)[NT][4]) {
+    auto load_tile = [&](int sub, uint4 (&xb)[NT][KS]) {
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int tok = min(sub * ST + (wave * NT + j) * 16 + n, n_tok - 1);   // rows past the chunk repeat its last vector
 #pragma unroll
-            for (int k = 0; k < 4; ++k) xb[j][k] = *reinterpret_cast<const uint4 *>(xg + (int64_t)tok * kD + 32 * k + 8 * kb);
+            for (int k = 0; k < KS; ++k) xb[j][k] = *reinterpret_cast<const uint4 *>(xg + (int64_t)tok * D + 32 * k + 8 * kb);
         }
     };
-    uint4 xb[NT][4];
+    uint4 xb[NT][KS];
     load_tile(0, xb);
 
     for (int i = tid; i < pad16(P); i += 64 * NW) cnt[i] = 0;
-    stage_patterns(Mg, P, tab_s, norm_s, red_s, 64 * NW);   // ends with a barrier
+    stage_patterns<D>(Mg, P, tab_s, norm_s, red_s, 64 * NW);   // ends with a barrier
     PatternTable tb;
     tb.lds_rows = tab_s;
     tb.nh = norm_s;
@@ -84,9 +94,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     for (int w = 1; w < NW; ++w) tb.norm2_max = fmaxf(tb.norm2_max, red_s[w]);
     tb.P = P;
 
-    // this wave's share of the sums: PW pattern tiles from pt0, CW channel tiles from ct0
+    // this wave's share of the sums: PW pattern tiles from pt0, CW channel tiles from ct0.  (With fewer pattern tiles than
+    // waves the channel tiles are split too; where they do not divide - 96 channels, one pattern tile - the last wave
+    // has none and repeats tile 0 without storing it.)
+    constexpr int CT = D / 16, CTX = XC / 16;   // channel tiles of a vector, and of the part of it that is in LDS
     constexpr int PW = NPT >= NW ? NPT / NW : 1;
-    constexpr int CW = NPT >= NW ? 8 : 8 * NPT / NW;
+    constexpr int CW = NPT >= NW ? CT : (CT * NPT + NW - 1) / NW;
+    constexpr bool kEven = NPT >= NW || CT * NPT % NW == 0;   // every wave has CW channel tiles of its own
+    static_assert(XC == D || CW == CT, "parts of the channels only where a wave takes all of them");
     const int pt0 = NPT >= NW ? wave * PW : wave % NPT;
     const int ct0 = NPT >= NW ? 0 : (wave / NPT) * CW;
     floatx4_t acc[PW][CW];
@@ -105,15 +120,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
         int bi[NT];
         float bv[NT], x2[NT];
         bool flag[NT];
-        assign_tiles_mfma<NT>(xb, tb, lane, bi, bv, x2, flag);
+        assign_tiles_mfma<NT, KS>(xb, tb, lane, bi, bv, x2, flag);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int tl = (wave * NT + j) * 16 + n, tok = sub * ST + tl;
             float bd = fmaxf(bv[j], 0.f);
-            resolve_flagged(xb[j], flag[j], xrow_s + wave * kD, tb, lane, bi[j], bd);
+            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd);
+            if constexpr (XC == D) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
-                *reinterpret_cast<uint4 *>(xs + tl * kMineXs + 32 * k + 8 * kb) = tok < n_tok ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
+                for (int k = 0; k < KS; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
+                    *reinterpret_cast<uint4 *>(xs + tl * kXs + 32 * k + 8 * kb) = tok < n_tok ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
+            }
             if (kb == 0) {
                 idx_s[tl] = __float2half_rn((float)bi[j]);   // integers below 2048 are exact
                 if (tok < n_tok) {
@@ -125,42 +142,59 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
                 }
             }
         }
-        if (sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation
-        __syncthreads();
 #pragma unroll
-        for (int ks = 0; ks < ST / 32; ++ks) {
-            // 32 vectors per step; this lane's k-slots 0-3 are vectors ta .. ta+3, its slots 4-7 the ones 16 later
-            const int ta = 32 * ks + 4 * kb;
-            const uint2 ia = *reinterpret_cast<const uint2 *>(idx_s + ta);
-            const uint2 ib = *reinterpret_cast<const uint2 *>(idx_s + ta + 16);
-            const half2m idh[4] = {__builtin_bit_cast(half2m, ia.x), __builtin_bit_cast(half2m, ia.y),
-                                   __builtin_bit_cast(half2m, ib.x), __builtin_bit_cast(half2m, ib.y)};
-            uint4 av[PW];
+        for (int part = 0; part < D / XC; ++part) {   // channels part * XC .. of the vectors
+            if constexpr (XC < D) {
 #pragma unroll
-            for (int pi = 0; pi < PW; ++pi) {
-                uint32_t aop[4];
+                for (int j = 0; j < NT; ++j) {
+                    const int tl = (wave * NT + j) * 16 + n;
+                    const bool in = sub * ST + tl < n_tok;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const half2m d = idh[j] - prow[pi];
-                    half2m oh = one2 - d * d;                       // 1 where the index equals the row, <= 0 elsewhere
-                    oh = __builtin_elementwise_min(__builtin_elementwise_max(oh, half2m{(_Float16)0.f, (_Float16)0.f}), one2);   // folds into the clamp bit
-                    aop[j] = __builtin_bit_cast(uint32_t, oh);
+                    for (int k = 0; k < XC / 32; ++k)
+                        *reinterpret_cast<uint4 *>(xs + tl * kXs + 32 * k + 8 * kb) = in ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
                 }
-                av[pi] = make_uint4(aop[0], aop[1], aop[2], aop[3]);
             }
-            // lane n of group kb addresses the 8-byte piece (n & 3) of row ta + n / 4 and receives column n of rows ta .. ta+3
-            const __half *piece = xs + (ta + (n >> 2)) * kMineXs + 16 * ct0 + 4 * (n & 3);
+            if (part == D / XC - 1 && sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation
+            __syncthreads();
 #pragma unroll
-            for (int ci = 0; ci < CW; ++ci) {
-                const short4m lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(piece + 16 * ci));
-                const short4m hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(piece + 16 * kMineXs + 16 * ci));
-                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-                const uint4 bop = make_uint4(l2.x, l2.y, h2.x, h2.y);
+            for (int ks = 0; ks < ST / 32; ++ks) {
+                // 32 vectors per step; this lane's k-slots 0-3 are vectors ta .. ta+3, its slots 4-7 the ones 16 later
+                const int ta = 32 * ks + 4 * kb;
+                const uint2 ia = *reinterpret_cast<const uint2 *>(idx_s + ta);
+                const uint2 ib = *reinterpret_cast<const uint2 *>(idx_s + ta + 16);
+                const half2m idh[4] = {__builtin_bit_cast(half2m, ia.x), __builtin_bit_cast(half2m, ia.y),
+                                       __builtin_bit_cast(half2m, ib.x), __builtin_bit_cast(half2m, ib.y)};
+                uint4 av[PW];
 #pragma unroll
-                for (int pi = 0; pi < PW; ++pi) acc[pi][ci] = mfma_f16(av[pi], bop, acc[pi][ci]);
+                for (int pi = 0; pi < PW; ++pi) {
+                    uint32_t aop[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const half2m d = idh[j] - prow[pi];
+                        half2m oh = one2 - d * d;                       // 1 where the index equals the row, <= 0 elsewhere
+                        oh = __builtin_elementwise_min(__builtin_elementwise_max(oh, half2m{(_Float16)0.f, (_Float16)0.f}), one2);   // folds into the clamp bit
+                        aop[j] = __builtin_bit_cast(uint32_t, oh);
+                    }
+                    av[pi] = make_uint4(aop[0], aop[1], aop[2], aop[3]);
+                }
+                // lane n of group kb addresses the 8-byte piece (n & 3) of row ta + n / 4 and receives column n of rows ta .. ta+3
+                const __half *piece = xs + (ta + (n >> 2)) * kXs + 4 * (n & 3);
+                constexpr int CP = XC == D ? CW : CTX;   // channel tiles of this part that the wave takes
+#pragma unroll
+                for (int ci = 0; ci < CP; ++ci) {
+                    const int at = XC == D ? (kEven || ct0 + ci < CT ? ct0 + ci : 0) : ci;   // channel tile inside the part
+                    const short4m lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(piece + 16 * at));
+                    const short4m hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_ptr)(piece + 16 * kXs + 16 * at));
+                    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                    const uint4 bop = make_uint4(l2.x, l2.y, h2.x, h2.y);
+                    constexpr int kParts = D / XC;
+                    const int ai = kParts == 1 ? ci : part * CTX + ci;
+#pragma unroll
+                    for (int pi = 0; pi < PW; ++pi) acc[pi][ai] = mfma_f16(av[pi], bop, acc[pi][ai]);
+                }
             }
+            __syncthreads();
         }
-        __syncthreads();
     }
     // partial sums of the chunk: D rows 4kb+i = pattern 16(pt0 + pi) + 4kb + i, column n = channel 16(ct0 + ci) + n
     const int64_t o = ((int64_t)s * a.tsplit + ck) * P;
@@ -171,7 +205,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             const int pr = 16 * (pt0 + pi) + 4 * kb + i;
             if (pr < P) {
 #pragma unroll
-                for (int ci = 0; ci < CW; ++ci) a.psum[(o + pr) * kD + 16 * (ct0 + ci) + n] = acc[pi][ci][i];
+                for (int ci = 0; ci < CW; ++ci)
+                    if (kEven || ct0 + ci < CT) a.psum[(o + pr) * D + 16 * (ct0 + ci) + n] = acc[pi][ci][i];
             }
         }
     }
@@ -180,9 +215,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
 
 // update step: centroid = mean of members (binary32 division), rounded to fp16;
 // an empty cluster keeps its centroid
-__global__ __launch_bounds__(128) void mine_update_kernel(MineArgs a)
+__global__ __launch_bounds__(256) void mine_update_kernel(MineArgs a)   // a.d threads, thread <-> channel
 {
-    const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x;
+    const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x, d = a.d;
     const int64_t o0 = (int64_t)s * a.tsplit * a.P + p, step = a.P;
     // chunks in increasing order, eight loads in flight at a time; the order of the additions is fixed
     float sum = 0.f;
@@ -193,7 +228,7 @@ __global__ __launch_bounds__(128) void mine_update_kernel(MineArgs a)
         int k[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            v[u] = a.psum[(o0 + (ts + u) * step) * kD + c];
+            v[u] = a.psum[(o0 + (ts + u) * step) * d + c];
             k[u] = a.pcnt[o0 + (ts + u) * step];
         }
 #pragma unroll
@@ -203,10 +238,10 @@ __global__ __launch_bounds__(128) void mine_update_kernel(MineArgs a)
         }
     }
     for (; ts < a.tsplit; ++ts) {
-        sum += a.psum[(o0 + ts * step) * kD + c];
+        sum += a.psum[(o0 + ts * step) * d + c];
         cnt += a.pcnt[o0 + ts * step];
     }
-    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * kD + c] = __float2half_rn(sum / (float)cnt);
+    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * d + c] = __float2half_rn(sum / (float)cnt);
 }
 
 // inertia of one assignment step: fixed-order sum of the best distances
@@ -253,25 +288,48 @@ __global__ __launch_bounds__(256) void window_pattern_kernel(const __half *x, in
     }
 }
 
-size_t step_lds_bytes(int P, int nw, int nt)
+// Instantiation for a head dimension and number of patterns: 16 * npt >= P table rows, nw waves, nt 16-vector tiles per wave
+// and pass over the table, xc channels of the vectors in LDS at a time.
+struct StepShape {
+    int npt, nw, nt, xc;
+};
+constexpr StepShape step_shape(int D, int P)
 {
-    size_t b = (size_t)pad16(P) * kTabStride * 2;
-    b += (size_t)pad16(P) * 4 + (size_t)pad16(P) * 4 + 16 * nw * nt * (size_t)kMineXs * 2 + 16 * nw * nt * 2 + (size_t)nw * kD * 2;
+    // 8 waves share the table when only one workgroup fits a CU (P > 128, or P > 64 at 256 channels, whose table rows and
+    // accumulators are twice as large; at 128 patterns of 128 channels two 4-wave workgroups measured faster than one
+    // 8-wave group).  From 128 patterns on a wave assigns two 16-vector tiles per table pass: reading the table out of LDS
+    // is what limits the assignment there, and every tile read then serves 32 vectors (at 64 patterns and below, and with
+    // the eight-step tiles of 256 channels, the smaller tile and its fewer registers win).
+    const int npt = P <= 16 ? 1 : P <= 32 ? 2 : P <= 64 ? 4 : P <= 128 ? 8 : 16;
+    const int nw = npt == 16 || (D == 256 && npt == 8) ? 8 : 4;
+    const int nt = npt >= 8 && D != 256 ? 2 : 1;
+    return {npt, nw, nt, D == 256 && npt == 16 ? 64 : D};
+}
+
+size_t step_lds_bytes(int D, int P, const StepShape &h)
+{
+    size_t b = (size_t)pad16(P) * (D + 16) * 2;
+    b += (size_t)pad16(P) * 4 + (size_t)pad16(P) * 4 + 16 * h.nw * h.nt * (size_t)(h.xc + 16) * 2 + 16 * h.nw * h.nt * 2;
+    if (h.xc == D) b += (size_t)h.nw * D * 2;
     return (b + 15) / 16 * 16;
 }
 
 }  // namespace
 
-// Workgroups of the step kernel that one compute unit holds at a time: registers allow four 4-wave groups up
-// to 64 patterns; the table and the vector tile in LDS allow two at 128 patterns and one 8-wave group above.
-static int step_groups_per_cu(int P) { return P <= 64 ? 4 : P <= 128 ? 2 : 1; }
+// Workgroups of the step kernel that one compute unit holds at a time: registers allow four 4-wave groups up to 64 patterns
+// (two at 256 channels); the table and the vector tile in LDS allow two at 128 patterns and one 8-wave group above.
+static int step_groups_per_cu(int P, int d)
+{
+    const StepShape h = step_shape(d, P);
+    return h.nw == 8 ? 1 : h.npt <= 4 && d <= 128 ? 4 : 2;
+}
 
-int mine_chunk(int T, int n_sets, int P)
+static int mine_chunk(int T, int n_sets, int P, int d)
 {
     // One resident round of workgroups over the chip's 256 compute units: all chunks then run side by side and
-    // take the same time, and every chunk writes its P*128 partial sums once, so fewer, longer chunks also
+    // take the same time, and every chunk writes its P*d partial sums once, so fewer, longer chunks also
     // mean less traffic.  At most 64 chunks per set, none shorter than 256 vectors.
-    const int64_t slots = 256 * step_groups_per_cu(P);
+    const int64_t slots = 256 * step_groups_per_cu(P, d);
     const int64_t per_set = slots / n_sets > 1 ? slots / n_sets : 1;
     int64_t c = (T + per_set - 1) / per_set;
     if (c < (T + 63) / 64) c = (T + 63) / 64;
@@ -280,53 +338,60 @@ int mine_chunk(int T, int n_sets, int P)
     return (int)c;
 }
 
-int mine_tsplit(int T, int n_sets, int P) { return (T + mine_chunk(T, n_sets, P) - 1) / mine_chunk(T, n_sets, P); }
-
-template <int NPT, int NW, int NT>
-static hipError_t launch_step(const MineArgs &a, int chunk, size_t lds, hipStream_t s, int outputs)
+static int chunks_of(int T, int n_sets, int P, int d) { return (T + mine_chunk(T, n_sets, P, d) - 1) / mine_chunk(T, n_sets, P, d); }
+int mine_tsplit(int T, int n_sets, int P)
 {
-    hipLaunchKernelGGL((mine_step_kernel<NPT, NW, NT>), dim3(a.tsplit, a.n_sets), dim3(64 * NW), lds, s, a, chunk, outputs);
+    // (at 256 channels no more groups fit a CU than at 128, at 96 as many)
+    return chunks_of(T, n_sets, P, kD);
+}
+
+// One launch of the step kernel for 16 * NPT patterns or fewer at head dimension D
+template <int D, int NPT>
+static hipError_t launch_step(const MineArgs &a, hipStream_t s, int outputs)
+{
+    constexpr StepShape h = step_shape(D, 16 * NPT);
+    static LdsOptIn opt_in;   // the most this instantiation needs: a table of 16 * NPT patterns
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>), opt_in,
+                                           step_lds_bytes(D, 16 * NPT, h));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>), dim3(a.tsplit, a.n_sets), dim3(64 * h.nw), step_lds_bytes(D, a.P, h), s,
+                       a, mine_chunk(a.T, a.n_sets, a.P, D), outputs);
     return hipGetLastError();
 }
 
-template <int NPT, int NW, int NT>
-static hipError_t prepare_step(const MineArgs &, int, size_t, hipStream_t, int)
+template <int D>
+static hipError_t launch_step_of(const MineArgs &a, hipStream_t s, int outputs)
 {
-    static LdsOptIn opt_in;   // the most this instantiation needs: a table of 16 * NPT patterns
-    return allow_dynamic_lds(reinterpret_cast<const void *>(&mine_step_kernel<NPT, NW, NT>), opt_in, step_lds_bytes(16 * NPT, NW, NT));
+    switch (step_shape(D, a.P).npt) {
+    case 1: return launch_step<D, 1>(a, s, outputs);
+    case 2: return launch_step<D, 2>(a, s, outputs);
+    case 4: return launch_step<D, 4>(a, s, outputs);
+    case 8: return launch_step<D, 8>(a, s, outputs);
+    default: return launch_step<D, 16>(a, s, outputs);
+    }
 }
 
-hipError_t launch_mine(const MineArgs &a, hipStream_t s)
+hipError_t launch_mine(const MineArgs &a_in, hipStream_t s)
 {
-    if (a.d != kD) return launch_generic_mine(a, s);
+    MineArgs a = a_in;
+    a.tsplit = chunks_of(a.T, a.n_sets, a.P, a.d);
+    if (a.d != kD && a.d != 96 && a.d != 256) return hipErrorInvalidValue;
     hipError_t e;
-    const int chunk = mine_chunk(a.T, a.n_sets, a.P);
-    const int npt = a.P <= 16 ? 1 : a.P <= 32 ? 2 : a.P <= 64 ? 4 : a.P <= 128 ? 8 : 16;
-    // 8 waves share the table when only one workgroup fits a CU (P > 128; at 128 patterns two 4-wave workgroups
-    // measured faster than one 8-wave group).  From 128 patterns on a wave assigns two 16-vector tiles per
-    // table pass: reading the table out of LDS is what limits the assignment there, and every tile read then
-    // serves 32 vectors (at 64 patterns and below the smaller tile and the higher occupancy win).
-    const int nt = npt >= 8 ? 2 : 1;
-    const int nw = a.P > 128 ? 8 : 4;
-    const size_t lds = step_lds_bytes(a.P, nw, nt);
-#define PK_STEP(CALL)                                                                                       \
-    (npt == 1 ? CALL<1, 4, 1> : npt == 2 ? CALL<2, 4, 1> : npt == 4 ? CALL<4, 4, 1> : npt == 8 ? CALL<8, 4, 2> : CALL<16, 8, 2>)
-    if ((e = PK_STEP(prepare_step)(a, chunk, lds, s, 0)) != hipSuccess) return e;
     if (!a.init_given) {
-        hipLaunchKernelGGL(mine_init_kernel, dim3((a.P * kRowChunks + 255) / 256, a.n_sets), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(mine_init_kernel, dim3((a.P * a.d / 8 + 255) / 256, a.n_sets), dim3(256), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int it = 0; it < a.iters; ++it) {
         const int outputs = (a.assign && it == a.iters - 1 ? 1 : 0) | (a.inertia ? 2 : 0);
-        if ((e = PK_STEP(launch_step)(a, chunk, lds, s, outputs)) != hipSuccess) return e;
+        e = a.d == kD ? launch_step_of<kD>(a, s, outputs) : a.d == 96 ? launch_step_of<96>(a, s, outputs) : launch_step_of<256>(a, s, outputs);
+        if (e != hipSuccess) return e;
         if (a.inertia) {
             hipLaunchKernelGGL(mine_inertia_kernel, dim3(a.n_sets), dim3(256), 0, s, a, it);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(mine_update_kernel, dim3(a.P, a.n_sets), dim3(128), 0, s, a);
+        hipLaunchKernelGGL(mine_update_kernel, dim3(a.P, a.n_sets), dim3(a.d), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-#undef PK_STEP
     return hipSuccess;
 }
 

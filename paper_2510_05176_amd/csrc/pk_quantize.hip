@@ -393,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) void quantize_k_kernel(QuantArgs a, int ti
         } else {   // the wave's NT 16-token tiles in one pass over the pattern table
             float bv[NT], x2[NT];
             bool flag[NT];
-            assign_tiles_mfma<NT>(xb, tb, lane, bi, bv, x2, flag);
+            assign_tiles_mfma<NT, 4>(xb, tb, lane, bi, bv, x2, flag);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 ? 2
                 float bv[NTA], x2[NTA];
                 bool flag[NTA];
                 int bj[NTA];
-                assign_tiles_mfma<NTA>(reinterpret_cast<const uint4 (&)[NTA][4]>(xb[j0]), tb, lane, bj, bv, x2, flag);
+                assign_tiles_mfma<NTA, 4>(reinterpret_cast<const uint4 (&)[NTA][4]>(xb[j0]), tb, lane, bj, bv, x2, flag);
 #pragma unroll
                 for (int j = 0; j < NTA; ++j) {
                     float bd;
@@ -701,7 +701,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
         } else {
             float bv[NT], x2[NT];
             bool flag[NT];
-            assign_tiles_mfma<NT>(xbs, tb, lane, bis, bv, x2, flag);
+            assign_tiles_mfma<NT, 4>(xbs, tb, lane, bis, bv, x2, flag);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;

@@ -959,3 +959,15 @@ def test_other_head_dimensions_decode_splits(oracle, pk, d, hkv, hq, bits, G, P,
     full.state = pk._State(*states[big][:3])
     one = pk.pk_decode_attention(full.cfg, full, dev(q[big:big + 1]), d ** -0.5, Mkd, Mvd).cpu().numpy()
     assert_attention(one[0], want[big])
+
+
+@pytest.mark.parametrize("d,P,T", [(96, 16, 333), (96, 17, 700), (96, 64, 257), (96, 128, 600), (96, 129, 700), (256, 9, 300),
+                                   (256, 32, 513), (256, 64, 700), (256, 65, 400), (256, 128, 513), (256, 200, 700), (256, 256, 640)])
+def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
+    """Two Lloyd iterations at head dimensions 96 and 256 for every instantiation of the step kernel (16 to 256 table rows;
+    at 256 channels beyond 128 patterns the vectors pass through LDS in parts), with ragged last sub-tiles and chunks."""
+    K, _ = synth.make_kv(300 + d + P, synth.KVSpec(1, 1, 2, 2, T, d, 24))
+    cur = K[0][:, :P].copy().view(np.uint16)
+    for _ in range(2):
+        new = _mining_step_parity(oracle, pk, K[0], P, cur, check_sets=range(2))
+        cur = np.stack([new[s] for s in range(2)])
