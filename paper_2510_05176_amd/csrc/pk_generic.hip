@@ -26,67 +26,6 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-// Nearest pattern of one vector per thread (lane <-> vector): the vector's D channels stay in registers as loaded,
-// the pattern rows pass through LDS in chunks of kTabRows and are read by all lanes at once (one broadcast read per
-// 8 channels), four patterns at a time.  Per pattern the metric is evaluated in binary32 - the squared differences
-// added in channel order into one accumulator, or d_mm = max - min of the differences (Sec. 3.2) - and patterns are compared in increasing order with a strict <, so the lowest index wins ties.  All threads of the
-// workgroup call this together (it has workgroup barriers).
-constexpr int kTabRows = 32;
-template <int D, int METRIC>
-__device__ __forceinline__ void nearest_pattern(const uint4 (&x)[D / 8], const __half *M, int P, __half *tab, int tid,
-                                                int &best_i, float &best_d)
-{
-    float bd = INFINITY;
-    int bi = 0;
-    for (int p0 = 0; p0 < P; p0 += kTabRows) {
-        const int np = min(kTabRows, P - p0);
-        __syncthreads();   // the previous chunk has been read
-        for (int k = tid; k < np * (D / 8); k += kGenThreads)
-            reinterpret_cast<uint4 *>(tab)[k] = reinterpret_cast<const uint4 *>(M + (int64_t)p0 * D)[k];
-        __syncthreads();
-        for (int p = 0; p < np; p += 4) {
-            const __half *m[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) m[j] = tab + min(p + j, np - 1) * D;   // rows past the chunk repeat its last one
-            float acc[4], mn[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                acc[j] = METRIC == PK_METRIC_MINMAX ? -INFINITY : 0.f;   // the running maximum under the min-max rule
-                mn[j] = INFINITY;
-            }
-#pragma unroll
-            for (int k = 0; k < D / 8; ++k) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint4 mv = *reinterpret_cast<const uint4 *>(m[j] + 8 * k);
-                    const uint32_t xw[4] = {x[k].x, x[k].y, x[k].z, x[k].w}, mw[4] = {mv.x, mv.y, mv.z, mv.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float r0 = sub_lo(xw[e], mw[e]), r1 = sub_hi(xw[e], mw[e]);   // binary32 differences
-                        if (METRIC == PK_METRIC_MINMAX) {
-                            acc[j] = fmaxf(fmaxf(acc[j], r0), r1);
-                            mn[j] = fminf(fminf(mn[j], r0), r1);
-                        } else {
-                            acc[j] = fmaf(r0, r0, acc[j]);
-                            acc[j] = fmaf(r1, r1, acc[j]);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float dist = METRIC == PK_METRIC_MINMAX ? acc[j] - mn[j] : acc[j];
-                if (p + j < np && dist < bd) {
-                    bd = dist;
-                    bi = p0 + p + j;
-                }
-            }
-        }
-    }
-    best_i = bi;
-    best_d = bd;
-}
-
 // ---------------------------------------------------------------------------------------------- Euclidean search
 // Nearest pattern under the Euclidean rule on the matrix cores at head dimension D (96 or 256), the scheme of the
 // tuned search with D / 32 operand steps: a wave ranks a 16-vector tile against 16 patterns per round,
@@ -264,25 +203,6 @@ __global__ __launch_bounds__(256) void gen_assign_mfma_kernel(QuantArgs a, int t
 }
 
 // ---------------------------------------------------------------------------------------------- quantize-append
-// Pattern index of every vector to quantize: a workgroup takes 256 consecutive vectors of a stream.
-template <int D, int METRIC>
-__global__ __launch_bounds__(kGenThreads) void gen_assign_kernel(QuantArgs a)
-{
-    __shared__ __align__(16) __half tab[kTabRows * D];
-    const int tid = threadIdx.x, ns = blockIdx.y, i = blockIdx.x * kGenThreads + tid;
-    take_sequence_entry(a, ns);
-    if ((int)(blockIdx.x * kGenThreads) >= a.nq) return;   // a ragged append: sized for the longest sequence
-    const bool live = i < a.nq;
-    uint4 x[D / 8];
-    const uint4 *row = reinterpret_cast<const uint4 *>(a.src.row_d(ns, live ? i : a.nq - 1, D));
-#pragma unroll
-    for (int k = 0; k < D / 8; ++k) x[k] = row[k];
-    int bi;
-    float bd;
-    nearest_pattern<D, METRIC>(x, a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D, a.P, tab, tid, bi, bd);
-    if (live) a.idx[a.map.pos(ns, a.t0 + i)] = (uint8_t)bi;
-}
-
 // K: one workgroup per (group of G tokens, stream), thread <-> channel.  Two passes over the group's residuals (the
 // second recomputes them): minimum / maximum -> parameters, then codes; a plane word of 32 channels is a wave ballot.
 // The group's indices are staged in LDS and the vectors and pattern rows are requested 16 tokens at a time, without
@@ -896,17 +816,6 @@ hipError_t launch_gen_decode_split(const DecodeArgs &a, dim3 grid, size_t lds, h
 
 // ---------------------------------------------------------------------------------------------- launchers
 template <int D>
-static hipError_t launch_gen_assign(const QuantArgs &a, hipStream_t s)
-{
-    const dim3 grid((a.nq + kGenThreads - 1) / kGenThreads, a.n_streams);
-    if (a.metric == PK_METRIC_MINMAX)
-        hipLaunchKernelGGL((gen_assign_kernel<D, PK_METRIC_MINMAX>), grid, dim3(kGenThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((gen_assign_kernel<D, PK_METRIC_L2>), grid, dim3(kGenThreads), 0, s, a);
-    return hipGetLastError();
-}
-
-template <int D>
 static hipError_t launch_gen_assign_mfma(const QuantArgs &a, hipStream_t s)
 {
     static LdsOptIn opt_in;   // per instantiation: the most it needs is a table of 256 patterns
@@ -928,7 +837,7 @@ hipError_t launch_generic_quantize(const QuantArgs &a, bool v_side, hipStream_t 
     if (a.d != 96 && a.d != 256) return hipErrorInvalidValue;
     hipError_t e;
     if (a.metric == PK_METRIC_MINMAX)
-        e = a.d == 96 ? launch_gen_assign<96>(a, s) : launch_gen_assign<256>(a, s);
+        e = launch_assign_minmax(a, s);
     else
         e = a.d == 96 ? launch_gen_assign_mfma<96>(a, s) : launch_gen_assign_mfma<256>(a, s);
     if (e != hipSuccess) return e;

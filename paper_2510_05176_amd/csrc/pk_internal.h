@@ -186,6 +186,7 @@ __device__ __forceinline__ void take_sequence_entry(QuantArgs &a, int stream)
 
 hipError_t launch_quantize_k(const QuantArgs &a, hipStream_t s);
 hipError_t launch_quantize_v(const QuantArgs &a, hipStream_t s);
+hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s);   // min-max search into a.idx, any head dimension
 
 struct TailCopyArgs {
     const __half *fresh_k, *fresh_v;

@@ -8,8 +8,8 @@
 // half to even, clamp); contraction into FMAs is switched off for this file so
 // that the sequence is exactly what is written.
 //
-// Kernels, in file order: assign_minmax_kernel (the min-max selection rule of Sec. 3.2 as a search of its own: it
-// writes the indices and the quantizers below then take them as given); quantize_k_kernel (groups of 128 tokens,
+// Kernels, in file order: assign_minmax_kernel (the min-max selection rule of Sec. 3.2 as a search of its own, at every
+// head dimension: it writes the indices and the quantizers below then take them as given); quantize_k_kernel (groups of 128 tokens,
 // a workgroup of eight waves per tile) and quantize_k_wave_kernel (groups of 32 / 64 tokens, a wave per group); quantize_v_kernel
 // (a wave per 16-token unit); tail_copy_kernel (the fp16 ring); seq_table_kernel (per-sequence launch parameters
 // of a ragged append).  Under the Euclidean rule the quantizers search on the matrix cores (pk_assign_mfma.h).
@@ -25,30 +25,41 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Min-max metric (Sec. 3.2): d_mm(x, m) = max_c (x_c - m_c) - min_c (x_c - m_c), argmin over the patterns, lowest
-// index on ties.  Every operation is exact in binary32 apart from one correctly rounded subtraction per
-// channel (fp16 values widened exactly), so the result is the definition's, bit for bit; it is not a
-// contraction and runs on the vector ALUs.  A wave takes 64 vectors, lane <-> vector, the vector's 128 channels
-// in registers as binary32; a pattern row is wave-uniform and comes through the scalar data path as packed fp16,
-// which the mixed-precision subtract (x * 1.0 - m with the fp16 half widened) reads directly: per pattern and
-// vector 128 subtractions and 128 three-operand maxima / minima.  The indices go to the cache's index array; the
-// quantizers below then skip their own search.
+// index on ties.  Every operation of the definition is exact in binary32 apart from one correctly rounded subtraction per
+// channel (fp16 values widened exactly) and the last one, so the result is the definition's, bit for bit; it is not a
+// contraction and runs on the vector ALUs.  A wave takes 64 vectors, lane <-> vector, the vector's channels in
+// registers as loaded.  The indices go to the cache's index array; the quantizers then skip their own search.
+//
+// Every pattern is ranked in packed fp16, two channels per operation: a subtraction (the pattern row wave-uniform, a
+// scalar operand), and half of a three-operand maximum and minimum each.  fp16 rounding is monotone, so the maximum and
+// minimum found are the roundings of the true ones, and the distance lies within 2^-11 (|max| + |min|) of their
+// difference; with twice that, c = 2^-10, difference - c (|max| + |min|) is a lower bound and the same + 2 c (|max| +
+// |min|) an upper one.  The three smallest lower bounds are tracked; where the second does not exceed the upper bound of the
+// first, the lane evaluates these two patterns in binary32; where the third does not exceed it either, the wave evaluates
+// the vector against all patterns, lane <-> pattern.
+// 1.1 vector operations per channel and pattern instead of the 2.1 of ranking in binary32 (a mixed-precision subtraction and
+// half of a three-operand maximum and minimum), bound by their issue: 256 streams x 8192 vectors, 64 patterns 998 -> 565 us
+// per search (485 at the issue rate of the packed operations), at 128 patterns a whole append 4.16 -> 2.53 ms, 128 streams
+// of 256 channels 3.32 -> 2.33 ms.  (Scalar loads of 32 channels per wait instead of 64: 650 us, and no gain at 256 channels,
+// whose two waves per SIMD did not cover their latency.)
+// Ruling patterns out by the range over a few channels first (the widest over the table) and evaluating the rest in full
+// measured 437 us on keys and 716 us on values in the same job, 1.4 times the binary32 scan's time on unclustered vectors,
+// and more than it at 250 patterns: candidates differ from vector to vector, so a wave runs as long as its worst one.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float sub_s_lo(float x, uint32_t m)   // x - half(m.lo), m wave-uniform
-{
-    float r;
-    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[0,0,1]" : "=v"(r) : "v"(x), "s"(m));
-    return r;
-}
-__device__ __forceinline__ float sub_s_hi(float x, uint32_t m)   // x - half(m.hi)
-{
-    float r;
-    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r) : "v"(x), "s"(m));
-    return r;
-}
+typedef _Float16 mm_half2 __attribute__((ext_vector_type(2)));
 
 // Sixteen consecutive dwords through the scalar data path (read only; address wave-uniform, 4-byte aligned), and the
 // wait for every scalar load issued so far; the values are tied to the wait so that no use can move ahead of it.
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ u32x16 sload16(const uint32_t *p)
+{
+    u32x16 r;
+    asm volatile("s_load_dwordx16 %0, %1, 0x0" : "=s"(r) : "s"(p) : "memory");
+    return r;
+}
+__device__ __forceinline__ void swait(u32x16 (&r)[1]) { asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0])); }
+__device__ __forceinline__ void swait(u32x16 (&r)[2]) { asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0]), "+s"(r[1])); }
+
 // Which run of tiles of its stream (blockIdx.y) a workgroup takes.  Workgroups go to the chip's eight XCDs in turn
 // by their linear index, y * gridDim.x + x; with the run taken as x itself an XCD would get the runs x = k, k + 8, ...
 // of EVERY stream, and when streams have different numbers of runs (a ragged append: the grid is sized for the
@@ -60,84 +71,187 @@ __device__ __forceinline__ int chunk_of_workgroup()
     return (int)((blockIdx.x + blockIdx.y) % gridDim.x);
 }
 
-__device__ __forceinline__ u32x16 sload16(const uint32_t *p)
+// Range of the differences of the vector x from the pattern m, in binary32: the definition.  Both rows are read from
+// memory (few lanes do this; the vector held in registers across it spills), kStep pieces of each in flight.
+template <int NC>
+__device__ __forceinline__ float minmax_distance(const __half *x, const __half *m)
 {
-    u32x16 r;
-    asm volatile("s_load_dwordx16 %0, %1, 0x0" : "=s"(r) : "s"(p) : "memory");
-    return r;
-}
-__device__ __forceinline__ void swait2(u32x16 &r0, u32x16 &r1)
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r0), "+s"(r1));
+    constexpr int kStep = 4;
+    // two running maxima and minima, so that consecutive operations do not wait for each other
+    float mxa = -INFINITY, mxb = -INFINITY, mna = INFINITY, mnb = INFINITY;
+    uint4 xv[kStep], mv[kStep];
+#pragma unroll
+    for (int i = 0; i < kStep; ++i) {
+        xv[i] = *reinterpret_cast<const uint4 *>(x + 8 * i);
+        mv[i] = *reinterpret_cast<const uint4 *>(m + 8 * i);
+    }
+#pragma unroll
+    for (int c0 = 0; c0 < NC; c0 += kStep) {
+        uint4 xw[kStep], mw[kStep];
+        if (c0 + kStep < NC) {
+#pragma unroll
+            for (int i = 0; i < kStep; ++i) {
+                xw[i] = *reinterpret_cast<const uint4 *>(x + 8 * (c0 + kStep + i));
+                mw[i] = *reinterpret_cast<const uint4 *>(m + 8 * (c0 + kStep + i));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+            const uint4 u = xv[i], v = mv[i];
+            const float d0 = sub_lo(u.x, v.x), d1 = sub_hi(u.x, v.x), d2 = sub_lo(u.y, v.y), d3 = sub_hi(u.y, v.y);
+            const float d4 = sub_lo(u.z, v.z), d5 = sub_hi(u.z, v.z), d6 = sub_lo(u.w, v.w), d7 = sub_hi(u.w, v.w);
+            mxa = fmaxf(fmaxf(mxa, d0), d1);
+            mna = fminf(fminf(mna, d0), d1);
+            mxb = fmaxf(fmaxf(mxb, d2), d3);
+            mnb = fminf(fminf(mnb, d2), d3);
+            mxa = fmaxf(fmaxf(mxa, d4), d5);
+            mna = fminf(fminf(mna, d4), d5);
+            mxb = fmaxf(fmaxf(mxb, d6), d7);
+            mnb = fminf(fminf(mnb, d6), d7);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kStep; ++i) {
+            xv[i] = xw[i];
+            mv[i] = mw[i];
+        }
+    }
+    float dist = fmaxf(mxa, mxb) - fminf(mna, mnb);
+    asm volatile("" : "+v"(dist));   // formed here: moved behind a condition, the maxima leave every difference waiting in a register
+    return dist;
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void assign_minmax_kernel(QuantArgs a, int tiles_per_wg)
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void assign_minmax_kernel(QuantArgs a, int tiles_per_wg)
 {
-    const int tid = threadIdx.x, lane = tid & 63, ns = blockIdx.y;
+    // 16-byte pieces of a vector; scalar loads (32 channels each) per step, steps
+    constexpr int NC = D / 8, W = D % 64 == 0 ? 2 : 1, NS = D / (32 * W);
+    const int tid = threadIdx.x, lane = tid & 63, ns = blockIdx.y, P = a.P;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t *Mg = reinterpret_cast<const uint32_t *>(a.patterns + (int64_t)a.sets.set_of(ns) * a.P * kD);
+    const __half *Mh = a.patterns + (int64_t)a.sets.set_of(ns) * P * D;
+    const uint32_t *Mg = reinterpret_cast<const uint32_t *>(Mh);
     take_sequence_entry(a, ns);
     const int n_tiles = a.nq / 64;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     for (int tile = tile0 + wave; tile < tile1; tile += 4) {
-        // the lane's vector, widened
-        float x[kD];
+        uint32_t x[D / 2];   // the lane's vector, two channels per register
         {
-            const __half *row = a.src.row(ns, tile * 64 + lane);
+            const __half *row = a.src.row_d(ns, tile * 64 + lane, D);
 #pragma unroll
-            for (int ch = 0; ch < kRowChunks; ++ch) {
+            for (int ch = 0; ch < NC; ++ch) {
                 const uint4 v = *reinterpret_cast<const uint4 *>(row + 8 * ch);
-                const __half2 *h2 = reinterpret_cast<const __half2 *>(&v);
+                x[4 * ch] = v.x;
+                x[4 * ch + 1] = v.y;
+                x[4 * ch + 2] = v.z;
+                x[4 * ch + 3] = v.w;
+            }
+        }
+        // Scalar loads return in any order, so a wait covers all that are outstanding: the next step's channels are
+        // requested right after the wait for the current ones and arrive under their 64 (96 channels: 32) vector operations.
+        constexpr float c = 9.765625e-4f;
+        uint32_t k1 = 0xffffffffu, k2 = 0xffffffffu, k3 = 0xffffffffu;   // the three smallest bounds, the pattern in the low byte
+        float t1 = 0.f;                                 // |max| + |min| of the first
+        mm_half2 mxa, mxb, mna, mnb;                    // two chains, so that consecutive operations do not wait for each other
+        auto scan = [&](const u32x16 &m, int s) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    x[8 * ch + 2 * k] = __low2float(h2[k]);
-                    x[8 * ch + 2 * k + 1] = __high2float(h2[k]);
+            for (int k = 0; k < 16; k += 4) {
+                const uint32_t m0 = m[k], m1 = m[k + 1], m2 = m[k + 2], m3 = m[k + 3];
+                const mm_half2 r0 = __builtin_bit_cast(mm_half2, x[16 * s + k]) - __builtin_bit_cast(mm_half2, m0);
+                const mm_half2 r1 = __builtin_bit_cast(mm_half2, x[16 * s + k + 1]) - __builtin_bit_cast(mm_half2, m1);
+                const mm_half2 r2 = __builtin_bit_cast(mm_half2, x[16 * s + k + 2]) - __builtin_bit_cast(mm_half2, m2);
+                const mm_half2 r3 = __builtin_bit_cast(mm_half2, x[16 * s + k + 3]) - __builtin_bit_cast(mm_half2, m3);
+                if (s == 0 && k == 0) {
+                    mxa = __builtin_elementwise_maximum(r0, r1);
+                    mna = __builtin_elementwise_minimum(r0, r1);
+                    mxb = __builtin_elementwise_maximum(r2, r3);
+                    mnb = __builtin_elementwise_minimum(r2, r3);
+                } else {
+                    mxa = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxa, r0), r1);
+                    mna = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mna, r0), r1);
+                    mxb = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxb, r2), r3);
+                    mnb = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mnb, r2), r3);
                 }
             }
-        }
-        float best = INFINITY;
-        int best_p = 0;
-        // A pattern row is taken in two halves of 64 channels (32 scalar registers each).  Scalar loads return
-        // in any order, so a wait covers all that are outstanding: the next half is requested right after the
-        // wait for the current one and arrives under the 192 vector operations of that half.
-        u32x16 a0 = sload16(Mg), a1 = sload16(Mg + 16), b0, b1;
-        // two running maxima and minima, so that consecutive operations do not wait for each other
-        float mxa, mxb, mna, mnb;
-        auto scan = [&](const u32x16 &m, int c0) {   // channels c0 .. c0+31
-#pragma unroll
-            for (int c4 = 0; c4 < 8; ++c4) {
-                const int c = c0 + 4 * c4;
-                const float d0 = sub_s_lo(x[c], m[2 * c4]), d1 = sub_s_hi(x[c + 1], m[2 * c4]);
-                const float d2 = sub_s_lo(x[c + 2], m[2 * c4 + 1]), d3 = sub_s_hi(x[c + 3], m[2 * c4 + 1]);
-                mxa = fmaxf(fmaxf(mxa, d0), d1);
-                mna = fminf(fminf(mna, d0), d1);
-                mxb = fmaxf(fmaxf(mxb, d2), d3);
-                mnb = fminf(fminf(mnb, d2), d3);
-            }
         };
-        for (int p = 0; p < a.P; ++p) {
-            const uint32_t *mrow = Mg + (size_t)p * (kD / 2);                                   // wave-uniform
-            const uint32_t *mnext = Mg + (size_t)min(p + 1, a.P - 1) * (kD / 2);                // (the last round repeats the last row; unused)
-            swait2(a0, a1);
-            b0 = sload16(mrow + 32);
-            b1 = sload16(mrow + 48);
-            mxa = mxb = -INFINITY;
-            mna = mnb = INFINITY;
-            scan(a0, 0);
-            scan(a1, 32);
-            swait2(b0, b1);
-            a0 = sload16(mnext);
-            a1 = sload16(mnext + 16);
-            scan(b0, 64);
-            scan(b1, 96);
-            const float dist = fmaxf(mxa, mxb) - fminf(mna, mnb);
-            if (dist < best) {   // patterns in increasing order: strict < keeps the lowest index
-                best = dist;
-                best_p = p;
+        u32x16 buf[2][W];
+        auto request = [&](const uint32_t *at, u32x16 (&to)[W]) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) to[w] = sload16(at + 16 * w);
+        };
+        request(Mg, buf[0]);
+        auto pattern = [&](int p, int at) {   // at: which buffer holds (will hold) its first step
+            const uint32_t *mrow = Mg + (size_t)p * (D / 2), *mnext = Mg + (size_t)min(p + 1, P - 1) * (D / 2);   // (past the last row: that row again; unused)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                swait(buf[(s + at) & 1]);
+                request(s + 1 < NS ? mrow + 16 * W * (s + 1) : mnext, buf[(s + at + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);   // (the scheduler would issue the request behind most of the scan)
+#pragma unroll
+                for (int w = 0; w < W; ++w) scan(buf[(s + at) & 1][w], s * W + w);
             }
+            const mm_half2 mx = __builtin_elementwise_maximum(mxa, mxb), mn = __builtin_elementwise_minimum(mna, mnb);
+            const float hi = (float)__builtin_elementwise_maximum(mx[0], mx[1]), lo = (float)__builtin_elementwise_minimum(mn[0], mn[1]);
+            const float t = fabsf(hi) + fabsf(lo);
+            // (not a number - a difference that overflowed fp16 - gives the bound 0 and leads to the exact evaluation)
+            const uint32_t key = (__float_as_uint(fmaxf(fmaf(t, -c, hi - lo), 0.f)) & 0xffffff00u) | (uint32_t)p;
+            t1 = key < k1 ? t : t1;
+            k3 = max(min(k2, k3), min(max(k2, k3), key));   // medians of three
+            k2 = max(min(k1, k2), min(max(k1, k2), key));
+            k1 = min(k1, key);
+        };
+        int p = 0;
+        for (; p + 1 < P; p += 2) {
+            pattern(p, 0);
+            pattern(p + 1, NS % 2);
         }
-        swait2(a0, a1);   // nothing may be in flight into registers that the next tile reuses
-        a.idx[a.map.pos(ns, a.t0 + tile * 64) + lane] = (uint8_t)best_p;
+        if (p < P) pattern(p, 0);
+        swait(buf[0]);   // nothing may be in flight into registers that the next tile reuses
+        swait(buf[1]);
+        int best = (int)(k1 & 0xffu);
+        const float first = __uint_as_float(k1 & 0xffffff00u);
+        // first's own low bits (2^-15 of it) belong to its upper bound
+        const float upper = fmaf(first, 6.103515625e-05f, fmaf(t1, 2.f * c, first));
+        const bool two = P > 1 && !(__uint_as_float(k2 & 0xffffff00u) > upper), more = P > 2 && two && !(__uint_as_float(k3 & 0xffffff00u) > upper);
+        if (two && !more) {
+            const __half *row = a.src.row_d(ns, tile * 64 + lane, D);
+            float bd = INFINITY;
+            int bi = 0;
+#pragma unroll 1
+            for (uint32_t i = 0, q = k1; i < 2; ++i, q = k2) {
+                const int cand = (int)(q & 0xffu);
+                const float dist = minmax_distance<NC>(row, Mh + (int64_t)cand * D);
+                const bool nearer = dist < bd || (dist == bd && cand < bi);
+                bd = nearer ? dist : bd;
+                bi = nearer ? cand : bi;
+            }
+            best = bi;
+        }
+        unsigned long long todo = __ballot(more);
+        while (todo) {
+            const int col = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const __half *row = a.src.row_d(ns, tile * 64 + col, D);
+            float bd = INFINITY;
+            int bi = 0;
+            for (int q = lane; q < P; q += 64) {
+                const float dist = minmax_distance<NC>(row, Mh + (int64_t)q * D);
+                if (dist < bd) {   // the lane's patterns in increasing order
+                    bd = dist;
+                    bi = q;
+                }
+            }
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const float od = __shfl_xor(bd, off);
+                const int oi = __shfl_xor(bi, off);
+                if (od < bd || (od == bd && oi < bi)) {
+                    bd = od;
+                    bi = oi;
+                }
+            }
+            if (lane == col) best = bi;
+        }
+        a.idx[a.map.pos(ns, a.t0 + tile * 64) + lane] = (uint8_t)best;
     }
 }
 
@@ -896,13 +1010,19 @@ static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t ma
 }
 
 // Min-max metric: the search kernel fills the index array, the quantizers then take the indices from there.
-static hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
+template <int D>
+static hipError_t launch_minmax(const QuantArgs &a, hipStream_t s)
 {
     const int n_tiles = a.nq / 64;
     int tpw = tiles_per_wg(n_tiles, a.n_streams);
     if (tpw < 4) tpw = 4;   // four waves, a 64-vector tile each per round
-    hipLaunchKernelGGL(assign_minmax_kernel, dim3((n_tiles + tpw - 1) / tpw, a.n_streams), dim3(256), 0, s, a, tpw);
+    hipLaunchKernelGGL(assign_minmax_kernel<D>, dim3((n_tiles + tpw - 1) / tpw, a.n_streams), dim3(256), 0, s, a, tpw);
     return hipGetLastError();
+}
+
+hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
+{
+    return a.d == kD ? launch_minmax<kD>(a, s) : a.d == 96 ? launch_minmax<96>(a, s) : launch_minmax<256>(a, s);
 }
 
 hipError_t launch_quantize_k(const QuantArgs &a_in, hipStream_t s)

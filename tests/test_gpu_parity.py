@@ -971,3 +971,24 @@ def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
     for _ in range(2):
         new = _mining_step_parity(oracle, pk, K[0], P, cur, check_sets=range(2))
         cur = np.stack([new[s] for s in range(2)])
+
+
+@pytest.mark.parametrize("d,P,n_c", [
+    (128, 1, 4), (128, 2, 1), (128, 33, 16), (128, 64, 1), (128, 65, 48), (128, 200, 100), (128, 256, 1),
+    (96, 7, 7), (96, 63, 1), (96, 130, 40),
+    (256, 20, 10), (256, 64, 1), (256, 129, 60), (256, 256, 128),     # 256 rows of 256 channels do not fit LDS
+])
+def test_minmax_search_parity(oracle, pk, d, P, n_c):
+    """The min-max rule's search over table sizes (one pattern, odd counts, block edges of 64, several blocks, the largest)
+    with clustered vectors, where few patterns stay candidates, and with one cluster only, where nearly all do; two equal
+    patterns, so that the lowest index must win: indices, codes and parameters are bit-equal."""
+    T, hkv = 448, 2
+    K, V = synth.make_kv(40 + d + P, synth.KVSpec(1, 1, hkv, hkv, T, d, n_c))
+    Mk, Mv = K[0][:, :P].copy(), V[0][:, T - P:].copy()
+    if P > 2:
+        Mk[:, P - 1], Mv[:, P // 2] = Mk[:, 0], Mv[:, 1]
+    Mk, Mv = np.ascontiguousarray(Mk).view(np.uint16), np.ascontiguousarray(Mv).view(np.uint16)
+    kw = dict(n_seq=1, n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, seqs_per_set=0, bits=2, group=32, recent=0,
+              flush=64, t_capacity=T, metric=1)
+    oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [64, T - 64])
+    assert compare_caches(oracle, oc, gc, 1) == 0
