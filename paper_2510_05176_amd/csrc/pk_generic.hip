@@ -26,366 +26,6 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
-// ---------------------------------------------------------------------------------------------- Euclidean search
-// Nearest pattern under the Euclidean rule on the matrix cores at head dimension D (96 or 256), the scheme of the
-// tuned search with D / 32 operand steps: a wave ranks a 16-vector tile against 16 patterns per round,
-// e = x.m - (|m|^2 + |x|^2) / 2 = -|x - m|^2 / 2 from v_mfma_f32_16x16x32_f16 (fp16 products are exact in binary32,
-// only the accumulation rounds); the binary32 patterns of e, read as unsigned integers with the pattern index in
-// the low byte, order like the distances; best and second best are tracked, and a vector whose gap between the
-// two is inside the rounding band of that form is evaluated again exactly by the whole wave - the squared binary32
-// differences over all patterns, lowest index on ties - so every index equals the exact argmin.  The table lives
-// in LDS (rows of D + 16 halves: 16-byte reads of 16 rows x 4 column groups fall on distinct banks), the whole of it
-// or, when it would not fit beside a second workgroup, one workgroup per CU.
-template <int D>
-struct GenSearchLds {
-    static constexpr int kStride = D + 16;   // halves per table row
-    __half *tab;      // [pad16(P)][kStride], rows past P zero
-    float *nh;        // [pad16(P)]  -|m|^2 / 2, -inf past P
-    float *red;       // [4]
-    __half *xrow;     // [4 waves][D]: the vector under exact evaluation
-    __device__ GenSearchLds(unsigned char *base, int P)
-    {
-        tab = reinterpret_cast<__half *>(base);
-        nh = reinterpret_cast<float *>(tab + (size_t)pad16(P) * kStride);
-        red = nh + pad16(P);
-        xrow = reinterpret_cast<__half *>(red + 4);
-    }
-    static size_t bytes(int P) { return (size_t)pad16(P) * kStride * 2 + (size_t)pad16(P) * 4 + 16 + (size_t)4 * D * 2; }
-};
-
-// Stage the table of one pattern set and the row norms; returns max_p |m_p|^2.  All 256 threads; ends with a barrier.
-template <int D>
-__device__ __forceinline__ float gen_search_stage(const __half *Mg, int P, const GenSearchLds<D> &sh)
-{
-    constexpr int kStride = GenSearchLds<D>::kStride;
-    const int tid = threadIdx.x, Pp = pad16(P);
-    for (int i = tid; i < Pp * (D / 8); i += 256) {
-        const int r = i / (D / 8), ch = i - r * (D / 8);
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r < P) v = *reinterpret_cast<const uint4 *>(Mg + (int64_t)r * D + 8 * ch);
-        *reinterpret_cast<uint4 *>(sh.tab + r * kStride + 8 * ch) = v;
-    }
-    __syncthreads();
-    float mx = 0.f;
-    for (int r = tid; r < Pp; r += 256) {
-        float acc = 0.f;
-        for (int ch = 0; ch < D / 8; ++ch) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(sh.tab + r * kStride + 8 * ch);
-            const half2_t *h = reinterpret_cast<const half2_t *>(&v);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
-        }
-        sh.nh[r] = r < P ? -0.5f * acc : -INFINITY;
-        mx = fmaxf(mx, acc);
-    }
-    mx = wave_max(mx);
-    if ((tid & 63) == 0) sh.red[tid >> 6] = mx;
-    __syncthreads();
-    return fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
-}
-
-// One 16-vector tile by one wave: row = the lane's vector (token n = lane % 16 of the tile).  Every lane of column n
-// returns the nearest pattern of token n and its squared distance (from the expanded form, 8 mantissa bits dropped,
-// or the exact one where the vector was evaluated again).
-template <int D>
-__device__ __forceinline__ void gen_search_tile(const __half *row, const GenSearchLds<D> &sh, float norm2_max, int P, __half *xrow,
-                                                int lane, int &best, float &best_d)
-{
-    constexpr int KS = D / 32;   // operand steps of 32 channels
-    constexpr int kStride = GenSearchLds<D>::kStride;
-    const int n = lane & 15, kb = lane >> 4, Pp = pad16(P);
-    uint4 xb[KS];   // B operand: token n, channels 32 s + 8 kb + j
-#pragma unroll
-    for (int s = 0; s < KS; ++s) xb[s] = *reinterpret_cast<const uint4 *>(row + 32 * s + 8 * kb);
-    float xx = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const half2_t *h = reinterpret_cast<const half2_t *>(&xb[s]);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) xx = __builtin_amdgcn_fdot2(h[k], h[k], xx, false);
-    }
-    xx += __shfl_xor(xx, 16);
-    xx += __shfl_xor(xx, 32);
-    const float hx = 0.5f * xx;
-    uint32_t k1 = 0xffffffffu, k2 = 0xffffffffu;
-    for (int p0 = 0; p0 < Pp; p0 += 16) {
-        const __half *arow = sh.tab + (p0 + n) * kStride + 8 * kb;
-        const float4 nh = *reinterpret_cast<const float4 *>(sh.nh + p0 + 4 * kb);
-        floatx4_t e = {nh.x - hx, nh.y - hx, nh.z - hx, nh.w - hx};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) e = mfma_f16(*reinterpret_cast<const uint4 *>(arow + 32 * s), xb[s], e);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t key = __builtin_amdgcn_perm(__float_as_uint(e[i]), (uint32_t)(p0 + 4 * kb + i), 0x07060500u);
-            k2 = max(min(k1, k2), min(max(k1, k2), key));   // second smallest so far
-            k1 = min(k1, key);
-        }
-    }
-#pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {   // the four lane groups of the column
-        const uint32_t o1 = (uint32_t)__shfl_xor((int)k1, off), o2 = (uint32_t)__shfl_xor((int)k2, off);
-        k2 = min(min(k2, o2), max(k1, o1));
-        k1 = min(k1, o1);
-    }
-    best = (int)(k1 & 0xffu);
-    const float bv = -2.f * __uint_as_float(k1 & 0xffffff00u), second = -2.f * __uint_as_float(k2 & 0xffffff00u);
-    best_d = fmaxf(bv, 0.f);
-    // rounding band: the accumulation over KS matrix instructions (far below 2^-21 (|x|^2 + |m|^2) each) and the 8
-    // mantissa bits the keys drop, with a wide margin
-    const float band = (KS > 4 ? 1.52587890625e-05f : 7.62939453125e-06f) * (xx + norm2_max) + 6.103515625e-05f * second;
-    const bool flag = P > 1 && !(second - bv > band);
-    unsigned long long todo = __ballot(flag) & 0xffffull;   // one bit per column
-    while (todo) {
-        const int col = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        if (n == col) {
-#pragma unroll
-            for (int s = 0; s < KS; ++s) *reinterpret_cast<uint4 *>(xrow + 32 * s + 8 * kb) = xb[s];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        float bd = INFINITY;
-        int bi = 0x7fffffff;
-        for (int p = lane; p < P; p += 64) {
-            const __half *m = sh.tab + p * kStride;
-            float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 4
-            for (int ch = 0; ch < D / 8; ++ch) {
-                const uint4 mv = *reinterpret_cast<const uint4 *>(m + 8 * ch);
-                const uint4 xv = *reinterpret_cast<const uint4 *>(xrow + 8 * ch);
-                const float d0 = sub_lo(xv.x, mv.x), d1 = sub_hi(xv.x, mv.x), d2 = sub_lo(xv.y, mv.y), d3 = sub_hi(xv.y, mv.y);
-                const float d4 = sub_lo(xv.z, mv.z), d5 = sub_hi(xv.z, mv.z), d6 = sub_lo(xv.w, mv.w), d7 = sub_hi(xv.w, mv.w);
-                a0 = fmaf(d0, d0, a0); a1 = fmaf(d1, d1, a1); a2 = fmaf(d2, d2, a2); a3 = fmaf(d3, d3, a3);
-                a0 = fmaf(d4, d4, a0); a1 = fmaf(d5, d5, a1); a2 = fmaf(d6, d6, a2); a3 = fmaf(d7, d7, a3);
-            }
-            const float dist = (a0 + a1) + (a2 + a3);
-            if (dist < bd) {
-                bd = dist;
-                bi = p;
-            }
-        }
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const float od = __shfl_xor(bd, off);
-            const int oi = __shfl_xor(bi, off);
-            if (od < bd || (od == bd && oi < bi)) {
-                bd = od;
-                bi = oi;
-            }
-        }
-        if (n == col) {
-            best = bi;
-            best_d = bd;
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// Pattern index of every vector to quantize under the Euclidean rule: a workgroup stages its stream's table once and
-// takes tiles_per_wg tiles of 16 vectors, a wave per tile.
-template <int D>
-__global__ __launch_bounds__(256) void gen_assign_mfma_kernel(QuantArgs a, int tiles_per_wg)
-{
-    extern __shared__ __align__(16) unsigned char gen_search_smem[];
-    const GenSearchLds<D> sh(gen_search_smem, a.P);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ns = blockIdx.y;
-    take_sequence_entry(a, ns);
-    const int n_tiles = a.nq / 16;   // nq is a multiple of the group size
-    const int tile0 = blockIdx.x * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
-    if (tile0 >= n_tiles) return;    // a ragged append: sized for the longest sequence
-    const float norm2_max = gen_search_stage<D>(a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D, a.P, sh);
-    for (int tile = tile0 + wave; tile < tile1; tile += 4) {
-        int best;
-        float bd;
-        gen_search_tile<D>(a.src.row_d(ns, tile * 16 + (lane & 15), D), sh, norm2_max, a.P, sh.xrow + wave * D, lane, best, bd);
-        if (lane < 16) a.idx[a.map.pos(ns, a.t0 + tile * 16) + lane] = (uint8_t)best;
-    }
-}
-
-// ---------------------------------------------------------------------------------------------- quantize-append
-// K: one workgroup per (group of G tokens, stream), thread <-> channel.  Two passes over the group's residuals (the
-// second recomputes them): minimum / maximum -> parameters, then codes; a plane word of 32 channels is a wave ballot.
-// The group's indices are staged in LDS and the vectors and pattern rows are requested 16 tokens at a time, without
-// branches (threads past the head dimension read its last channel and store nothing).
-__global__ __launch_bounds__(kGenThreads) void gen_quantize_k_kernel(QuantArgs a)
-{
-    __shared__ uint8_t idx_s[128];   // G <= 128
-    const int c = threadIdx.x, lane = c & 63, ns = blockIdx.y, g = blockIdx.x, d = a.d, G = a.G;
-    take_sequence_entry(a, ns);
-    if (g * G >= a.nq) return;   // a ragged append: sized for the longest sequence
-    const bool on = c < d;
-    const int cc = on ? c : d - 1;
-    const __half *M = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * d + cc;
-    const int64_t p0 = a.map.pos(ns, a.t0 + g * G);   // a group never straddles a page
-    if (c < G) idx_s[c] = a.idx[p0 + c];
-    __syncthreads();
-    float mn = INFINITY, mx = -INFINITY;
-    for (int t0 = 0; t0 < G; t0 += 16) {
-        float xr[16], mr[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            xr[k] = h2f(a.src.row_d(ns, g * G + t0 + k, d)[cc]);
-            mr[k] = h2f(M[(int64_t)idx_s[t0 + k] * d]);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float r = xr[k] - mr[k];
-            mn = fminf(mn, r);
-            mx = fmaxf(mx, r);
-        }
-    }
-    const GroupParams gp = group_params(mn, mx, a.bits);
-    if (on) {
-        a.scale[(p0 / G) * d + c] = __ushort_as_half(gp.s16);
-        a.zero[(p0 / G) * d + c] = __ushort_as_half(gp.z16);
-    }
-    const int words = d / 32;
-    const int w = (c >> 6) * 2 + (lane >> 5);
-    const bool writer = (lane & 31) == 0 && w < words;
-    for (int t0 = 0; t0 < G; t0 += 16) {
-        float xr[16], mr[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            xr[k] = h2f(a.src.row_d(ns, g * G + t0 + k, d)[cc]);
-            mr[k] = h2f(M[(int64_t)idx_s[t0 + k] * d]);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int code = on ? quantize_one(xr[k] - mr[k], gp, a.bits) : 0;
-            for (int j = 0; j < a.bits; ++j) {
-                const unsigned long long m = __ballot((code >> j) & 1);   // bit l <-> channel 64 * wave + l
-                if (writer) a.codes_k[((p0 + t0 + k) * words + w) * a.bits + j] = (uint32_t)(m >> (lane & 32));
-            }
-        }
-    }
-}
-
-// Minimum or maximum over each half (32 lanes) of a wave with data-parallel-primitive moves, no LDS traffic: an
-// inclusive scan over the rows of 16 lanes (row_shr 1, 2, 4, 8; a lane without a source keeps its own value), then
-// lane 15 of rows 0 and 2 is broadcast into rows 1 and 3 (row_bcast15).  The result is in lanes 31 and 63.
-template <bool MAX>
-__device__ __forceinline__ float half_wave_reduce_to_last(float v)
-{
-#define PK_DPP_STEP(CTRL, ROWS)                                                                                               \
-    {                                                                                                                         \
-        const float o = __builtin_bit_cast(                                                                                   \
-            float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), CTRL, ROWS, 0xf, false)); \
-        v = MAX ? fmaxf(v, o) : fminf(v, o);                                                                                  \
-    }
-    PK_DPP_STEP(0x111, 0xf)
-    PK_DPP_STEP(0x112, 0xf)
-    PK_DPP_STEP(0x114, 0xf)
-    PK_DPP_STEP(0x118, 0xf)
-    PK_DPP_STEP(0x142, 0xa)
-#undef PK_DPP_STEP
-    return v;
-}
-
-// V: one workgroup per (16-token unit, stream) in three phases.  (1) thread <-> channel: residuals of the 16 tokens;
-// minimum and maximum of the residuals (and, for the adaptive threshold, of the vector) over every 32 channels by
-// data-parallel-primitive moves inside half a wave, left in LDS.  (2) thread <-> (token, channel group): the
-// threshold's decision of Sec. 3.3 for the whole vector, the group's minimum and maximum from the halves, the stored
-// parameters - all 16 tokens of a group in one pass - to LDS and, 16 tokens side by side, to memory.  (3) thread <->
-// channel again: codes against the parameters of its group, the bits of the channel's 16 tokens collected in the
-// words it stores.
-__global__ __launch_bounds__(kGenThreads) void gen_quantize_v_kernel(QuantArgs a)
-{
-    constexpr int kHalves = kGenThreads / 32;
-    __shared__ float4 half_mm[16][kHalves];     // per token and 32 channels: min r, max r, min x, max x
-    __shared__ float4 par[16][kHalves];         // per token and channel group: z, 1/s, s, raw flag
-    const int c = threadIdx.x, ns = blockIdx.y, u = blockIdx.x, d = a.d;
-    take_sequence_entry(a, ns);
-    if (u * 16 >= a.nq) return;   // a ragged append: sized for the longest sequence
-    const bool on = c < d;
-    const int cc = on ? c : d - 1;   // threads past the head dimension read its last channel and store nothing
-    const int Gc = a.G < d ? a.G : d, NG = d / Gc, g = cc / Gc;
-    const __half *M = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * d + cc;
-    const int64_t p0 = a.map.pos(ns, a.t0 + u * 16);   // a multiple of 16: the unit's 16 index bytes are one aligned piece
-    const uint4 iw = *reinterpret_cast<const uint4 *>(a.idx + p0);
-    const uint32_t iws[4] = {iw.x, iw.y, iw.z, iw.w};
-    const bool thresholded = a.v_rho > 0.f;
-    float xs[16], rs[16];   // the unit's vectors and residuals
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        xs[i] = h2f(a.src.row_d(ns, u * 16 + i, d)[cc]);
-        rs[i] = h2f(M[(int64_t)((iws[i >> 2] >> (8 * (i & 3))) & 255) * d]);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        rs[i] = xs[i] - rs[i];
-        const float rmn = half_wave_reduce_to_last<false>(on ? rs[i] : INFINITY);
-        const float rmx = half_wave_reduce_to_last<true>(on ? rs[i] : -INFINITY);
-        float xmn = 0.f, xmx = 0.f;
-        if (thresholded) {   // the vector's own range is needed for the threshold only
-            xmn = half_wave_reduce_to_last<false>(on ? xs[i] : INFINITY);
-            xmx = half_wave_reduce_to_last<true>(on ? xs[i] : -INFINITY);
-        }
-        if ((c & 31) == 31) half_mm[i][c >> 5] = make_float4(rmn, rmx, xmn, xmx);
-    }
-    __syncthreads();
-    if (c < 16 * NG) {   // token i, channel group gg
-        const int i = c & 15, gg = c >> 4;
-        bool raw = false;   // the vector itself is quantized, stored under the index that says so
-        if (thresholded) {
-            float4 row = half_mm[i][0];
-            for (int k = 1; k < d / 32; ++k) {
-                const float4 o = half_mm[i][k];
-                row = make_float4(fminf(row.x, o.x), fmaxf(row.y, o.y), fminf(row.z, o.z), fmaxf(row.w, o.w));
-            }
-            raw = !((row.y - row.x) <= a.v_rho * (row.w - row.z));
-        }
-        float mn = INFINITY, mx = -INFINITY;
-        for (int k = gg * (Gc / 32); k < (gg + 1) * (Gc / 32); ++k) {
-            const float4 o = half_mm[i][k];
-            mn = fminf(mn, raw ? o.z : o.x);
-            mx = fmaxf(mx, raw ? o.w : o.y);
-        }
-        const GroupParams gp = group_params(mn, mx, a.bits);
-        par[i][gg] = make_float4(gp.z, gp.inv, gp.s, raw ? 1.f : 0.f);
-        a.scale[((p0 >> 4) * NG + gg) * 16 + i] = __ushort_as_half(gp.s16);
-        a.zero[((p0 >> 4) * NG + gg) * 16 + i] = __ushort_as_half(gp.z16);
-        if (gg == 0 && raw) a.idx[p0 + i] = (uint8_t)PK_NO_PATTERN;
-    }
-    __syncthreads();
-    uint32_t word[2] = {0u, 0u};
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float4 pr = par[i][g];
-        GroupParams gp;
-        gp.z = pr.x;
-        gp.inv = pr.y;
-        gp.s = pr.z;
-        const int code = quantize_one(pr.w != 0.f ? xs[i] : rs[i], gp, a.bits);
-        for (int j = 0; j < a.bits; ++j) word[j >> 1] |= (uint32_t)((code >> j) & 1) << (16 * (j & 1) + i);
-    }
-    if (on) {
-        uint32_t *codes = reinterpret_cast<uint32_t *>(a.codes_v);
-        const int64_t w0 = (((p0 >> 4) * 16 + (c & 15)) * (d / 16) + (c >> 4)) * (a.bits / 2);
-        for (int k = 0; k < a.bits / 2; ++k) codes[w0 + k] = word[k];
-    }
-}
-
-__global__ __launch_bounds__(256) void gen_tail_copy_kernel(TailCopyArgs a)
-{
-    const int n = blockIdx.y, side = blockIdx.z, chunks = a.d / 8;
-    if (a.seq_table) {   // a ragged append: the ring state and the range of the stream's own sequence
-        const int32_t *e = a.seq_table + (int64_t)(n / a.n_kv_heads) * kSeqEntry;
-        a.ring_start = e[kSeqRingStart];
-        a.n_ring = e[kSeqNRing];
-        a.i0 = e[kSeqI0];
-        a.i1 = e[kSeqI1];
-    }
-    const int64_t work = (int64_t)(a.i1 - a.i0) * chunks;
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= work) return;
-    const int i = a.i0 + (int)(w / chunks), ch = (int)(w % chunks);
-    const __half *fresh = side == 0 ? a.fresh_k : a.fresh_v;
-    __half *ring = side == 0 ? a.ring_k : a.ring_v;
-    const uint4 v = *reinterpret_cast<const uint4 *>(fresh + (int64_t)n * a.fresh_stride + (int64_t)(i - a.n_ring) * a.d + ch * 8);
-    const int slot = (int)(((int64_t)a.ring_start + i) % a.ring_len);
-    *reinterpret_cast<uint4 *>(ring + ((int64_t)n * a.ring_len + slot) * a.d + ch * 8) = v;
-}
-
 // ---------------------------------------------------------------------------------------------- window pattern
 __global__ __launch_bounds__(kGenThreads) void gen_window_pattern_kernel(const __half *x, int64_t set_stride, int n, int d,
                                                                         __half *out, int64_t out_stride)
@@ -815,48 +455,6 @@ hipError_t launch_gen_decode_split(const DecodeArgs &a, dim3 grid, size_t lds, h
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------- launchers
-template <int D>
-static hipError_t launch_gen_assign_mfma(const QuantArgs &a, hipStream_t s)
-{
-    static LdsOptIn opt_in;   // per instantiation: the most it needs is a table of 256 patterns
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&gen_assign_mfma_kernel<D>), opt_in, GenSearchLds<D>::bytes(256));
-    if (e != hipSuccess) return e;
-    // aim at ~2048 workgroups, each staging the table once for at least 16 and at most 256 tiles of 16 vectors
-    const int n_tiles = a.nq / 16;
-    const int64_t total = (int64_t)n_tiles * a.n_streams;
-    int tpw = (int)((total + 2047) / 2048);
-    tpw = tpw < 16 ? 16 : tpw > 256 ? 256 : tpw;
-    hipLaunchKernelGGL(gen_assign_mfma_kernel<D>, dim3((n_tiles + tpw - 1) / tpw, a.n_streams), dim3(256), GenSearchLds<D>::bytes(a.P), s, a,
-                       tpw);
-    return hipGetLastError();
-}
-
-hipError_t launch_generic_quantize(const QuantArgs &a, bool v_side, hipStream_t s)
-{
-    if (a.nq <= 0) return hipSuccess;
-    if (a.d != 96 && a.d != 256) return hipErrorInvalidValue;
-    hipError_t e;
-    if (a.metric == PK_METRIC_MINMAX)
-        e = launch_assign_minmax(a, s);
-    else
-        e = a.d == 96 ? launch_gen_assign_mfma<96>(a, s) : launch_gen_assign_mfma<256>(a, s);
-    if (e != hipSuccess) return e;
-    const dim3 block(a.d <= 128 ? 128 : kGenThreads);   // thread <-> channel: two waves hold 96 channels (and the 128 indices of a group)
-    if (v_side)
-        hipLaunchKernelGGL(gen_quantize_v_kernel, dim3(a.nq / 16, a.n_streams), block, 0, s, a);
-    else
-        hipLaunchKernelGGL(gen_quantize_k_kernel, dim3(a.nq / a.G, a.n_streams), block, 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_generic_tail_copy(const TailCopyArgs &a, hipStream_t s)
-{
-    const int64_t work = (int64_t)(a.i1 - a.i0) * (a.d / 8);
-    if (work <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gen_tail_copy_kernel, dim3((unsigned)((work + 255) / 256), a.n_streams, 2), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_generic_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, int d, __half *out,
                                          int64_t out_stride, hipStream_t s)
 {

@@ -152,7 +152,7 @@ struct QuantArgs {
     SetMap sets;
     const __half *patterns;   // [n_sets][P][kD]
     int32_t P, metric, bits, G;
-    int32_t d;                // head dimension: kD runs the tuned kernels, 96 and 256 the generic ones (pk_generic.hip)
+    int32_t d;                // head dimension: 96, 128 or 256
     int32_t idx_given;        // the index array already holds every vector's pattern (min-max metric: searched by a kernel of its own)
     float v_rho;              // V side: adaptive threshold (0 = off)
     int32_t n_streams;
@@ -186,7 +186,6 @@ __device__ __forceinline__ void take_sequence_entry(QuantArgs &a, int stream)
 
 hipError_t launch_quantize_k(const QuantArgs &a, hipStream_t s);
 hipError_t launch_quantize_v(const QuantArgs &a, hipStream_t s);
-hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s);   // min-max search into a.idx, any head dimension
 
 struct TailCopyArgs {
     const __half *fresh_k, *fresh_v;
@@ -232,8 +231,6 @@ hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets
                                  hipStream_t s);
 
 // Head dimensions other than kD (pk_generic.hip): plain kernels, thread <-> channel, same results to the same bars.
-hipError_t launch_generic_quantize(const QuantArgs &a, bool v_side, hipStream_t s);
-hipError_t launch_generic_tail_copy(const TailCopyArgs &a, hipStream_t s);
 hipError_t launch_generic_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, int d, __half *out,
                                          int64_t out_stride, hipStream_t s);
 

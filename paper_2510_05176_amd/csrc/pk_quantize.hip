@@ -9,8 +9,8 @@
 // that the sequence is exactly what is written.
 //
 // Kernels, in file order: assign_minmax_kernel (the min-max selection rule of Sec. 3.2 as a search of its own, at every
-// head dimension: it writes the indices and the quantizers below then take them as given); quantize_k_kernel (groups of 128 tokens,
-// a workgroup of eight waves per tile) and quantize_k_wave_kernel (groups of 32 / 64 tokens, a wave per group); quantize_v_kernel
+// head dimension: it writes the indices and the quantizers below then take them as given); quantize_k_group_kernel (groups of 128 tokens,
+// a workgroup of eight waves per group) and quantize_k_wave_kernel (groups of 32 / 64 tokens, a wave per group); quantize_v_kernel
 // (a wave per 16-token unit); tail_copy_kernel (the fp16 ring); seq_table_kernel (per-sequence launch parameters
 // of a ragged append).  Under the Euclidean rule the quantizers search on the matrix cores (pk_assign_mfma.h).
 #pragma clang fp contract(off)
@@ -257,19 +257,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
 
 // ===========================================================================
 // Euclidean metric: nearest pattern on the matrix cores (pk_assign_mfma.h).  A wave owns 16-token
-// tiles; lane 16*kb + n holds, of token n, the 32 channels 32*k + 8*kb + j (k < 4, j < 8) - the MFMA
-// B-operand layout - and keeps the residuals of those channels in registers through quantization and
-// bit-plane packing.
+// tiles; lane 16*kb + n holds, of token n, the D/4 channels 32*k + 8*kb + j (k < D/32, j < 8) - the MFMA
+// B-operand layout - and forms the residuals of those channels in registers.
 //
-// K: residuals also go to an LDS tile so that the per-channel minimum / maximum over the group's tokens
-//    is a column scan; the parameters come back through LDS; every lane then forms one byte of each
-//    plane word (8 channels) and stores it.
+// K: the per-channel minimum / maximum over the group's tokens goes through a small LDS tile of the wave, 32 channels at a
+//    time; the parameters come back through LDS; every lane then forms one byte of each plane word (8 channels).
 // V: everything per token stays inside the wave: group minimum / maximum by two cross-lane steps,
 //    16 codes per plane packed per lane, and a 16x16 bit transpose across the 16 token lanes turns
 //    them into the words of 16 tokens per channel.
+// The kernels are templates on the head dimension D: 128, and 96 and 256 (the other two head sizes that Sec. 3.3 names),
+// which had a search kernel and thread <-> channel quantizers of their own that read the vectors three times: 256 streams x
+// 4096 vectors of 96 channels in 32-token groups 583 -> 154 us, of 256 channels in 64-token groups (whole append) 1150 ->
+// 350 us.
 // ===========================================================================
-
-constexpr int kRStride = kD + 4;           // floats per row of the residual tile (16-byte aligned rows, bank skew 4)
 
 // (sub_lo / sub_hi, the fp16 differences with one rounding, live in pk_assign_mfma.h: the exact search uses them too)
 __device__ __forceinline__ float subz_lo(float x, uint32_t z)   // x - half(z.lo)
@@ -303,102 +303,76 @@ __device__ __forceinline__ uint32_t plane_byte_shifted(uint32_t lo, uint32_t hi,
     return __builtin_amdgcn_udot4(hi & m, 0x80402010u, acc, false);
 }
 
-struct TileShared {
-    __half *tab;      // [pad16(P)][kTabStride]
+// The pattern table at the start of the dynamic LDS of every quantizer: rows, -|m|^2 / 2, one maximum per wave.
+struct TableLds {
+    __half *tab;      // [pad16(P)][kTabStrideOf<D>]
     float *nh;        // [pad16(P)]
-    unsigned char *wsc;   // V: [4 waves][kWaveScratch] (re-evaluation row, output staging)
-    float *red;       // [8]: one maximum per wave from stage_patterns
-    float *rt;        // K: [TT][kRStride]
-    uint16_t *pz;     // K: [TT/G][kD] zero points (fp16 bits), then [TT/G][kD] scales
-    float *pinv;      // K: [TT/G][kD] 1/s
+    float *red;       // [16]
 };
-
-// Per-wave output staging: the pieces a wave produces for its 16 tokens are put together in LDS so that
-// every global store is one contiguous run of 8- or 16-byte lane pieces.
-constexpr int kWsRow = 0;          // 256 B: one vector for the exact re-evaluation
-constexpr int kWsCodes = 256;      // up to 1024 B: the unit's code words in memory order
-constexpr int kWsIdx = 1280;       // 16 B: pattern indices
-constexpr int kWsScale = 1296;     // up to 128 B: scales [group][16]
-constexpr int kWsZero = 1424;      // up to 128 B: zero points [group][16]
-constexpr int kWaveScratch = 1552;
-
-// TT = 0: no residual tile (V)
-__host__ __device__ inline size_t carve_offsets(int P, int TT, int G, size_t (&o)[7])
+template <int D>
+__host__ __device__ constexpr size_t table_lds_bytes(int P)
 {
-    size_t at = 0;
-    o[0] = at; at += (size_t)pad16(P) * kTabStride * 2;
-    o[1] = at; at += (size_t)pad16(P) * 4;
-    o[2] = at; at += TT ? 0 : 4 * kWaveScratch;   // K stages in its own residual rows instead
-    o[3] = at; at += 32;
-    o[4] = at; at += (size_t)TT * kRStride * 4;
-    const int ngrp = TT ? TT / G : 0;
-    o[5] = at; at += (size_t)ngrp * kD * 2 * 2;
-    o[6] = at; at += (size_t)ngrp * kD * 4;
-    return at;
+    return (size_t)pad16(P) * kTabStrideOf<D> * 2 + (size_t)pad16(P) * 4 + 64;
 }
-
-__device__ __forceinline__ TileShared carve(unsigned char *smem, int P, int TT, int G)
+template <int D>
+__device__ __forceinline__ TableLds table_lds(unsigned char *smem, int P)
 {
-    size_t o[7];
-    carve_offsets(P, TT, G, o);
-    TileShared t;
-    t.tab = reinterpret_cast<__half *>(smem + o[0]);
-    t.nh = reinterpret_cast<float *>(smem + o[1]);
-    t.wsc = smem + o[2];
-    t.red = reinterpret_cast<float *>(smem + o[3]);
-    t.rt = reinterpret_cast<float *>(smem + o[4]);
-    t.pz = reinterpret_cast<uint16_t *>(smem + o[5]);
-    t.pinv = reinterpret_cast<float *>(smem + o[6]);
+    TableLds t;
+    t.tab = reinterpret_cast<__half *>(smem);
+    t.nh = reinterpret_cast<float *>(smem + (size_t)pad16(P) * kTabStrideOf<D> * 2);
+    t.red = t.nh + pad16(P);
     return t;
 }
 
-static size_t tile_lds_bytes(int P, int TT, int G)
-{
-    size_t o[7];
-    return carve_offsets(P, TT, G, o);
-}
-
-__device__ __forceinline__ PatternTable make_table(const TileShared &sh, const __half *Mg, int P)
+template <int NW>
+__device__ __forceinline__ PatternTable make_table(const TableLds &sh, int P)
 {
     PatternTable tb;
     tb.lds_rows = sh.tab;
     tb.nh = sh.nh;
-    tb.norm2_max = fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
+    tb.norm2_max = sh.red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) tb.norm2_max = fmaxf(tb.norm2_max, sh.red[w]);
     tb.P = P;
     return tb;
 }
 
 // B operand of one 16-token tile: vectors i0 .. i0+15 of stream ns.
-__device__ __forceinline__ void load_tile(const QuantArgs &a, int ns, int i0, uint4 (&xb)[4])
+template <int KS>
+__device__ __forceinline__ void load_tile(const QuantArgs &a, int ns, int i0, uint4 (&xb)[KS])
 {
     const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
-    const __half *row = a.src.row(ns, i0 + n);
+    const __half *row = a.src.row_d(ns, i0 + n, 32 * KS);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) xb[k] = *reinterpret_cast<const uint4 *>(row + 32 * k + 8 * kb);
+    for (int k = 0; k < KS; ++k) xb[k] = *reinterpret_cast<const uint4 *>(row + 32 * k + 8 * kb);
+}
+
+// Residuals r[j] of channel 32k + 8kb + j: eight channels of a vector minus those of a pattern.
+__device__ __forceinline__ void residuals8(const uint4 xv, const uint4 mv, float *r)   // (mv by value: one 16-byte LDS read)
+{
+    r[0] = sub_lo(xv.x, mv.x);
+    r[1] = sub_hi(xv.x, mv.x);
+    r[2] = sub_lo(xv.y, mv.y);
+    r[3] = sub_hi(xv.y, mv.y);
+    r[4] = sub_lo(xv.z, mv.z);
+    r[5] = sub_hi(xv.z, mv.z);
+    r[6] = sub_lo(xv.w, mv.w);
+    r[7] = sub_hi(xv.w, mv.w);
 }
 
 // Residuals r[8k + j] of channel 32k + 8kb + j of the lane's token against pattern bi.
-__device__ __forceinline__ void residuals(const TileShared &sh, const __half *Mg, const uint4 (&xb)[4], int bi, float (&r)[32])
+template <int KS>
+__device__ __forceinline__ void residuals(const TableLds &sh, const uint4 (&xb)[KS], int bi, float (&r)[8 * KS])
 {
     const int kb = (threadIdx.x & 63) >> 4;
-    const __half *mrow = sh.tab + bi * kTabStride + 8 * kb;
+    const __half *mrow = sh.tab + bi * kTabStrideOf<32 * KS> + 8 * kb;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint4 mv = *reinterpret_cast<const uint4 *>(mrow + 32 * k);
-        const uint4 xv = xb[k];
-        r[8 * k + 0] = sub_lo(xv.x, mv.x);
-        r[8 * k + 1] = sub_hi(xv.x, mv.x);
-        r[8 * k + 2] = sub_lo(xv.y, mv.y);
-        r[8 * k + 3] = sub_hi(xv.y, mv.y);
-        r[8 * k + 4] = sub_lo(xv.z, mv.z);
-        r[8 * k + 5] = sub_hi(xv.z, mv.z);
-        r[8 * k + 6] = sub_lo(xv.w, mv.w);
-        r[8 * k + 7] = sub_hi(xv.w, mv.w);
-    }
+    for (int k = 0; k < KS; ++k) residuals8(xb[k], *reinterpret_cast<const uint4 *>(mrow + 32 * k), r + 8 * k);
 }
 
 // Nearest pattern of the tile's tokens (exact).
-__device__ __forceinline__ int assign_index(const PatternTable &tb, const __half *Mg, const uint4 (&xb)[4], __half *xrow)
+template <int KS>
+__device__ __forceinline__ int assign_index(const PatternTable &tb, const uint4 (&xb)[KS], __half *xrow)
 {
     const int lane = threadIdx.x & 63;
     int bi;
@@ -406,14 +380,6 @@ __device__ __forceinline__ int assign_index(const PatternTable &tb, const __half
     bool flag;
     assign_tile_mfma(xb, tb, lane, bi, bv, x2, flag);
     resolve_flagged(xb, flag, xrow, tb, lane, bi, bd);
-    return bi;
-}
-
-__device__ __forceinline__ int assign_residuals(const TileShared &sh, const PatternTable &tb, const __half *Mg,
-                                                const uint4 (&xb)[4], __half *xrow, float (&r)[32])
-{
-    const int bi = assign_index(tb, Mg, xb, xrow);
-    residuals(sh, Mg, xb, bi, r);
     return bi;
 }
 
@@ -425,167 +391,208 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Codes of the lane's 32 channels of one token against the group's parameters in LDS (zero points as fp16
-// bits, 1/s as binary32, indexed by channel); 8 channels = one byte of a plane word, written to the token's
-// row of the staging area stg ([16 tokens][4 words][BITS planes] words, memory order).
-template <int BITS>
-__device__ __forceinline__ void k_codes_to_staging(const float (&r)[32], const uint16_t *pz, const float *pinv, uint8_t *stg)
+// Contiguous store of BYTES bytes from LDS by a wave, in 8- or 16-byte lane pieces.
+template <int BYTES>
+__device__ __forceinline__ void wave_store(uint8_t *dst, const uint8_t *src)
 {
-    const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
-    uint8_t *mine = stg + n * 16 * BITS + kb;
+    const int lane = threadIdx.x & 63;
+    if (BYTES == 512) {
+        reinterpret_cast<uint2 *>(dst)[lane] = reinterpret_cast<const uint2 *>(src)[lane];
+    } else {
+        static_assert(BYTES == 512 || BYTES % 16 == 0, "whole pieces");
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint4 zq = *reinterpret_cast<const uint4 *>(pz + 32 * k + 8 * kb);
-        const float4 i0 = *reinterpret_cast<const float4 *>(pinv + 32 * k + 8 * kb);
-        const float4 i1 = *reinterpret_cast<const float4 *>(pinv + 32 * k + 8 * kb + 4);
-        uint32_t lo = 0u, hi = 0u;
-        lo = put_code(subz_lo(r[8 * k + 0], zq.x), i0.x, 0, lo);
-        lo = put_code(subz_hi(r[8 * k + 1], zq.x), i0.y, 1, lo);
-        lo = put_code(subz_lo(r[8 * k + 2], zq.y), i0.z, 2, lo);
-        lo = put_code(subz_hi(r[8 * k + 3], zq.y), i0.w, 3, lo);
-        hi = put_code(subz_lo(r[8 * k + 4], zq.z), i1.x, 0, hi);
-        hi = put_code(subz_hi(r[8 * k + 5], zq.z), i1.y, 1, hi);
-        hi = put_code(subz_lo(r[8 * k + 6], zq.w), i1.z, 2, hi);
-        hi = put_code(subz_hi(r[8 * k + 7], zq.w), i1.w, 3, hi);
-#pragma unroll
-        for (int p = 0; p < BITS; ++p) mine[(k * BITS + p) * 4] = (uint8_t)(plane_byte_shifted(lo, hi, p) >> p);
+        for (int i = 0; i < BYTES / 16; i += 64)
+            if (BYTES / 16 - i >= 64 || i + lane < BYTES / 16)
+                reinterpret_cast<uint4 *>(dst)[i + lane] = reinterpret_cast<const uint4 *>(src)[i + lane];
     }
 }
 
-// Staging area -> global: the 16 tokens' code words as one contiguous run, then their 16 indices.
-template <int BITS>
-__device__ __forceinline__ void k_store_staging(const QuantArgs &a, int64_t tok0, const uint8_t *stg)
+// ---- K ------------------------------------------------------------------------------------------------------------
+// LDS of a wave: the 32-channel residual tile of 16 tokens (also the row under exact evaluation and the output staging:
+// code words in memory order, then the indices).  Parameters of a group: zero points and scales (fp16 bits), 1/s.
+constexpr int kWkStride = 32 + 4;                     // floats per row of the residual tile
+constexpr int kWkTile = 16 * kWkStride * 4;           // bytes: 16 tokens x 32 channels
+template <int D>
+constexpr int kKParams = D * 2 * 2 + D * 4;           // bytes of one group's parameters
+
+// Running minimum / maximum per channel over a 16-token tile: the residuals of 32 channels (operand step k) at a time
+// pass through the wave's LDS tile; lane <-> (channel 32k + lane%32, token half lane/32).
+__device__ __forceinline__ void scan_channels(const float *r, float *rt, float &mn, float &mx)
 {
-    const int lane = threadIdx.x & 63;
-    uint8_t *codes = reinterpret_cast<uint8_t *>(a.codes_k);
-    if (BITS == 2)
-        reinterpret_cast<uint2 *>(codes + tok0 * 32)[lane] = reinterpret_cast<const uint2 *>(stg)[lane];
-    else
-        reinterpret_cast<uint4 *>(codes + tok0 * 64)[lane] = reinterpret_cast<const uint4 *>(stg)[lane];
-    if (lane == 0) *reinterpret_cast<uint4 *>(a.idx + tok0) = *reinterpret_cast<const uint4 *>(stg + 16 * 16 * BITS);
+    const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4, sc = lane & 31, sth = lane >> 5;
+    float4 *dst = reinterpret_cast<float4 *>(rt + n * kWkStride + 8 * kb);
+    dst[0] = make_float4(r[0], r[1], r[2], r[3]);
+    dst[1] = make_float4(r[4], r[5], r[6], r[7]);
+    wave_lds_sync();
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+        const float v0 = rt[(8 * sth + t) * kWkStride + sc], v1 = rt[(8 * sth + t + 1) * kWkStride + sc];
+        mn = fminf(fminf(mn, v0), v1);
+        mx = fmaxf(fmaxf(mx, v0), v1);
+    }
+    wave_lds_sync();
 }
 
-// K: workgroup = NW waves, tiles of TT = max(64, G) tokens of one stream; wave w owns the 16-token
-// tiles w*NT .. w*NT + NT-1 of the tile.  Launched for groups of 128 tokens with NW = 8, one 16-token tile per
-// wave: the 128-token residual tile (68 KB) beside the pattern table leaves room for one workgroup per CU from 128
-// patterns on, and eight waves give every SIMD two (four waves measured 12 % slower, on a bulk job at 64 patterns
-// as on the 4-stream job at 256).
-template <int G, int BITS, int NW>
-__global__ __launch_bounds__(64 * NW) void quantize_k_kernel(QuantArgs a, int tiles_per_wg)
+// The stored parameters of channel c
+__device__ __forceinline__ void put_params(float mn, float mx, int bits, int c, int D, uint16_t *pz, float *pinv)
 {
-    constexpr int TT = G == 128 ? 128 : 64, NT = TT / (16 * NW);
-    static_assert(NT >= 1, "every wave takes at least one 16-token tile");
-    constexpr int LPC = TT / 32;          // lanes that share one channel in the column scan, 32 tokens each
-    constexpr int CPR = 64 * NW / LPC;    // channels per round of the scan
-    constexpr int NGRP = TT / G;          // parameter groups per tile
+    const GroupParams gp = group_params(mn, mx, bits);
+    pz[c] = gp.z16;
+    pz[D + c] = gp.s16;
+    pinv[c] = gp.inv;
+}
+
+// Stored parameters of a group, 16-byte pieces by one wave: zero points, then scales
+template <int D>
+__device__ __forceinline__ void store_params(const QuantArgs &a, int64_t group, const uint16_t *pz)
+{
+    const int lane = threadIdx.x & 63;
+    if (D == 256 || lane < D / 4) {
+        const int arr = lane / (D / 8), piece = lane % (D / 8);
+        const uint4 v = *reinterpret_cast<const uint4 *>(pz + arr * D + piece * 8);
+        *reinterpret_cast<uint4 *>((arr ? a.scale : a.zero) + group * D + piece * 8) = v;
+    }
+}
+
+// Codes of eight channels of one token (operand step k) against the group's parameters in LDS (zero points as fp16
+// bits, 1/s as binary32, indexed by channel): one byte of each plane word, written to the token's row of the staging
+// area stg ([16 tokens][D/32 words][BITS planes] words, memory order).
+template <int D, int BITS>
+__device__ __forceinline__ void k_codes8(const float *r, int k, const uint16_t *pz, const float *pinv, uint8_t *stg)
+{
+    const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
+    const uint4 zq = *reinterpret_cast<const uint4 *>(pz + 32 * k + 8 * kb);
+    const float4 i0 = *reinterpret_cast<const float4 *>(pinv + 32 * k + 8 * kb);
+    const float4 i1 = *reinterpret_cast<const float4 *>(pinv + 32 * k + 8 * kb + 4);
+    uint32_t lo = 0u, hi = 0u;
+    lo = put_code(subz_lo(r[0], zq.x), i0.x, 0, lo);
+    lo = put_code(subz_hi(r[1], zq.x), i0.y, 1, lo);
+    lo = put_code(subz_lo(r[2], zq.y), i0.z, 2, lo);
+    lo = put_code(subz_hi(r[3], zq.y), i0.w, 3, lo);
+    hi = put_code(subz_lo(r[4], zq.z), i1.x, 0, hi);
+    hi = put_code(subz_hi(r[5], zq.z), i1.y, 1, hi);
+    hi = put_code(subz_lo(r[6], zq.w), i1.z, 2, hi);
+    hi = put_code(subz_hi(r[7], zq.w), i1.w, 3, hi);
+    uint8_t *mine = stg + n * (D / 8) * BITS + kb;
+#pragma unroll
+    for (int p = 0; p < BITS; ++p) mine[(k * BITS + p) * 4] = (uint8_t)(plane_byte_shifted(lo, hi, p) >> p);
+}
+
+// Staging area -> global: the 16 tokens' code words as one contiguous run, then their 16 indices.
+template <int D, int BITS>
+__device__ __forceinline__ void k_store_staging(const QuantArgs &a, int64_t tok0, const uint8_t *stg)
+{
+    constexpr int kBytes = 16 * D * BITS / 8;
+    static_assert(kBytes + 16 <= kWkTile, "output staging fits the residual tile");
+    wave_store<kBytes>(reinterpret_cast<uint8_t *>(a.codes_k) + tok0 * (D * BITS / 8), stg);
+    if ((threadIdx.x & 63) == 0) *reinterpret_cast<uint4 *>(a.idx + tok0) = *reinterpret_cast<const uint4 *>(stg + kBytes);
+}
+
+// K, groups of 128 tokens: 8 / NT waves take one group at a time, NT 16-token tiles each.  Every wave reduces its own tokens
+// per channel (scan_channels) and leaves the minima and maxima in its LDS tile; between two barriers a thread per channel
+// combines them and forms the parameters.  A workgroup holds GR groups side by side.  Beyond 128 patterns (up to 128
+// channels) the table leaves room for one workgroup per CU only: sixteen waves cover the barriers' latency, in four groups
+// with two tiles per pass over the table where a workgroup has that many groups to take, else in two.
+// (A residual tile of the whole group in LDS, scanned by columns, took 68 KB at 128 channels beside the table: one workgroup
+// per CU from 128 patterns on, and no room at all at 256 channels.  Appends, K and V: 256 streams x 8192 at 64 patterns 374
+// -> 349 us; 64 streams, 4 bits, 128 patterns 174 -> 150; 4 streams x 131072 at 256 patterns, with the first decode, 220 ->
+// 210 - one group of eight waves there measured 235, two groups with a tile per pass 221.)
+template <int D, int NT>
+constexpr int kGroupLds = 8 / NT * kWkTile + kKParams<D>;   // bytes of LDS per group
+
+template <int D, int BITS, int GR, int NT>
+__global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void quantize_k_group_kernel(QuantArgs a, int tiles_per_wg)
+{
+    constexpr int KS = D / 32, TT = 128, NW = 8 / NT, NTH = 64 * NW;   // waves and threads of a group
+    static_assert(2 * D * 4 <= kWkTile, "a wave's minima and maxima fit its tile");
     extern __shared__ __align__(16) unsigned char smem[];
-    const TileShared sh = carve(smem, a.P, TT, G);
-    const int tid = threadIdx.x, ns = blockIdx.y;
+    const TableLds sh = table_lds<D>(smem, a.P);
+    const int gr = GR == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTH);
+    const int tid = threadIdx.x % NTH, ns = blockIdx.y;          // thread inside the group
     const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
-    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * kD;
+    unsigned char *work = smem + table_lds_bytes<D>(a.P) + gr * kGroupLds<D, NT>;
+    float *rt = reinterpret_cast<float *>(work + wave * kWkTile);
+    uint16_t *pz = reinterpret_cast<uint16_t *>(work + NW * kWkTile);   // [D] zero points, then [D] scales
+    float *pinv = reinterpret_cast<float *>(pz + 2 * D);
+    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
     const int n_tiles = a.nq / TT;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
-    uint4 xb[NT][4];
+    uint4 xb[NT][KS];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) load_tile(a, ns, tile0 * TT + (wave * NT + j) * 16, xb[j]);   // in flight while the table is staged
+    for (int j = 0; j < NT; ++j) load_tile(a, ns, min(tile0 + gr, tile1 - 1) * TT + (wave * NT + j) * 16, xb[j]);   // in flight while the table is staged
+    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red, NTH * GR);
+    const PatternTable tb = make_table<NW * GR>(sh, a.P);
 
-    stage_patterns(Mg, a.P, sh.tab, sh.nh, sh.red, 64 * NW);
-    PatternTable tb = make_table(sh, Mg, a.P);
-    if (NW == 8) tb.norm2_max = fmaxf(tb.norm2_max, fmaxf(fmaxf(sh.red[4], sh.red[5]), fmaxf(sh.red[6], sh.red[7])));
-
-    const int q = tid % LPC, cc = tid / LPC;
-    for (int tile = tile0; tile < tile1; ++tile) {
-        const int64_t tq0 = (int64_t)a.t0 + (int64_t)tile * TT;
-        const int64_t pq0 = a.map.pos(ns, (int)tq0);   // where the tile's first token is stored
-        float r[NT][32];
+    for (int tile_base = tile0; tile_base < tile1; tile_base += GR) {
+        // (a group past the range repeats the last one, up to the barriers, and stores nothing)
+        const bool live = GR == 1 || tile_base + gr < tile1;
+        const int tile = live ? tile_base + gr : tile1 - 1;
+        const int64_t pq0 = a.map.pos(ns, a.t0 + tile * TT);   // where the group's first token is stored
         int bi[NT];
         if (a.idx_given) {   // searched beforehand (min-max metric)
 #pragma unroll
             for (int j = 0; j < NT; ++j) bi[j] = a.idx[pq0 + (wave * NT + j) * 16 + n];
-        } else {   // the wave's NT 16-token tiles in one pass over the pattern table
+        } else {
             float bv[NT], x2[NT];
             bool flag[NT];
-            assign_tiles_mfma<NT, 4>(xb, tb, lane, bi, bv, x2, flag);
+            assign_tiles_mfma<NT, KS>(xb, tb, lane, bi, bv, x2, flag);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;
-                // scratch for the exact re-evaluation: the tile's own residual rows, which are written only below
-                resolve_flagged(xb[j], flag[j], reinterpret_cast<__half *>(sh.rt + (wave * NT + j) * 16 * kRStride), tb, lane,
-                                bi[j], bd);
+                resolve_flagged(xb[j], flag[j], reinterpret_cast<__half *>(rt), tb, lane, bi[j], bd);
+            }
+        }
+        float mn[KS], mx[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            mn[k] = INFINITY;
+            mx[k] = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                float r[8];
+                residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
+                scan_channels(r, rt, mn[k], mx[k]);
             }
         }
 #pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int tl = (wave * NT + j) * 16 + n;   // token slot inside the tile
-            residuals(sh, Mg, xb[j], bi[j], r[j]);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                float4 *dst = reinterpret_cast<float4 *>(sh.rt + tl * kRStride + 32 * k + 8 * kb);
-                dst[0] = make_float4(r[j][8 * k], r[j][8 * k + 1], r[j][8 * k + 2], r[j][8 * k + 3]);
-                dst[1] = make_float4(r[j][8 * k + 4], r[j][8 * k + 5], r[j][8 * k + 6], r[j][8 * k + 7]);
-            }
-        }
-        __syncthreads();
-        if (tile + 1 < tile1) {   // next tile's vectors: hidden behind the rest of this tile
-#pragma unroll
-            for (int j = 0; j < NT; ++j) load_tile(a, ns, (tile + 1) * TT + (wave * NT + j) * 16, xb[j]);
-        }
-
-        // column scan: lane q of a channel takes tokens 32q .. 32q+31, in an order rotated by q*16/LPC so
-        // that the lanes of a wave fall on distinct banks
-#pragma unroll
-        for (int rd = 0; rd < 128 / CPR; ++rd) {
-            const int c = cc + rd * CPR;
-            float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < 32; t += 2) {
-                const float v0 = sh.rt[(32 * q + ((t + q * (16 / LPC)) & 31)) * kRStride + c];
-                const float v1 = sh.rt[(32 * q + ((t + 1 + q * (16 / LPC)) & 31)) * kRStride + c];
-                mn = fminf(fminf(mn, v0), v1);
-                mx = fmaxf(fmaxf(mx, v0), v1);
-            }
-            if (G >= 64) {
-                mn = fminf(mn, __shfl_xor(mn, 1));
-                mx = fmaxf(mx, __shfl_xor(mx, 1));
-            }
-            if (G == 128) {
-                mn = fminf(mn, __shfl_xor(mn, 2));
-                mx = fmaxf(mx, __shfl_xor(mx, 2));
-            }
-            const GroupParams gp = group_params(mn, mx, BITS);
-            const int grp = G == 32 ? q : 0;
-            if (G == 32 || q == 0) {
-                sh.pz[grp * kD + c] = gp.z16;
-                sh.pz[(NGRP + grp) * kD + c] = gp.s16;
-                sh.pinv[grp * kD + c] = gp.inv;
-            }
+        for (int k = 0; k < KS; ++k) {   // the two token halves
+            mn[k] = fminf(mn[k], __shfl_xor(mn[k], 32));
+            mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 32));
+            rt[(lane < 32 ? 0 : D) + 32 * k + (lane & 31)] = lane < 32 ? mn[k] : mx[k];
         }
         __syncthreads();
-        // stored parameters of the tile's groups: 16-byte pieces, zero points then scales
-        if (wave == NW - 1 && lane < NGRP * 32) {
-            const int grp = lane >> 5, arr = (lane >> 4) & 1, piece = lane & 15;
-            const uint4 v = *reinterpret_cast<const uint4 *>(sh.pz + (arr * NGRP + grp) * kD + piece * 8);
-            __half *dstp = (arr ? a.scale : a.zero) + (pq0 / G + grp) * kD + piece * 8;
-            *reinterpret_cast<uint4 *>(dstp) = v;
+        for (int c = tid; c < D; c += NTH) {
+            const float *all = reinterpret_cast<const float *>(work) + c;
+            float lo = all[0], hi = all[D];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) {
+                lo = fminf(lo, all[w * (kWkTile / 4)]);
+                hi = fmaxf(hi, all[w * (kWkTile / 4) + D]);
+            }
+            put_params(lo, hi, BITS, c, D, pz, pinv);
         }
-
-        // codes of the lane's 32 channels per token; 8 channels = one byte of a plane word.  The bytes of the
-        // wave's 16 tokens are put together in its own residual rows (no longer read by anyone) and leave as
-        // one contiguous store.
+        __syncthreads();
+        if (!live) continue;   // (the last round: no barrier follows)
+        if (wave == NW - 1) store_params<D>(a, pq0 / TT, pz);
+        // codes; a tile's 16 tokens are put together in the wave's own LDS tile (read by nobody else any more)
+        uint8_t *stg = reinterpret_cast<uint8_t *>(rt);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int tl0 = (wave * NT + j) * 16;
-            const int grp = G == 32 ? tl0 >> 5 : 0;
-            uint8_t *stg = reinterpret_cast<uint8_t *>(sh.rt + tl0 * kRStride);
-            k_codes_to_staging<BITS>(r[j], sh.pz + grp * kD, sh.pinv + grp * kD, stg);
-            if (kb == 0) stg[16 * 16 * BITS + n] = (uint8_t)bi[j];
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                float r[8];
+                residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
+                k_codes8<D, BITS>(r, k, pz, pinv, stg);
+            }
+            if (kb == 0) stg[16 * D * BITS / 8 + n] = (uint8_t)bi[j];
             wave_lds_sync();
-            k_store_staging<BITS>(a, pq0 + tl0, stg);
+            if (tile_base + GR < tile1) load_tile(a, ns, min(tile + GR, tile1 - 1) * TT + (wave * NT + j) * 16, xb[j]);
+            k_store_staging<D, BITS>(a, pq0 + (wave * NT + j) * 16, stg);
+            wave_lds_sync();
         }
-        // the residual tile is rewritten only after the next barrier-separated scan has been passed by
-        // every wave: the scan of this tile ended before the barrier above
+        // (the parameters are rewritten only behind the next group's first barrier, which every wave has to reach)
     }
 }
 
@@ -595,60 +602,49 @@ __global__ __launch_bounds__(64 * NW) void quantize_k_kernel(QuantArgs a, int ti
 // through a small LDS tile to a per-channel running minimum / maximum, pass B forms the residuals again,
 // quantizes and stores.  A tile's registers are refilled with the wave's next group as soon as pass B
 // has used them.
-constexpr int kWkStride = 32 + 4;                     // floats per row of the quarter-width residual tile
-constexpr int kWkTile = 16 * kWkStride * 4;           // bytes: 16 tokens x 32 channels (also the output staging area)
-constexpr int kWkWave = kWkTile + kD * 2 * 2 + kD * 4;   // + zero points, scales (fp16 bits), 1/s
+template <int D>
+constexpr int kWkWave = kWkTile + kKParams<D>;   // bytes of LDS per wave
 
-static size_t wave_k_lds_bytes(int P)
+template <int D, int G, int BITS, int NTA>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || (D == 256 && G == 64) ? 2 : 3))) void quantize_k_wave_kernel(QuantArgs a, int tiles_per_wg)
 {
-    return (size_t)pad16(P) * kTabStride * 2 + (size_t)pad16(P) * 4 + 16 + 4 * (size_t)kWkWave;
-}
-
-template <int G, int BITS, int NTA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 ? 2 : 3))) void quantize_k_wave_kernel(QuantArgs a, int tiles_per_wg)
-{
-    constexpr int NTG = G / 16;
+    constexpr int NTG = G / 16, KS = D / 32;
     static_assert(G == 32 || G == 64, "a wave holds the group's tiles in registers");
-    static_assert(16 * 16 * BITS + 16 <= kWkTile, "output staging fits the residual tile");
     extern __shared__ __align__(16) unsigned char smem[];
-    TileShared sh;
-    size_t at = 0;
-    sh.tab = reinterpret_cast<__half *>(smem);
-    at += (size_t)pad16(a.P) * kTabStride * 2;
-    sh.nh = reinterpret_cast<float *>(smem + at);
-    at += (size_t)pad16(a.P) * 4;
-    sh.red = reinterpret_cast<float *>(smem + at);
-    at += 16;
+    const TableLds sh = table_lds<D>(smem, a.P);
     const int tid = threadIdx.x, ns = blockIdx.y;
     const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
-    unsigned char *mine = smem + at + (size_t)wave * kWkWave;
+    unsigned char *mine = smem + table_lds_bytes<D>(a.P) + (size_t)wave * kWkWave<D>;
     float *rt = reinterpret_cast<float *>(mine);
-    uint16_t *pz = reinterpret_cast<uint16_t *>(mine + kWkTile);   // [kD] zero points, then [kD] scales
-    float *pinv = reinterpret_cast<float *>(mine + kWkTile + kD * 2 * 2);
+    uint16_t *pz = reinterpret_cast<uint16_t *>(mine + kWkTile);   // [D] zero points, then [D] scales
+    float *pinv = reinterpret_cast<float *>(mine + kWkTile + D * 2 * 2);
 
-    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * kD;
+    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
     const int n_tiles = a.nq / 64;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
     const int g_end = tile1 * (64 / G);
     int g = tile0 * (64 / G) + wave;
-    uint4 xb[NTG][4];
+    uint4 xb[NTG][KS];
     if (g < g_end) {
 #pragma unroll
         for (int j = 0; j < NTG; ++j) load_tile(a, ns, g * G + j * 16, xb[j]);   // in flight while the table is staged
     }
-    stage_patterns(Mg, a.P, sh.tab, sh.nh, sh.red);
-    const PatternTable tb = make_table(sh, Mg, a.P);
+    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red);
+    const PatternTable tb = make_table<4>(sh, a.P);
 
     for (; g < g_end; g += 4) {
         const int64_t tq0 = (int64_t)a.t0 + (int64_t)g * G;   // logical position of the group's first token
         const int64_t pq0 = a.map.pos(ns, (int)tq0);            // where it is stored
-        // ---- pass A: indices; running minimum / maximum per channel.  The residuals pass through the LDS tile a
-        //      quarter (32 channels = one operand step) at a time; lane <-> (channel lane%32, token half lane/32)
-        float mn[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        // ---- pass A: indices; running minimum / maximum per channel
+        float mn[KS], mx[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            mn[k] = INFINITY;
+            mx[k] = -INFINITY;
+        }
         int bi[NTG];
-        const int sc = lane & 31, sth = lane >> 5;
         if (a.idx_given) {   // searched beforehand (min-max metric)
 #pragma unroll
             for (int j = 0; j < NTG; ++j) bi[j] = a.idx[pq0 + j * 16 + n];
@@ -658,7 +654,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 ? 2
                 float bv[NTA], x2[NTA];
                 bool flag[NTA];
                 int bj[NTA];
-                assign_tiles_mfma<NTA, 4>(reinterpret_cast<const uint4 (&)[NTA][4]>(xb[j0]), tb, lane, bj, bv, x2, flag);
+                assign_tiles_mfma<NTA, KS>(reinterpret_cast<const uint4 (&)[NTA][KS]>(xb[j0]), tb, lane, bj, bv, x2, flag);
 #pragma unroll
                 for (int j = 0; j < NTA; ++j) {
                     float bd;
@@ -669,63 +665,77 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 ? 2
         }
 #pragma unroll
         for (int j = 0; j < NTG; ++j) {
-            float r[32];
-            if (NTA > 1 || a.idx_given)
-                residuals(sh, Mg, xb[j], bi[j], r);
-            else
-                bi[j] = assign_residuals(sh, tb, Mg, xb[j], reinterpret_cast<__half *>(rt), r);
+            if (NTA == 1 && !a.idx_given) bi[j] = assign_index(tb, xb[j], reinterpret_cast<__half *>(rt));
+            if constexpr (KS <= 4) {
+                float r[8 * KS];
+                residuals(sh, xb[j], bi[j], r);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {   // channels 32k .. 32k+31
-                float4 *dst = reinterpret_cast<float4 *>(rt + n * kWkStride + 8 * kb);
-                dst[0] = make_float4(r[8 * k], r[8 * k + 1], r[8 * k + 2], r[8 * k + 3]);
-                dst[1] = make_float4(r[8 * k + 4], r[8 * k + 5], r[8 * k + 6], r[8 * k + 7]);
-                wave_lds_sync();
+                for (int k = 0; k < KS; ++k) scan_channels(r + 8 * k, rt, mn[k], mx[k]);
+            } else {   // 256 channels: the tiles alone take half of the registers
 #pragma unroll
-                for (int t = 0; t < 8; t += 2) {
-                    const float v0 = rt[(8 * sth + t) * kWkStride + sc], v1 = rt[(8 * sth + t + 1) * kWkStride + sc];
-                    mn[k] = fminf(fminf(mn[k], v0), v1);
-                    mx[k] = fmaxf(fmaxf(mx[k], v0), v1);
+                for (int k = 0; k < KS; ++k) {
+                    float r[8];
+                    residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
+                    scan_channels(r, rt, mn[k], mx[k]);
                 }
-                wave_lds_sync();
             }
         }
         // ---- parameters of the group: the two token halves are combined, then lane (c, half) takes the channels
-        //      32(2 half) + c and 32(2 half + 1) + c
+        //      32(2h + half) + c
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < KS; ++k) {
             mn[k] = fminf(mn[k], __shfl_xor(mn[k], 32));
             mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 32));
         }
+        const int sc = lane & 31, sth = lane >> 5;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const GroupParams gp = group_params(sth ? mn[2 + h] : mn[h], sth ? mx[2 + h] : mx[h], BITS);
-            const int c = 32 * (2 * sth + h) + sc;
-            pz[c] = gp.z16;
-            pz[kD + c] = gp.s16;
-            pinv[c] = gp.inv;
+        for (int h = 0; h < (KS + 1) / 2; ++h) {
+            constexpr int last = KS - 1;
+            const int k1 = 2 * h + 1 < KS ? 2 * h + 1 : last;
+            if (KS % 2 == 0 || 2 * h + 1 < KS || sth == 0)
+                put_params(sth ? mn[k1] : mn[2 * h], sth ? mx[k1] : mx[2 * h], BITS, 32 * (2 * h + sth) + sc, D, pz, pinv);
         }
         wave_lds_sync();
-        if (lane < 32) {   // stored parameters: 16-byte pieces, zero points then scales
-            const int arr = lane >> 4, piece = lane & 15;
-            const uint4 v = *reinterpret_cast<const uint4 *>(pz + arr * kD + piece * 8);
-            __half *dstp = (arr ? a.scale : a.zero) + (pq0 / G) * kD + piece * 8;
-            *reinterpret_cast<uint4 *>(dstp) = v;
-        }
+        store_params<D>(a, pq0 / G, pz);
         // ---- pass B: residuals again, codes, planes; the tile's registers then take the next group
         uint8_t *stg = reinterpret_cast<uint8_t *>(rt);
 #pragma unroll
         for (int j = 0; j < NTG; ++j) {
-            float r[32];
-            residuals(sh, Mg, xb[j], bi[j], r);
-            if (g + 4 < g_end) load_tile(a, ns, (g + 4) * G + j * 16, xb[j]);
-            k_codes_to_staging<BITS>(r, pz, pinv, stg);
-            if (kb == 0) stg[16 * 16 * BITS + n] = (uint8_t)bi[j];
+            if constexpr (KS <= 4) {
+                float r[8 * KS];
+                residuals(sh, xb[j], bi[j], r);
+                if (g + 4 < g_end) load_tile(a, ns, (g + 4) * G + j * 16, xb[j]);
+#pragma unroll
+                for (int k = 0; k < KS; ++k) k_codes8<D, BITS>(r + 8 * k, k, pz, pinv, stg);
+            } else {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    float r[8];
+                    residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
+                    k_codes8<D, BITS>(r, k, pz, pinv, stg);
+                }
+                if (g + 4 < g_end) load_tile(a, ns, (g + 4) * G + j * 16, xb[j]);
+            }
+            if (kb == 0) stg[16 * D * BITS / 8 + n] = (uint8_t)bi[j];
             wave_lds_sync();
-            k_store_staging<BITS>(a, pq0 + j * 16, stg);
+            k_store_staging<D, BITS>(a, pq0 + j * 16, stg);
             wave_lds_sync();   // the staging area is rewritten by the next tile
         }
     }
 }
+
+// ---- V ------------------------------------------------------------------------------------------------------------
+// Per-wave output staging: the pieces a wave produces for its 16 tokens are put together in LDS so that
+// every global store is one contiguous run of 8- or 16-byte lane pieces.
+template <int D>
+struct VStaging {
+    static constexpr int kRow = 0;                     // D halves: one vector for the exact re-evaluation
+    static constexpr int kCodes = 2 * D;               // up to 8 D bytes: the unit's code words in memory order (4 bits)
+    static constexpr int kIdx = kCodes + 8 * D;        // 16 B: pattern indices
+    static constexpr int kScale = kIdx + 16;           // up to D B: scales [group][16]
+    static constexpr int kZero = kScale + D;           // up to D B: zero points [group][16]
+    static constexpr int kBytes = kZero + D;
+};
 
 // 16x16 bit transpose across the 16 lanes of a row, on both 16-bit halves of x at once:
 // on return bit t of a half in lane i is what bit i of that half was in lane t.
@@ -757,31 +767,34 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
 }
 
 // V: workgroup = 256 threads, blocks of 64 tokens of one stream; wave w owns the 16-token unit w of the
-// block.  NG = channel groups per token (kD / Gc).  NT = blocks taken together: the wave assigns its units of
+// block.  NG = channel groups per token (D / Gc).  NT = blocks taken together: the wave assigns its units of
 // NT consecutive blocks in one pass over the pattern table (every table tile read from LDS serves all of
 // them), then quantizes them one after the other.
-template <int BITS, int NG, int NT>
+template <int D, int BITS, int NG, int NT>
 __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
 {
-    constexpr int TT = 64, WPU = BITS / 2, BPG = 4 / NG;   // BPG = 32-channel blocks per group
+    using St = VStaging<D>;
+    constexpr int TT = 64, WPU = BITS / 2, KS = D / 32, BPG = KS / NG;   // BPG = 32-channel blocks per group
+    static_assert(KS % NG == 0, "groups of whole 32-channel blocks");
+    constexpr int GL = (NG + 3) / 4;   // groups whose parameters a lane works out
     extern __shared__ __align__(16) unsigned char smem[];
-    const TileShared sh = carve(smem, a.P, 0, 1);
+    const TableLds sh = table_lds<D>(smem, a.P);
     const int tid = threadIdx.x, ns = blockIdx.y;
     const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
-    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * kD;
+    const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
     const int n_tiles = a.nq / TT;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
-    uint4 xbs[NT][4];
+    uint4 xbs[NT][KS];
 #pragma unroll
     for (int j = 0; j < NT; ++j)   // a block past the workgroup's range repeats the last one; its result is not used
         load_tile(a, ns, min(tile0 + j, tile1 - 1) * TT + wave * 16, xbs[j]);
 
-    stage_patterns(Mg, a.P, sh.tab, sh.nh, sh.red);
-    const PatternTable tb = make_table(sh, Mg, a.P);
+    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red);
+    const PatternTable tb = make_table<4>(sh, a.P);
     const TransposeConst tc = transpose_const(n);
-    unsigned char *wsc = sh.wsc + wave * kWaveScratch;
+    unsigned char *wsc = smem + table_lds_bytes<D>(a.P) + wave * St::kBytes;
 
     // Contiguous stores of a finished unit (code words, parameters, indices) out of the wave's staging area.
     // They are issued at the start of the NEXT unit, after that unit's vectors have arrived and before the
@@ -791,17 +804,13 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
     auto store_pending = [&]() {
         if (pend_tok0 < 0) return;
         const int64_t tok0 = pend_tok0;
-        const uint32_t *stg = reinterpret_cast<const uint32_t *>(wsc + kWsCodes);
-        if (BITS == 2)
-            reinterpret_cast<uint2 *>(a.codes_v + tok0 * (kD * BITS / 8))[lane] = reinterpret_cast<const uint2 *>(stg)[lane];
-        else
-            reinterpret_cast<uint4 *>(a.codes_v + tok0 * (kD * BITS / 8))[lane] = reinterpret_cast<const uint4 *>(stg)[lane];
+        wave_store<16 * D * BITS / 8>(a.codes_v + tok0 * (D * BITS / 8), wsc + St::kCodes);
         if (lane < 4 * NG) {   // NG*32 bytes per array = 2*NG pieces of 16 bytes; scales first, then zero points
             const int arr = lane / (2 * NG), piece = lane % (2 * NG);
-            const uint4 v = *reinterpret_cast<const uint4 *>(wsc + (arr ? kWsZero : kWsScale) + piece * 16);
+            const uint4 v = *reinterpret_cast<const uint4 *>(wsc + (arr ? St::kZero : St::kScale) + piece * 16);
             *reinterpret_cast<uint4 *>((arr ? a.zero : a.scale) + tok0 * NG + piece * 8) = v;
         }
-        if (lane == 63) *reinterpret_cast<uint4 *>(a.idx + tok0) = *reinterpret_cast<const uint4 *>(wsc + kWsIdx);
+        if (lane == 63) *reinterpret_cast<uint4 *>(a.idx + tok0) = *reinterpret_cast<const uint4 *>(wsc + St::kIdx);
         wave_lds_sync();   // the staging area is rewritten by the unit that follows
         pend_tok0 = -1;
     };
@@ -815,34 +824,34 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
         } else {
             float bv[NT], x2[NT];
             bool flag[NT];
-            assign_tiles_mfma<NT, 4>(xbs, tb, lane, bis, bv, x2, flag);
+            assign_tiles_mfma<NT, KS>(xbs, tb, lane, bis, bv, x2, flag);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;
-                resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + kWsRow), tb, lane, bis[j], bd);
+                resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + St::kRow), tb, lane, bis[j], bd);
             }
         }
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
         const int tile = tile_base + j;
         if (tile >= tile1) break;
-        uint4 (&xb)[4] = xbs[j];
-        float r[32];
+        uint4 (&xb)[KS] = xbs[j];
+        float r[8 * KS];
         int bi = bis[j];
         store_pending();
-        residuals(sh, Mg, xb, bi, r);
+        residuals(sh, xb, bi, r);
         if (a.v_rho > 0.f) {
             // adaptive threshold (Sec. 3.3): keep the pattern iff R_flat <= rho * R_raw, ranges over all d
-            // channels of the token: lane-local over its 32 channels, then over the token's 4 lanes
+            // channels of the token: lane-local over its channels, then over the token's 4 lanes
             float rmn = fminf(r[0], r[1]), rmx = fmaxf(r[0], r[1]);
             half2_t xmn = __builtin_bit_cast(half2_t, xb[0].x), xmx = xmn;
 #pragma unroll
-            for (int e = 2; e < 32; e += 2) {
+            for (int e = 2; e < 8 * KS; e += 2) {
                 rmn = fminf(fminf(rmn, r[e]), r[e + 1]);
                 rmx = fmaxf(fmaxf(rmx, r[e]), r[e + 1]);
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < KS; ++k) {
                 const uint32_t w[4] = {xb[k].x, xb[k].y, xb[k].z, xb[k].w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -862,7 +871,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
             if (!keep) {   // quantize the vector itself
                 bi = PK_NO_PATTERN;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
+                for (int k = 0; k < KS; ++k) {
                     const uint32_t w[4] = {xb[k].x, xb[k].y, xb[k].z, xb[k].w};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -892,49 +901,55 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
                 mx[g] = fmaxf(mx[g], __shfl_xor(mx[g], off));
             }
         }
-        // lane kb works out the parameters of group kb % NG and stores them; the others fetch them
-        float my_mn = mn[0], my_mx = mx[0];
-#pragma unroll
-        for (int g = 1; g < NG; ++g) {
-            if ((kb & (NG - 1)) == g) {
-                my_mn = mn[g];
-                my_mx = mx[g];
-            }
-        }
-        const GroupParams gp = group_params(my_mn, my_mx, BITS);
-        if (kb < NG) {
-            reinterpret_cast<uint16_t *>(wsc + kWsScale)[kb * 16 + n] = gp.s16;
-            reinterpret_cast<uint16_t *>(wsc + kWsZero)[kb * 16 + n] = gp.z16;
-        }
-        if (kb == 0) wsc[kWsIdx + n] = (uint8_t)bi;
+        // lane kb works out the parameters of group kb % NG (eight groups: of kb and kb + 4) and stores them; the others
+        // fetch them
         float z[NG], inv[NG];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            z[g] = NG == 1 ? gp.z : __shfl(gp.z, n + 16 * g);
-            inv[g] = NG == 1 ? gp.inv : __shfl(gp.inv, n + 16 * g);
+        for (int l = 0; l < GL; ++l) {
+            float my_mn = mn[4 * l], my_mx = mx[4 * l];
+#pragma unroll
+            for (int g = 4 * l + 1; g < NG && g < 4 * l + 4; ++g) {
+                if ((NG == 2 ? (kb & 1) : kb) == g - 4 * l) {
+                    my_mn = mn[g];
+                    my_mx = mx[g];
+                }
+            }
+            const GroupParams gp = group_params(my_mn, my_mx, BITS);
+            if (kb + 4 * l < NG) {
+                reinterpret_cast<uint16_t *>(wsc + St::kScale)[(kb + 4 * l) * 16 + n] = gp.s16;
+                reinterpret_cast<uint16_t *>(wsc + St::kZero)[(kb + 4 * l) * 16 + n] = gp.z16;
+            }
+#pragma unroll
+            for (int g = 4 * l; g < NG && g < 4 * l + 4; ++g) {
+                z[g] = NG == 1 ? gp.z : __shfl(gp.z, n + 16 * (g - 4 * l));
+                inv[g] = NG == 1 ? gp.inv : __shfl(gp.inv, n + 16 * (g - 4 * l));
+            }
         }
+        if (kb == 0) wsc[St::kIdx + n] = (uint8_t)bi;
 
         // block b = channels 32*(2b + i/8) + 8*kb + i%8, i < 16: codes -> planes -> transpose -> words, put in
-        // memory order in the wave's staging area
-        uint32_t *stg = reinterpret_cast<uint32_t *>(wsc + kWsCodes);
+        // memory order in the wave's staging area.  (96 channels: the last block has eight channels per lane.)
+        uint32_t *stg = reinterpret_cast<uint32_t *>(wsc + St::kCodes);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < (KS + 1) / 2; ++b) {
+            constexpr int kAll = 8 * KS;
             uint32_t cw[4] = {0u, 0u, 0u, 0u};   // codes of elements 4q .. 4q+3 in the bytes of cw[q]
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int e = 16 * b + i, g = (e / 8) / BPG;
-                cw[i >> 2] = put_code(r[e] - z[g], inv[g], i & 3, cw[i >> 2]);
+                const int e = 16 * b + i < kAll ? 16 * b + i : kAll - 1, g = (e / 8) / BPG;
+                if (16 * b + i < kAll) cw[i >> 2] = put_code(r[e] - z[g], inv[g], i & 3, cw[i >> 2]);
             }
             // channel of this lane after the transpose: i = n
             const int c = 32 * (2 * b + (n >> 3)) + 8 * kb + (n & 7);
-            uint32_t *dst = stg + ((c & 15) * (kD / 16) + (c >> 4)) * WPU;
+            uint32_t *dst = stg + ((c & 15) * (D / 16) + (c >> 4)) * WPU;
 #pragma unroll
             for (int w = 0; w < WPU; ++w) {
                 // t_p = (bits p of the 16 codes) << p; low half of x = plane 2w, high half = plane 2w+1
                 const uint32_t t0 = (plane_byte_shifted(cw[2], cw[3], 2 * w) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w);
                 const uint32_t t1 = (plane_byte_shifted(cw[2], cw[3], 2 * w + 1) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w + 1);
                 const uint32_t x = (t0 >> (2 * w)) | (t1 << (15 - 2 * w));
-                dst[w] = transpose16(x, tc);
+                const uint32_t word = transpose16(x, tc);
+                if (16 * b + 16 <= kAll || n < 8) dst[w] = word;
             }
         }
         wave_lds_sync();
@@ -947,8 +962,10 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
 // ---------------------------------------------------------------------------
 // Tail ring: place logical vectors [i0, i1) of an append into their ring slots.
 // ---------------------------------------------------------------------------
+template <int D>
 __global__ __launch_bounds__(256) void tail_copy_kernel(TailCopyArgs a)
 {
+    constexpr int kPieces = D / 8;   // 16-byte pieces of a vector
     const int n = blockIdx.y, side = blockIdx.z;
     if (a.seq_table) {   // a ragged append: the ring state and the range of the stream's own sequence
         const int32_t *e = a.seq_table + (int64_t)(n / a.n_kv_heads) * kSeqEntry;
@@ -957,16 +974,15 @@ __global__ __launch_bounds__(256) void tail_copy_kernel(TailCopyArgs a)
         a.i0 = e[kSeqI0];
         a.i1 = e[kSeqI1];
     }
-    const int64_t work = (int64_t)(a.i1 - a.i0) * kRowChunks;
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= work) return;
-    const int i = a.i0 + (int)(w >> 4), ch = (int)(w & 15);
+    const uint32_t w = blockIdx.x * 256 + threadIdx.x;   // (at most recent + flush vectors)
+    const int i = a.i0 + (int)(w / kPieces), ch = (int)(w % kPieces);
+    if (i >= a.i1) return;
     const __half *fresh = side == 0 ? a.fresh_k : a.fresh_v;
     __half *ring = side == 0 ? a.ring_k : a.ring_v;
     const uint4 v = *reinterpret_cast<const uint4 *>(fresh + (int64_t)n * a.fresh_stride +
-                                                     (int64_t)(i - a.n_ring) * kD + ch * 8);
+                                                     (int64_t)(i - a.n_ring) * D + ch * 8);
     const int slot = (int)(((int64_t)a.ring_start + i) % a.ring_len);
-    *reinterpret_cast<uint4 *>(ring + ((int64_t)n * a.ring_len + slot) * kD + ch * 8) = v;
+    *reinterpret_cast<uint4 *>(ring + ((int64_t)n * a.ring_len + slot) * D + ch * 8) = v;
 }
 
 __global__ __launch_bounds__(kSeqChunk * kSeqEntry) void seq_table_kernel(SeqTableArgs a)
@@ -1020,87 +1036,131 @@ static hipError_t launch_minmax(const QuantArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
+static hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
 {
     return a.d == kD ? launch_minmax<kD>(a, s) : a.d == 96 ? launch_minmax<96>(a, s) : launch_minmax<256>(a, s);
 }
 
+// Tiles per pass over the pattern table and launch sizes follow the table: every table tile read from LDS serves all the
+// 16-token tiles of a pass.  A large table (beyond 128 patterns, or 64 of 256 channels) leaves room for one or two
+// workgroups per CU, each of which stages up to 128 KB, so a small job is cut into one resident round of `resident`
+// workgroups rather than many short ones.
+static int one_round(const QuantArgs &a, int TT, int resident)
+{
+    const int64_t tiles = (int64_t)(a.nq / TT) * a.n_streams;
+    return a.P * a.d > 128 * kD && tiles <= (int64_t)resident * 64 ? (int)((tiles + resident - 1) / resident) : 1;
+}
+
+template <int D, int G, int BITS>
+static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
+{
+    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)kWkWave<D>, mx = table_lds_bytes<D>(256) + 4 * (size_t)kWkWave<D>;
+    constexpr int kMin = G / 16;   // a wave owns whole groups: at least four groups per workgroup
+    if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
+        const int round = one_round(a, 64, 256);
+        return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
+    } else if constexpr (G == 64) {   // pairs keep three waves per SIMD; the whole group takes two, which pays above 128 patterns
+        if (a.P > 128) {
+            const int round = one_round(a, 64, 256);
+            return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 4>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
+        }
+        return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, kMin);
+    } else {                          // 32-token groups gain from pairs only once the table is large
+        return a.P >= 128 ? launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, kMin)
+                          : launch_tiled<quantize_k_wave_kernel<D, G, BITS, 1>>(a, 64, lds, mx, s, kMin);
+    }
+}
+
+template <int D, int BITS>
+static hipError_t launch_k_bits(const QuantArgs &a, hipStream_t s)
+{
+    if (a.G == 32) return launch_k_wave<D, 32, BITS>(a, s);
+    if constexpr (D != 96) {   // (64 does not divide 96 channels)
+        if (a.G == 64) return launch_k_wave<D, 64, BITS>(a, s);
+    }
+    const size_t lds = table_lds_bytes<D>(a.P), mx = table_lds_bytes<D>(256);
+    const int round = one_round(a, 128, 256);
+    if constexpr (D != 256) {
+        if (a.P > 128) {
+            constexpr size_t four = 4 * (size_t)kGroupLds<D, 2>, two = 2 * (size_t)kGroupLds<D, 1>;
+            if (round >= 4 || tiles_per_wg(a.nq / 128, a.n_streams) >= 4)
+                return launch_tiled<quantize_k_group_kernel<D, BITS, 4, 2>, 1024>(a, 128, lds + four, mx + four, s, round);
+            return launch_tiled<quantize_k_group_kernel<D, BITS, 2, 1>, 1024>(a, 128, lds + two, mx + two, s, round);
+        }
+    }
+    constexpr size_t one = kGroupLds<D, 1>;
+    return launch_tiled<quantize_k_group_kernel<D, BITS, 1, 1>, 512>(a, 128, lds + one, mx + one, s, round);
+}
+
+template <int D>
+static hipError_t launch_k_of(const QuantArgs &a, hipStream_t s)
+{
+    return a.bits == 2 ? launch_k_bits<D, 2>(a, s) : launch_k_bits<D, 4>(a, s);
+}
+
+// the min-max metric's search goes ahead; the indices are then given
+static hipError_t search_ahead(QuantArgs &a, hipStream_t s)
+{
+    if (a.metric != PK_METRIC_MINMAX) return hipSuccess;
+    a.idx_given = 1;
+    return launch_assign_minmax(a, s);
+}
+
 hipError_t launch_quantize_k(const QuantArgs &a_in, hipStream_t s)
 {
-    if (a_in.d != kD) return launch_generic_quantize(a_in, false, s);
     QuantArgs a = a_in;
-    if (a.metric == PK_METRIC_MINMAX) {
-        const hipError_t e = launch_assign_minmax(a, s);
-        if (e != hipSuccess) return e;
-        a.idx_given = 1;
+    const hipError_t e = search_ahead(a, s);
+    if (e != hipSuccess) return e;
+    return a.d == kD ? launch_k_of<kD>(a, s) : a.d == 96 ? launch_k_of<96>(a, s) : launch_k_of<256>(a, s);
+}
+
+template <int D, int BITS, int NG>
+static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
+{
+    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)VStaging<D>::kBytes, mx = table_lds_bytes<D>(256) + 4 * (size_t)VStaging<D>::kBytes;
+    const int round = one_round(a, 64, 512);
+    if constexpr (D != 256) {   // two blocks per table pass (three waves per SIMD instead of four) pay from 128 patterns on
+        if (a.P >= 128) return launch_tiled<quantize_v_kernel<D, BITS, NG, 2>>(a, 64, lds, mx, s, round);
     }
-    {
-        // (the pattern table, at most 256 rows = 74 KB, lives in LDS)
-        // Tiles of a group assigned per pass over the pattern table (every table tile read from LDS serves all of
-        // them): pairs keep three waves per SIMD; the whole 64-token group takes two, which pays above 128
-        // patterns; 32-token groups gain from pairs only once the table is large.
-        const int kmulti = a.G == 64 ? (a.P > 128 ? 4 : 2) : (a.P >= 128 ? 2 : 1);
-        // group 128 with a large table: one workgroup fills a CU's LDS and stages 64 KB of patterns, so a small
-        // job is cut into one resident round (256 workgroups) rather than many short ones
-        const int64_t tiles64k = (int64_t)(a.nq / 64) * a.n_streams;   // the same for the group-64 wave kernel above 128 patterns (one workgroup per CU)
-        const int bigw = a.P > 128 && tiles64k <= 256 * 64 ? (int)((tiles64k + 255) / 256) : 1;
-        const int64_t tiles128 = (int64_t)(a.nq / 128) * a.n_streams;
-        const int big1 = a.P > 128 && tiles128 <= 256 * 64 ? (int)((tiles128 + 255) / 256) : 1;
-#define PK_LAUNCH_K2(GG, BB)                                                                                       \
-    if (a.G == GG && a.bits == BB) {                                                                               \
-        constexpr int TT = GG == 128 ? 128 : 64;                                                                   \
-        return launch_tiled<quantize_k_kernel<GG, BB, 8>, 512>(a, TT, tile_lds_bytes(a.P, TT, GG), tile_lds_bytes(256, TT, GG), s, big1); \
+    return launch_tiled<quantize_v_kernel<D, BITS, NG, 1>>(a, 64, lds, mx, s, round);
+}
+
+template <int D, int BITS>
+static hipError_t launch_v_bits(const QuantArgs &a, hipStream_t s)
+{
+    if constexpr (D == 96) {
+        return a.G == 32 ? launch_v_groups<D, BITS, 3>(a, s) : launch_v_groups<D, BITS, 1>(a, s);
+    } else {
+        return a.G == 32 ? launch_v_groups<D, BITS, D / 32>(a, s) : a.G == 64 ? launch_v_groups<D, BITS, D / 64>(a, s)
+                                                                              : launch_v_groups<D, BITS, D / 128>(a, s);
     }
-#define PK_LAUNCH_KW(GG, BB)                                                                                       \
-    if (a.G == GG && a.bits == BB) {                                                                               \
-        /* a wave owns whole groups: at least four groups per workgroup */                                        \
-        const size_t lds = wave_k_lds_bytes(a.P), mx = wave_k_lds_bytes(256);                                      \
-        return kmulti == 4 && GG == 64 ? launch_tiled<quantize_k_wave_kernel<GG, BB, GG / 16>>(a, 64, lds, mx, s, bigw > GG / 16 ? bigw : GG / 16) \
-               : kmulti >= 2 ? launch_tiled<quantize_k_wave_kernel<GG, BB, 2>>(a, 64, lds, mx, s, GG / 16)         \
-                             : launch_tiled<quantize_k_wave_kernel<GG, BB, 1>>(a, 64, lds, mx, s, GG / 16);        \
-    }
-        PK_LAUNCH_KW(32, 2) PK_LAUNCH_KW(64, 2) PK_LAUNCH_K2(128, 2)
-        PK_LAUNCH_KW(32, 4) PK_LAUNCH_KW(64, 4) PK_LAUNCH_K2(128, 4)
-#undef PK_LAUNCH_KW
-#undef PK_LAUNCH_K2
-        return hipErrorInvalidValue;
-    }
+}
+
+template <int D>
+static hipError_t launch_v_of(const QuantArgs &a, hipStream_t s)
+{
+    return a.bits == 2 ? launch_v_bits<D, 2>(a, s) : launch_v_bits<D, 4>(a, s);
 }
 
 hipError_t launch_quantize_v(const QuantArgs &a_in, hipStream_t s)
 {
-    if (a_in.d != kD) return launch_generic_quantize(a_in, true, s);
     QuantArgs a = a_in;
-    if (a.metric == PK_METRIC_MINMAX) {
-        const hipError_t e = launch_assign_minmax(a, s);
-        if (e != hipSuccess) return e;
-        a.idx_given = 1;
-    }
-    {
-        const int ng = kD / (a.G < kD ? a.G : kD);
-        const size_t lds = tile_lds_bytes(a.P, 0, 1), mx = tile_lds_bytes(256, 0, 1);
-        const bool two = a.P >= 128;   // two blocks per table pass (three waves per SIMD instead of four) pay from 128 patterns on
-        // a large table (two workgroups per CU, 64 KB of patterns staged by each): a small job as one resident round
-        const int64_t tiles64 = (int64_t)(a.nq / 64) * a.n_streams;
-        const int big1 = a.P > 128 && tiles64 <= 512 * 64 ? (int)((tiles64 + 511) / 512) : 1;
-#define PK_LAUNCH_V2(BB, NN)                                                                   \
-    if (a.bits == BB && ng == NN)                                                              \
-        return two ? launch_tiled<quantize_v_kernel<BB, NN, 2>>(a, 64, lds, mx, s, big1)       \
-                   : launch_tiled<quantize_v_kernel<BB, NN, 1>>(a, 64, lds, mx, s);
-        PK_LAUNCH_V2(2, 1) PK_LAUNCH_V2(2, 2) PK_LAUNCH_V2(2, 4)
-        PK_LAUNCH_V2(4, 1) PK_LAUNCH_V2(4, 2) PK_LAUNCH_V2(4, 4)
-#undef PK_LAUNCH_V2
-        return hipErrorInvalidValue;
-    }
+    const hipError_t e = search_ahead(a, s);
+    if (e != hipSuccess) return e;
+    return a.d == kD ? launch_v_of<kD>(a, s) : a.d == 96 ? launch_v_of<96>(a, s) : launch_v_of<256>(a, s);
 }
 
 hipError_t launch_tail_copy(const TailCopyArgs &a, hipStream_t s)
 {
-    if (a.d != kD) return launch_generic_tail_copy(a, s);
-    const int64_t work = (int64_t)(a.i1 - a.i0) * kRowChunks;
+    const int64_t work = (int64_t)(a.i1 - a.i0) * (a.d / 8);
     if (work <= 0) return hipSuccess;
     const dim3 grid((unsigned)((work + 255) / 256), a.n_streams, 2), block(256);
-    hipLaunchKernelGGL(tail_copy_kernel, grid, block, 0, s, a);
+    if (a.d == kD)
+        hipLaunchKernelGGL(tail_copy_kernel<kD>, grid, block, 0, s, a);
+    else if (a.d == 96)
+        hipLaunchKernelGGL(tail_copy_kernel<96>, grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL(tail_copy_kernel<256>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

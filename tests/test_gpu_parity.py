@@ -992,3 +992,21 @@ def test_minmax_search_parity(oracle, pk, d, P, n_c):
               flush=64, t_capacity=T, metric=1)
     oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [64, T - 64])
     assert compare_caches(oracle, oc, gc, 1) == 0
+
+
+@pytest.mark.parametrize("d,bits,G,P,rho", [
+    (96, 2, 32, 16, 0.0), (96, 4, 32, 130, 0.8), (96, 2, 128, 200, 0.0), (96, 4, 128, 64, 0.0),
+    (256, 2, 32, 64, 0.8), (256, 4, 32, 250, 0.0), (256, 2, 64, 130, 0.0), (256, 4, 64, 16, 0.0), (256, 2, 128, 256, 0.0),
+    (128, 4, 128, 129, 0.0),      # two groups of 128 tokens per workgroup, an odd number of groups
+])
+def test_quantizers_over_head_dimensions(oracle, pk, d, bits, G, P, rho):
+    """The quantizers' instantiations over head dimension, bits, group and table size (tables that take one workgroup per
+    CU included) with ragged tails and groups that do not fill a workgroup: bytes equal the oracle's where indices do."""
+    hkv, T, F = 2, 640 + 37, max(64, G)
+    K, V = synth.make_kv(500 + d + P + bits, synth.KVSpec(1, 1, hkv, hkv, T, d, 20))
+    Mk = np.ascontiguousarray(K[0][:, :P]).view(np.uint16)
+    Mv = np.ascontiguousarray(V[0][:, T - P:]).view(np.uint16)
+    kw = dict(n_seq=1, n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G, recent=5,
+              flush=F, t_capacity=-(-T // F) * F, metric=0, v_rho=rho)
+    oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [200, 1, T - 201])
+    assert compare_caches(oracle, oc, gc, 0) <= 4
