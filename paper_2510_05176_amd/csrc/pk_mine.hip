@@ -38,6 +38,19 @@ __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 // vectors of 96 channels at 64 patterns 9.40 -> 2.14 ms (step 103 us), of 256 channels (8192 vectors) 19.9 -> 5.0 ms; 64
 // sets of 256 channels at 200 patterns 14.0 -> 3.4 ms.  Bound by instruction issue and LDS reads, not by the vectors (39 us
 // of traffic in a step at 96 channels).
+// Sorted sub-tiles (step_sorts): a wave sums a few pattern tiles only, but walked every vector of the sub-tile and multiplied it by
+// a one-hot operand that is mostly zero.  The vectors are stored to the tile in the order of the wave that sums their
+// pattern instead (a counting sort: ranks by ballot, the counts of all waves through LDS, a scan), and a wave walks its own run
+// of rows, 32 at a time from a multiple of four; rows of its neighbours in the first and last step match none of its
+// patterns.  The barrier of the counts replaces the one behind the sums.  The next sub-tile's vectors are requested before the
+// search, into a buffer of their own, so that they are in flight for the whole of it (without the sort that gained nothing).
+// A quarter (two thirds at 256 patterns) of the matrix instructions less per vector; 256 sets, 2 x 10 iterations: 32768
+// vectors at 128 patterns 14.8 -> 13.8 ms (15.1 -> 14.2 on another card); 8 sets x 16384 at 256
+// patterns 817 -> 787 us; 64 sets of 256 channels at 200 patterns 3.50 -> 3.16 ms.  With 64 patterns the sort costs more than
+// the two steps that it saves (2.6 -> 2.8 ms on 256 sets x 8192), and at 256 channels and 128 patterns it gained nothing
+// (2.79 -> 2.80 ms).  Neither matrix cores (24 % busy) nor vector ALUs (44 %) nor HBM (57 %) bound the step at 128
+// patterns: two waves per SIMD, a third of their time waiting at barriers and for loads; four waves per SIMD at 96
+// channels gained 3 %, at 128 they spill.
 // With XC < D (256 channels and more than 128 patterns: the table alone takes 139 KB) the vectors pass through the LDS tile
 // XC channels at a time, the sums of those channels being formed between two barriers each; a wave's own rows of that tile
 // then serve as its re-evaluation row.
@@ -47,9 +60,26 @@ template <int XC>
 constexpr int kMineXsOf = XC + 16;   // halves per row of the vector tile: 8 words modulo 16, so the eight rows that 32
                                      // lanes of a transposing read touch (8 words each) fall on 64 distinct banks
 
+// sum over the lanes up to this one (the first N lanes, 16 or 64)
+template <int N>
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row shifts by 1, 2, 4 and 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    if constexpr (N > 16) {
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    }
+    return v;
+}
+
 typedef _Float16 half2m __attribute__((ext_vector_type(2)));
 typedef short short4m __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4m *lds_short4_ptr;
+
+constexpr bool step_sorts(int D, int NPT) { return NPT == 16 || (NPT == 8 && D <= 128); }
 
 template <int D, int NPT, int NW, int NT, int XC>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && NPT <= 4 && D <= 128 ? 4 : 2))) void mine_step_kernel(MineArgs a, int chunk, int outputs)
@@ -62,10 +92,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     int *cnt = reinterpret_cast<int *>(norm_s + pad16(P));
     __half *xs = reinterpret_cast<__half *>(cnt + pad16(P));
     constexpr int ST = 16 * NT * NW;     // vectors per sub-tile: NT 16-vector tiles per wave
-    __half *idx_s = xs + ST * kXs;       // pattern index of every vector of the sub-tile, as an fp16 number
+    __half *idx_s = xs + ST * kXs;       // pattern index of every row of the sub-tile, as an fp16 number
     __shared__ float red_s[NW];
+    constexpr bool kSort = step_sorts(D, NPT);
+    constexpr int kStepUnroll = kSort ? 1 : ST / 32;
+    __shared__ int bucket_s[NW * NW];   // [bucket][wave]: vectors of the wave's in the bucket (the pattern rows that one wave sums)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     static_assert(XC == D || 16 * NT * kXs >= D, "a wave's rows of the vector tile hold one vector");
     __half *xrow_s = XC == D ? idx_s + ST + wave * D : xs + wave * NT * 16 * kXs;
     const int ck = blockIdx.x, s = blockIdx.y;
@@ -81,8 +115,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             for (int k = 0; k < KS; ++k) xb[j][k] = *reinterpret_cast<const uint4 *>(xg + (int64_t)tok * D + 32 * k + 8 * kb);
         }
     };
-    uint4 xb[NT][KS];
-    load_tile(0, xb);
+    constexpr bool kAhead = kSort && D <= 128;   // a vector buffer more: loads are in flight for a whole sub-tile
+    uint4 xb[NT][KS], xn[NT][KS];
+    load_tile(0, kAhead ? xn : xb);
 
     for (int i = tid; i < pad16(P); i += 64 * NW) cnt[i] = 0;
     stage_patterns<D>(Mg, P, tab_s, norm_s, red_s, 64 * NW);   // ends with a barrier
@@ -117,22 +152,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
 
     const int n_sub = (n_tok + ST - 1) / ST;
     for (int sub = 0; sub < n_sub; ++sub) {
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) xb[j][k] = xn[j][k];
+            }
+            if (sub + 1 < n_sub) load_tile(sub + 1, xn);
+        }
         int bi[NT];
         float bv[NT], x2[NT];
         bool flag[NT];
         assign_tiles_mfma<NT, KS>(xb, tb, lane, bi, bv, x2, flag);
+        int at[NT];   // row of the tile that takes the lane's vector
+        int step0 = 0, n_steps = ST / 32;   // this wave's 32-vector steps: rows step0 .. step0 + 32 n_steps - 1
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const int tl = (wave * NT + j) * 16 + n, tok = sub * ST + tl;
             float bd = fmaxf(bv[j], 0.f);
             resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd);
-            if constexpr (XC == D) {
-#pragma unroll
-                for (int k = 0; k < KS; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
-                    *reinterpret_cast<uint4 *>(xs + tl * kXs + 32 * k + 8 * kb) = tok < n_tok ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
-            }
+            at[j] = (wave * NT + j) * 16 + n;
+            const int tok = sub * ST + at[j];
             if (kb == 0) {
-                idx_s[tl] = __float2half_rn((float)bi[j]);   // integers below 2048 are exact
                 if (tok < n_tok) {
                     // per-vector outputs only where somebody reads them: indices from the last step (if asked
                     // for), distances when the objective is reported
@@ -142,24 +182,62 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
                 }
             }
         }
+        if constexpr (kSort) {
+            // lane (n, kb = j) speaks for vector n of tile j: its bucket, and its rank among the wave's vectors of that bucket
+            int mine = bi[0];
+#pragma unroll
+            for (int j = 1; j < NT; ++j) mine = kb == j ? bi[j] : mine;
+            const int bucket = min(mine / (16 * PW), NW - 1);   // (a vector that is not a number has no nearest pattern; it gets a row too)
+            int rank = 0;
+            int count = 0;   // lane w: vectors in bucket w
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const uint64_t in = __ballot(bucket == w) & ((1ull << 16 * (NT - 1) << 16) - 1);
+                const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0u));
+                rank = bucket == w ? below : rank;
+                count = lane == w ? __popcll(in) : count;
+            }
+            if (lane < NW) bucket_s[lane * NW + wave] = count;
+            __syncthreads();   // also: every wave has read the previous sub-tile's rows
+            // first row of every (bucket, wave): the sum of all entries before it
+            const int own = lane < NW * NW ? bucket_s[lane] : 0;
+            const int upto = wave_scan<NW * NW>(own);
+            const int first = upto - own;
+            const int row = __shfl(first, bucket * NW + wave) + rank;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) at[j] = __shfl(row, 16 * j + n);
+            const int start = __builtin_amdgcn_readlane(first, wave_u * NW), end = __builtin_amdgcn_readlane(upto, wave_u * NW + NW - 1);
+            step0 = start & ~3;
+            n_steps = end > start ? (end - step0 + 31) / 32 : 0;
+            step0 = min(step0, ST - 32 * n_steps);   // the last step stays inside the tile
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
+            if constexpr (XC == D) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
+                    *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
+            }
+            if (kb == 0) idx_s[at[j]] = __float2half_rn((float)bi[j]);   // integers below 2048 are exact
+        }
 #pragma unroll
         for (int part = 0; part < D / XC; ++part) {   // channels part * XC .. of the vectors
             if constexpr (XC < D) {
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
-                    const int tl = (wave * NT + j) * 16 + n;
-                    const bool in = sub * ST + tl < n_tok;
+                    const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
 #pragma unroll
                     for (int k = 0; k < XC / 32; ++k)
-                        *reinterpret_cast<uint4 *>(xs + tl * kXs + 32 * k + 8 * kb) = in ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
+                        *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
                 }
             }
-            if (part == D / XC - 1 && sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation
+            if (!kAhead && part == D / XC - 1 && sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation
             __syncthreads();
-#pragma unroll
-            for (int ks = 0; ks < ST / 32; ++ks) {
-                // 32 vectors per step; this lane's k-slots 0-3 are vectors ta .. ta+3, its slots 4-7 the ones 16 later
-                const int ta = 32 * ks + 4 * kb;
+#pragma unroll kStepUnroll
+            for (int ks = 0; ks < n_steps; ++ks) {
+                // 32 rows per step; this lane's k-slots 0-3 are rows ta .. ta+3, its slots 4-7 the ones 16 later
+                const int ta = step0 + 32 * ks + 4 * kb;
                 const uint2 ia = *reinterpret_cast<const uint2 *>(idx_s + ta);
                 const uint2 ib = *reinterpret_cast<const uint2 *>(idx_s + ta + 16);
                 const half2m idh[4] = {__builtin_bit_cast(half2m, ia.x), __builtin_bit_cast(half2m, ia.y),
@@ -193,7 +271,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
                     for (int pi = 0; pi < PW; ++pi) acc[pi][ai] = mfma_f16(av[pi], bop, acc[pi][ai]);
                 }
             }
-            __syncthreads();
+            // (sorted: the next sub-tile's barrier behind its search comes before anything is stored to the tile again)
+            if (!kSort || XC < D) __syncthreads();
         }
     }
     // partial sums of the chunk: D rows 4kb+i = pattern 16(pt0 + pi) + 4kb + i, column n = channel 16(ct0 + ci) + n

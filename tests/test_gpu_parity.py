@@ -973,6 +973,19 @@ def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
         cur = np.stack([new[s] for s in range(2)])
 
 
+@pytest.mark.parametrize("d,P,T", [(128, 65, 1500), (128, 128, 900), (128, 129, 900), (128, 256, 1300), (96, 97, 700), (256, 130, 700)])
+def test_mining_parity_uneven_clusters(oracle, pk, d, P, T):
+    """Sub-tiles that are sorted by the wave that sums a vector's pattern: hundreds of vectors in a row that are all
+    nearest to the first pattern (one wave sums whole sub-tiles, the others nothing), then as many of the last one, among
+    vectors spread over the table, with ragged ends."""
+    K, _ = synth.make_kv(700 + d + P, synth.KVSpec(1, 1, 2, 2, T, d, 24))
+    x = K[0].copy()
+    noise = np.random.default_rng(P).normal(0.0, 0.02, (2, 200, d)).astype(np.float16)
+    x[:, P:P + 200] = x[:, :1] + noise
+    x[:, P + 200:P + 400] = x[:, P - 1:P] + noise
+    _mining_step_parity(oracle, pk, x, P, x[:, :P].copy().view(np.uint16), check_sets=range(2))
+
+
 @pytest.mark.parametrize("d,P,n_c", [
     (128, 1, 4), (128, 2, 1), (128, 33, 16), (128, 64, 1), (128, 65, 48), (128, 200, 100), (128, 256, 1),
     (96, 7, 7), (96, 63, 1), (96, 130, 40),
