@@ -24,7 +24,8 @@ template <int RP>
 __global__ __launch_bounds__(256) void decode_tail_kernel(DecodeArgs a)
 {
     __shared__ TailShared<RP> sh;
-    decode_tail_body<RP>(a, blockIdx.x, blockIdx.y, blockIdx.z, sh);
+    const int r = a.n_q_heads / a.n_kv_heads / a.head_groups;
+    decode_tail_body<RP>(a, blockIdx.x, blockIdx.y, blockIdx.z * r, r, sh);
 }
 
 // log-sum-exp merge of the partials of one (sequence, query head); 128*NQ threads, thread <-> (channel c,
@@ -184,8 +185,8 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
     const int r = a.n_q_heads / a.n_kv_heads;
     // the matrix-core kernel holds the (head, V channel group) pairs of a group of heads in the 16 columns of one tile
     // and takes up to 8 heads per group, the heads of a KV head in one group or two; what does not fit (5 or 7 heads
-    // with 32-channel groups, an odd head count above 8, more than 16 heads) and the other head dimensions run the
-    // plain kernels
+    // with 32-channel groups, an odd head count above 8, more than 16 heads) and the other head dimensions run the kernel of
+    // pk_generic.hip
     const int rg = r / a.head_groups;
     if (a.d != kD || rg > 8 || rg * (kD / (a.G < kD ? a.G : kD)) > 16) return launch_generic_decode(a, s);
     const int N = a.n_seq * a.n_kv_heads;

@@ -32,6 +32,7 @@
 // n >= 8 the second (the other operand is zero): output rows rho and rho + 8 are two partial sums of one (h, g)
 // pair and are added in the epilogue.
 #include "pk_internal.h"
+#include "pk_decode_fields.h"
 #include "pk_decode_tail.h"
 
 namespace pk {
@@ -39,62 +40,6 @@ namespace pk {
 namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
-
-__device__ __forceinline__ floatx4 mfma16(const uint32_t *a, const uint32_t *b, floatx4 c)
-{
-    union { uint32_t u[4]; half8 h; } A, B;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        A.u[i] = a[i];
-        B.u[i] = b[i];
-    }
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(A.h, B.h, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t pack2(_Float16 lo, _Float16 hi)
-{
-    half2v v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, v);
-}
-__device__ __forceinline__ uint32_t pk_mul(uint32_t a, uint32_t b)
-{
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, a) * __builtin_bit_cast(half2v, b));
-}
-__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
-{
-    return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, a), __builtin_bit_cast(half2v, b), c, false);
-}
-__device__ __forceinline__ uint32_t cvt2(float lo, float hi)
-{
-    float2v f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, half2v));
-}
-
-// Sixteen 2-bit fields at the even bit positions of X -> eight operand registers.  Register v
-// holds, in its low half, the field of X-bit e_lo(v) and, in its high half, the field of X-bit
-// e_lo(v) + 16, both at mantissa position pos(v):
-//   v = 0..4: e_lo = 2v, pos = 2v ;  v = 5..7: e_lo = 10 + 2(v-5), pos = 2(v-5).
-__device__ __forceinline__ void fields_to_operand(uint32_t X, uint32_t *out)
-{
-    out[0] = X & 0x00030003u;
-    out[1] = X & 0x000C000Cu;
-    out[2] = X & 0x00300030u;
-    out[3] = X & 0x00C000C0u;
-    out[4] = X & 0x03000300u;
-    const uint32_t Y = X >> 10;
-    out[5] = Y & 0x00030003u;
-    out[6] = Y & 0x000C000Cu;
-    out[7] = Y & 0x00300030u;
-}
-__host__ __device__ constexpr int e_lo(int v) { return v < 5 ? 2 * v : 10 + 2 * (v - 5); }
-__host__ __device__ constexpr int fpos(int v) { return v < 5 ? 2 * v : 2 * (v - 5); }
 
 struct GroupOperand {
     uint32_t Bq[16];   // q[h][c] * s[g][c] * 2^(8-pos) rounded to fp16, operand order
@@ -152,10 +97,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         const int id = ((int)blockIdx.y - NG2) * (int)gridDim.x + (int)blockIdx.x;
         if (id >= NG2 * (a.prefix.t_tail > 0 ? 2 : 1)) return;
         const int which = id / NG2, sg = id - which * NG2;
-        if (a.n_q_heads / a.n_kv_heads / a.head_groups <= 4)
-            decode_tail_body<4>(a, which, sg / a.head_groups, sg % a.head_groups, *reinterpret_cast<TailShared<4> *>(dyn_smem));
+        const int rg = a.n_q_heads / a.n_kv_heads / a.head_groups;
+        if (rg <= 4)
+            decode_tail_body<4>(a, which, sg / a.head_groups, sg % a.head_groups * rg, rg, *reinterpret_cast<TailShared<4> *>(dyn_smem));
         else
-            decode_tail_body<8>(a, which, sg / a.head_groups, sg % a.head_groups, *reinterpret_cast<TailShared<8> *>(dyn_smem));
+            decode_tail_body<8>(a, which, sg / a.head_groups, sg % a.head_groups * rg, rg, *reinterpret_cast<TailShared<8> *>(dyn_smem));
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kb = lane >> 4;

@@ -230,7 +230,7 @@ int mine_tsplit(int T, int n_sets, int P);   // the most chunks per set launch_m
 hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, __half *out, int64_t out_stride,
                                  hipStream_t s);
 
-// Head dimensions other than kD (pk_generic.hip): plain kernels, thread <-> channel, same results to the same bars.
+// Head dimensions other than kD (pk_generic.hip)
 hipError_t launch_generic_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, int d, __half *out,
                                          int64_t out_stride, hipStream_t s);
 

@@ -961,6 +961,47 @@ def test_other_head_dimensions_decode_splits(oracle, pk, d, hkv, hq, bits, G, P,
     assert_attention(one[0], want[big])
 
 
+@pytest.mark.parametrize("d,G,bits,hkv,hq,n_seq,R", [
+    (256, 64, 2, 8, 32, 32, 40),      # two blocks per wave and split
+    (256, 32, 4, 8, 8, 40, 70),       # two K groups per block, r = 1; four blocks per wave
+    (256, 128, 2, 4, 28, 64, 0),      # r = 7
+    (96, 32, 2, 8, 24, 40, 0), (96, 128, 4, 2, 18, 128, 5),   # r = 9: a second workgroup with one head
+    (128, 32, 2, 4, 28, 80, 33),      # 128 channels, a head count that the fp16 kernel does not take
+])
+def test_decode_binary32_accuracy(pk, d, G, bits, hkv, hq, n_seq, R):
+    """The decode of head dimensions 96 and 256 (and of odd head counts) against attention in 64 bits over the reconstructed
+    cache, with K scales far above and V scales far apart from what a fixed fp16 scaling would hold (V grows by 300 from block
+    to block: the accumulators are rescaled).  Bound: binary32 sums of 1024 terms, and scores of magnitude 30 with an
+    error of a few units of 2^-24 * 30 each, which the exponential passes on: 1e-5 leaves a factor of five."""
+    T, P, F = 1024, 16, max(64, G)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + G + hq)
+    K = torch.randn((n_seq, hkv, T, d), generator=gen, device="cuda")
+    K[..., ::16] *= 8.0
+    K = (K * 200.0).half()
+    V = (torch.randn(K.shape, generator=gen, device="cuda") * torch.tensor([1e-2, 3.0], device="cuda").repeat(T // 128).repeat_interleave(64)[:, None]).half()
+    q = (torch.randn((n_seq, hq, d), generator=gen, device="cuda") / 200.0).half()
+    Mk, Mv = K[0, :, :P].contiguous(), V[0, :, 60:60 + P].contiguous()
+    cfg = pk.Config(n_seq=n_seq, n_kv_heads=hkv, n_q_heads=hq, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G,
+                    recent=R, flush=F, t_capacity=T, metric=0)
+    cache = pk.Cache(cfg)
+    pk.pk_quantize_append(cfg, cache, K, V, Mk, Mv)
+    got = pk.pk_decode_attention(cfg, cache, q, d ** -0.5, Mk, Mv).double()
+    kd, vd = pk.pk_dequantize(cfg, cache, Mk, Mv)
+    tq = cache.t_quant
+    kd = torch.cat([kd.view(n_seq, hkv, tq, d).double(), K[:, :, tq:].double()], 2)
+    vd = torch.cat([vd.view(n_seq, hkv, tq, d).double(), V[:, :, tq:].double()], 2)
+    qd = q.double().view(n_seq, hkv, hq // hkv, d)
+    want = torch.empty_like(qd)
+    for i in range(n_seq):
+        for h in range(hkv):
+            want[i, h] = torch.softmax(qd[i, h] @ kd[i, h].T.contiguous() * d ** -0.5, -1) @ vd[i, h]
+    want = want.view(n_seq, hq, d)
+    err = ((got - want).norm(dim=2) / want.norm(dim=2))
+    assert tq >= T - R - F and torch.isfinite(got).all()
+    assert float((got - want).norm() / want.norm()) <= 1e-5, (float(err.max()), float(err.median()))
+
+
 @pytest.mark.parametrize("d,P,T", [(96, 16, 333), (96, 17, 700), (96, 64, 257), (96, 128, 600), (96, 129, 700), (256, 9, 300),
                                    (256, 32, 513), (256, 64, 700), (256, 65, 400), (256, 128, 513), (256, 200, 700), (256, 256, 640)])
 def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
