@@ -124,8 +124,8 @@ typedef struct {
     int32_t n_q_heads;    /* multiple of n_kv_heads; r = n_q_heads/n_kv_heads in 1..64 (at d = 128 the matrix-core
                              decode kernel takes r <= 8 and even r up to 16, with G = 32 r = 1..4, 6 or 8; other head
                              counts decode through a kernel of their own)                         */
-    int32_t head_dim;     /* d: 128 (the tuned kernels), or 96 / 256 (the other head sizes of Sec. 3.3: plain
-                             vector-ALU kernels; every call takes them).  min(G, d)
+    int32_t head_dim;     /* d: 128, or 96 / 256 (the other head sizes of Sec. 3.3; every call takes them; their
+                             decode computes in binary32 accuracy).  min(G, d)
                              must divide d (d = 96: G = 32 or 128)                                  */
     int32_t n_patterns;   /* P: 1..256 (indices are stored in one byte)                       */
     int32_t seqs_per_set; /* see "Streams and pattern sets" above; >= 0                       */
