@@ -222,6 +222,9 @@ pk_status pk_decode_plan(const pk_config *cfg, int64_t own_packed, int64_t prefi
  *              step (taken against the centroids before the last update)
  *   inertia    optional [n_sets][iters] float: within-cluster sum of squares
  *              seen by each assignment step
+ * A vector with an infinite or NaN channel has no nearest pattern: it belongs to no cluster (its
+ * assignment is 0x7fffffff) and its distance in the inertia is infinite; the other vectors are
+ * mined as if it were not there.
  * Sums are formed in a fixed order: results are reproducible bit for bit.
  */
 pk_status pk_mine_patterns(const pk_config *cfg, const void *x, int64_t set_stride, int32_t n_sets,

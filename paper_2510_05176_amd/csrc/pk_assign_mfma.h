@@ -28,6 +28,9 @@ template <int D>
 constexpr int kTabStrideOf = D + 16;
 constexpr int kTabStride = kTabStrideOf<kD>;
 
+// Index of a vector that no pattern is nearest to: it is not finite, or no pattern is, so that no distance is below infinity.
+constexpr int kNoNearest = 0x7fffffff;
+
 __host__ __device__ constexpr int pad16(int p) { return (p + 15) & ~15; }
 
 struct PatternTable {
@@ -172,7 +175,7 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], con
             a2 = min(min(a2, o2), max(a1, o1));
             a1 = min(a1, o1);
         }
-        best_i[j] = (int)(a1 & 0xffu);
+        best_i[j] = tb.P > 1 ? (int)(a1 & 0xffu) : 0;   // (not a number, a single pattern could lose to the rows behind the table)
         best_v[j] = -2.f * __uint_as_float(a1 & 0xffffff00u);
         const float second = -2.f * __uint_as_float(a2 & 0xffffff00u);
         x2[j] = xx[j];
@@ -199,13 +202,14 @@ __device__ __forceinline__ void assign_tile_mfma(const uint4 (&xb)[KS], const Pa
 }
 
 // Exact re-evaluation of one token by a whole wave: xrow_s = its D channels (fp16) in LDS.
-// Every lane returns the exact argmin (lowest index on ties) and its distance.
+// Every lane returns the exact argmin (lowest index on ties) and its distance; kNoNearest and infinity where no distance
+// is below infinity.
 template <int D>
 __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const PatternTable &tb, int lane, int &best_i,
                                                   float &best_d)
 {
     float bd = INFINITY;
-    int bi = 0x7fffffff;
+    int bi = kNoNearest;
     for (int p = lane; p < tb.P; p += 64) {
         // the pattern rows come from the LDS copy of the table (the same fp16 values): read from global memory they
         // missed L2 often enough to add a fifth to the HBM traffic of a mining step on a large job
@@ -240,10 +244,11 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
     best_d = bd;
 }
 
-// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.
+// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.  A token that no pattern is
+// nearest to (always flagged: its gap is not a number or infinite) gets the index `none`.
 template <int KS>
 __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag, __half *xrow_s, const PatternTable &tb,
-                                                int lane, int &best_i, float &best_d)
+                                                int lane, int &best_i, float &best_d, int none)
 {
     const int n = lane & 15, kb = lane >> 4;
     unsigned long long todo = __ballot(flag) & 0xffffull;   // one bit per column
@@ -260,7 +265,7 @@ __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag
         float bd;
         exact_argmin_wave<32 * KS>(xrow_s, tb, lane, bi, bd);
         if (n == col) {
-            best_i = bi;
+            best_i = bi == kNoNearest ? none : bi;
             best_d = bd;
         }
         __builtin_amdgcn_wave_barrier();

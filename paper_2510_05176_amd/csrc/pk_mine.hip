@@ -165,21 +165,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
         bool flag[NT];
         assign_tiles_mfma<NT, KS>(xb, tb, lane, bi, bv, x2, flag);
         int at[NT];   // row of the tile that takes the lane's vector
+        bool member[NT];   // the vector belongs to a cluster: inside the chunk, and some pattern is nearest to it
         int step0 = 0, n_steps = ST / 32;   // this wave's 32-vector steps: rows step0 .. step0 + 32 n_steps - 1
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             float bd = fmaxf(bv[j], 0.f);
-            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd);
+            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd, kNoNearest);
             at[j] = (wave * NT + j) * 16 + n;
             const int tok = sub * ST + at[j];
+            if (!(x2[j] < INFINITY)) {   // (a single pattern is never evaluated again)
+                bi[j] = kNoNearest;
+                bd = INFINITY;
+            }
+            member[j] = tok < n_tok && bi[j] < P;
             if (kb == 0) {
                 if (tok < n_tok) {
                     // per-vector outputs only where somebody reads them: indices from the last step (if asked
                     // for), distances when the objective is reported
                     if (outputs & 1) a.assign[(int64_t)s * a.T + t_begin + tok] = bi[j];
                     if (outputs & 2) a.best[(int64_t)s * a.T + t_begin + tok] = bd;
-                    atomicAdd(&cnt[bi[j]], 1);
                 }
+                if (member[j]) atomicAdd(&cnt[bi[j]], 1);
             }
         }
         if constexpr (kSort) {
@@ -187,7 +193,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             int mine = bi[0];
 #pragma unroll
             for (int j = 1; j < NT; ++j) mine = kb == j ? bi[j] : mine;
-            const int bucket = min(mine / (16 * PW), NW - 1);   // (a vector that is not a number has no nearest pattern; it gets a row too)
+            const int bucket = min(mine / (16 * PW), NW - 1);   // (a vector without a nearest pattern gets a row too, of zeros)
             int rank = 0;
             int count = 0;   // lane w: vectors in bucket w
 #pragma unroll
@@ -213,11 +219,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
         }
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
             if constexpr (XC == D) {
 #pragma unroll
-                for (int k = 0; k < KS; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
-                    *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
+                for (int k = 0; k < KS; ++k)   // the row of a vector that is no member is stored as zeros, so it adds nothing to any sum
+                    *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = member[j] ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
             }
             if (kb == 0) idx_s[at[j]] = __float2half_rn((float)bi[j]);   // integers below 2048 are exact
         }
@@ -226,10 +231,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             if constexpr (XC < D) {
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
-                    const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
 #pragma unroll
                     for (int k = 0; k < XC / 32; ++k)
-                        *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
+                        *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = member[j] ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
                 }
             }
             if (!kAhead && part == D / XC - 1 && sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation

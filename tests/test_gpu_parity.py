@@ -1064,3 +1064,37 @@ def test_quantizers_over_head_dimensions(oracle, pk, d, bits, G, P, rho):
               flush=F, t_capacity=-(-T // F) * F, metric=0, v_rho=rho)
     oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [200, 1, T - 201])
     assert compare_caches(oracle, oc, gc, 0) <= 4
+
+
+@pytest.mark.parametrize("d,P", [(128, 1), (128, 16), (128, 64), (128, 128), (128, 200), (96, 1), (96, 17), (96, 130),
+                                 (256, 1), (256, 64), (256, 80), (256, 256)])
+def test_mining_leaves_non_finite_vectors_out(oracle, pk, d, P):
+    """One infinite and one NaN channel in vectors of a set (inside a sub-tile, and the last one of a ragged chunk): the vectors
+    belong to no cluster, and all others are mined as if they were not there."""
+    T = 700
+    K, _ = synth.make_kv(900 + d + P, synth.KVSpec(1, 1, 2, 2, T, d, 24))
+    x = K[0].copy()
+    x[0, P + 5, 3], x[0, T - 1, d - 1] = np.inf, np.nan
+    x[1, P, 0], x[1, P + 131, d // 2] = np.nan, -np.inf
+    bad = {0: [P + 5, T - 1], 1: [P, P + 131]}
+    cur = x[:, :P].copy().view(np.uint16)
+    pat = dev(cur.view(np.float16)).clone()
+    asg = torch.empty((2, T), dtype=torch.int32, device="cuda")
+    J = torch.empty((2, 1), dtype=torch.float32, device="cuda")
+    pk.pk_mine_patterns(pk.Config(n_patterns=P, head_dim=d), dev(x), 1, patterns=pat, init_given=True, assign=asg, inertia=J)
+    ag, Mg = asg.cpu().numpy(), host_u16(pat)
+    assert np.isposinf(J.cpu().numpy()).all()
+    for s in range(2):
+        assert (ag[s][bad[s]] == 0x7fffffff).all()
+        good = np.delete(x[s], bad[s], axis=0).view(np.uint16)
+        Mo, ao, _, _ = oracle.mine(good[None], P, 1, init=cur[s:s + 1])
+        ag_good = np.delete(ag[s], bad[s])
+        diff = ag_good != ao[0]
+        if diff.any():
+            _, best, second = oracle.assign(good, cur[s], 0)
+            assert np.all((second - best)[diff] < 1e-4 * second[diff])
+        clean = np.ones(P, bool)
+        clean[np.unique(np.concatenate([ag_good[diff], ao[0][diff]]))] = False
+        assert _ulp_diff(Mg[s][clean], Mo[0][clean]).max() <= 1
+    tables = pk.pk_mine_patterns(pk.Config(n_patterns=P, head_dim=d), dev(x), 4)   # the first P vectors are finite
+    assert torch.isfinite(tables).all()
