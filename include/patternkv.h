@@ -242,7 +242,8 @@ pk_status pk_mine_patterns(const pk_config *cfg, const void *x, int64_t set_stri
  *                 base + n*stream_stride elements (stream_stride 0 = n_new*d)
  *   patterns_k/_v [n_sets][P][d] fp16
  *   state         host, in/out
- * n_new == 0 is a no-op.  Prefill is one call with n_new = prompt length.
+ * n_new == 0 is a no-op.  Prefill is one call with n_new = prompt length.  A vector with an infinite or
+ * NaN channel takes pattern 0 where no pattern is nearer.
  */
 pk_status pk_quantize_append(const pk_config *cfg, const pk_cache *cache, pk_state *state,
                              const void *k_new, const void *v_new, int32_t n_new,

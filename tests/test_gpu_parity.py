@@ -1098,3 +1098,49 @@ def test_mining_leaves_non_finite_vectors_out(oracle, pk, d, P):
         assert _ulp_diff(Mg[s][clean], Mo[0][clean]).max() <= 1
     tables = pk.pk_mine_patterns(pk.Config(n_patterns=P, head_dim=d), dev(x), 4)   # the first P vectors are finite
     assert torch.isfinite(tables).all()
+
+
+@pytest.mark.parametrize("d,bits,G,P,rho", [(128, 2, 64, 16, 0.0), (128, 4, 128, 40, 0.0), (128, 2, 128, 200, 0.0), (128, 2, 32, 130, 0.8),
+                                            (96, 2, 32, 17, 0.0), (96, 4, 128, 130, 0.8), (256, 2, 64, 64, 0.0), (256, 4, 128, 256, 0.0)])
+def test_append_of_non_finite_vectors(oracle, pk, d, bits, G, P, rho):
+    """Vectors with an infinite or a NaN channel take the lowest index under the Euclidean rule; only the parameters of the
+    groups that hold such a channel depend on it: every other parameter and code equals the oracle's."""
+    T, F = 384, max(64, G)
+    K, V = synth.make_kv(950 + d + P, synth.KVSpec(1, 1, 1, 1, T, d, 20))
+    Mk = np.ascontiguousarray(K[0][:, 100:100 + P]).view(np.uint16)
+    Mv = np.ascontiguousarray(V[0][:, 100:100 + P]).view(np.uint16)
+    K, V = K.copy(), V.copy()
+    bad = [(7, 3, np.inf), (200, d - 1, np.nan), (383, d // 2, -np.inf)]
+    for t, c, v in bad:
+        K[0, 0, t, c] = V[0, 0, t, c] = v
+    kw = dict(n_seq=1, n_kv_heads=1, n_q_heads=1, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G, recent=0,
+              flush=F, t_capacity=T, metric=0, v_rho=rho)
+    oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [T])
+    g = gpu_arrays(gc, oc)
+    tok_bad = np.zeros(T, bool)
+    tok_bad[[t for t, _, _ in bad]] = True
+    assert (g["k_idx"][0, tok_bad] == 0).all()
+    if rho == 0.0:
+        assert (g["v_idx"][0, tok_bad] == 0).all()
+    same_k = (g["k_idx"] == oc.k_idx)[0]
+    same_v = (g["v_idx"] == oc.v_idx)[0]
+    for side, same in (("k", same_k), ("v", same_v)):
+        best, second = getattr(oc, side + "_best")[0], getattr(oc, side + "_second")[0]
+        assert np.all((second - best)[~same & ~tok_bad] < 1e-4 * second[~same & ~tok_bad])
+    # K: (group, channel) pairs without a bad value, groups with the oracle's indices
+    clean = np.repeat(same_k.reshape(-1, G).all(1)[:, None], d, axis=1)
+    for t, c, _ in bad:
+        clean[t // G, c] = False
+    assert clean.sum() >= (T // G - 2) * d - len(bad)
+    assert np.array_equal(g["k_scale"][0][clean], oc.k_scale[0][clean])
+    assert np.array_equal(g["k_zero"][0][clean], oc.k_zero[0][clean])
+    code = lambda words: (words[:, :, None, :] >> np.arange(32, dtype=np.uint32)[None, None, :, None]) & 1   # [t][word][bit][plane]
+    cg, co = (code(w[0]).reshape(T, d, bits) for w in (g["k_codes"], oc.k_codes))
+    assert np.array_equal(cg[np.repeat(clean, G, axis=0)], co[np.repeat(clean, G, axis=0)])
+    # V: all tokens without a bad value
+    good = same_v & ~tok_bad
+    by_tok = lambda a: a[0].transpose(0, 2, 1).reshape(T, -1)
+    assert np.array_equal(by_tok(g["v_scale"])[good], by_tok(oc.v_scale)[good])
+    assert np.array_equal(by_tok(g["v_zero"])[good], by_tok(oc.v_zero)[good])
+    bpt = d * bits // 32
+    assert np.array_equal(oracle.unpack_v(g["v_codes"][0], T, d, bits)[good], oracle.unpack_v(oc.v_codes[0], T, d, bits)[good])
