@@ -175,7 +175,7 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], con
             a2 = min(min(a2, o2), max(a1, o1));
             a1 = min(a1, o1);
         }
-        best_i[j] = tb.P > 1 ? (int)(a1 & 0xffu) : 0;   // (not a number, a single pattern could lose to the rows behind the table)
+        best_i[j] = (int)(a1 & (tb.P > 1 ? 0xffu : 0u));   // (a single pattern could lose to the rows behind the table if e is not a number)
         best_v[j] = -2.f * __uint_as_float(a1 & 0xffffff00u);
         const float second = -2.f * __uint_as_float(a2 & 0xffffff00u);
         x2[j] = xx[j];
@@ -244,15 +244,15 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
     best_d = bd;
 }
 
-// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.  A token that no pattern is
-// nearest to (always flagged: its gap is not a number or infinite) gets the index `none`.
-template <int KS>
+// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.  The lanes of a token that no
+// pattern is nearest to (always flagged: its gap is not a number or infinite) call none() after their index became kNoNearest.
+template <int KS, class NONE>
 __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag, __half *xrow_s, const PatternTable &tb,
-                                                int lane, int &best_i, float &best_d, int none)
+                                                int lane, int &best_i, float &best_d, NONE none)
 {
     const int n = lane & 15, kb = lane >> 4;
     unsigned long long todo = __ballot(flag) & 0xffffull;   // one bit per column
-    while (todo) {
+    while (__builtin_expect(todo != 0, 0)) {   // (one token in several hundred: out of the way of the code around it)
         const int col = __ffsll((long long)todo) - 1;
         todo &= todo - 1;
         if (n == col) {
@@ -265,8 +265,9 @@ __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag
         float bd;
         exact_argmin_wave<32 * KS>(xrow_s, tb, lane, bi, bd);
         if (n == col) {
-            best_i = bi == kNoNearest ? none : bi;
+            best_i = bi;
             best_d = bd;
+            if (bi == kNoNearest) none();
         }
         __builtin_amdgcn_wave_barrier();
     }

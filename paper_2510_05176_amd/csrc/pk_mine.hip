@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 // With XC < D (256 channels and more than 128 patterns: the table alone takes 139 KB) the vectors pass through the LDS tile
 // XC channels at a time, the sums of those channels being formed between two barriers each; a wave's own rows of that tile
 // then serve as its re-evaluation row.
-// Dynamic LDS: [table pad16(P) rows] [-norm2/2 pad16(P)] [cnt pad16(P)] [xs 16 NT NW rows of XC]
+// Dynamic LDS: [table pad16(P) rows] [-norm2/2 pad16(P)] [cnt pad16(P) + 4] [xs 16 NT NW rows of XC]
 //              [idx 16 NT NW halves] [xrow NW*D halves, unless XC < D]
 template <int XC>
 constexpr int kMineXsOf = XC + 16;   // halves per row of the vector tile: 8 words modulo 16, so the eight rows that 32
@@ -90,7 +90,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     __half *tab_s = reinterpret_cast<__half *>(smem);
     float *norm_s = reinterpret_cast<float *>(smem + (size_t)pad16(P) * kTabStrideOf<D> * 2);
     int *cnt = reinterpret_cast<int *>(norm_s + pad16(P));
-    __half *xs = reinterpret_cast<__half *>(cnt + pad16(P));
+    const int kNone = pad16(P);   // index of a vector without a nearest pattern: counted behind the table's rows, summed nowhere
+    __half *xs = reinterpret_cast<__half *>(cnt + pad16(P) + 4);
     constexpr int ST = 16 * NT * NW;     // vectors per sub-tile: NT 16-vector tiles per wave
     __half *idx_s = xs + ST * kXs;       // pattern index of every row of the sub-tile, as an fp16 number
     __shared__ float red_s[NW];
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     uint4 xb[NT][KS], xn[NT][KS];
     load_tile(0, kAhead ? xn : xb);
 
-    for (int i = tid; i < pad16(P); i += 64 * NW) cnt[i] = 0;
+    for (int i = tid; i <= kNone; i += 64 * NW) cnt[i] = 0;
     stage_patterns<D>(Mg, P, tab_s, norm_s, red_s, 64 * NW);   // ends with a barrier
     PatternTable tb;
     tb.lds_rows = tab_s;
@@ -165,27 +166,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
         bool flag[NT];
         assign_tiles_mfma<NT, KS>(xb, tb, lane, bi, bv, x2, flag);
         int at[NT];   // row of the tile that takes the lane's vector
-        bool member[NT];   // the vector belongs to a cluster: inside the chunk, and some pattern is nearest to it
+        bool lost[NT];   // the lane's vector belongs to no cluster: its row is cleared again (0 * infinity is not 0)
         int step0 = 0, n_steps = ST / 32;   // this wave's 32-vector steps: rows step0 .. step0 + 32 n_steps - 1
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             float bd = fmaxf(bv[j], 0.f);
-            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd, kNoNearest);
+            if (NPT == 1 && P == 1) flag[j] = !(x2[j] < INFINITY);
             at[j] = (wave * NT + j) * 16 + n;
             const int tok = sub * ST + at[j];
-            if (!(x2[j] < INFINITY)) {   // (a single pattern is never evaluated again)
-                bi[j] = kNoNearest;
-                bd = INFINITY;
-            }
-            member[j] = tok < n_tok && bi[j] < P;
+            lost[j] = false;
+            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd, [&]() {
+                bi[j] = kNone;
+                lost[j] = true;
+            });
             if (kb == 0) {
                 if (tok < n_tok) {
                     // per-vector outputs only where somebody reads them: indices from the last step (if asked
                     // for), distances when the objective is reported
-                    if (outputs & 1) a.assign[(int64_t)s * a.T + t_begin + tok] = bi[j];
+                    if (outputs & 1) a.assign[(int64_t)s * a.T + t_begin + tok] = bi[j] < P ? bi[j] : kNoNearest;
                     if (outputs & 2) a.best[(int64_t)s * a.T + t_begin + tok] = bd;
+                    atomicAdd(&cnt[bi[j]], 1);
                 }
-                if (member[j]) atomicAdd(&cnt[bi[j]], 1);
             }
         }
         if constexpr (kSort) {
@@ -219,10 +220,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
         }
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
+            const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
             if constexpr (XC == D) {
 #pragma unroll
-                for (int k = 0; k < KS; ++k)   // the row of a vector that is no member is stored as zeros, so it adds nothing to any sum
-                    *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = member[j] ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
+                for (int k = 0; k < KS; ++k)   // a row past the chunk is stored as zeros, so it adds nothing to any sum
+                    *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][k] : make_uint4(0u, 0u, 0u, 0u);
             }
             if (kb == 0) idx_s[at[j]] = __float2half_rn((float)bi[j]);   // integers below 2048 are exact
         }
@@ -231,12 +233,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             if constexpr (XC < D) {
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
+                    const bool in = sub * ST + (wave * NT + j) * 16 + n < n_tok;
 #pragma unroll
                     for (int k = 0; k < XC / 32; ++k)
-                        *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = member[j] ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
+                        *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = in ? xb[j][part * (XC / 32) + k] : make_uint4(0u, 0u, 0u, 0u);
                 }
             }
             if (!kAhead && part == D / XC - 1 && sub + 1 < n_sub) load_tile(sub + 1, xb);   // in flight during the accumulation
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {   // (behind the loads, which the next sub-tile waits for)
+                if (__builtin_expect(lost[j], 0)) {
+#pragma unroll
+                    for (int k = 0; k < XC / 32; ++k) *reinterpret_cast<uint4 *>(xs + at[j] * kXs + 32 * k + 8 * kb) = make_uint4(0u, 0u, 0u, 0u);
+                }
+            }
             __syncthreads();
 #pragma unroll kStepUnroll
             for (int ks = 0; ks < n_steps; ++ks) {
@@ -392,7 +402,7 @@ constexpr StepShape step_shape(int D, int P)
 size_t step_lds_bytes(int D, int P, const StepShape &h)
 {
     size_t b = (size_t)pad16(P) * (D + 16) * 2;
-    b += (size_t)pad16(P) * 4 + (size_t)pad16(P) * 4 + 16 * h.nw * h.nt * (size_t)(h.xc + 16) * 2 + 16 * h.nw * h.nt * 2;
+    b += (size_t)pad16(P) * 4 + (size_t)(pad16(P) + 4) * 4 + 16 * h.nw * h.nt * (size_t)(h.xc + 16) * 2 + 16 * h.nw * h.nt * 2;
     if (h.xc == D) b += (size_t)h.nw * D * 2;
     return (b + 15) / 16 * 16;
 }
