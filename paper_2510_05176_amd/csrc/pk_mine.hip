@@ -308,9 +308,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
 
 // update step: centroid = mean of members (binary32 division), rounded to fp16;
 // an empty cluster keeps its centroid
-__global__ __launch_bounds__(256) void mine_update_kernel(MineArgs a)   // a.d threads, thread <-> channel
+template <int D>
+__global__ __launch_bounds__(D) void mine_update_kernel(MineArgs a)   // thread <-> channel
 {
-    const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x, d = a.d;
+    const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x;
     const int64_t o0 = (int64_t)s * a.tsplit * a.P + p, step = a.P;
     // chunks in increasing order, eight loads in flight at a time; the order of the additions is fixed
     float sum = 0.f;
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(256) void mine_update_kernel(MineArgs a)   // a.d t
         int k[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            v[u] = a.psum[(o0 + (ts + u) * step) * d + c];
+            v[u] = a.psum[(o0 + (ts + u) * step) * D + c];
             k[u] = a.pcnt[o0 + (ts + u) * step];
         }
 #pragma unroll
@@ -331,10 +332,10 @@ __global__ __launch_bounds__(256) void mine_update_kernel(MineArgs a)   // a.d t
         }
     }
     for (; ts < a.tsplit; ++ts) {
-        sum += a.psum[(o0 + ts * step) * d + c];
+        sum += a.psum[(o0 + ts * step) * D + c];
         cnt += a.pcnt[o0 + ts * step];
     }
-    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * d + c] = __float2half_rn(sum / (float)cnt);
+    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * D + c] = __float2half_rn(sum / (float)cnt);
 }
 
 // inertia of one assignment step: fixed-order sum of the best distances
@@ -438,54 +439,52 @@ int mine_tsplit(int T, int n_sets, int P)
     return chunks_of(T, n_sets, P, kD);
 }
 
-// One launch of the step kernel for 16 * NPT patterns or fewer at head dimension D
+// All iterations for 16 * NPT patterns or fewer at head dimension D
 template <int D, int NPT>
-static hipError_t launch_step(const MineArgs &a, hipStream_t s, int outputs)
+static hipError_t launch_iterations(const MineArgs &a_in, hipStream_t s)
 {
     constexpr StepShape h = step_shape(D, 16 * NPT);
+    constexpr auto step = mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>;
     static LdsOptIn opt_in;   // the most this instantiation needs: a table of 16 * NPT patterns
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>), opt_in,
-                                           step_lds_bytes(D, 16 * NPT, h));
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(step), opt_in, step_lds_bytes(D, 16 * NPT, h));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>), dim3(a.tsplit, a.n_sets), dim3(64 * h.nw), step_lds_bytes(D, a.P, h), s,
-                       a, mine_chunk(a.T, a.n_sets, a.P, D), outputs);
-    return hipGetLastError();
-}
-
-template <int D>
-static hipError_t launch_step_of(const MineArgs &a, hipStream_t s, int outputs)
-{
-    switch (step_shape(D, a.P).npt) {
-    case 1: return launch_step<D, 1>(a, s, outputs);
-    case 2: return launch_step<D, 2>(a, s, outputs);
-    case 4: return launch_step<D, 4>(a, s, outputs);
-    case 8: return launch_step<D, 8>(a, s, outputs);
-    default: return launch_step<D, 16>(a, s, outputs);
-    }
-}
-
-hipError_t launch_mine(const MineArgs &a_in, hipStream_t s)
-{
     MineArgs a = a_in;
-    a.tsplit = chunks_of(a.T, a.n_sets, a.P, a.d);
-    if (a.d != kD && a.d != 96 && a.d != 256) return hipErrorInvalidValue;
-    hipError_t e;
+    a.tsplit = chunks_of(a.T, a.n_sets, a.P, D);
+    const int chunk = mine_chunk(a.T, a.n_sets, a.P, D);
+    const size_t lds = step_lds_bytes(D, a.P, h);
     if (!a.init_given) {
-        hipLaunchKernelGGL(mine_init_kernel, dim3((a.P * a.d / 8 + 255) / 256, a.n_sets), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(mine_init_kernel, dim3((a.P * D / 8 + 255) / 256, a.n_sets), dim3(256), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (int it = 0; it < a.iters; ++it) {
         const int outputs = (a.assign && it == a.iters - 1 ? 1 : 0) | (a.inertia ? 2 : 0);
-        e = a.d == kD ? launch_step_of<kD>(a, s, outputs) : a.d == 96 ? launch_step_of<96>(a, s, outputs) : launch_step_of<256>(a, s, outputs);
-        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(step, dim3(a.tsplit, a.n_sets), dim3(64 * h.nw), lds, s, a, chunk, outputs);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
         if (a.inertia) {
             hipLaunchKernelGGL(mine_inertia_kernel, dim3(a.n_sets), dim3(256), 0, s, a, it);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(mine_update_kernel, dim3(a.P, a.n_sets), dim3(a.d), 0, s, a);
+        hipLaunchKernelGGL(mine_update_kernel<D>, dim3(a.P, a.n_sets), dim3(D), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+template <int D>
+static hipError_t launch_mine_of(const MineArgs &a, hipStream_t s)
+{
+    switch (step_shape(D, a.P).npt) {
+    case 1: return launch_iterations<D, 1>(a, s);
+    case 2: return launch_iterations<D, 2>(a, s);
+    case 4: return launch_iterations<D, 4>(a, s);
+    case 8: return launch_iterations<D, 8>(a, s);
+    default: return launch_iterations<D, 16>(a, s);
+    }
+}
+
+hipError_t launch_mine(const MineArgs &a, hipStream_t s)
+{
+    return a.d == kD ? launch_mine_of<kD>(a, s) : a.d == 96 ? launch_mine_of<96>(a, s) : a.d == 256 ? launch_mine_of<256>(a, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, __half *out, int64_t out_stride,
