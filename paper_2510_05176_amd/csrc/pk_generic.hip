@@ -167,19 +167,38 @@ __device__ __forceinline__ void fields_to_normal(uint32_t X, uint32_t *out)
     for (int v = 0; v < 8; ++v) out[v] = pk_mul(out[v], 0x74007400u);   // 2^14
 }
 
+// The V codes of plane pair F (bits 2F and 2F + 1) as normal numbers (field - 3/2) * 4^F * 2^-11, so that the pairs of a word add up to
+// the code less half of the largest one.  One factor for all positions of a word: the other operand then has the whole of
+// fp16's range for the weights.
+__host__ __device__ constexpr uint32_t half_pair(int e) { return (uint32_t)(e + 15) * 0x04000400u; }   // 2^e twice, -14 <= e <= 15
+template <int F>
+__device__ __forceinline__ void fields_to_centred(uint32_t X, uint32_t *out)
+{
+    fields_to_operand(X, out);
+    const half2v c = {(_Float16)(-1.5f * (F ? 4.f : 1.f) / 2048.f), (_Float16)(-1.5f * (F ? 4.f : 1.f) / 2048.f)};
+#pragma unroll
+    for (int v = 0; v < 8; ++v)   // (a field is code * 2^(fpos - 24); the results are exact)
+        out[v] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(half2v, out[v]),
+                                                                        __builtin_bit_cast(half2v, half_pair(13 + 2 * F - fpos(v))), c));
+}
+
 // Packed part on the matrix cores.  A wave walks 64-token blocks of its own run with its own online softmax; operands and
 // lane roles are those of the tuned kernel (pk_decode_packed.hip), with one difference: the sixteen columns (rows on the V
 // side) of a tile are eight heads twice, column n with the fp16 rounding of the other operand and column n + 8 with 2^11 times
-// what that rounding dropped, again rounded to fp16.  The sum of the two columns has 22 significant bits of q * s_K (that product of two fp16
-// numbers has 22) and of p * s_V, and the codes are exact, so the result is as accurate as the binary32 vector arithmetic
-// that this replaces (rounding of every product to 24 bits and of a serial sum).  The operands are brought
+// what that rounding dropped, again rounded to fp16.  The sum of the two columns is q * s_K exactly (that product of two fp16
+// numbers has 22 significant bits) and p * s_V to 23 bits, the codes are exact, and the matrix instruction adds eight products at
+// a time to its binary32 accumulator, so that the sums are rounded an eighth as often as the serial sums of the binary32 vector
+// arithmetic that this replaces.  The operands are brought
 // into fp16's range by powers of two: q * s_K per head and K group, by the largest |q * s_K|; p * s_V per wave, by the largest
-// scale met so far (the accumulators follow by an exact multiplication when a block exceeds it).
+// scale met so far (the accumulators follow by an exact multiplication when a block exceeds it), to 2^15, so that a weight has
+// its 23 bits down to 2^-27 of the largest and eleven of them down to 2^-39 (a pattern's mass has the unit 2^-31).
 // Bound by vector instruction issue (operand building, 1.5 k instructions per block and wave at 256 channels against 64
 // matrix instructions).  Replaces a kernel on the vector ALUs (a thread per token, every code taken apart for every head); whole
 // decodes, 256 streams x 4096 tokens, 4 heads: d 256, 64-token groups 342 -> 102 us, d 96, 32-token groups 180 -> 74; one
 // head 233 -> 92; 7 heads over 32-channel groups at 128 channels (128 streams) 167 -> 64.  Error
-// against 64 bits 2e-7 (5e-7 before), with queries 20 times as large 2e-6 (1.1e-5 before).
+// against 64 bits, largest over d 256 / 96 / 128, 2 and 4 bits, 16384 tokens in splits of 8192 (the vector arithmetic's in
+// brackets): values about 1 1.1e-7 (1.3e-7), about zero 3.5e-6 (2.4e-5), a first token 9 above the others' scores whose value is small
+// 2.6e-7 (1.2e-6), 18 above 7.4e-6 (5.1e-5), keys 20 times as large 3.4e-6 (5.8e-6).
 template <int D, int G, int BITS>
 __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))) void gen_decode_kernel(DecodeArgs a)
 {
@@ -319,8 +338,11 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
     for (int g = 0; g < NG; ++g) pz[g] = 0.f;
     bool started = false;
-    float s_lim = 0.f;   // power of two, at least the largest V scale so far; the accumulators hold kUp / s_lim / 4 times the sums
-    constexpr float kUp = BITS == 4 ? 16.f : 64.f;
+    // Values: sum p (s code + z) = sum (p s) (code - mid) + sum p (z + s mid), mid half of the largest code.  (With the code
+    // and z as they are, two sums of one sign each all but cancel where V is spread about zero.)
+    constexpr float kMid = 0.5f * (float)((1 << BITS) - 1);
+    float s_lim = 0.f;   // power of two above the largest V scale so far; the accumulators hold kUp / s_lim / 2048 times the sums
+    constexpr float kUp = 32768.f;
     floatx4 O[D / 16];
 #pragma unroll
     for (int t = 0; t < D / 16; ++t) O[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -426,19 +448,21 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
             for (int k = 0; k < 16; ++k) S[k] -= delta;
             started = true;
         }
-        float pr[16];
+        // columns n and n + 8 hold the same weights; of the sums that are not contractions each takes half of the tokens
+        float pr[16], own[8];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            pr[k] = __builtin_amdgcn_exp2f(S[k]);
-            l_run += pr[k];
+        for (int k = 0; k < 16; ++k) pr[k] = __builtin_amdgcn_exp2f(S[k]);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            own[k] = upper ? pr[k + 8] : pr[k];
+            l_run += own[k];
         }
-        // ---- softmax mass per V pattern: columns n and n + 8 take half of the tokens each
+        // ---- softmax mass per V pattern
         if (h < nh) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const float w = upper ? pr[k + 8] : pr[k];
                 const int id = (int)(((upper ? vid[2 + (k >> 2)] : vid[k >> 2]) >> (8 * (k & 3))) & 255u);
-                atomicAdd(&Ws[(wave * nh + h) * WS + min(id, WS - 1)], (unsigned long long)(w * kWUnit));
+                atomicAdd(&Ws[(wave * nh + h) * WS + min(id, WS - 1)], (unsigned long long)(own[k] * kWUnit));
             }
         }
         // ---- values
@@ -457,13 +481,13 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         const float up = s_lim > 0.f ? kUp / s_lim : 0.f;
         float pu[16];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) pu[k] = pr[k] * (up * (float)(1 << (8 - fpos(k >> 1))));
+        for (int k = 0; k < 16; ++k) pu[k] = pr[k] * up;
         const int64_t unit = (pos0 >> 4) + kb;
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             const uint4 *sp = reinterpret_cast<const uint4 *>(cv.v_scale + (unit * NG + g) * 16), *zp = reinterpret_cast<const uint4 *>(cv.v_zero + (unit * NG + g) * 16);
-            const uint4 s0 = sp[0], s1 = sp[1], z0 = zp[0], z1 = zp[1];
-            const uint32_t sw[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w}, zw[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+            const uint4 s0 = sp[0], s1 = sp[1], z = zp[upper ? 1 : 0];
+            const uint32_t sw[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w}, zw[4] = {z.x, z.y, z.z, z.w};
             uint32_t vw[TPG * WPU];
             const uint2 *vsrc = reinterpret_cast<const uint2 *>(vwords + ((unit * 16 + n) * (D / 16) + g * TPG) * WPU);
 #pragma unroll
@@ -472,15 +496,17 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
                 vw[2 * i] = v.x;
                 vw[2 * i + 1] = v.y;
             }
-            uint32_t Ap[8], Ap4[8];
+            uint32_t Ap[8];
 #pragma unroll
             for (int V = 0; V < 8; ++V) {
-                const half2v sh = __builtin_bit_cast(half2v, sw[V]), zh = __builtin_bit_cast(half2v, zw[V]);
-                pz[g] = fmaf(pr[2 * V], (float)zh[0], pz[g]);
-                pz[g] = fmaf(pr[2 * V + 1], (float)zh[1], pz[g]);
-                const float x = pu[2 * V] * (float)sh[0], y = pu[2 * V + 1] * (float)sh[1];
-                Ap[V] = split_pair(x, y, part);
-                if (BITS == 4) Ap4[V] = pk_mul(Ap[V], pack2((_Float16)4.f, (_Float16)4.f));
+                const half2v sh = __builtin_bit_cast(half2v, sw[V]);
+                Ap[V] = split_pair(pu[2 * V] * (float)sh[0], pu[2 * V + 1] * (float)sh[1], part);
+            }
+#pragma unroll
+            for (int V = 0; V < 4; ++V) {
+                const half2v sh = __builtin_bit_cast(half2v, upper ? sw[V + 4] : sw[V]), zh = __builtin_bit_cast(half2v, zw[V]);
+                pz[g] = fmaf(own[2 * V], fmaf((float)sh[0], kMid, (float)zh[0]), pz[g]);
+                pz[g] = fmaf(own[2 * V + 1], fmaf((float)sh[1], kMid, (float)zh[1]), pz[g]);
             }
 #pragma unroll
             for (int i = 0; i < TPG; ++i) {
@@ -492,9 +518,12 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
                     uint32_t Bv[8];
                     const uint32_t W = vw[i * WPU + f];
                     const uint32_t u = bfi(0x0000AAAAu, W >> 15, W);
-                    fields_to_normal(bfi(0x55550000u, W << 15, u), Bv);
-                    O[t] = mfma16(f ? &Ap4[0] : &Ap[0], &Bv[0], O[t]);
-                    O[t] = mfma16(f ? &Ap4[4] : &Ap[4], &Bv[4], O[t]);
+                    if (f == 0)
+                        fields_to_centred<0>(bfi(0x55550000u, W << 15, u), Bv);
+                    else
+                        fields_to_centred<1>(bfi(0x55550000u, W << 15, u), Bv);
+                    O[t] = mfma16(&Ap[0], &Bv[0], O[t]);
+                    O[t] = mfma16(&Ap[4], &Bv[4], O[t]);
                 }
             }
         }
@@ -502,10 +531,12 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     if (!started) m_run = -INFINITY;   // a wave without blocks contributes nothing to the merge
 
     // ---- merge the four waves of the workgroup
+    l_run += other_half(l_run);
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
+        pz[g] += other_half(pz[g]);
         pz[g] += __shfl_xor(pz[g], 16);
         pz[g] += __shfl_xor(pz[g], 32);
         if (lane < 8) stat_pz[wave][n][g] = pz[g];
@@ -528,7 +559,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     __syncthreads();
     // every wave leaves its outputs, scaled to the workgroup's reference, in slabs of its own over the start of the dynamic LDS
     float *Os = reinterpret_cast<float *>(gen_decode_smem);
-    const float down = s_lim * (4.f / kUp);
+    const float down = s_lim * (2048.f / kUp);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int hh = 4 * kb + i;   // (rows 8-15: the dropped parts)

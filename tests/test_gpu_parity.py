@@ -1002,6 +1002,59 @@ def test_decode_binary32_accuracy(pk, d, G, bits, hkv, hq, n_seq, R):
     assert float((got - want).norm() / want.norm()) <= 1e-5, (float(err.max()), float(err.median()))
 
 
+@pytest.mark.parametrize("d,G,bits,hkv,hq", [(256, 64, 2, 2, 8), (256, 32, 4, 2, 4), (256, 128, 4, 1, 8), (96, 32, 2, 2, 6), (96, 128, 4, 2, 2),
+                                             (128, 32, 2, 1, 7)])
+@pytest.mark.parametrize("what", ["small_weights", "cancelling"])
+def test_decode_binary32_accuracy_of_weights(pk, d, G, bits, hkv, hq, what):
+    """The weights of the decode in binary32 accuracy where an fp16 operand of them would not have it, against attention in 64
+    bits over the stored codes and parameters.
+    small_weights: the first token's score is 22 above the others', its value is a pattern's (nothing but zeros), so that the
+    result is the sum of 4096 weights of about 2^-31.  A score of 31 in the log2 domain has an ulp of 2^-19, which is 1.3e-6 of
+    the weight: 5e-6 leaves four of them.
+    cancelling: values spread about zero, whose weighted sum is 1 / 64 of them.  Weights off by 2^-22 each (independent of each
+    other) give 2.4e-7 of the result, the roundings of the running sums, about a hundred of 2^-25 of it at random, 3e-7: 1e-6.
+    (Sums of the codes and of the zero points by themselves, which all but cancel, gave 2.2e-6 to 2.7e-6.)"""
+    T, P, F, U, n_seq = 4096, 4, max(64, G), 2, 128 // hkv
+    r = hq // hkv
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + G + hq)
+    K = torch.randn((U, hkv, T, d), generator=gen, device="cuda") * 0.5
+    V = torch.randn((U, hkv, T, d), generator=gen, device="cuda") * 0.3
+    q = torch.randn((U, hkv, 1, d), generator=gen, device="cuda") + 0.05 * torch.randn((U, hkv, r, d), generator=gen, device="cuda")
+    if what == "small_weights":
+        K[:, :, 0] = q[:, :, 0] * (22.0 * d ** 0.5 / q[:, :, 0].square().sum(-1, keepdim=True))
+        V += 1.0
+        V[:, :, 0] = 0.0
+    K, V, q = K.half(), V.half(), q.half()
+    Mk, Mv = K[0, :, 1:1 + P].contiguous(), torch.zeros((hkv, P, d), dtype=torch.float16, device="cuda")
+    cfg = pk.Config(n_seq=n_seq, n_kv_heads=hkv, n_q_heads=hq, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G,
+                    recent=0, flush=F, t_capacity=T, metric=0)
+    cache = pk.Cache(cfg)
+    many = lambda x: x.repeat(n_seq // U, 1, 1, 1)
+    pk.pk_quantize_append(cfg, cache, many(K), many(V), Mk, Mv)
+    got = pk.pk_decode_attention(cfg, cache, many(q).reshape(n_seq, hq, d).contiguous(), d ** -0.5, Mk, Mv)
+    assert cache.t_quant == T and torch.equal(got[:U], got[-U:])
+    # K^, V^ of the first sequences in 64 bits
+    N, Gc = U * hkv, min(G, d)
+    bits32, steps = torch.arange(32, device="cuda"), torch.arange(16, device="cuda")
+    part = lambda name, dtype, shape: cache.array(name).view(dtype).view(n_seq * hkv, *shape)[:N]
+    kw = part("k_codes", torch.int32, (T, d // 32, bits))
+    code = sum(((kw[..., j, None] >> bits32) & 1) << j for j in range(bits)).reshape(N, T, d).double()
+    by_group = lambda name: part(name, torch.float16, (T // G, d)).double().repeat_interleave(G, 1)
+    set_of = torch.arange(N, device="cuda") % hkv
+    ki = part("k_idx", torch.uint8, (T,)).long()
+    Kd = Mk.double()[set_of[:, None], ki] + (code * by_group("k_scale") + by_group("k_zero"))
+    vw = part("v_codes", torch.int32, (T // 16, 16, d // 16, bits // 2))
+    code = sum(((vw[:, :, None, :, :, j // 2] >> (16 * (j % 2) + steps)[None, None, :, None, None]) & 1) << j for j in range(bits))
+    code = code.permute(0, 1, 2, 4, 3).reshape(N, T, d).double()
+    by_token = lambda name: part(name, torch.float16, (T // 16, d // Gc, 16)).double().permute(0, 1, 3, 2).reshape(N, T, -1).repeat_interleave(Gc, 2)
+    Vd = code * by_token("v_scale") + by_token("v_zero")
+    qd = q.double().reshape(N, r, d)
+    want = torch.stack([torch.softmax(qd[i] @ Kd[i].T.contiguous() * d ** -0.5, -1) @ Vd[i] for i in range(N)])
+    err = float((got[:U].double().reshape(N, r, d) - want).norm() / want.norm())
+    assert err <= (5e-6 if what == "small_weights" else 1e-6), err
+
+
 @pytest.mark.parametrize("d,P,T", [(96, 16, 333), (96, 17, 700), (96, 64, 257), (96, 128, 600), (96, 129, 700), (256, 9, 300),
                                    (256, 32, 513), (256, 64, 700), (256, 65, 400), (256, 128, 513), (256, 200, 700), (256, 256, 640)])
 def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
