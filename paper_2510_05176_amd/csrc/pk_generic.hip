@@ -373,7 +373,10 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
         // the block's 64 * NG V scales, NG of them per lane
         float s_big = 0.f;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) s_big = fmaxf(s_big, h2f(cv.v_scale[(pos0 >> 4) * NG * 16 + g * 64 + lane]));
+        for (int g = 0; g < NG; ++g) {
+            const float s = h2f(cv.v_scale[(pos0 >> 4) * NG * 16 + g * 64 + lane]);
+            s_big = fmaxf(s_big, s < INFINITY ? s : 0.f);   // (an infinite one spoils its own channel group only)
+        }
 
         if (TWO || b == b0 || tb % G == 0) build(pos0 / G, ga);
         if (TWO) build(pos0 / G + 1, gb);

@@ -1055,6 +1055,31 @@ def test_decode_binary32_accuracy_of_weights(pk, d, G, bits, hkv, hq, what):
     assert err <= (5e-6 if what == "small_weights" else 1e-6), err
 
 
+@pytest.mark.parametrize("d,G,bits", [(256, 64, 2), (96, 32, 4)])
+def test_decode_infinite_value_spoils_its_channel_group_only(pk, d, G, bits):
+    """One infinite channel in one V vector: its group of channels has an infinite scale.  The other groups' outputs equal
+    attention in 64 bits, also with scales of some hundred, whose weights need the common power of two."""
+    T, P, hkv, hq = 512, 8, 2, 4
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    K = torch.randn((1, hkv, T, d), generator=gen, device="cuda").half()
+    V = (torch.randn((1, hkv, T, d), generator=gen, device="cuda") * 300.0).half()
+    Mk, Mv = K[0, :, :P].contiguous(), V[0, :, :P].contiguous()
+    V[:, :, 100, 5] = float("inf")
+    q = torch.randn((1, hq, d), generator=gen, device="cuda").half()
+    cfg = pk.Config(n_seq=1, n_kv_heads=hkv, n_q_heads=hq, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G, recent=0,
+                    flush=64, t_capacity=T, metric=0)
+    cache = pk.Cache(cfg)
+    pk.pk_quantize_append(cfg, cache, K, V, Mk, Mv)
+    got = pk.pk_decode_attention(cfg, cache, q, d ** -0.5, Mk, Mv).double().view(hkv, hq // hkv, d)
+    kd, vd = pk.pk_dequantize(cfg, cache, Mk, Mv)
+    kd, vd = kd.double().view(hkv, T, d), vd.double().view(hkv, T, d)[:, :, G:]
+    qd = q.double().view(hkv, hq // hkv, d)
+    want = torch.stack([torch.softmax(qd[h] @ kd[h].T.contiguous() * d ** -0.5, -1) @ vd[h] for h in range(hkv)])
+    assert not torch.isfinite(got[:, :, 5]).any()
+    assert float((got[:, :, G:] - want).norm() / want.norm()) <= 1e-5
+
+
 @pytest.mark.parametrize("d,P,T", [(96, 16, 333), (96, 17, 700), (96, 64, 257), (96, 128, 600), (96, 129, 700), (256, 9, 300),
                                    (256, 32, 513), (256, 64, 700), (256, 65, 400), (256, 128, 513), (256, 200, 700), (256, 256, 640)])
 def test_mining_parity_other_head_dimensions(oracle, pk, d, P, T):
