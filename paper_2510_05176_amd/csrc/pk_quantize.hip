@@ -48,17 +48,16 @@ namespace {
 // ---------------------------------------------------------------------------
 typedef _Float16 mm_half2 __attribute__((ext_vector_type(2)));
 
-// Sixteen consecutive dwords through the scalar data path (read only; address wave-uniform, 4-byte aligned), and the
-// wait for every scalar load issued so far; the values are tied to the wait so that no use can move ahead of it.
+// Sixteen consecutive dwords through the scalar data path (read only: the constant address space; address wave-uniform, 4-byte
+// aligned).  arrived(): a use of the values, so that the compiler waits for them here and not behind the next request.
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+typedef u32x16 u32x16_dword_aligned __attribute__((aligned(4)));
 __device__ __forceinline__ u32x16 sload16(const uint32_t *p)
 {
-    u32x16 r;
-    asm volatile("s_load_dwordx16 %0, %1, 0x0" : "=s"(r) : "s"(p) : "memory");
-    return r;
+    return *(const __attribute__((address_space(4))) u32x16_dword_aligned *)(uintptr_t)p;
 }
-__device__ __forceinline__ void swait(u32x16 (&r)[1]) { asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0])); }
-__device__ __forceinline__ void swait(u32x16 (&r)[2]) { asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0]), "+s"(r[1])); }
+__device__ __forceinline__ void arrived(u32x16 (&r)[1]) { asm volatile("" : "+s"(r[0])); }
+__device__ __forceinline__ void arrived(u32x16 (&r)[2]) { asm volatile("" : "+s"(r[0]), "+s"(r[1])); }
 
 // Which run of tiles of its stream (blockIdx.y) a workgroup takes.  Workgroups go to the chip's eight XCDs in turn
 // by their linear index, y * gridDim.x + x; with the run taken as x itself an XCD would get the runs x = k, k + 8, ...
@@ -183,7 +182,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             const uint32_t *mrow = Mg + (size_t)p * (D / 2), *mnext = Mg + (size_t)min(p + 1, P - 1) * (D / 2);   // (past the last row: that row again; unused)
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
-                swait(buf[(s + at) & 1]);
+                arrived(buf[(s + at) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
                 request(s + 1 < NS ? mrow + 16 * W * (s + 1) : mnext, buf[(s + at + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);   // (the scheduler would issue the request behind most of the scan)
 #pragma unroll
@@ -205,8 +205,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             pattern(p + 1, NS % 2);
         }
         if (p < P) pattern(p, 0);
-        swait(buf[0]);   // nothing may be in flight into registers that the next tile reuses
-        swait(buf[1]);
         int best = (int)(k1 & 0xffu);
         const float first = __uint_as_float(k1 & 0xffffff00u);
         // first's own low bits (2^-15 of it) belong to its upper bound
