@@ -36,7 +36,11 @@ namespace {
 // difference; with twice that, c = 2^-10, difference - c (|max| + |min|) is a lower bound and the same + 2 c (|max| +
 // |min|) an upper one.  The three smallest lower bounds are tracked; where the second does not exceed the upper bound of the
 // first, the lane evaluates these two patterns in binary32; where the third does not exceed it either, the wave evaluates
-// the vector against all patterns, lane <-> pattern.
+// the vector against all patterns, lane <-> pattern.  Where that is so for many vectors of a tile - repeated patterns, vectors
+// so far from the table that all distances lie within the bounds of each other - the tile and the wave's further ones are
+// searched in binary32 throughout (minmax_nearest; already after a quarter of the table if it is so by then): 128 streams x 4096
+// vectors, every one of 64 patterns four times 2714 -> 637 us for the append (binary32 ranking 640), of 200 8847 -> 1656
+// (1658), vectors of spread 0.05 at a distance of 3 1317 -> 705 (591) and 4910 -> 1723 (1646).
 // 1.1 vector operations per channel and pattern instead of the 2.1 of ranking in binary32 (a mixed-precision subtraction and
 // half of a three-operand maximum and minimum), bound by their issue: 256 streams x 8192 vectors, 64 patterns 998 -> 565 us
 // per search (485 at the issue rate of the packed operations), at 128 patterns a whole append 4.16 -> 2.53 ms, 128 streams
@@ -58,6 +62,20 @@ __device__ __forceinline__ u32x16 sload16(const uint32_t *p)
 }
 __device__ __forceinline__ void arrived(u32x16 (&r)[1]) { asm volatile("" : "+s"(r[0])); }
 __device__ __forceinline__ void arrived(u32x16 (&r)[2]) { asm volatile("" : "+s"(r[0]), "+s"(r[1])); }
+
+// x - half(m.lo), x - half(m.hi) of two fp16 numbers, m a scalar operand
+__device__ __forceinline__ float sub_s_lo(uint32_t x, uint32_t m)
+{
+    float r;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(x), "s"(m));
+    return r;
+}
+__device__ __forceinline__ float sub_s_hi(uint32_t x, uint32_t m)
+{
+    float r;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(x), "s"(m));
+    return r;
+}
 
 // Which run of tiles of its stream (blockIdx.y) a workgroup takes.  Workgroups go to the chip's eight XCDs in turn
 // by their linear index, y * gridDim.x + x; with the run taken as x itself an XCD would get the runs x = k, k + 8, ...
@@ -120,135 +138,212 @@ __device__ __forceinline__ float minmax_distance(const __half *x, const __half *
     return dist;
 }
 
+// A wave evaluates one vector against all patterns in the time in which a scan takes 5 of its 64 vectors: beyond this many open
+// vectors of a tile the scan is the faster one.
+constexpr int kOpen = 12;
+
+// The table's rows through the scalar path.  Scalar loads return in any order, so a wait covers all that are outstanding: the next
+// step's channels are requested right after the wait for the current ones and arrive under their 64 (96 channels: 32) vector
+// operations.
+template <int D>
+struct RowSteps {
+    static constexpr int W = D % 64 == 0 ? 2 : 1, NS = D / (32 * W);   // scalar loads (32 channels each) per step, steps
+    const uint32_t *M;
+    int P;
+    u32x16 buf[2][W];
+    __device__ __forceinline__ void request(const uint32_t *at, u32x16 (&to)[W])
+    {
+#pragma unroll
+        for (int w = 0; w < W; ++w) to[w] = sload16(at + 16 * w);
+    }
+    // step(32 channels, which) over pattern p's row; at: which buffer holds (will hold) its first step
+    template <class STEP>
+    __device__ __forceinline__ void row(int p, int at, STEP step)
+    {
+        const uint32_t *mrow = M + (size_t)p * (D / 2), *mnext = M + (size_t)min(p + 1, P - 1) * (D / 2);   // (past the last row: that row again; unused)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            arrived(buf[(s + at) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            request(s + 1 < NS ? mrow + 16 * W * (s + 1) : mnext, buf[(s + at + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);   // (the scheduler would issue the request behind most of the scan)
+#pragma unroll
+            for (int w = 0; w < W; ++w) step(buf[(s + at) & 1][w], s * W + w);
+        }
+    }
+    // pattern(p, at) over the table; given up in front of pattern `probe` (even; 0: never) if give_up() says so
+    template <class PATTERN, class GIVE_UP>
+    __device__ __forceinline__ void all(PATTERN pattern, int probe, GIVE_UP give_up)
+    {
+        request(M, buf[0]);
+        int p = 0;
+        for (int end = probe;; end = P) {
+            for (; p + 1 < end; p += 2) {
+                pattern(p, 0);
+                pattern(p + 1, NS % 2);
+            }
+            if (end == P) break;
+            if (probe > 0 && give_up()) return;
+        }
+        if (p < P) pattern(p, 0);
+    }
+};
+
+// The lane's vector, two channels per register
+template <int D>
+__device__ __forceinline__ void load_vector(const __half *row, uint32_t (&x)[D / 2])
+{
+#pragma unroll
+    for (int ch = 0; ch < D / 8; ++ch) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(row + 8 * ch);
+        x[4 * ch] = v.x;
+        x[4 * ch + 1] = v.y;
+        x[4 * ch + 2] = v.z;
+        x[4 * ch + 3] = v.w;
+    }
+}
+
+// Nearest pattern of the lane's vector, all of them in binary32: the definition, 2.1 vector operations per channel and pattern.
+template <int D>
+__device__ __forceinline__ int minmax_nearest(const __half *xrow, const uint32_t *M, int P)
+{
+    uint32_t x[D / 2];
+    load_vector<D>(xrow, x);
+    RowSteps<D> rows;
+    rows.M = M;
+    rows.P = P;
+    float bd = INFINITY;
+    int bi = 0;
+    rows.all([&](int p, int at) {
+        float pa = -INFINITY, pb = -INFINITY, na = INFINITY, nb = INFINITY;   // two chains, as below
+        rows.row(p, at, [&](const u32x16 &m, int s) {
+#pragma unroll
+            for (int k = 0; k < 16; k += 2) {
+                const uint32_t m0 = m[k], m1 = m[k + 1];
+                const float d0 = sub_s_lo(x[16 * s + k], m0), d1 = sub_s_hi(x[16 * s + k], m0);
+                const float d2 = sub_s_lo(x[16 * s + k + 1], m1), d3 = sub_s_hi(x[16 * s + k + 1], m1);
+                pa = fmaxf(fmaxf(pa, d0), d1);
+                na = fminf(fminf(na, d0), d1);
+                pb = fmaxf(fmaxf(pb, d2), d3);
+                nb = fminf(fminf(nb, d2), d3);
+            }
+        });
+        const float dist = fmaxf(pa, pb) - fminf(na, nb);
+        bi = dist < bd ? p : bi;   // patterns in increasing order
+        bd = fminf(dist, bd);
+    }, 0, []() { return false; });
+    return bi;
+}
+
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void assign_minmax_kernel(QuantArgs a, int tiles_per_wg)
 {
-    // 16-byte pieces of a vector; scalar loads (32 channels each) per step, steps
-    constexpr int NC = D / 8, W = D % 64 == 0 ? 2 : 1, NS = D / (32 * W);
+    constexpr int NC = D / 8;   // 16-byte pieces of a vector
     const int tid = threadIdx.x, lane = tid & 63, ns = blockIdx.y, P = a.P;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const __half *Mh = a.patterns + (int64_t)a.sets.set_of(ns) * P * D;
+    const __half *Mh = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     const uint32_t *Mg = reinterpret_cast<const uint32_t *>(Mh);
     take_sequence_entry(a, ns);
     const int n_tiles = a.nq / 64;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
+    bool undecided = false;   // the bounds left many vectors of a tile open: this tile and the wave's further ones without them
     for (int tile = tile0 + wave; tile < tile1; tile += 4) {
-        uint32_t x[D / 2];   // the lane's vector, two channels per register
-        {
-            const __half *row = a.src.row_d(ns, tile * 64 + lane, D);
+        int best;
+        if (!undecided) {
+            uint32_t x[D / 2];
+            load_vector<D>(a.src.row_d(ns, tile * 64 + lane, D), x);
+            constexpr float c = 9.765625e-4f;
+            uint32_t k1 = 0xffffffffu, k2 = 0xffffffffu, k3 = 0xffffffffu;   // the three smallest bounds, the pattern in the low byte
+            float t1 = 0.f;                                 // |max| + |min| of the first
+            mm_half2 mxa, mxb, mna, mnb;                    // two chains, so that consecutive operations do not wait for each other
+            auto scan = [&](const u32x16 &m, int s) {
 #pragma unroll
-            for (int ch = 0; ch < NC; ++ch) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(row + 8 * ch);
-                x[4 * ch] = v.x;
-                x[4 * ch + 1] = v.y;
-                x[4 * ch + 2] = v.z;
-                x[4 * ch + 3] = v.w;
-            }
-        }
-        // Scalar loads return in any order, so a wait covers all that are outstanding: the next step's channels are
-        // requested right after the wait for the current ones and arrive under their 64 (96 channels: 32) vector operations.
-        constexpr float c = 9.765625e-4f;
-        uint32_t k1 = 0xffffffffu, k2 = 0xffffffffu, k3 = 0xffffffffu;   // the three smallest bounds, the pattern in the low byte
-        float t1 = 0.f;                                 // |max| + |min| of the first
-        mm_half2 mxa, mxb, mna, mnb;                    // two chains, so that consecutive operations do not wait for each other
-        auto scan = [&](const u32x16 &m, int s) {
-#pragma unroll
-            for (int k = 0; k < 16; k += 4) {
-                const uint32_t m0 = m[k], m1 = m[k + 1], m2 = m[k + 2], m3 = m[k + 3];
-                const mm_half2 r0 = __builtin_bit_cast(mm_half2, x[16 * s + k]) - __builtin_bit_cast(mm_half2, m0);
-                const mm_half2 r1 = __builtin_bit_cast(mm_half2, x[16 * s + k + 1]) - __builtin_bit_cast(mm_half2, m1);
-                const mm_half2 r2 = __builtin_bit_cast(mm_half2, x[16 * s + k + 2]) - __builtin_bit_cast(mm_half2, m2);
-                const mm_half2 r3 = __builtin_bit_cast(mm_half2, x[16 * s + k + 3]) - __builtin_bit_cast(mm_half2, m3);
-                if (s == 0 && k == 0) {
-                    mxa = __builtin_elementwise_maximum(r0, r1);
-                    mna = __builtin_elementwise_minimum(r0, r1);
-                    mxb = __builtin_elementwise_maximum(r2, r3);
-                    mnb = __builtin_elementwise_minimum(r2, r3);
-                } else {
-                    mxa = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxa, r0), r1);
-                    mna = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mna, r0), r1);
-                    mxb = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxb, r2), r3);
-                    mnb = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mnb, r2), r3);
+                for (int k = 0; k < 16; k += 4) {
+                    const uint32_t m0 = m[k], m1 = m[k + 1], m2 = m[k + 2], m3 = m[k + 3];
+                    const mm_half2 r0 = __builtin_bit_cast(mm_half2, x[16 * s + k]) - __builtin_bit_cast(mm_half2, m0);
+                    const mm_half2 r1 = __builtin_bit_cast(mm_half2, x[16 * s + k + 1]) - __builtin_bit_cast(mm_half2, m1);
+                    const mm_half2 r2 = __builtin_bit_cast(mm_half2, x[16 * s + k + 2]) - __builtin_bit_cast(mm_half2, m2);
+                    const mm_half2 r3 = __builtin_bit_cast(mm_half2, x[16 * s + k + 3]) - __builtin_bit_cast(mm_half2, m3);
+                    if (s == 0 && k == 0) {
+                        mxa = __builtin_elementwise_maximum(r0, r1);
+                        mna = __builtin_elementwise_minimum(r0, r1);
+                        mxb = __builtin_elementwise_maximum(r2, r3);
+                        mnb = __builtin_elementwise_minimum(r2, r3);
+                    } else {
+                        mxa = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxa, r0), r1);
+                        mna = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mna, r0), r1);
+                        mxb = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mxb, r2), r3);
+                        mnb = __builtin_elementwise_minimum(__builtin_elementwise_minimum(mnb, r2), r3);
+                    }
                 }
-            }
-        };
-        u32x16 buf[2][W];
-        auto request = [&](const uint32_t *at, u32x16 (&to)[W]) {
-#pragma unroll
-            for (int w = 0; w < W; ++w) to[w] = sload16(at + 16 * w);
-        };
-        request(Mg, buf[0]);
-        auto pattern = [&](int p, int at) {   // at: which buffer holds (will hold) its first step
-            const uint32_t *mrow = Mg + (size_t)p * (D / 2), *mnext = Mg + (size_t)min(p + 1, P - 1) * (D / 2);   // (past the last row: that row again; unused)
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                arrived(buf[(s + at) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                request(s + 1 < NS ? mrow + 16 * W * (s + 1) : mnext, buf[(s + at + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);   // (the scheduler would issue the request behind most of the scan)
-#pragma unroll
-                for (int w = 0; w < W; ++w) scan(buf[(s + at) & 1][w], s * W + w);
-            }
-            const mm_half2 mx = __builtin_elementwise_maximum(mxa, mxb), mn = __builtin_elementwise_minimum(mna, mnb);
-            const float hi = (float)__builtin_elementwise_maximum(mx[0], mx[1]), lo = (float)__builtin_elementwise_minimum(mn[0], mn[1]);
-            const float t = fabsf(hi) + fabsf(lo);
-            // (not a number - a difference that overflowed fp16 - gives the bound 0 and leads to the exact evaluation)
-            const uint32_t key = (__float_as_uint(fmaxf(fmaf(t, -c, hi - lo), 0.f)) & 0xffffff00u) | (uint32_t)p;
-            t1 = key < k1 ? t : t1;
-            k3 = max(min(k2, k3), min(max(k2, k3), key));   // medians of three
-            k2 = max(min(k1, k2), min(max(k1, k2), key));
-            k1 = min(k1, key);
-        };
-        int p = 0;
-        for (; p + 1 < P; p += 2) {
-            pattern(p, 0);
-            pattern(p + 1, NS % 2);
-        }
-        if (p < P) pattern(p, 0);
-        int best = (int)(k1 & 0xffu);
-        const float first = __uint_as_float(k1 & 0xffffff00u);
-        // first's own low bits (2^-15 of it) belong to its upper bound
-        const float upper = fmaf(first, 6.103515625e-05f, fmaf(t1, 2.f * c, first));
-        const bool two = P > 1 && !(__uint_as_float(k2 & 0xffffff00u) > upper), more = P > 2 && two && !(__uint_as_float(k3 & 0xffffff00u) > upper);
-        if (two && !more) {
-            const __half *row = a.src.row_d(ns, tile * 64 + lane, D);
-            float bd = INFINITY;
-            int bi = 0;
+            };
+            // whether the lower bound of a key does not exceed the first one's upper bound (first's own low bits, 2^-15 of it, belong to that)
+            auto reaches = [&](uint32_t k) {
+                const float first = __uint_as_float(k1 & 0xffffff00u);
+                return !(__uint_as_float(k & 0xffffff00u) > fmaf(first, 6.103515625e-05f, fmaf(t1, 2.f * c, first)));
+            };
+            RowSteps<D> rows;
+            rows.M = Mg;
+            rows.P = P;
+            rows.all([&](int p, int at) {
+                rows.row(p, at, scan);
+                const mm_half2 mx = __builtin_elementwise_maximum(mxa, mxb), mn = __builtin_elementwise_minimum(mna, mnb);
+                const float hi = (float)__builtin_elementwise_maximum(mx[0], mx[1]), lo = (float)__builtin_elementwise_minimum(mn[0], mn[1]);
+                const float t = fabsf(hi) + fabsf(lo);
+                // (not a number - a difference that overflowed fp16 - gives the bound 0 and leads to the exact evaluation)
+                const uint32_t key = (__float_as_uint(fmaxf(fmaf(t, -c, hi - lo), 0.f)) & 0xffffff00u) | (uint32_t)p;
+                t1 = key < k1 ? t : t1;
+                k3 = max(min(k2, k3), min(max(k2, k3), key));   // medians of three
+                k2 = max(min(k1, k2), min(max(k1, k2), key));
+                k1 = min(k1, key);
+            }, P >= 16 ? P / 4 & ~1 : 0, [&]() {   // (as open as that after a quarter of the table, the rest of it seldom decides)
+                undecided = __popcll(__ballot(reaches(k3))) > kOpen;
+                return undecided;
+            });
+            best = (int)(k1 & 0xffu);
+            const bool two = P > 1 && reaches(k2), more = P > 2 && two && reaches(k3);
+            if (two && !more && !undecided) {
+                const __half *row = a.src.row_d(ns, tile * 64 + lane, D);
+                float bd = INFINITY;
+                int bi = 0;
 #pragma unroll 1
-            for (uint32_t i = 0, q = k1; i < 2; ++i, q = k2) {
-                const int cand = (int)(q & 0xffu);
-                const float dist = minmax_distance<NC>(row, Mh + (int64_t)cand * D);
-                const bool nearer = dist < bd || (dist == bd && cand < bi);
-                bd = nearer ? dist : bd;
-                bi = nearer ? cand : bi;
-            }
-            best = bi;
-        }
-        unsigned long long todo = __ballot(more);
-        while (todo) {
-            const int col = __ffsll((long long)todo) - 1;
-            todo &= todo - 1;
-            const __half *row = a.src.row_d(ns, tile * 64 + col, D);
-            float bd = INFINITY;
-            int bi = 0;
-            for (int q = lane; q < P; q += 64) {
-                const float dist = minmax_distance<NC>(row, Mh + (int64_t)q * D);
-                if (dist < bd) {   // the lane's patterns in increasing order
-                    bd = dist;
-                    bi = q;
+                for (uint32_t i = 0, q = k1; i < 2; ++i, q = k2) {
+                    const int cand = (int)(q & 0xffu);
+                    const float dist = minmax_distance<NC>(row, Mh + (int64_t)cand * D);
+                    const bool nearer = dist < bd || (dist == bd && cand < bi);
+                    bd = nearer ? dist : bd;
+                    bi = nearer ? cand : bi;
                 }
+                best = bi;
             }
+            unsigned long long todo = __ballot(more);
+            undecided = undecided || __popcll(todo) > kOpen;
+            while (!undecided && todo) {
+                const int col = __ffsll((long long)todo) - 1;
+                todo &= todo - 1;
+                const __half *row = a.src.row_d(ns, tile * 64 + col, D);
+                float bd = INFINITY;
+                int bi = 0;
+                for (int q = lane; q < P; q += 64) {
+                    const float dist = minmax_distance<NC>(row, Mh + (int64_t)q * D);
+                    if (dist < bd) {   // the lane's patterns in increasing order
+                        bd = dist;
+                        bi = q;
+                    }
+                }
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const float od = __shfl_xor(bd, off);
-                const int oi = __shfl_xor(bi, off);
-                if (od < bd || (od == bd && oi < bi)) {
-                    bd = od;
-                    bi = oi;
+                for (int off = 1; off < 64; off <<= 1) {
+                    const float od = __shfl_xor(bd, off);
+                    const int oi = __shfl_xor(bi, off);
+                    if (od < bd || (od == bd && oi < bi)) {
+                        bd = od;
+                        bi = oi;
+                    }
                 }
+                if (lane == col) best = bi;
             }
-            if (lane == col) best = bi;
         }
+        if (undecided) best = minmax_nearest<D>(a.src.row_d(ns, tile * 64 + lane, D), Mg, P);
         a.idx[a.map.pos(ns, a.t0 + tile * 64) + lane] = (uint8_t)best;
     }
 }

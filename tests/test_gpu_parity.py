@@ -1108,11 +1108,11 @@ def test_mining_parity_uneven_clusters(oracle, pk, d, P, T):
 @pytest.mark.parametrize("d,P,n_c", [
     (128, 1, 4), (128, 2, 1), (128, 33, 16), (128, 64, 1), (128, 65, 48), (128, 200, 100), (128, 256, 1),
     (96, 7, 7), (96, 63, 1), (96, 130, 40),
-    (256, 20, 10), (256, 64, 1), (256, 129, 60), (256, 256, 128),     # 256 rows of 256 channels do not fit LDS
+    (256, 20, 10), (256, 64, 1), (256, 129, 60), (256, 256, 128),
 ])
 def test_minmax_search_parity(oracle, pk, d, P, n_c):
-    """The min-max rule's search over table sizes (one pattern, odd counts, block edges of 64, several blocks, the largest)
-    with clustered vectors, where few patterns stay candidates, and with one cluster only, where nearly all do; two equal
+    """The min-max rule's search over table sizes (one pattern, odd counts, below and above 64, the largest)
+    with clustered vectors, where few patterns stay candidates, and with one cluster only, where more do; two equal
     patterns, so that the lowest index must win: indices, codes and parameters are bit-equal."""
     T, hkv = 448, 2
     K, V = synth.make_kv(40 + d + P, synth.KVSpec(1, 1, hkv, hkv, T, d, n_c))
@@ -1124,6 +1124,45 @@ def test_minmax_search_parity(oracle, pk, d, P, n_c):
               flush=64, t_capacity=T, metric=1)
     oc, gc, _, _ = run_appends(oracle, pk, oracle.Config(**kw), pk.Config(**kw), K, V, Mk, Mv, [64, T - 64])
     assert compare_caches(oracle, oc, gc, 1) == 0
+
+
+@pytest.mark.parametrize("d,P", [(128, 33), (96, 16), (256, 40)])
+@pytest.mark.parametrize("what", ["every pattern four times", "far from the table", "mixed", "overflow"])
+def test_minmax_search_undecided(pk, d, P, what):
+    """The min-max rule where the bounds of the packed search decide little - tables with repeated patterns, vectors so far from the
+    table that the distances lie within the bounds of each other - so that whole tiles are searched in binary32, also in a wave's
+    later tiles (two per wave here), and differences that overflow fp16: indices equal the definition, evaluated in binary32 by
+    torch in increasing order of the patterns."""
+    n_seq, hkv, T = 8, 8, 4160
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + P)
+    x = torch.randn((n_seq, hkv, T, d), generator=gen, device="cuda")
+    m = torch.randn((hkv, P, d), generator=gen, device="cuda")
+    if what == "every pattern four times":
+        m = m[:, torch.arange(P, device="cuda") // 4]
+    elif what == "far from the table":
+        x, m = x * 0.05 + 3.0, m * 0.05
+    elif what == "mixed":
+        x[::2, :, 64::128] = x[::2, :, 64::128] * 0.05 + 3.0
+        m[:, ::3] *= 0.05
+    else:
+        x[:, :, ::5, 7] = 40000.0
+        x[:, :, 3::5, 8] = -40000.0
+        m[:, 1::2, 7] = -40000.0
+    x, m = x.half(), m.half().contiguous()
+    cfg = pk.Config(n_seq=n_seq, n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, seqs_per_set=0, bits=2, group=32, recent=0,
+                    flush=64, t_capacity=T, metric=1)
+    cache = pk.Cache(cfg)
+    pk.pk_quantize_append(cfg, cache, x, x, m, m)
+    best = torch.full((n_seq, hkv, T), float("inf"), device="cuda")
+    index = torch.zeros((n_seq, hkv, T), dtype=torch.uint8, device="cuda")
+    for p in range(P):
+        r = x.float() - m[:, p].float()[None, :, None]
+        dist = r.amax(-1) - r.amin(-1)
+        index[dist < best] = p
+        best = torch.minimum(best, dist)
+    for side in ("k_idx", "v_idx"):
+        assert torch.equal(cache.array(side).view(torch.uint8).view(n_seq, hkv, T), index), side
 
 
 @pytest.mark.parametrize("d,bits,G,P,rho", [
