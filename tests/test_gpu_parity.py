@@ -1168,7 +1168,7 @@ def test_minmax_search_undecided(pk, d, P, what):
 @pytest.mark.parametrize("d,bits,G,P,rho", [
     (96, 2, 32, 16, 0.0), (96, 4, 32, 130, 0.8), (96, 2, 128, 200, 0.0), (96, 4, 128, 64, 0.0),
     (256, 2, 32, 64, 0.8), (256, 4, 32, 250, 0.0), (256, 2, 64, 130, 0.0), (256, 4, 64, 16, 0.0), (256, 2, 128, 256, 0.0),
-    (128, 4, 128, 129, 0.0),      # two groups of 128 tokens per workgroup, an odd number of groups
+    (128, 4, 128, 129, 0.0),      # workgroups with room for two groups of 128 tokens that get one
 ])
 def test_quantizers_over_head_dimensions(oracle, pk, d, bits, G, P, rho):
     """The quantizers' instantiations over head dimension, bits, group and table size (tables that take one workgroup per
@@ -1261,3 +1261,33 @@ def test_append_of_non_finite_vectors(oracle, pk, d, bits, G, P, rho):
     assert np.array_equal(by_tok(g["v_zero"])[good], by_tok(oc.v_zero)[good])
     bpt = d * bits // 32
     assert np.array_equal(oracle.unpack_v(g["v_codes"][0], T, d, bits)[good], oracle.unpack_v(oc.v_codes[0], T, d, bits)[good])
+
+
+@pytest.mark.parametrize("d,bits,P,groups", [
+    (128, 2, 136, 40), (128, 4, 200, 75), (96, 2, 180, 75),      # two groups side by side: two and three per workgroup
+    (128, 4, 136, 138), (128, 2, 256, 155), (96, 4, 171, 138),   # four: five and six per workgroup, the last one's range shorter
+    (96, 2, 130, 600),                                           # a table that leaves room for several workgroups, many groups
+])
+def test_quantize_groups_of_128_tokens_side_by_side(pk, d, bits, P, groups):
+    """Groups of 128 tokens against tables of more than 128 patterns: workgroups of two or four groups, with numbers of groups
+    that leave some of them without one in the last round.  The cache equals, byte for byte, the one that the same vectors give
+    when they are appended four groups at a time, a workgroup's first group each (which the other tests compare with the
+    oracle)."""
+    n_seq, hkv, T = 2, 4, 128 * groups
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + P)
+    center = torch.randn((hkv, 1, 40, d), generator=gen, device="cuda")
+    pick = torch.randint(0, 40, (n_seq, hkv, T), generator=gen, device="cuda")
+    x = torch.gather(center.expand(hkv, n_seq, 40, d).transpose(0, 1), 2, pick[..., None].expand(-1, -1, -1, d))
+    x = (x + 0.3 * torch.randn(x.shape, generator=gen, device="cuda")).half()
+    Mk, Mv = x[0, :, :P].contiguous(), x[1, :, 100:100 + P].contiguous()
+    cfg = pk.Config(n_seq=n_seq, n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=128,
+                    recent=0, flush=128, t_capacity=T, metric=0)
+    whole, pieces = pk.Cache(cfg), pk.Cache(cfg)
+    v = x.flip(2).contiguous()
+    pk.pk_quantize_append(cfg, whole, x, v, Mk, Mv)
+    for t in range(0, T, 512):
+        pk.pk_quantize_append(cfg, pieces, x[:, :, t:t + 512].contiguous(), v[:, :, t:t + 512].contiguous(), Mk, Mv)
+    assert whole.t_quant == pieces.t_quant == T
+    for name in ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx"):
+        assert torch.equal(whole.array(name), pieces.array(name)), name
