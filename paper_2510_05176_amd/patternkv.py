@@ -7,6 +7,7 @@ fallback: if the library has not been built, importing this module raises.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 from dataclasses import dataclass, replace
 
@@ -117,6 +118,9 @@ def pk_status_string(status: int) -> str:
     return _lib.pk_status_string(int(status)).decode()
 
 
+_config_values = operator.attrgetter(*(n for n, _ in _Config._fields_))
+
+
 @dataclass
 class Config:
     n_seq: int = 1
@@ -136,11 +140,9 @@ class Config:
     n_pages: int = 0
 
     def c(self) -> _Config:
-        # field by field: dataclasses.asdict, which copies recursively, took longer than a short call's kernels (a step of one
-        # token over 1.1k vectors on 8 streams, append and decode: 56 -> 41 us with 26 us of kernels)
-        return _Config(self.n_seq, self.n_kv_heads, self.n_q_heads, self.head_dim, self.n_patterns, self.seqs_per_set,
-                       self.bits, self.group, self.recent, self.flush, self.t_capacity, self.metric, self.v_rho,
-                       self.page_tokens, self.n_pages)
+        # the structure's fields by name, in its order: dataclasses.asdict, which copies recursively, took longer than a short
+        # call's kernels (a step of one token over 1.1k vectors on 8 streams, append and decode: 56 -> 41 us with 26 us of kernels)
+        return _Config(*_config_values(self))
 
     @property
     def n_streams(self) -> int:
@@ -185,7 +187,7 @@ def pk_workspace_bytes(cfg: Config, op: int, a: int, b: int = 0) -> int:
     return int(_lib.pk_workspace_bytes(C.byref(c), op, a, b))
 
 
-_ARRAYS = ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx", "tail_k", "tail_v")
+_ARRAYS = tuple(n for n, _ in _Cache._fields_ if n != "page_table")
 
 
 class Cache:
@@ -206,8 +208,8 @@ class Cache:
         if self.page_table is not None:
             assert self.page_table.dtype == torch.int32 and self.page_table.is_contiguous()
             assert tuple(self.page_table.shape) == (self.cfg.n_seq, self.cfg.t_capacity // self.cfg.page_tokens)
-        return _Cache(*[self.buf[n].data_ptr() for n in _ARRAYS],   # (the fields' order)
-                      None if self.page_table is None else self.page_table.data_ptr())
+        return _Cache(*[self.buf[n].data_ptr() for n in _ARRAYS],   # (the order of the structure's fields)
+                      page_table=None if self.page_table is None else self.page_table.data_ptr())
 
     @property
     def t_quant(self):

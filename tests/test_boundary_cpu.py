@@ -259,3 +259,17 @@ def test_window_pattern_argument_errors_before_launch(pk):
     assert wp(x=None) == 1 and wp(out=None) == 1 and wp(n=0) == 1 and wp(n_sets=0) == 1
     assert wp(d=64) == 2
     assert wp(x=odd) == 4 and wp(out=odd) == 4 and wp(ss=100) == 4 and wp(os=130) == 4
+
+
+def test_structures_are_filled_by_name(pk):
+    """Every field of the C structures receives the attribute (array) of its name, in whatever order either side declares them."""
+    names = [n for n, _ in pk._Config._fields_]
+    values = {n: 0.25 if n == "v_rho" else 3 + i for i, n in enumerate(names)}
+    c = pk.Config(**values).c()
+    assert {n: getattr(c, n) for n in names} == values
+    cache = pk.Cache(pk.Config(n_seq=2, n_kv_heads=1, group=64, flush=128, t_capacity=512, page_tokens=128, n_pages=9), device="cpu")
+    c = cache.c()
+    assert {n for n, _ in pk._Cache._fields_} == set(cache.buf) | {"page_table"}
+    for n in cache.buf:
+        assert getattr(c, n) == cache.buf[n].data_ptr(), n
+    assert c.page_table == cache.page_table.data_ptr()
