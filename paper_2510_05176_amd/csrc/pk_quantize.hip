@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(256) void tail_copy_kernel(TailCopyArgs a)
         a.i0 = e[kSeqI0];
         a.i1 = e[kSeqI1];
     }
-    const uint32_t w = blockIdx.x * 256 + threadIdx.x;   // (at most recent + flush vectors)
+    const uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x;
     const int i = a.i0 + (int)(w / kPieces), ch = (int)(w % kPieces);
     if (i >= a.i1) return;
     const __half *fresh = side == 0 ? a.fresh_k : a.fresh_v;
