@@ -545,7 +545,6 @@ static pk_status decode_impl(const pk_config *cfg, const pk_cache *cache, const 
     a.bits = cfg->bits;
     a.G = cfg->group;
     a.d = cfg->head_dim;
-    a.v_thresholded = (cfg->v_rho > 0.f || (has_prefix && prefix_cfg->v_rho > 0.f)) ? 1 : 0;
     {   // 6 or 8 heads per KV head over 32-channel groups, or 10 to 16 heads: two groups of heads, each with at
         // most 8 heads and 16 (head, V channel group) pairs
         const int64_t ng = kD / (cfg->group < kD ? cfg->group : kD);

@@ -26,7 +26,6 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 // which 16-byte reads of 16 rows x 4 column groups run at full rate.
 template <int D>
 constexpr int kTabStrideOf = D + 16;
-constexpr int kTabStride = kTabStrideOf<kD>;
 
 // Index of a vector that no pattern is nearest to: it is not finite, or no pattern is, so that no distance is below infinity.
 constexpr int kNoNearest = 0x7fffffff;

@@ -206,7 +206,6 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     constexpr int WPU = BITS / 2;
     constexpr int Gc = G < D ? G : D, NG = D / Gc, TPG = Gc / 16;   // V channel groups, 16-channel tiles of one
     constexpr bool TWO = G == 32;                     // two K groups per block
-    constexpr float kWUnit = kMassUnit;
     extern __shared__ __align__(16) unsigned char gen_decode_smem[];
     __shared__ float stat_m[4][8], stat_l[4][8], stat_pz[4][8][NG];
     const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kb = lane >> 4, P = a.P;
@@ -465,7 +464,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int id = (int)(((upper ? vid[2 + (k >> 2)] : vid[k >> 2]) >> (8 * (k & 3))) & 255u);
-                atomicAdd(&Ws[(wave * nh + h) * WS + min(id, WS - 1)], (unsigned long long)(own[k] * kWUnit));
+                atomicAdd(&Ws[(wave * nh + h) * WS + min(id, WS - 1)], (unsigned long long)(own[k] * kMassUnit));
             }
         }
         // ---- values
@@ -556,7 +555,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
             float acc = 0.f;
 #pragma unroll
             for (int w = 0; w < 4; ++w) acc = fmaf(__builtin_amdgcn_exp2f(stat_m[w][hh] - M), (float)Ws[(w * nh + hh) * WS + p], acc);
-            a.part_w[(pb + hh) * P + p] = acc * (1.f / kWUnit);
+            a.part_w[(pb + hh) * P + p] = acc * (1.f / kMassUnit);
         }
     }
     __syncthreads();
@@ -685,14 +684,13 @@ hipError_t launch_generic_decode(const DecodeArgs &a, hipStream_t s)
     // with 232 of them in the tail take 56 us instead of 41, 128 streams 73 instead of 55, 512 streams x 500 of 96 channels
     // 55.5 instead of 52.7, 2048 streams x 600 220 instead of 213.
     const int n_packed = a.splits_prefix + a.splits_own, N = a.n_seq * a.n_kv_heads, hz = (r + 7) / 8;
-    const bool apart = n_packed == 0;
     hipError_t e;
     if (n_packed > 0) {
-        const dim3 grid(N, n_packed + (apart ? 0 : 2), hz);
+        const dim3 grid(N, n_packed + 2, hz);
         e = a.d == kD ? launch_gen_decode_of<kD>(a, grid, s) : a.d == 96 ? launch_gen_decode_of<96>(a, grid, s) : launch_gen_decode_of<256>(a, grid, s);
         if (e != hipSuccess) return e;
     }
-    if (apart) {
+    if (n_packed == 0) {
         const dim3 grid(N, 2, hz), block(kGenThreads);
         if (a.d == kD)
             hipLaunchKernelGGL(gen_tail_kernel<kD>, grid, block, gen_tail_lds_bytes<kD>(r), s, a);

@@ -12,29 +12,19 @@
 
 namespace pk {
 
-constexpr int kD = 128;          // head_dim supported by the kernels
-constexpr int kRowChunks = 16;   // 16-byte chunks per fp16 row of kD elements
+constexpr int kD = 128;   // the head dimension that most kernels are written for (or default to)
 
 // Where the logical vectors of an append come from: first the old fp16 tail
 // (a ring), then the freshly passed vectors.
 struct RowSource {
-    const __half *ring;        // [N][ring_len][kD]
+    const __half *ring;        // [N][ring_len][d]
     const __half *fresh;       // stream n at fresh + n*fresh_stride
     int64_t fresh_stride;      // elements
     int32_t ring_len;
     int32_t ring_start;        // slot of logical vector 0
     int32_t n_ring;            // logical vectors [0, n_ring) live in the ring
 
-    __device__ __forceinline__ const __half *row(int n, int i) const
-    {
-        if (i < n_ring) {
-            int slot = ring_start + i;
-            if (slot >= ring_len) slot -= ring_len;
-            return ring + ((int64_t)n * ring_len + slot) * kD;
-        }
-        return fresh + (int64_t)n * fresh_stride + (int64_t)(i - n_ring) * kD;
-    }
-    // the same for rows of d elements (the generic kernels for head dimensions other than kD)
+    // row of d elements of logical vector i
     __device__ __forceinline__ const __half *row_d(int n, int i, int d) const
     {
         if (i < n_ring) {
@@ -150,7 +140,7 @@ inline hipError_t allow_dynamic_lds(const void *kernel, LdsOptIn &st, size_t max
 struct QuantArgs {
     RowSource src;
     SetMap sets;
-    const __half *patterns;   // [n_sets][P][kD]
+    const __half *patterns;   // [n_sets][P][d]
     int32_t P, metric, bits, G;
     int32_t d;                // head dimension: 96, 128 or 256
     int32_t idx_given;        // the index array already holds every vector's pattern (min-max metric: searched by a kernel of its own)
@@ -249,11 +239,10 @@ struct CacheView {
 struct DecodeArgs {
     CacheView own, prefix;        // prefix.t_quant == prefix.t_tail == 0 when unused
     SetMap sets;
-    const __half *q;              // [n_seq][Hq][kD]
+    const __half *q;              // [n_seq][Hq][d]
     const __half *patterns_k, *patterns_v;
     int32_t n_seq, n_kv_heads, n_q_heads, P, bits, G;
     int32_t d;                    // head dimension
-    int32_t v_thresholded;        // v_idx may hold PK_NO_PATTERN (read by the generic decode; the tuned one needs no flag)
     float softmax_scale;
     int32_t chunk;                // packed tokens per split
     int32_t w_stride;             // entries per (wave, head) row of the per-pattern softmax mass in LDS: P, or 256
@@ -262,7 +251,7 @@ struct DecodeArgs {
     int32_t head_groups;          // the matrix-core kernel takes the r query heads of a KV head in this many groups of
                                   // r / head_groups heads, a workgroup row per (stream, group): 1, or 2 when the
                                   // (head, V channel group) pairs of all r heads exceed a tile's 16 columns or r > 8
-    float *part_o;                // [N][S][r][kD]  unnormalised partial outputs
+    float *part_o;                // [N][S][r][d]  unnormalised partial outputs
     float *part_w;                // [N][S][r][P]   softmax mass per V pattern (packed splits only)
     float *part_ml;               // [N][S][r][2]   running maximum (log2 domain) and sum
     float *out, *lse;

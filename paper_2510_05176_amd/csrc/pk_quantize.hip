@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
 // 350 us.
 // ===========================================================================
 
-// (sub_lo / sub_hi, the fp16 differences with one rounding, live in pk_assign_mfma.h: the exact search uses them too)
+// (sub_lo / sub_hi, the fp16 differences with one rounding, live in pk_internal.h: the exact search uses them too)
 __device__ __forceinline__ float subz_lo(float x, uint32_t z)   // x - half(z.lo)
 {
     float r;
