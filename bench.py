@@ -55,7 +55,7 @@ VALU_LANE_OPS_PEAK_T = 256 * 4 * 16 * 2.4e9 / 1e12
 WORKLOADS = {
     "cfg2": dict(spec="cfg2", layers=1, batch=1, P=64, iters=10, group=64, recent=0, flush=64),
     "cfg2x32": dict(spec="cfg2", layers=32, batch=1, P=64, iters=10, group=64, recent=0, flush=64),
-    # config 2's 32 layers at head dimensions 96 and 256: the plain kernels of pk_generic.hip
+    # config 2's 32 layers at head dimensions 96 and 256
     "cfg2x32_d96": dict(spec="cfg2_d96", layers=32, batch=1, P=64, iters=10, group=32, recent=0, flush=64),
     "cfg2x32_d256": dict(spec="cfg2_d256", layers=32, batch=1, P=64, iters=10, group=64, recent=0, flush=64),
     "cfg3": dict(spec="cfg3", layers=32, batch=16, P=128, iters=10, group=64, recent=128, flush=128),
@@ -67,6 +67,7 @@ WORKLOADS = {
     "cfg3r": dict(spec="cfg3"),  # config 3's shape with a mix of sequence lengths: ragged prefill + ragged decode, see run_ragged()
 }
 DECODE_KERNELS = "decode_packed_kernel(+decode_tail_kernel+decode_merge_kernel)"
+DECODE_KERNELS_OTHER_D = "gen_decode_kernel(+gen_tail_kernel+gen_decode_merge_kernel)"   # head dimensions 96 and 256
 
 
 def stored_traffic(workload, bits):
@@ -206,13 +207,9 @@ def run_static(name, args, torch, pk, synth, steps, warmup, metric=None, cpu_bas
     mine_bytes = 2.0 * L * Hkv * iters * T * d * 2            # per Lloyd iteration: one pass over x
     traffic = stored_traffic(name, bits) if metric == pk.METRIC_L2 else {}
 
-    generic = d != 128   # head dimensions 96 and 256 run the plain kernels
+    quantize_kernels = ("quantize_k_group_kernel" if G == 128 else "quantize_k_wave_kernel") + "+quantize_v_kernel"
 
     def roof(stage, bound, achieved, peak, unit, kernels):
-        if generic:
-            kernels = {"mine": "gen_mine_assign_kernel+gen_mine_sums_kernel+gen_mine_update_kernel",
-                       "quantize_append": "gen_assign_kernel+gen_quantize_k_kernel+gen_quantize_v_kernel",
-                       "decode_attention": "gen_decode_split_kernel+gen_decode_merge_kernel"}[stage]
         return {"bound": bound, "achieved": round(achieved, 3), "peak": peak, "unit": unit,
                 "frac": round(achieved / peak, 4), "traffic": traffic.get(stage), "kernel": kernels}
 
@@ -225,19 +222,20 @@ def run_static(name, args, torch, pk, synth, steps, warmup, metric=None, cpu_bas
     q_s = stage_ms["quantize_append"] * 1e-3
     if metric == pk.METRIC_L2:
         q_roof = roof("quantize_append", "hbm", quant_bytes / q_s / 1e9, HBM_PEAK_GBPS, "GB/s",
-                      "quantize_k_wave_kernel+quantize_v_kernel")
+                      quantize_kernels)
     else:
-        # d_mm of one vector against one pattern (Sec. 3.2) in its shortest instruction form: d binary32 subtractions,
-        # d/2 three-operand maxima and d/2 three-operand minima = 2 lane operations per channel, for K and for V
-        lane_ops = 2.0 * N * cap * P * 2 * d
+        # d_mm of one vector against one pattern (Sec. 3.2) in its shortest instruction form, packed fp16: per two channels a
+        # subtraction and half of a three-operand maximum and minimum each = 1 lane operation per channel, for K and for V
+        # (few pairs are evaluated again in binary32; they are not counted)
+        lane_ops = 1.0 * N * cap * P * 2 * d
         q_roof = roof("quantize_append", "alu", lane_ops / q_s / 1e12, round(VALU_LANE_OPS_PEAK_T, 2), "T lane-ops/s",
-                      "assign_minmax_kernel(+quantize_k_wave_kernel+quantize_v_kernel)")
+                      f"assign_minmax_kernel(+{quantize_kernels})")
         q_roof["hbm_GB/s"] = round(quant_bytes / q_s / 1e9, 2)
     rl = {
         "mine": mine_roof,
         "quantize_append": q_roof,
         "decode_attention": roof("decode_attention", "hbm", dec_bytes / (stage_ms["decode_attention"] * 1e-3) / 1e9,
-                                 HBM_PEAK_GBPS, "GB/s", DECODE_KERNELS),
+                                 HBM_PEAK_GBPS, "GB/s", DECODE_KERNELS if d == 128 else DECODE_KERNELS_OTHER_D),
     }
     stage_out = {
         "mine": {"ms": round(stage_ms["mine"], 4), "ms_min": round(stage_ms_min["mine"], 4),
@@ -501,7 +499,7 @@ def measure_peaks(torch, pk):
         "fma_f32_TFLOP/s": round(2.0 * 16 * fma_iters * 2048 * 256 / t_fma / 1e9, 2),
         "mfma_f16_TFLOP/s": round(2.0 * 16 * 16 * 32 * 8 * mfma_iters * 2048 * 4 / t_mfma / 1e9, 1),
         "note": "read: 4 GiB streamed once; copy: 2 GiB read + 2 GiB written; fma: plain v_fma_f32, 16 independent chains "
-                "per lane (this build uses no packed fp32 instructions); mfma: v_mfma_f32_16x16x32_f16, 8 independent "
+                "per lane (this library uses no packed fp32 instructions); mfma: v_mfma_f32_16x16x32_f16, 8 independent "
                 "accumulators per wave",
     }
 
@@ -614,7 +612,7 @@ def main():
     if args.summarise_pmc:
         return summarise_pmc(args.summarise_pmc[0], args.summarise_pmc[1], args.calls, args.key, args.cmd)
     if args.gpus != 1:
-        print("bench.py: this build runs on one GPU; --gpus must be 1 (no sharding or collectives are part of it)",
+        print("bench.py: this library runs on one GPU; --gpus must be 1 (no sharding or collectives are part of it)",
               file=sys.stderr)
         sys.exit(2)
 

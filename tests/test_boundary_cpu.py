@@ -273,3 +273,13 @@ def test_structures_are_filled_by_name(pk):
     for n in cache.buf:
         assert getattr(c, n) == cache.buf[n].data_ptr(), n
     assert c.page_table == cache.page_table.data_ptr()
+
+
+def test_bench_names_kernels_that_exist():
+    """The kernels that bench.py reports for a stage are kernels of the library's sources."""
+    csrc = os.path.join(ROOT, "paper_2510_05176_amd", "csrc")
+    source = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith((".hip", ".h")))
+    kernels = set(re.findall(r"__global__[^;{]*?\b(\w+_kernel)\s*\(", source))
+    named = set(re.findall(r"\b[a-z_]+_kernel\b", open(os.path.join(ROOT, "bench.py")).read()))
+    assert {"mine_step_kernel", "gen_decode_kernel", "quantize_k_group_kernel"} <= named
+    assert named <= kernels, named - kernels
