@@ -151,14 +151,14 @@ int64_t decode_slots_bound(int64_t N, int64_t a, int64_t b)
 struct MineCarve {
     size_t best, psum, pcnt, total;
 };
-MineCarve mine_carve(int64_t S, int64_t T, int P, int d)
+// chunks: of all sets together
+MineCarve mine_carve(int64_t S, int64_t T, int64_t chunks, int P, int d)
 {
     MineCarve m;
-    const int ts = mine_tsplit((int)T, (int)S, P);
     m.best = 0;
     m.psum = round_up(m.best + (uint64_t)S * T * 4, 256);
-    m.pcnt = round_up(m.psum + (uint64_t)S * ts * P * d * 4, 256);
-    m.total = round_up(m.pcnt + (uint64_t)S * ts * P * 4, 256);
+    m.pcnt = round_up(m.psum + (uint64_t)chunks * P * d * 4, 256);
+    m.total = round_up(m.pcnt + (uint64_t)chunks * P * 4, 256);
     return m;
 }
 
@@ -215,7 +215,7 @@ size_t pk_workspace_bytes(const pk_config *cfg, pk_op op, int64_t a, int64_t b)
     if (op == PK_OP_MINE) {
         const int hd = cfg->head_dim;
         if ((hd != kD && hd != 96 && hd != 256) || cfg->n_patterns < 1 || cfg->n_patterns > 256 || b < 1) return 0;
-        return mine_carve(b, a, cfg->n_patterns, hd).total;
+        return mine_carve(b, a, mine_chunks_bound(a, b, cfg->n_patterns), cfg->n_patterns, hd).total;
     }
     if (check_config(cfg) != PK_OK) return 0;
     if (op == PK_OP_APPEND) return (size_t)cfg->n_seq * kSeqEntry * sizeof(int32_t);
@@ -256,7 +256,7 @@ pk_status pk_mine_patterns(const pk_config *cfg, const void *x, int64_t set_stri
     if (!init_given && T < cfg->n_patterns) return PK_ERR_SHAPE;
     if (set_stride < (int64_t)T * hd || set_stride % 8 != 0) return PK_ERR_SHAPE;
     if (!aligned16(x) || !aligned16(patterns) || (assign && !aligned16(assign))) return PK_ERR_ALIGNMENT;
-    const MineCarve mc = mine_carve(n_sets, T, cfg->n_patterns, hd);
+    const MineCarve mc = mine_carve(n_sets, T, (int64_t)n_sets * mine_tsplit(T, n_sets, cfg->n_patterns), cfg->n_patterns, hd);
     if (!workspace || workspace_bytes < mc.total) return PK_ERR_WORKSPACE;
     if (!aligned16(workspace)) return PK_ERR_ALIGNMENT;
 

@@ -217,6 +217,7 @@ struct MineArgs {
 };
 hipError_t launch_mine(const MineArgs &a, hipStream_t s);
 int mine_tsplit(int T, int n_sets, int P);   // the most chunks per set launch_mine uses at any head dimension
+int64_t mine_chunks_bound(int64_t T, int64_t n_sets, int P);   // at least n_sets times that, non-decreasing in T and n_sets
 hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, __half *out, int64_t out_stride,
                                  hipStream_t s);
 

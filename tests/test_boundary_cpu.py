@@ -283,3 +283,18 @@ def test_bench_names_kernels_that_exist():
     named = set(re.findall(r"\b[a-z_]+_kernel\b", open(os.path.join(ROOT, "bench.py")).read()))
     assert {"mine_step_kernel", "gen_decode_kernel", "quantize_k_group_kernel"} <= named
     assert named <= kernels, named - kernels
+
+
+@pytest.mark.parametrize("d,P", [(96, 16), (128, 64), (128, 128), (128, 200), (256, 64), (256, 256)])
+def test_mining_workspace_grows_with_the_job(pk, d, P):
+    """pk_workspace_bytes of mining is non-decreasing in the vectors per set and in the sets: a workspace for the largest job
+    serves the smaller ones (whose chunks per set are more where the sets are fewer)."""
+    cfg = pk.Config(head_dim=d, n_patterns=P)
+    size = lambda T, S: pk.pk_workspace_bytes(cfg, pk.OP_MINE, T, S)
+    lengths = sorted(set(range(256, 70000, 1021)) | {16384, 16385, 32768, 32769, 65536})
+    for S in (1, 3, 16, 128, 129, 256, 513, 1025):
+        sizes = [size(T, S) for T in lengths]
+        assert sizes == sorted(sizes), S
+    for T in (1000, 8192, 16384, 40000):
+        sizes = [size(T, S) for S in range(1, 1300, 3)]
+        assert sizes == sorted(sizes), T
