@@ -27,9 +27,6 @@ typedef float floatx4_t __attribute__((ext_vector_type(4)));
 template <int D>
 constexpr int kTabStrideOf = D + 16;
 
-// Index of a vector that no pattern is nearest to: it is not finite, or no pattern is, so that no distance is below infinity.
-constexpr int kNoNearest = 0x7fffffff;
-
 __host__ __device__ constexpr int pad16(int p) { return (p + 15) & ~15; }
 
 struct PatternTable {
@@ -201,14 +198,14 @@ __device__ __forceinline__ void assign_tile_mfma(const uint4 (&xb)[KS], const Pa
 }
 
 // Exact re-evaluation of one token by a whole wave: xrow_s = its D channels (fp16) in LDS.
-// Every lane returns the exact argmin (lowest index on ties) and its distance; kNoNearest and infinity where no distance
-// is below infinity.
+// Every lane returns the exact argmin (lowest index on ties) and its distance; `none` and infinity for a token that no
+// pattern is nearest to: it is not finite, or no pattern is, so that no distance is below infinity.
 template <int D>
-__device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const PatternTable &tb, int lane, int &best_i,
+__device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const PatternTable &tb, int lane, int none, int &best_i,
                                                   float &best_d)
 {
     float bd = INFINITY;
-    int bi = kNoNearest;
+    int bi = none;
     for (int p = lane; p < tb.P; p += 64) {
         // the pattern rows come from the LDS copy of the table (the same fp16 values): read from global memory they
         // missed L2 often enough to add a fifth to the HBM traffic of a mining step on a large job
@@ -243,15 +240,20 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
     best_d = bd;
 }
 
-// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.  The lanes of a token that no
-// pattern is nearest to (always flagged: its gap is not a number or infinite) call none() after their index became kNoNearest.
-template <int KS, class NONE>
+// Re-evaluate the flagged tokens of a tile.  xrow_s: per-wave LDS scratch of 32 * KS halves.  A token that no pattern is nearest
+// to is always flagged (its gap is not a number or infinite); its index becomes `none`.  seen(index): called by the lanes of
+// every token that was evaluated again.  UNLIKELY: the loop is put out of the way of the code around it (one token in several
+// hundred takes it): a mining step of 8 sets 0.3 % faster; in the quantizers, whose registers are all taken, it costs a spill.
+struct Ignore {
+    __device__ __forceinline__ void operator()(int) const {}
+};
+template <int KS, bool UNLIKELY = false, class SEEN = Ignore>
 __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag, __half *xrow_s, const PatternTable &tb,
-                                                int lane, int &best_i, float &best_d, NONE none)
+                                                int lane, int none, int &best_i, float &best_d, SEEN seen = SEEN())
 {
     const int n = lane & 15, kb = lane >> 4;
     unsigned long long todo = __ballot(flag) & 0xffffull;   // one bit per column
-    while (__builtin_expect(todo != 0, 0)) {   // (one token in several hundred: out of the way of the code around it)
+    while (UNLIKELY ? __builtin_expect(todo != 0, 0) : todo != 0) {
         const int col = __ffsll((long long)todo) - 1;
         todo &= todo - 1;
         if (n == col) {
@@ -262,11 +264,11 @@ __device__ __forceinline__ void resolve_flagged(const uint4 (&xb)[KS], bool flag
         __builtin_amdgcn_wave_barrier();
         int bi;
         float bd;
-        exact_argmin_wave<32 * KS>(xrow_s, tb, lane, bi, bd);
+        exact_argmin_wave<32 * KS>(xrow_s, tb, lane, none, bi, bd);
         if (n == col) {
             best_i = bi;
             best_d = bd;
-            if (bi == kNoNearest) none();
+            seen(bi);
         }
         __builtin_amdgcn_wave_barrier();
     }

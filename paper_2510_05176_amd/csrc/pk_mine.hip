@@ -175,15 +175,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             at[j] = (wave * NT + j) * 16 + n;
             const int tok = sub * ST + at[j];
             lost[j] = false;
-            resolve_flagged<KS>(xb[j], flag[j], xrow_s, tb, lane, bi[j], bd, [&]() {
-                bi[j] = kNone;
-                lost[j] = true;
-            });
+            resolve_flagged<KS, true>(xb[j], flag[j], xrow_s, tb, lane, kNone, bi[j], bd, [&](int b) { lost[j] = b == kNone; });
             if (kb == 0) {
                 if (tok < n_tok) {
                     // per-vector outputs only where somebody reads them: indices from the last step (if asked
                     // for), distances when the objective is reported
-                    if (outputs & 1) a.assign[(int64_t)s * a.T + t_begin + tok] = bi[j] < P ? bi[j] : kNoNearest;
+                    if (outputs & 1) a.assign[(int64_t)s * a.T + t_begin + tok] = bi[j] < P ? bi[j] : 0x7fffffff;
                     if (outputs & 2) a.best[(int64_t)s * a.T + t_begin + tok] = bd;
                     atomicAdd(&cnt[bi[j]], 1);
                 }

@@ -473,7 +473,7 @@ __device__ __forceinline__ int assign_index(const PatternTable &tb, const uint4 
     float bv, x2, bd;
     bool flag;
     assign_tile_mfma(xb, tb, lane, bi, bv, x2, flag);
-    resolve_flagged(xb, flag, xrow, tb, lane, bi, bd, [&]() { bi = 0; });
+    resolve_flagged(xb, flag, xrow, tb, lane, 0, bi, bd);
     return bi;
 }
 
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;
-                resolve_flagged(xb[j], flag[j], reinterpret_cast<__half *>(rt), tb, lane, bi[j], bd, [&]() { bi[j] = 0; });
+                resolve_flagged(xb[j], flag[j], reinterpret_cast<__half *>(rt), tb, lane, 0, bi[j], bd);
             }
         }
         float mn[KS], mx[KS];
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
 #pragma unroll
                 for (int j = 0; j < NTA; ++j) {
                     float bd;
-                    resolve_flagged(xb[j0 + j], flag[j], reinterpret_cast<__half *>(rt), tb, lane, bj[j], bd, [&]() { bj[j] = 0; });
+                    resolve_flagged(xb[j0 + j], flag[j], reinterpret_cast<__half *>(rt), tb, lane, 0, bj[j], bd);
                     bi[j0 + j] = bj[j];
                 }
             }
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 float bd;
-                resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + St::kRow), tb, lane, bis[j], bd, [&]() { bis[j] = 0; });
+                resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + St::kRow), tb, lane, 0, bis[j], bd);
             }
         }
 #pragma unroll
