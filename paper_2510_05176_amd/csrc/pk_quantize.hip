@@ -1068,8 +1068,15 @@ __global__ __launch_bounds__(256) void tail_copy_kernel(TailCopyArgs a)
         a.i0 = e[kSeqI0];
         a.i1 = e[kSeqI1];
     }
-    const uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    const int i = a.i0 + (int)(w / kPieces), ch = (int)(w % kPieces);
+    int i, ch;   // (the pieces of a ring may be more than 32 bits count, its vectors are not)
+    if constexpr (256 % kPieces == 0) {
+        i = a.i0 + (int)(blockIdx.x * (256 / kPieces) + threadIdx.x / kPieces);
+        ch = threadIdx.x % kPieces;
+    } else {
+        const uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+        i = a.i0 + (int)(w / kPieces);
+        ch = (int)(w % kPieces);
+    }
     if (i >= a.i1) return;
     const __half *fresh = side == 0 ? a.fresh_k : a.fresh_v;
     __half *ring = side == 0 ? a.ring_k : a.ring_v;

@@ -187,7 +187,8 @@ def pk_workspace_bytes(cfg: Config, op: int, a: int, b: int = 0) -> int:
     return int(_lib.pk_workspace_bytes(C.byref(c), op, a, b))
 
 
-_ARRAYS = tuple(n for n, _ in _Cache._fields_ if n != "page_table")
+_ARRAYS = tuple(n for n, _ in _Cache._fields_[:-1])
+assert _Cache._fields_[-1][0] == "page_table"   # (Cache.c fills the structure in this order)
 
 
 class Cache:
@@ -209,7 +210,7 @@ class Cache:
             assert self.page_table.dtype == torch.int32 and self.page_table.is_contiguous()
             assert tuple(self.page_table.shape) == (self.cfg.n_seq, self.cfg.t_capacity // self.cfg.page_tokens)
         return _Cache(*[self.buf[n].data_ptr() for n in _ARRAYS],   # (the order of the structure's fields)
-                      page_table=None if self.page_table is None else self.page_table.data_ptr())
+                      None if self.page_table is None else self.page_table.data_ptr())
 
     @property
     def t_quant(self):
