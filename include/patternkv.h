@@ -360,8 +360,8 @@ pk_status pk_decode_attention_noalloc(const pk_config *cfg, const pk_cache *cach
  * growing one means re-laying it out) and uses the grown table for the following appends and decodes.
  *   x           device, fp16, window s at x + s*set_stride elements, n rows of head_dim contiguous
  *   pattern_out device, fp16, row s at pattern_out + s*out_stride elements (head_dim values)
- * Errors (before any launch): NULL pointers, n_sets < 1, n < 1 -> PK_ERR_INVALID_ARG; head_dim != 128 ->
- * PK_ERR_UNSUPPORTED; pointers or strides not 16-byte aligned -> PK_ERR_ALIGNMENT.  Asynchronous on `stream`.
+ * Errors (before any launch): NULL pointers, n_sets < 1, n < 1 -> PK_ERR_INVALID_ARG; head_dim not 96, 128
+ * or 256 -> PK_ERR_UNSUPPORTED; pointers or strides not 16-byte aligned -> PK_ERR_ALIGNMENT.  Asynchronous on `stream`.
  */
 pk_status pk_window_pattern(const void *x, int64_t set_stride, int32_t n_sets, int32_t n, int32_t head_dim,
                             void *pattern_out, int64_t out_stride, void *stream);

@@ -46,7 +46,8 @@ __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 // search, into a buffer of their own, so that they are in flight for the whole of it (without the sort that gained nothing).
 // A quarter (two thirds at 256 patterns) of the matrix instructions less per vector; 256 sets, 2 x 10 iterations: 32768
 // vectors at 128 patterns 14.8 -> 13.8 ms (15.1 -> 14.2 on another card); 8 sets x 16384 at 256
-// patterns 817 -> 787 us; 64 sets of 256 channels at 200 patterns 3.50 -> 3.16 ms.  With 64 patterns the sort costs more than
+// patterns 817 -> 787 us; 64 sets of 256 channels at 200 patterns 3.50 -> 3.16 ms; 256 sets x 8192 at 66, 80, 96 and 112 patterns
+// 3.24 -> 3.01, 3.33 -> 3.10, 3.55 -> 3.43 and 3.81 -> 3.81 ms.  With 64 patterns the sort costs more than
 // the two steps that it saves (2.6 -> 2.8 ms on 256 sets x 8192), and at 256 channels and 128 patterns it gained nothing
 // (2.79 -> 2.80 ms).  Neither matrix cores (24 % busy) nor vector ALUs (44 %) nor HBM (57 %) bound the step at 128
 // patterns: two waves per SIMD, a third of their time waiting at barriers and for loads; four waves per SIMD at 96
