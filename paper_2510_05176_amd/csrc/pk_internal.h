@@ -217,7 +217,14 @@ struct MineArgs {
 };
 hipError_t launch_mine(const MineArgs &a, hipStream_t s);
 int mine_tsplit(int T, int n_sets, int P);   // the most chunks per set launch_mine uses at any head dimension
-int64_t mine_chunks_bound(int64_t T, int64_t n_sets, int P);   // at least n_sets times that, non-decreasing in T and n_sets
+// At least n_sets times that, non-decreasing in T and n_sets: at most 64 chunks per set, of 256 vectors or more, and no more
+// in all than the chip holds at once (four workgroups per CU up to 64 patterns, two up to 128, one above) unless the sets are more.
+inline int64_t mine_chunks_bound(int64_t T, int64_t n_sets, int P)
+{
+    const int64_t per_set = (T + 255) / 256 < 64 ? (T + 255) / 256 : 64, slots = 256 * (P <= 64 ? 4 : P <= 128 ? 2 : 1);
+    const int64_t all = n_sets * per_set, resident = n_sets > slots ? n_sets : slots;
+    return all < resident ? all : resident;
+}
 hipError_t launch_window_pattern(const __half *x, int64_t set_stride, int n_sets, int n, __half *out, int64_t out_stride,
                                  hipStream_t s);
 

@@ -437,14 +437,6 @@ int mine_tsplit(int T, int n_sets, int P)
     return chunks_of(T, n_sets, P, kD);
 }
 
-int64_t mine_chunks_bound(int64_t T, int64_t n_sets, int P)
-{
-    // at most 64 chunks per set, of 256 vectors or more, and no more than the chip holds at once unless the sets are more
-    const int64_t per_set = (T + 255) / 256 < 64 ? (T + 255) / 256 : 64, slots = 256 * step_groups_per_cu(P, kD);
-    const int64_t all = n_sets * per_set, resident = n_sets > slots ? n_sets : slots;
-    return all < resident ? all : resident;
-}
-
 // All iterations for 16 * NPT patterns or fewer at head dimension D
 template <int D, int NPT>
 static hipError_t launch_iterations(const MineArgs &a_in, hipStream_t s)
