@@ -272,25 +272,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
     // Offsets from a base fit 32 bits (the host refuses capacities for which they would not).
     // (PAGED is a template parameter: the re-basing branches cost the contiguous case 1 % when decided at run time)
     constexpr bool paged = PAGED;
+    const StreamMap map = cv.map.of(cstream);
     const char *kcodes, *kscale, *kzero, *kidx, *vcodes, *vscale, *vzero, *vidx;
     // (the page of a block is looked up one block ahead of its first use, so that the scalar load of the table entry
     // is not on the path of the block's loads: with the lookup in place a scrambled cache of 128-token pages read
     // 33 % slower than contiguous streams)
     auto set_k_bases = [&](int tb, int page) {
-        const int64_t delta = cv.map.pos_in(page, cstream, tb) - tb;   // a multiple of the page size (or stream * capacity)
+        const int64_t delta = map.pos_in(page, tb) - tb;   // a multiple of the page size (or stream * capacity)
         kcodes = reinterpret_cast<const char *>(cv.k_codes + delta * 4 * BITS);
         kscale = reinterpret_cast<const char *>(cv.k_scale + (delta >> lgG) * kD);
         kzero = reinterpret_cast<const char *>(cv.k_zero + (delta >> lgG) * kD);
         kidx = reinterpret_cast<const char *>(cv.k_idx + delta);
     };
     auto set_v_bases = [&](int tb, int page) {
-        const int64_t delta = cv.map.pos_in(page, cstream, tb) - tb;
+        const int64_t delta = map.pos_in(page, tb) - tb;
         vcodes = reinterpret_cast<const char *>(cv.v_codes) + delta * (kD * BITS / 8);
         vscale = reinterpret_cast<const char *>(cv.v_scale + delta * NG);
         vzero = reinterpret_cast<const char *>(cv.v_zero + delta * NG);
         vidx = reinterpret_cast<const char *>(cv.v_idx + delta);
     };
-    int pg_cur = paged ? cv.map.page_of(cstream, t_begin + (b0 << 6)) : 0, pg_next = pg_cur;   // pages of this wave's current / next block
+    int pg_cur = paged ? map.page_of(t_begin + (b0 << 6)) : 0, pg_next = pg_cur;   // pages of this wave's current / next block
     set_k_bases(t_begin + (b0 << 6), pg_cur);
     set_v_bases(t_begin + (b0 << 6), pg_cur);
     int pg_v = pg_cur;   // page the V-side bases stand for
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                 set_v_bases(tb, pg_cur);
                 pg_v = pg_cur;
             }
-            if (b + 1 < b1 && ((tb + 64) & ((1 << cv.map.page_shift) - 1)) == 0) pg_next = cv.map.page_of(cstream, tb + 64);
+            if (b + 1 < b1 && ((tb + 64) & ((1 << map.shift) - 1)) == 0) pg_next = map.page_of(tb + 64);
         }
         const int unit = (tb >> 4) + kb;   // 16-token unit of this lane group
         uint32_t vidw[NTK / 4];

@@ -15,7 +15,7 @@ __global__ __launch_bounds__(128) void dequant_kernel(DequantArgs a)
     const int t = a.t0 + blockIdx.x, n = blockIdx.y, c = threadIdx.x;
     const int set = a.sets.set_of(n);
     const int G = a.G, Gc = G < kD ? G : kD, ng = kD / Gc;
-    const int64_t tok = a.c.map.pos(n, t);   // where token t of the stream is stored
+    const int64_t tok = a.c.map.of(n).pos(t);   // where token t of the stream is stored
     const int64_t orow = ((int64_t)n * (a.t1 - a.t0) + (t - a.t0)) * kD + c;
     if (a.k_out) {
         int code = 0;

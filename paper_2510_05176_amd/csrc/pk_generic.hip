@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kGenThreads) void gen_dequant_kernel(DequantArgs a)
     if (c >= d) return;
     const int set = a.sets.set_of(n);
     const int Gc = a.G < d ? a.G : d;
-    const int64_t pos = a.c.map.pos(n, t);
+    const int64_t pos = a.c.map.of(n).pos(t);
     const int64_t orow = ((int64_t)n * (a.t1 - a.t0) + (t - a.t0)) * d + c;
     if (a.k_out) a.k_out[orow] = k_hat(a.c, a.patterns_k + (int64_t)set * a.P * d, pos, c, d, a.bits, a.G);
     if (a.v_out) a.v_out[orow] = v_hat(a.c, a.patterns_v + (int64_t)set * a.P * d, pos, c, d, a.bits, Gc, a.v_thresholded);
@@ -347,10 +347,11 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))
     for (int t = 0; t < D / 16; ++t) O[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     Operand ga, gb;   // gb: second K group of a block
     const uint32_t *vwords = reinterpret_cast<const uint32_t *>(cv.v_codes);
+    const StreamMap map = cv.map.of(stream);
 
     for (int b = b0; b < b1; ++b) {
         const int tb = t_begin + (b << 6);
-        const int64_t pos0 = cv.map.pos(stream, tb);   // (a 64-token block never straddles a page)
+        const int64_t pos0 = map.pos(tb);   // (a 64-token block never straddles a page)
         // ---- inputs of the block
         uint32_t kw[4][KW][BITS];
 #pragma unroll

@@ -36,30 +36,49 @@ struct RowSource {
     }
 };
 
-// Where token `tok` of stream `stream` lives in the packed arrays, in tokens: stream * capacity + tok for contiguous
+// Where the tokens of one stream live in the packed arrays, in tokens: stream * capacity + tok for contiguous
 // streams; through the sequence's page table for a paged cache (a page = [n_kv_heads][page_tokens] tokens).  A table
 // entry is clamped to the pool, so whatever the table holds the position stays inside the arrays.  Quantization
 // groups, 64-token blocks and tiles never straddle a page (page_tokens is a power of two >= 128), so a kernel asks
 // for the position of a tile's first token and adds offsets inside the tile.
+// Wave-uniform throughout (the token too).  The page table is read only while a kernel runs, so its entries come through the
+// scalar data path: as vector loads, each with a wait for all loads before it, they held up the vectors that the
+// quantizers and the decode kernel had requested ahead (16 prompts of 2k to 32k tokens in 128-token pages, K and V quantizers
+// of one layer @@ us).
+struct StreamMap {
+    const int32_t *pages;   // the sequence's row of the page table, or null
+    int32_t shift, last, n_pages, n_kv_heads;   // log2(page_tokens); last entry of the row
+    int64_t base;           // contiguous: stream * capacity; paged: the head's offset inside a page
+    // physical page of the token (clamped to the pool); 0 for contiguous streams
+    __device__ __forceinline__ int page_of(int tok) const
+    {
+        if (!pages) return 0;
+        const int page = *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)(pages + min(tok >> shift, last));
+        return min(max(page, 0), n_pages - 1);
+    }
+    // position of the token given its page (as page_of returns it)
+    __device__ __forceinline__ int64_t pos_in(int page, int tok) const
+    {
+        if (!pages) return base + tok;
+        return (((int64_t)page * n_kv_heads) << shift) + base + (tok & ((1 << shift) - 1));
+    }
+    __device__ __forceinline__ int64_t pos(int tok) const { return pos_in(page_of(tok), tok); }
+};
+
 struct PackedMap {
     const int32_t *page_table;   // device [n_seq][pages_per_seq], or null
     int32_t page_shift;          // log2(page_tokens)
     int32_t pages_per_seq, n_pages, n_kv_heads, t_capacity;
-    // physical page of the stream's token (clamped to the pool); 0 for contiguous streams
-    __device__ __forceinline__ int page_of(int stream, int tok) const
+    __device__ __forceinline__ StreamMap of(int stream) const
     {
-        if (!page_table) return 0;
-        const int page = page_table[(int64_t)(stream / n_kv_heads) * pages_per_seq + min(tok >> page_shift, pages_per_seq - 1)];
-        return min(max(page, 0), n_pages - 1);
+        StreamMap m = {nullptr, page_shift, pages_per_seq - 1, n_pages, n_kv_heads, (int64_t)stream * t_capacity};
+        if (page_table) {
+            const int seq = stream / n_kv_heads;
+            m.pages = page_table + (int64_t)seq * pages_per_seq;
+            m.base = (int64_t)(stream - seq * n_kv_heads) << page_shift;
+        }
+        return m;
     }
-    // position of the token given its page (as page_of returns it)
-    __device__ __forceinline__ int64_t pos_in(int page, int stream, int tok) const
-    {
-        if (!page_table) return (int64_t)stream * t_capacity + tok;
-        const int head = stream % n_kv_heads;
-        return (((int64_t)page * n_kv_heads + head) << page_shift) + (tok & ((1 << page_shift) - 1));
-    }
-    __device__ __forceinline__ int64_t pos(int stream, int tok) const { return pos_in(page_of(stream, tok), stream, tok); }
 };
 
 struct SetMap {

@@ -244,6 +244,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
     const __half *Mh = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     const uint32_t *Mg = reinterpret_cast<const uint32_t *>(Mh);
     take_sequence_entry(a, ns);
+    const StreamMap map = a.map.of(ns);
     const int n_tiles = a.nq / 64;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     bool undecided = false;   // the bounds left many vectors of a tile open: this tile and the wave's further ones without them
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 
             }
         }
         if (undecided) best = minmax_nearest<D>(a.src.row_d(ns, tile * 64 + lane, D), Mg, P);
-        a.idx[a.map.pos(ns, a.t0 + tile * 64) + lane] = (uint8_t)best;
+        a.idx[map.pos(a.t0 + tile * 64) + lane] = (uint8_t)best;
     }
 }
 
@@ -430,14 +431,23 @@ __device__ __forceinline__ PatternTable make_table(const TableLds &sh, int P)
     return tb;
 }
 
-// B operand of one 16-token tile: vectors i0 .. i0+15 of stream ns.
+// B operand of one 16-token tile: vectors i0 .. i0+15 of stream ns (i0 wave-uniform).  A tile without vectors of the ring - nearly
+// all of a long append - takes one scalar address and fixed lane offsets.
 template <int KS>
 __device__ __forceinline__ void load_tile(const QuantArgs &a, int ns, int i0, uint4 (&xb)[KS])
 {
+    constexpr int D = 32 * KS;
     const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
-    const __half *row = a.src.row_d(ns, i0 + n, 32 * KS);
+    if (i0 >= a.src.n_ring) {
+        const __half *tile = a.src.fresh + (int64_t)ns * a.src.fresh_stride + (int64_t)(i0 - a.src.n_ring) * D;
+        const uint32_t at = n * D + 8 * kb;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) xb[k] = *reinterpret_cast<const uint4 *>(row + 32 * k + 8 * kb);
+        for (int k = 0; k < KS; ++k) xb[k] = *reinterpret_cast<const uint4 *>(tile + at + 32 * k);
+    } else {
+        const __half *row = a.src.row_d(ns, i0 + n, D);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) xb[k] = *reinterpret_cast<const uint4 *>(row + 32 * k + 8 * kb);
+    }
 }
 
 // Residuals r[j] of channel 32k + 8kb + j: eight channels of a vector minus those of a pattern.
@@ -603,13 +613,15 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
     const TableLds sh = table_lds<D>(smem, a.P);
     const int gr = GR == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTH);
     const int tid = threadIdx.x % NTH, ns = blockIdx.y;          // thread inside the group
-    const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
+    const int lane = tid & 63, n = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned char *work = smem + table_lds_bytes<D>(a.P) + gr * kGroupLds<D, NT>;
     float *rt = reinterpret_cast<float *>(work + wave * kWkTile);
     uint16_t *pz = reinterpret_cast<uint16_t *>(work + NW * kWkTile);   // [D] zero points, then [D] scales
     float *pinv = reinterpret_cast<float *>(pz + 2 * D);
     const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
+    const StreamMap map = a.map.of(ns);
     const int n_tiles = a.nq / TT;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
@@ -623,7 +635,7 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
         // (a group past the range repeats the last one, up to the barriers, and stores nothing)
         const bool live = GR == 1 || tile_base + gr < tile1;
         const int tile = live ? tile_base + gr : tile1 - 1;
-        const int64_t pq0 = a.map.pos(ns, a.t0 + tile * TT);   // where the group's first token is stored
+        const int64_t pq0 = map.pos(a.t0 + tile * TT);   // where the group's first token is stored
         int bi[NT];
         if (a.idx_given) {   // searched beforehand (min-max metric)
 #pragma unroll
@@ -707,7 +719,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
     extern __shared__ __align__(16) unsigned char smem[];
     const TableLds sh = table_lds<D>(smem, a.P);
     const int tid = threadIdx.x, ns = blockIdx.y;
-    const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
+    const int lane = tid & 63, n = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned char *mine = smem + table_lds_bytes<D>(a.P) + (size_t)wave * kWkWave<D>;
     float *rt = reinterpret_cast<float *>(mine);
     uint16_t *pz = reinterpret_cast<uint16_t *>(mine + kWkTile);   // [D] zero points, then [D] scales
@@ -715,6 +728,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
 
     const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
+    const StreamMap map = a.map.of(ns);
     const int n_tiles = a.nq / 64;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
@@ -730,7 +744,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
 
     for (; g < g_end; g += 4) {
         const int64_t tq0 = (int64_t)a.t0 + (int64_t)g * G;   // logical position of the group's first token
-        const int64_t pq0 = a.map.pos(ns, (int)tq0);            // where it is stored
+        const int64_t pq0 = map.pos((int)tq0);            // where it is stored
         // ---- pass A: indices; running minimum / maximum per channel
         float mn[KS], mx[KS];
 #pragma unroll
@@ -874,9 +888,11 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
     extern __shared__ __align__(16) unsigned char smem[];
     const TableLds sh = table_lds<D>(smem, a.P);
     const int tid = threadIdx.x, ns = blockIdx.y;
-    const int lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
+    const int lane = tid & 63, n = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const __half *Mg = a.patterns + (int64_t)a.sets.set_of(ns) * a.P * D;
     take_sequence_entry(a, ns);
+    const StreamMap map = a.map.of(ns);
     const int n_tiles = a.nq / TT;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
@@ -914,7 +930,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
         if (a.idx_given) {   // searched beforehand (min-max metric); a block past the range repeats the last one
 #pragma unroll
             for (int j = 0; j < NT; ++j)
-                bis[j] = a.idx[a.map.pos(ns, a.t0 + min(tile_base + j, tile1 - 1) * TT) + wave * 16 + n];
+                bis[j] = a.idx[map.pos(a.t0 + min(tile_base + j, tile1 - 1) * TT) + wave * 16 + n];
         } else {
             float bv[NT], x2[NT];
             bool flag[NT];
@@ -1047,7 +1063,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
             }
         }
         wave_lds_sync();
-        pend_tok0 = a.map.pos(ns, a.t0 + tile * TT) + wave * 16;   // stored at the start of the next unit
+        pend_tok0 = map.pos(a.t0 + tile * TT) + wave * 16;   // stored at the start of the next unit
       }
     }
     store_pending();
