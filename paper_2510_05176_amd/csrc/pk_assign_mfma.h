@@ -15,6 +15,7 @@
 #pragma once
 
 #include "pk_internal.h"
+#include "pk_lanes.h"
 
 namespace pk {
 
@@ -119,7 +120,7 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], con
                                                   float (&best_v)[NT], float (&x2)[NT], bool (&flag)[NT])
 {
     const int n = lane & 15, kb = lane >> 4;
-    float xx[NT], hx[NT];
+    float part[NT], hx[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         float acc = 0.f;
@@ -129,11 +130,10 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], con
 #pragma unroll
             for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
         }
-        acc += __shfl_xor(acc, 16);
-        acc += __shfl_xor(acc, 32);
-        xx[j] = acc;
-        hx[j] = 0.5f * acc;
+        part[j] = acc;
     }
+    const float xx = fold_rows<NT>(part, AddF());   // |x|^2 of the lane's column in tile kb % NT
+    spread_rows<NT>(0.5f * xx, hx);
 
     // the key's index bits are p0 + i here; the lane's 4*kb is added after the loop (no carries: p0 % 16 == 0)
     uint32_t k1[NT], k2[NT];
@@ -161,24 +161,40 @@ __device__ __forceinline__ void assign_tiles_mfma(const uint4 (&xb)[NT][KS], con
             for (int j = 0; j < NT; ++j) rank_pattern_tile(xb[j], ta, hx[j], p0, k1[j], k2[j]);
         }
     }
+    // merge the four lane groups of the columns; from here on row kb speaks for tile kb % NT
+    uint32_t a1[NT], a2[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        uint32_t a1 = k1[j] | (uint32_t)kb << 2, a2 = k2[j] | (uint32_t)kb << 2;
-        // merge the four lane groups of the column
+        a1[j] = k1[j] | (uint32_t)kb << 2;
+        a2[j] = k2[j] | (uint32_t)kb << 2;
+    }
+    auto merge = [](rows2 p1, rows2 p2, uint32_t &m1, uint32_t &m2) {
+        m1 = min(p1[0], p1[1]);
+        m2 = min(min(p2[0], p2[1]), max(p1[0], p1[1]));
+    };
+    uint32_t m1, m2;
+    merge(swap16(a1[0], a1[NT > 1 ? 1 : 0]), swap16(a2[0], a2[NT > 1 ? 1 : 0]), m1, m2);
+    if constexpr (NT == 4) {
+        uint32_t h1, h2;
+        merge(swap16(a1[2], a1[3]), swap16(a2[2], a2[3]), h1, h2);
+        merge(swap32(m1, h1), swap32(m2, h2), m1, m2);
+    } else {
+        merge(swap32(m1, m1), swap32(m2, m2), m1, m2);
+    }
+    const float best = -2.f * __uint_as_float(m1 & 0xffffff00u), second = -2.f * __uint_as_float(m2 & 0xffffff00u);
+    // accumulation error of e is far below 2^-21 (|x|^2 + |m|^2) per chain of four matrix instructions, the keys
+    // drop 8 mantissa bits: flag with a wide margin.  A single pattern has nothing to be confused with.
+    constexpr float kBand = KS > 4 ? 1.52587890625e-05f : 7.62939453125e-06f;
+    const bool open = tb.P > 1 && !(second - best > kBand * (xx + tb.norm2_max) + 6.103515625e-05f * second);
+    // (a single pattern could lose to the rows behind the table if e is not a number)
+    uint32_t word[NT];
+    spread_rows<NT>((m1 & (tb.P > 1 ? 0xffu : 0u)) | (open ? 0x80000000u : 0u), word);
+    spread_rows<NT>(best, best_v);
+    spread_rows<NT>(xx, x2);
 #pragma unroll
-        for (int off = 16; off <= 32; off <<= 1) {
-            const uint32_t o1 = (uint32_t)__shfl_xor((int)a1, off), o2 = (uint32_t)__shfl_xor((int)a2, off);
-            a2 = min(min(a2, o2), max(a1, o1));
-            a1 = min(a1, o1);
-        }
-        best_i[j] = (int)(a1 & (tb.P > 1 ? 0xffu : 0u));   // (a single pattern could lose to the rows behind the table if e is not a number)
-        best_v[j] = -2.f * __uint_as_float(a1 & 0xffffff00u);
-        const float second = -2.f * __uint_as_float(a2 & 0xffffff00u);
-        x2[j] = xx[j];
-        // accumulation error of e is far below 2^-21 (|x|^2 + |m|^2) per chain of four matrix instructions, the keys
-        // drop 8 mantissa bits: flag with a wide margin.  A single pattern has nothing to be confused with.
-        constexpr float kBand = KS > 4 ? 1.52587890625e-05f : 7.62939453125e-06f;
-        flag[j] = tb.P > 1 && !(second - best_v[j] > kBand * (xx[j] + tb.norm2_max) + 6.103515625e-05f * second);
+    for (int j = 0; j < NT; ++j) {
+        best_i[j] = (int)(word[j] & 0xffu);
+        flag[j] = (int)word[j] < 0;
     }
 }
 

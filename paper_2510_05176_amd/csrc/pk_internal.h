@@ -110,28 +110,18 @@ __device__ __forceinline__ float sub_hi(uint32_t x, uint32_t m)   // half(x.hi) 
     asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(x), "v"(m));
     return r;
 }
-// largest binary16 value <= f
+// Largest binary16 value <= f, smallest one >= f: the nearest value, or its neighbour one bit pattern away where that is on the wrong
+// side.  (A zero on the wrong side has the sign that makes its neighbour in the bit patterns the right one: -0 is the nearest
+// value of a negative f, +0 of a positive one.)  Without branches, which cost more than the rest of the parameters.
 __device__ __forceinline__ unsigned short f2h_down(float f)
 {
-    unsigned short u = __half_as_ushort(__float2half_rn(f));
-    if (hbits2f(u) > f) {
-        if ((u & 0x7fffu) == 0) u = 0x8001u;   // +-0 -> smallest negative subnormal
-        else if (u & 0x8000u) u += 1;          // negative: one step away from zero
-        else u -= 1;                           // positive: one step towards zero
-    }
-    return u;
+    const int u = (short)__half_as_ushort(__float2half_rn(f));
+    return (unsigned short)(u + (hbits2f((unsigned short)u) > f ? -1 - 2 * (u >> 31) : 0));
 }
-
-// smallest binary16 value >= f
 __device__ __forceinline__ unsigned short f2h_up(float f)
 {
-    unsigned short u = __half_as_ushort(__float2half_rn(f));
-    if (hbits2f(u) < f) {
-        if ((u & 0x7fffu) == 0) u = 0x0001u;
-        else if (u & 0x8000u) u -= 1;
-        else u += 1;
-    }
-    return u;
+    const int u = (short)__half_as_ushort(__float2half_rn(f));
+    return (unsigned short)(u + (hbits2f((unsigned short)u) < f ? 1 + 2 * (u >> 31) : 0));
 }
 
 // ---- launchers (host) -------------------------------------------------------

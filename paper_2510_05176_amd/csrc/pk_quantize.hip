@@ -663,10 +663,10 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
             }
         }
 #pragma unroll
-        for (int k = 0; k < KS; ++k) {   // the two token halves
-            mn[k] = fminf(mn[k], __shfl_xor(mn[k], 32));
-            mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 32));
-            rt[(lane < 32 ? 0 : D) + 32 * k + (lane & 31)] = lane < 32 ? mn[k] : mx[k];
+        for (int k = 0; k < KS; ++k) {   // the two token halves: minima in the lower half of the lanes, maxima in the upper one
+            const rows2 v = swap32(bits_of(mn[k]), bits_of(mx[k]));
+            const float lo = op_rows(v, MinF()), hi = op_rows(v, MaxF());
+            rt[(lane < 32 ? 0 : D) + 32 * k + (lane & 31)] = lane < 32 ? lo : hi;
         }
         __syncthreads();
         for (int c = tid; c < D; c += NTH) {
@@ -788,20 +788,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
                 }
             }
         }
-        // ---- parameters of the group: the two token halves are combined, then lane (c, half) takes the channels
+        // ---- parameters of the group: the two token halves are combined, lane (c, half) gets the channels
         //      32(2h + half) + c
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            mn[k] = fminf(mn[k], __shfl_xor(mn[k], 32));
-            mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], 32));
-        }
         const int sc = lane & 31, sth = lane >> 5;
 #pragma unroll
         for (int h = 0; h < (KS + 1) / 2; ++h) {
             constexpr int last = KS - 1;
             const int k1 = 2 * h + 1 < KS ? 2 * h + 1 : last;
-            if (KS % 2 == 0 || 2 * h + 1 < KS || sth == 0)
-                put_params(sth ? mn[k1] : mn[2 * h], sth ? mx[k1] : mx[2 * h], BITS, 32 * (2 * h + sth) + sc, D, pz, pinv);
+            const float lo = op_rows(swap32(bits_of(mn[2 * h]), bits_of(mn[k1])), MinF());
+            const float hi = op_rows(swap32(bits_of(mx[2 * h]), bits_of(mx[k1])), MaxF());
+            if (KS % 2 == 0 || 2 * h + 1 < KS || sth == 0) put_params(lo, hi, BITS, 32 * (2 * h + sth) + sc, D, pz, pinv);
         }
         wave_lds_sync();
         store_params<D>(a, pq0 / G, pz);
@@ -970,14 +966,11 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
                 }
             }
             float x_lo = fminf((float)xmn[0], (float)xmn[1]), x_hi = fmaxf((float)xmx[0], (float)xmx[1]);
-#pragma unroll
-            for (int off = 16; off <= 32; off <<= 1) {
-                rmn = fminf(rmn, __shfl_xor(rmn, off));
-                rmx = fmaxf(rmx, __shfl_xor(rmx, off));
-                x_lo = fminf(x_lo, __shfl_xor(x_lo, off));
-                x_hi = fmaxf(x_hi, __shfl_xor(x_hi, off));
-            }
-            const bool keep = (rmx - rmn) <= a.v_rho * (x_hi - x_lo);
+            // (even rows: of the residual, odd rows: of the vector)
+            const float lows[2] = {rmn, x_lo}, highs[2] = {rmx, x_hi};
+            float range[2];
+            spread_rows<2>(fold_rows<2>(highs, MaxF()) - fold_rows<2>(lows, MinF()), range);
+            const bool keep = range[0] <= a.v_rho * range[1];
             if (!keep) {   // quantize the vector itself
                 bi = PK_NO_PATTERN;
 #pragma unroll
@@ -994,7 +987,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
         }
         if (tile + NT < tile1) load_tile(a, ns, (tile + NT) * TT + wave * 16, xb);   // else the registers keep this block
 
-        // minimum / maximum per channel group: lane-local over its channels, then over the 4 lanes of the token
+        // minimum / maximum per channel group: lane-local over its channels here, then over the 4 lanes of the token
         float mn[NG], mx[NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
@@ -1005,34 +998,32 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
                 mn[g] = fminf(fminf(mn[g], r[e]), r[e + 1]);
                 mx[g] = fmaxf(fmaxf(mx[g], r[e]), r[e + 1]);
             }
-#pragma unroll
-            for (int off = 16; off <= 32; off <<= 1) {
-                mn[g] = fminf(mn[g], __shfl_xor(mn[g], off));
-                mx[g] = fmaxf(mx[g], __shfl_xor(mx[g], off));
-            }
         }
-        // lane kb works out the parameters of group kb % NG (eight groups: of kb and kb + 4) and stores them; the others
+        // row kb works out the parameters of group kb % NG (eight groups: of kb and kb + 4) and stores them; the others
         // fetch them
         float z[NG], inv[NG];
 #pragma unroll
         for (int l = 0; l < GL; ++l) {
-            float my_mn = mn[4 * l], my_mx = mx[4 * l];
+            constexpr int NF = NG == 3 || NG > 4 ? 4 : NG;   // groups folded together (three: the first one twice)
+            float lows[NF], highs[NF], zs[NF], invs[NF];
 #pragma unroll
-            for (int g = 4 * l + 1; g < NG && g < 4 * l + 4; ++g) {
-                if ((NG == 2 ? (kb & 1) : kb) == g - 4 * l) {
-                    my_mn = mn[g];
-                    my_mx = mx[g];
-                }
+            for (int i = 0; i < NF; ++i) {
+                lows[i] = mn[4 * l + i < NG ? 4 * l + i : 0];
+                highs[i] = mx[4 * l + i < NG ? 4 * l + i : 0];
             }
-            const GroupParams gp = group_params(my_mn, my_mx, BITS);
+            const GroupParams gp = group_params(fold_rows<NF>(lows, MinF()), fold_rows<NF>(highs, MaxF()), BITS);
             if (kb + 4 * l < NG) {
                 reinterpret_cast<uint16_t *>(wsc + St::kScale)[(kb + 4 * l) * 16 + n] = gp.s16;
                 reinterpret_cast<uint16_t *>(wsc + St::kZero)[(kb + 4 * l) * 16 + n] = gp.z16;
             }
+            spread_rows<NF>(gp.z, zs);
+            spread_rows<NF>(gp.inv, invs);
 #pragma unroll
-            for (int g = 4 * l; g < NG && g < 4 * l + 4; ++g) {
-                z[g] = NG == 1 ? gp.z : __shfl(gp.z, n + 16 * (g - 4 * l));
-                inv[g] = NG == 1 ? gp.inv : __shfl(gp.inv, n + 16 * (g - 4 * l));
+            for (int i = 0; i < NF; ++i) {
+                if (4 * l + i < NG) {
+                    z[4 * l + i] = zs[i];
+                    inv[4 * l + i] = invs[i];
+                }
             }
         }
         if (kb == 0) wsc[St::kIdx + n] = (uint8_t)bi;
