@@ -397,6 +397,12 @@ __device__ __forceinline__ uint32_t plane_byte_shifted(uint32_t lo, uint32_t hi,
     return __builtin_amdgcn_udot4(hi & m, 0x80402010u, acc, false);
 }
 
+// Sum of the 8 codes held in the bytes of (lo, hi), code i times 2^i.
+__device__ __forceinline__ uint32_t byte_sum(uint32_t lo, uint32_t hi)
+{
+    return __builtin_amdgcn_udot4(hi, 0x80402010u, __builtin_amdgcn_udot4(lo, 0x08040201u, 0u, false), false);
+}
+
 // The pattern table at the start of the dynamic LDS of every quantizer: rows, -|m|^2 / 2, one maximum per wave.
 struct TableLds {
     __half *tab;      // [pad16(P)][kTabStrideOf<D>]
@@ -520,22 +526,34 @@ template <int D>
 constexpr int kKParams = D * 2 * 2 + D * 4;           // bytes of one group's parameters
 
 // Running minimum / maximum per channel over a 16-token tile: the residuals of 32 channels (operand step k) at a time
-// pass through the wave's LDS tile; lane <-> (channel 32k + lane%32, token half lane/32).
-__device__ __forceinline__ void scan_channels(const float *r, float *rt, float &mn, float &mx)
-{
-    const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4, sc = lane & 31, sth = lane >> 5;
-    float4 *dst = reinterpret_cast<float4 *>(rt + n * kWkStride + 8 * kb);
-    dst[0] = make_float4(r[0], r[1], r[2], r[3]);
-    dst[1] = make_float4(r[4], r[5], r[6], r[7]);
-    wave_lds_sync();
+// pass through the wave's LDS tile; lane <-> (channel 32k + lane%32, token half lane/32).  A step's values are used behind the next
+// step's stores (the LDS takes a wave's accesses in order): between its own stores and its use a step's loads would be waited for.
+struct ChannelScan {
+    float v[8];
+    float *mn, *mx;   // of the step that v belongs to; null: none
+    __device__ __forceinline__ void use()
+    {
 #pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-        const float v0 = rt[(8 * sth + t) * kWkStride + sc], v1 = rt[(8 * sth + t + 1) * kWkStride + sc];
-        mn = fminf(fminf(mn, v0), v1);
-        mx = fmaxf(fmaxf(mx, v0), v1);
+        for (int t = 0; t < 8; t += 2) {
+            *mn = fminf(fminf(*mn, v[t]), v[t + 1]);
+            *mx = fmaxf(fmaxf(*mx, v[t]), v[t + 1]);
+        }
     }
-    wave_lds_sync();
-}
+    __device__ __forceinline__ void step(const float *r, float *rt, float &low, float &high)
+    {
+        const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4, sc = lane & 31, sth = lane >> 5;
+        float4 *dst = reinterpret_cast<float4 *>(rt + n * kWkStride + 8 * kb);
+        dst[0] = make_float4(r[0], r[1], r[2], r[3]);
+        dst[1] = make_float4(r[4], r[5], r[6], r[7]);
+        if (mn) use();
+        wave_lds_sync();
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = rt[(8 * sth + t) * kWkStride + sc];
+        wave_lds_sync();
+        mn = &low;
+        mx = &high;
+    }
+};
 
 // The stored parameters of channel c
 __device__ __forceinline__ void put_params(float mn, float mx, int bits, int c, int D, uint16_t *pz, float *pinv)
@@ -651,6 +669,7 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
             }
         }
         float mn[KS], mx[KS];
+        ChannelScan scan = {};
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
             mn[k] = INFINITY;
@@ -659,9 +678,10 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
             for (int j = 0; j < NT; ++j) {
                 float r[8];
                 residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
-                scan_channels(r, rt, mn[k], mx[k]);
+                scan.step(r, rt, mn[k], mx[k]);
             }
         }
+        scan.use();
 #pragma unroll
         for (int k = 0; k < KS; ++k) {   // the two token halves: minima in the lower half of the lanes, maxima in the upper one
             const rows2 v = swap32(bits_of(mn[k]), bits_of(mx[k]));
@@ -753,6 +773,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
             mx[k] = -INFINITY;
         }
         int bi[NTG];
+        ChannelScan scan = {};
         if (a.idx_given) {   // searched beforehand (min-max metric)
 #pragma unroll
             for (int j = 0; j < NTG; ++j) bi[j] = a.idx[pq0 + j * 16 + n];
@@ -778,16 +799,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
                 float r[8 * KS];
                 residuals(sh, xb[j], bi[j], r);
 #pragma unroll
-                for (int k = 0; k < KS; ++k) scan_channels(r + 8 * k, rt, mn[k], mx[k]);
+                for (int k = 0; k < KS; ++k) scan.step(r + 8 * k, rt, mn[k], mx[k]);
             } else {   // 256 channels: the tiles alone take half of the registers
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
                     float r[8];
                     residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
-                    scan_channels(r, rt, mn[k], mx[k]);
+                    scan.step(r, rt, mn[k], mx[k]);
                 }
             }
         }
+        scan.use();
         // ---- parameters of the group: the two token halves are combined, lane (c, half) gets the channels
         //      32(2h + half) + c
         const int sc = lane & 31, sth = lane >> 5;
@@ -842,9 +864,11 @@ struct VStaging {
 };
 
 // 16x16 bit transpose across the 16 lanes of a row, on both 16-bit halves of x at once:
-// on return bit t of a half in lane i is what bit i of that half was in lane t.
+// on return bit t of a half in lane i is what bit i of that half was in lane t.  The partner's word comes by lane permutations inside
+// the row, folded into the mask operation (permutes through LDS left a wave waiting for four of them in turn).
 struct TransposeConst {
-    uint32_t sh[4], keep[4];   // stage d = 8, 4, 2, 1: rotation of the partner's word, bits kept from the own word
+    uint32_t sh[4], keep[4];   // stage d = 8, 4, 2, 1: rotation of the partner's bits; bits kept of the own word, which are also the places
+                               // of those that the partner's word gives, before the rotation
 };
 __device__ __forceinline__ TransposeConst transpose_const(int n)
 {
@@ -859,13 +883,19 @@ __device__ __forceinline__ TransposeConst transpose_const(int n)
     }
     return c;
 }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
 __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst &c)
 {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        const uint32_t partner = (uint32_t)__shfl_xor((int)x, 8 >> s);
-        const uint32_t rot = __builtin_amdgcn_alignbit(partner, partner, c.sh[s]);   // bits that cross a half are masked out
-        x = (x & c.keep[s]) | (rot & ~c.keep[s]);
+        // lane n ^ 8: a rotation of the row; n ^ 4: n ^ 7 (mirrored half row), then ^ 3; n ^ 2, n ^ 1: inside quads
+        const uint32_t partner = s == 0 ? dpp<0x128>(x) : s == 1 ? dpp<0x1b>(dpp<0x141>(x)) : s == 2 ? dpp<0x4e>(x) : dpp<0xb1>(x);
+        const uint32_t t = partner & c.keep[s];
+        x = (x & c.keep[s]) | __builtin_amdgcn_alignbit(t, t, c.sh[s]);
     }
     return x;
 }
@@ -1043,6 +1073,13 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
             // channel of this lane after the transpose: i = n
             const int c = 32 * (2 * b + (n >> 3)) + 8 * kb + (n & 7);
             uint32_t *dst = stg + ((c & 15) * (D / 16) + (c >> 4)) * WPU;
+            if constexpr (BITS == 2) {
+                // sums of code << i and of (code & 2) << i over the sixteen codes, twice plane 1; their difference is plane 0
+                const uint32_t all = (byte_sum(cw[2], cw[3]) << 8) + byte_sum(cw[0], cw[1]);
+                const uint32_t hi2 = (plane_byte_shifted(cw[2], cw[3], 1) << 8) + plane_byte_shifted(cw[0], cw[1], 1);
+                const uint32_t word = transpose16(__umul24(hi2, 32767u) + all, tc);   // all - hi2 + (hi2 / 2 << 16)
+                if (16 * b + 16 <= kAll || n < 8) dst[0] = word;
+            } else {
 #pragma unroll
             for (int w = 0; w < WPU; ++w) {
                 // t_p = (bits p of the 16 codes) << p; low half of x = plane 2w, high half = plane 2w+1
@@ -1051,6 +1088,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
                 const uint32_t x = (t0 >> (2 * w)) | (t1 << (15 - 2 * w));
                 const uint32_t word = transpose16(x, tc);
                 if (16 * b + 16 <= kAll || n < 8) dst[w] = word;
+            }
             }
         }
         wave_lds_sync();
@@ -1168,7 +1206,7 @@ static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
         const int round = one_round(a, 64, 256);
         return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
     } else if constexpr (G == 64) {   // pairs keep three waves per SIMD; the whole group takes two, which pays above 128 patterns
-        if (a.P > 128) {
+        if (a.P > 32) {
             const int round = one_round(a, 64, 256);
             return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 4>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
         }
