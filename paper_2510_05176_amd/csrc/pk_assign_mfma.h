@@ -45,29 +45,39 @@ __device__ __forceinline__ floatx4_t mfma_f16(const uint4 &a, const uint4 &b, fl
 // Stage a pattern table into LDS (nthr threads, a multiple of 64; the loop is guarded) and compute the row norms; red_s
 // gets one maximum per wave.  Ends with a barrier.
 // Work item i = (row, 16-byte piece): the kLanes lanes of a row (16, or 32 at D = 256; lanes past the row's D / 8 pieces
-// idle at D = 96) sum their squares.
+// idle at D = 96) sum their squares.  kAhead items of a thread are requested before the first is stored: one after the other each
+// waited for its own load (@@).
 template <int D = kD>
 __device__ __forceinline__ void stage_patterns(const __half *Mg, int P, __half *tab_s, float *nh_s, float *red_s,
                                                int nthr = 256)
 {
-    constexpr int kLanes = D <= 128 ? 16 : 32, kPieces = D / 8, kStride = kTabStrideOf<D>;
-    const int tid = threadIdx.x;
+    constexpr int kLanes = D <= 128 ? 16 : 32, kPieces = D / 8, kStride = kTabStrideOf<D>, kAhead = 8;
+    const int tid = threadIdx.x, total = pad16(P) * kLanes;
     float mx = 0.f;
-    // pad16(P) * kLanes is a multiple of 256, and every kLanes consecutive work items sit in one wave: the row sums
+    // total is a multiple of 256, and every kLanes consecutive work items sit in one wave: the row sums
     // below see whole rows (a trailing half round of a 512-thread group has whole waves idle)
-    for (int i = tid; i < pad16(P) * kLanes; i += nthr) {
-        const int r = i / kLanes, ch = i % kLanes;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r < P && (kPieces == kLanes || ch < kPieces)) v = *reinterpret_cast<const uint4 *>(Mg + (int64_t)r * D + ch * 8);
-        if (kPieces == kLanes || ch < kPieces) *reinterpret_cast<uint4 *>(tab_s + r * kStride + ch * 8) = v;   // rows past P are zero
-        const half2_t *h = reinterpret_cast<const half2_t *>(&v);
-        float acc = 0.f;
+    for (int i0 = tid; i0 < total; i0 += kAhead * nthr) {
+        uint4 v[kAhead];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * nthr, r = i / kLanes, ch = i % kLanes;
+            v[u] = make_uint4(0u, 0u, 0u, 0u);
+            if (r < P && (kPieces == kLanes || ch < kPieces)) v[u] = *reinterpret_cast<const uint4 *>(Mg + (int64_t)r * D + ch * 8);
+        }
 #pragma unroll
-        for (int off = 1; off < kLanes; off <<= 1) acc += __shfl_xor(acc, off);
-        if (ch == 0) nh_s[r] = r < P ? -0.5f * acc : -INFINITY;   // rows past the table never win
-        mx = fmaxf(mx, acc);
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * nthr, r = i / kLanes, ch = i % kLanes;
+            if (i >= total) break;
+            if (kPieces == kLanes || ch < kPieces) *reinterpret_cast<uint4 *>(tab_s + r * kStride + ch * 8) = v[u];   // rows past P are zero
+            const half2_t *h = reinterpret_cast<const half2_t *>(&v[u]);
+            float acc = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_fdot2(h[k], h[k], acc, false);
+            acc = row_sum(acc);
+            if (kLanes == 32) acc = op_rows(swap16(bits_of(acc), bits_of(acc)), AddF());
+            if (ch == 0) nh_s[r] = r < P ? -0.5f * acc : -INFINITY;   // rows past the table never win
+            mx = fmaxf(mx, acc);
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
@@ -243,15 +253,24 @@ __device__ __forceinline__ void exact_argmin_wave(const __half *xrow_s, const Pa
             bi = p;
         }
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float od = __shfl_xor(bd, off);
-        const int oi = __shfl_xor(bi, off);
-        if (od < bd || (od == bd && oi < bi)) {
+    auto nearer = [&](uint32_t d, uint32_t i) {
+        const float od = __uint_as_float(d);
+        if (od < bd || (od == bd && (int)i < bi)) {
             bd = od;
-            bi = oi;
+            bi = (int)i;
         }
-    }
+    };
+    // lanes n ^ 1 and n ^ 2, mirrored half rows and rows (as in row_sum), then the four rows
+    nearer(dpp<0xb1>(bits_of(bd)), dpp<0xb1>((uint32_t)bi));
+    nearer(dpp<0x4e>(bits_of(bd)), dpp<0x4e>((uint32_t)bi));
+    nearer(dpp<0x141>(bits_of(bd)), dpp<0x141>((uint32_t)bi));
+    nearer(dpp<0x140>(bits_of(bd)), dpp<0x140>((uint32_t)bi));
+    rows2 od = swap16(bits_of(bd), bits_of(bd)), oi = swap16((uint32_t)bi, (uint32_t)bi);
+    nearer(od[0], oi[0]);
+    nearer(od[1], oi[1]);
+    od = swap32(bits_of(bd), bits_of(bd)), oi = swap32((uint32_t)bi, (uint32_t)bi);
+    nearer(od[0], oi[0]);
+    nearer(od[1], oi[1]);
     best_i = bi;
     best_d = bd;
 }

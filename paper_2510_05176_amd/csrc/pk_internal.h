@@ -217,6 +217,8 @@ struct MineArgs {
     int32_t n_sets, T, P, iters, init_given;
     int32_t d;             // head dimension
     __half *patterns;
+    const __half *table;   // the table that a step starts from: patterns, or (first step) the first vectors of the sets
+    int64_t table_stride;  // elements between the tables of two sets
     int32_t *assign;       // [n_sets][T] caller's, or null
     float *best;           // [n_sets][T] workspace (written when inertia is asked for)
     float *psum;           // [n_sets][tsplit][P][d]

@@ -47,6 +47,21 @@ __device__ __forceinline__ float op_rows(rows2 v, OP op)
     return op(__builtin_bit_cast(float, first), __builtin_bit_cast(float, second));
 }
 
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x)   // the value of another lane of the row (data-parallel-primitive control word)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+// Sum over the 16 lanes of a row, in every lane: lanes n ^ 1, n ^ 2, then half rows and rows mirrored, which are n ^ 4 and n ^ 8 by then
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += __builtin_bit_cast(float, dpp<0xb1>(bits_of(v)));
+    v += __builtin_bit_cast(float, dpp<0x4e>(bits_of(v)));
+    v += __builtin_bit_cast(float, dpp<0x141>(bits_of(v)));
+    v += __builtin_bit_cast(float, dpp<0x140>(bits_of(v)));
+    return v;
+}
+
 // Reduction of N values (1, 2 or 4) over the four rows: row kb gets the total of value kb % N.  Rows are combined as neighbours first.
 template <int N, class OP>
 __device__ __forceinline__ float fold_rows(const float (&x)[N], OP op)

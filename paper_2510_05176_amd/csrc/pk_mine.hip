@@ -4,6 +4,8 @@
 // One iteration = mine_step_kernel (assignment step and per-chunk cluster sums, both on the matrix
 // cores) followed by mine_update_kernel (fixed-order reduction over the chunks, mean, fp16 rounding).
 // Every sum is formed in a fixed order, so results are reproducible bit for bit.
+#include <type_traits>
+
 #include "pk_assign_mfma.h"
 #include "pk_internal.h"
 
@@ -11,7 +13,7 @@ namespace pk {
 
 namespace {
 
-// patterns[s][p] <- x[s][p], p < P  (initialisation from the first P vectors)
+// patterns[s][p] <- x[s][p], p < P  (initialisation from the first P vectors, where no step follows: a first step reads them itself)
 __global__ __launch_bounds__(256) void mine_init_kernel(MineArgs a)
 {
     const int s = blockIdx.y;
@@ -80,7 +82,7 @@ typedef _Float16 half2m __attribute__((ext_vector_type(2)));
 typedef short short4m __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4m *lds_short4_ptr;
 
-constexpr bool step_sorts(int D, int NPT) { return NPT == 16 || (NPT == 8 && D <= 128); }
+constexpr bool step_sorts(int D, int NPT, int NW) { return NW <= 8 && (NPT == 16 || (NPT == 8 && D <= 128)); }
 
 template <int D, int NPT, int NW, int NT, int XC>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && NPT <= 4 && D <= 128 ? 4 : 2))) void mine_step_kernel(MineArgs a, int chunk, int outputs)
@@ -96,9 +98,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     constexpr int ST = 16 * NT * NW;     // vectors per sub-tile: NT 16-vector tiles per wave
     __half *idx_s = xs + ST * kXs;       // pattern index of every row of the sub-tile, as an fp16 number
     __shared__ float red_s[NW];
-    constexpr bool kSort = step_sorts(D, NPT);
+    constexpr bool kSort = step_sorts(D, NPT, NW);
     constexpr int kStepUnroll = kSort ? 1 : ST / 32;
-    __shared__ int bucket_s[NW * NW];   // [bucket][wave]: vectors of the wave's in the bucket (the pattern rows that one wave sums)
+    __shared__ int bucket_s[kSort ? NW * NW : 1];   // [bucket][wave]: vectors of the wave's in the bucket (the pattern rows that one wave sums)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 15, kb = lane >> 4;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     const int ck = blockIdx.x, s = blockIdx.y;
     const int t_begin = ck * chunk, n_tok = min(chunk, a.T - t_begin);
     const __half *xg = a.x + (int64_t)s * a.set_stride + (int64_t)t_begin * D;
-    const __half *Mg = a.patterns + (int64_t)s * P * D;
+    const __half *Mg = a.table + (int64_t)s * a.table_stride;
 
     auto load_tile = [&](int sub, uint4 (&xb)[NT][KS]) {
 #pragma unroll
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
             for (int k = 0; k < KS; ++k) xb[j][k] = *reinterpret_cast<const uint4 *>(xg + (int64_t)tok * D + 32 * k + 8 * kb);
         }
     };
-    constexpr bool kAhead = kSort && D <= 128;   // a vector buffer more: loads are in flight for a whole sub-tile
+    constexpr bool kAhead = kSort && D <= 128 && NT > 1;   // a vector buffer more: loads are in flight for a whole sub-tile
     uint4 xb[NT][KS], xn[NT][KS];
     load_tile(0, kAhead ? xn : xb);
 
@@ -311,29 +313,36 @@ __global__ __launch_bounds__(D) void mine_update_kernel(MineArgs a)   // thread 
 {
     const int p = blockIdx.x, s = blockIdx.y, c = threadIdx.x;
     const int64_t o0 = (int64_t)s * a.tsplit * a.P + p, step = a.P;
-    // chunks in increasing order, eight loads in flight at a time; the order of the additions is fixed
+    // chunks in increasing order, up to 32 loads in flight at a time; the order of the additions is fixed
     float sum = 0.f;
-    int cnt = 0;
-    int ts = 0;
-    for (; ts + 8 <= a.tsplit; ts += 8) {
-        float v[8];
-        int k[8];
+    int cnt = 0, ts = 0;
+    auto take = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        float v[N];
+        int k[N];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < N; ++u) {
             v[u] = a.psum[(o0 + (ts + u) * step) * D + c];
             k[u] = a.pcnt[o0 + (ts + u) * step];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < N; ++u) {
             sum += v[u];
             cnt += k[u];
         }
-    }
-    for (; ts < a.tsplit; ++ts) {
-        sum += a.psum[(o0 + ts * step) * D + c];
-        cnt += a.pcnt[o0 + ts * step];
-    }
-    if (cnt > 0) a.patterns[((int64_t)s * a.P + p) * D + c] = __float2half_rn(sum / (float)cnt);
+        ts += N;
+    };
+    while (ts + 32 <= a.tsplit) take(std::integral_constant<int, 32>());
+    if (ts + 16 <= a.tsplit) take(std::integral_constant<int, 16>());
+    if (ts + 8 <= a.tsplit) take(std::integral_constant<int, 8>());
+    if (ts + 4 <= a.tsplit) take(std::integral_constant<int, 4>());
+    if (ts + 2 <= a.tsplit) take(std::integral_constant<int, 2>());
+    if (ts < a.tsplit) take(std::integral_constant<int, 1>());
+    __half *out = a.patterns + ((int64_t)s * a.P + p) * D + c;
+    if (cnt > 0)
+        *out = __float2half_rn(sum / (float)cnt);
+    else if (a.table != a.patterns)   // (the first step, whose table is not the caller's)
+        *out = a.table[(int64_t)s * a.table_stride + p * D + c];
 }
 
 // inertia of one assignment step: fixed-order sum of the best distances
@@ -382,10 +391,11 @@ __global__ __launch_bounds__(256) void window_pattern_kernel(const __half *x, in
 
 // Instantiation for a head dimension and number of patterns: 16 * npt >= P table rows, nw waves, nt 16-vector tiles per wave
 // and pass over the table, xc channels of the vectors in LDS at a time.
+// wide: eight waves per workgroup where four would leave the chip's wave slots empty (few_chunks below).
 struct StepShape {
     int npt, nw, nt, xc;
 };
-constexpr StepShape step_shape(int D, int P)
+constexpr StepShape step_shape(int D, int P, bool wide = false)
 {
     // 8 waves share the table when only one workgroup fits a CU (P > 128, or P > 64 at 256 channels, whose table rows and
     // accumulators are twice as large; at 128 patterns of 128 channels two 4-wave workgroups measured faster than one
@@ -395,6 +405,7 @@ constexpr StepShape step_shape(int D, int P)
     const int npt = P <= 16 ? 1 : P <= 32 ? 2 : P <= 64 ? 4 : P <= 128 ? 8 : 16;
     const int nw = npt == 16 || (D == 256 && npt == 8) ? 8 : 4;
     const int nt = npt >= 8 && D != 256 ? 2 : 1;
+    if (wide) return {npt, 8, 1, D};
     return {npt, nw, nt, D == 256 && npt == 16 ? 64 : D};
 }
 
@@ -438,10 +449,10 @@ int mine_tsplit(int T, int n_sets, int P)
 }
 
 // All iterations for 16 * NPT patterns or fewer at head dimension D
-template <int D, int NPT>
+template <int D, int NPT, bool WIDE>
 static hipError_t launch_iterations(const MineArgs &a_in, hipStream_t s)
 {
-    constexpr StepShape h = step_shape(D, 16 * NPT);
+    constexpr StepShape h = step_shape(D, 16 * NPT, WIDE);
     constexpr auto step = mine_step_kernel<D, NPT, h.nw, h.nt, h.xc>;
     static LdsOptIn opt_in;   // the most this instantiation needs: a table of 16 * NPT patterns
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(step), opt_in, step_lds_bytes(D, 16 * NPT, h));
@@ -450,11 +461,14 @@ static hipError_t launch_iterations(const MineArgs &a_in, hipStream_t s)
     a.tsplit = chunks_of(a.T, a.n_sets, a.P, D);
     const int chunk = mine_chunk(a.T, a.n_sets, a.P, D);
     const size_t lds = step_lds_bytes(D, a.P, h);
-    if (!a.init_given) {
+    if (!a.init_given && a.iters < 1) {
         hipLaunchKernelGGL(mine_init_kernel, dim3((a.P * D / 8 + 255) / 256, a.n_sets), dim3(256), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return hipGetLastError();
     }
     for (int it = 0; it < a.iters; ++it) {
+        const bool from_vectors = it == 0 && !a.init_given;
+        a.table = from_vectors ? a.x : a.patterns;
+        a.table_stride = from_vectors ? a.set_stride : (int64_t)a.P * D;
         const int outputs = (a.assign && it == a.iters - 1 ? 1 : 0) | (a.inertia ? 2 : 0);
         hipLaunchKernelGGL(step, dim3(a.tsplit, a.n_sets), dim3(64 * h.nw), lds, s, a, chunk, outputs);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -468,15 +482,37 @@ static hipError_t launch_iterations(const MineArgs &a_in, hipStream_t s)
     return hipSuccess;
 }
 
+// Whether the workgroups of a step are so few that eight waves in each still have slots side by side: up to 64 patterns two such groups
+// per CU (one at 256 channels, whose vector tile takes the LDS), up to 128 patterns one.  A step then walks half as many
+// sub-tiles, one after the other, as with four waves; 10 iterations, four and eight waves: 8 sets x 1024 vectors at 64 patterns 134 and 111 us,
+// 8 x 8192 185 and 164, 4 x 32768 258 and 215, 16 x 8192 225 and 220; 8 x 8192 at 128 patterns 242 and 233, of 96 channels at 64 164 and
+// 147, of 256 channels 259 and 235.  Not with more groups (32 x 8192 315 and 344; at 128 patterns 16 x 8192 312 and 365), and not beyond
+// 128 patterns, where eight waves are the rule and two tiles per table pass worth more.  (Sixteen waves: 168 us for 8 x 8192, 265 for 16 x 8192.)
+template <int D, int NPT>
+static bool few_chunks(const MineArgs &a)
+{
+    const int64_t groups = (int64_t)a.n_sets * chunks_of(a.T, a.n_sets, a.P, D);
+    return groups <= (NPT <= 4 && D <= 128 ? 512 : 256);
+}
+
+template <int D, int NPT>
+static hipError_t launch_size(const MineArgs &a, hipStream_t s)
+{
+    if constexpr (NPT <= 4 || (NPT == 8 && D <= 128)) {
+        if (few_chunks<D, NPT>(a)) return launch_iterations<D, NPT, true>(a, s);
+    }
+    return launch_iterations<D, NPT, false>(a, s);
+}
+
 template <int D>
 static hipError_t launch_mine_of(const MineArgs &a, hipStream_t s)
 {
     switch (step_shape(D, a.P).npt) {
-    case 1: return launch_iterations<D, 1>(a, s);
-    case 2: return launch_iterations<D, 2>(a, s);
-    case 4: return launch_iterations<D, 4>(a, s);
-    case 8: return launch_iterations<D, 8>(a, s);
-    default: return launch_iterations<D, 16>(a, s);
+    case 1: return launch_size<D, 1>(a, s);
+    case 2: return launch_size<D, 2>(a, s);
+    case 4: return launch_size<D, 4>(a, s);
+    case 8: return launch_size<D, 8>(a, s);
+    default: return launch_size<D, 16>(a, s);
     }
 }
 

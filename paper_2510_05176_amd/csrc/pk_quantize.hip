@@ -883,11 +883,6 @@ __device__ __forceinline__ TransposeConst transpose_const(int n)
     }
     return c;
 }
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t x)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
-}
 __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst &c)
 {
 #pragma unroll
