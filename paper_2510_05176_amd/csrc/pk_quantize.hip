@@ -853,14 +853,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
 // ---- V ------------------------------------------------------------------------------------------------------------
 // Per-wave output staging: the pieces a wave produces for its 16 tokens are put together in LDS so that
 // every global store is one contiguous run of 8- or 16-byte lane pieces.
-template <int D>
+template <int D, int BITS, int NG>
 struct VStaging {
-    static constexpr int kRow = 0;                     // D halves: one vector for the exact re-evaluation
-    static constexpr int kCodes = 2 * D;               // up to 8 D bytes: the unit's code words in memory order (4 bits)
-    static constexpr int kIdx = kCodes + 8 * D;        // 16 B: pattern indices
-    static constexpr int kScale = kIdx + 16;           // up to D B: scales [group][16]
-    static constexpr int kZero = kScale + D;           // up to D B: zero points [group][16]
-    static constexpr int kBytes = kZero + D;
+    static constexpr int kCodes = 0;                   // the unit's code words in memory order; D halves: one vector for the exact re-evaluation
+    static constexpr int kIdx = 2 * D * BITS;          // 16 B: pattern indices
+    static constexpr int kScale = kIdx + 16;           // scales [group][16]
+    static constexpr int kZero = kScale + 32 * NG;     // zero points [group][16]
+    static constexpr int kBytes = kZero + 32 * NG;
 };
 
 // 16x16 bit transpose across the 16 lanes of a row, on both 16-bit halves of x at once:
@@ -902,7 +901,7 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
 template <int D, int BITS, int NG, int NT>
 __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
 {
-    using St = VStaging<D>;
+    using St = VStaging<D, BITS, NG>;
     constexpr int TT = 64, WPU = BITS / 2, KS = D / 32, BPG = KS / NG;   // BPG = 32-channel blocks per group
     static_assert(KS % NG == 0, "groups of whole 32-channel blocks");
     constexpr int GL = (NG + 3) / 4;   // groups whose parameters a lane works out
@@ -956,10 +955,16 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
             float bv[NT], x2[NT];
             bool flag[NT];
             assign_tiles_mfma<NT, KS>(xbs, tb, lane, bis, bv, x2, flag);
+            bool any = flag[0];
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                float bd;
-                resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + St::kRow), tb, lane, 0, bis[j], bd);
+            for (int j = 1; j < NT; ++j) any = any || flag[j];
+            if (__ballot(any) != 0ull) {
+                store_pending();   // the vector under re-evaluation takes the codes' place
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    float bd;
+                    resolve_flagged(xbs[j], flag[j], reinterpret_cast<__half *>(wsc + St::kCodes), tb, lane, 0, bis[j], bd);
+                }
             }
         }
 #pragma unroll
@@ -1258,7 +1263,7 @@ hipError_t launch_quantize_k(const QuantArgs &a_in, hipStream_t s)
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
 {
-    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)VStaging<D>::kBytes, mx = table_lds_bytes<D>(256) + 4 * (size_t)VStaging<D>::kBytes;
+    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)VStaging<D, BITS, NG>::kBytes, mx = table_lds_bytes<D>(256) + 4 * (size_t)VStaging<D, BITS, NG>::kBytes;
     const int round = one_round(a, 64, 512);
     if constexpr (D != 256) {   // two blocks per table pass (three waves per SIMD instead of four) pay from 128 patterns on
         if (a.P >= 128) return launch_tiled<quantize_v_kernel<D, BITS, NG, 2>>(a, 64, lds, mx, s, round);
