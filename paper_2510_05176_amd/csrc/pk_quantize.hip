@@ -731,8 +731,8 @@ __global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D
 template <int D>
 constexpr int kWkWave = kWkTile + kKParams<D>;   // bytes of LDS per wave
 
-template <int D, int G, int BITS, int NTA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || (D == 256 && G == 64) ? 2 : 3))) void quantize_k_wave_kernel(QuantArgs a, int tiles_per_wg)
+template <int D, int G, int BITS, int NTA, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 256 && G == 64 ? 2 : 3))) void quantize_k_wave_kernel(QuantArgs a, int tiles_per_wg)
 {
     constexpr int NTG = G / 16, KS = D / 32;
     static_assert(G == 32 || G == 64, "a wave holds the group's tiles in registers");
@@ -759,10 +759,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
 #pragma unroll
         for (int j = 0; j < NTG; ++j) load_tile(a, ns, g * G + j * 16, xb[j]);   // in flight while the table is staged
     }
-    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red);
-    const PatternTable tb = make_table<4>(sh, a.P);
+    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red, 64 * NW);
+    const PatternTable tb = make_table<NW>(sh, a.P);
 
-    for (; g < g_end; g += 4) {
+    for (; g < g_end; g += NW) {
         const int64_t tq0 = (int64_t)a.t0 + (int64_t)g * G;   // logical position of the group's first token
         const int64_t pq0 = map.pos((int)tq0);            // where it is stored
         // ---- pass A: indices; running minimum / maximum per channel
@@ -830,7 +830,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
             if constexpr (KS <= 4) {
                 float r[8 * KS];
                 residuals(sh, xb[j], bi[j], r);
-                if (g + 4 < g_end) load_tile(a, ns, (g + 4) * G + j * 16, xb[j]);
+                if (g + NW < g_end) load_tile(a, ns, (g + NW) * G + j * 16, xb[j]);
 #pragma unroll
                 for (int k = 0; k < KS; ++k) k_codes8<D, BITS>(r + 8 * k, k, pz, pinv, stg);
             } else {
@@ -840,7 +840,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTA > 2 || 
                     residuals8(xb[j][k], *reinterpret_cast<const uint4 *>(sh.tab + bi[j] * kTabStrideOf<D> + 8 * kb + 32 * k), r);
                     k_codes8<D, BITS>(r, k, pz, pinv, stg);
                 }
-                if (g + 4 < g_end) load_tile(a, ns, (g + 4) * G + j * 16, xb[j]);
+                if (g + NW < g_end) load_tile(a, ns, (g + NW) * G + j * 16, xb[j]);
             }
             if (kb == 0) stg[16 * D * BITS / 8 + n] = (uint8_t)bi[j];
             wave_lds_sync();
@@ -898,8 +898,8 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
 // block.  NG = channel groups per token (D / Gc).  NT = blocks taken together: the wave assigns its units of
 // NT consecutive blocks in one pass over the pattern table (every table tile read from LDS serves all of
 // them), then quantizes them one after the other.
-template <int D, int BITS, int NG, int NT>
-__global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
+template <int D, int BITS, int NG, int NT, int NW>
+__global__ __launch_bounds__(64 * NW) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
 {
     using St = VStaging<D, BITS, NG>;
     constexpr int TT = 64, WPU = BITS / 2, KS = D / 32, BPG = KS / NG;   // BPG = 32-channel blocks per group
@@ -916,13 +916,15 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
     const int n_tiles = a.nq / TT;
     const int tile0 = chunk_of_workgroup() * tiles_per_wg, tile1 = min(n_tiles, tile0 + tiles_per_wg);
     if (tile0 >= n_tiles) return;   // a ragged append: this sequence has fewer tiles than the launch was sized for
+    const int unit = wave % 4 * 16, first = tile0 + wave / 4 * NT;   // the wave's unit of its blocks, its first block
+    constexpr int kRound = NW / 4 * NT;                              // blocks that the workgroup takes at a time
     uint4 xbs[NT][KS];
 #pragma unroll
     for (int j = 0; j < NT; ++j)   // a block past the workgroup's range repeats the last one; its result is not used
-        load_tile(a, ns, min(tile0 + j, tile1 - 1) * TT + wave * 16, xbs[j]);
+        load_tile(a, ns, min(first + j, tile1 - 1) * TT + unit, xbs[j]);
 
-    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red);
-    const PatternTable tb = make_table<4>(sh, a.P);
+    stage_patterns<D>(Mg, a.P, sh.tab, sh.nh, sh.red, 64 * NW);
+    const PatternTable tb = make_table<NW>(sh, a.P);
     const TransposeConst tc = transpose_const(n);
     unsigned char *wsc = smem + table_lds_bytes<D>(a.P) + wave * St::kBytes;
 
@@ -945,12 +947,12 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
         pend_tok0 = -1;
     };
 
-    for (int tile_base = tile0; tile_base < tile1; tile_base += NT) {
+    for (int tile_base = first; tile_base < tile1; tile_base += kRound) {
         int bis[NT];
         if (a.idx_given) {   // searched beforehand (min-max metric); a block past the range repeats the last one
 #pragma unroll
             for (int j = 0; j < NT; ++j)
-                bis[j] = a.idx[map.pos(a.t0 + min(tile_base + j, tile1 - 1) * TT) + wave * 16 + n];
+                bis[j] = a.idx[map.pos(a.t0 + min(tile_base + j, tile1 - 1) * TT) + unit + n];
         } else {
             float bv[NT], x2[NT];
             bool flag[NT];
@@ -1015,7 +1017,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
                 }
             }
         }
-        if (tile + NT < tile1) load_tile(a, ns, (tile + NT) * TT + wave * 16, xb);   // else the registers keep this block
+        if (tile + kRound < tile1) load_tile(a, ns, (tile + kRound) * TT + unit, xb);   // else the registers keep this block
 
         // minimum / maximum per channel group: lane-local over its channels here, then over the 4 lanes of the token
         float mn[NG], mx[NG];
@@ -1092,7 +1094,7 @@ __global__ __launch_bounds__(256) void quantize_v_kernel(QuantArgs a, int tiles_
             }
         }
         wave_lds_sync();
-        pend_tok0 = map.pos(a.t0 + tile * TT) + wave * 16;   // stored at the start of the next unit
+        pend_tok0 = map.pos(a.t0 + tile * TT) + unit;   // stored at the start of the next unit
       }
     }
     store_pending();
@@ -1159,13 +1161,14 @@ static int tiles_per_wg(int n_tiles, int n_streams)
 }
 
 template <auto KERNEL, int THREADS = 256>
-static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t max_lds, hipStream_t s, int min_tiles = 1)
+static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t max_lds, hipStream_t s, int min_tiles = 1, int multiple = 1)
 {
     static LdsOptIn opt_in;   // per kernel instantiation; max_lds: what it needs with a table of 256 patterns
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(KERNEL), opt_in, max_lds);
     if (e != hipSuccess) return e;
     int tpw = tiles_per_wg(a.nq / TT, a.n_streams);
     if (tpw < min_tiles) tpw = min_tiles;
+    tpw = (tpw + multiple - 1) / multiple * multiple;   // (whole rounds of the workgroup's waves)
     const int n_tiles = a.nq / TT;
     hipLaunchKernelGGL(KERNEL, dim3((n_tiles + tpw - 1) / tpw, a.n_streams), dim3(THREADS), lds, s, a, tpw);
     return hipGetLastError();
@@ -1194,26 +1197,37 @@ static hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
 static int one_round(const QuantArgs &a, int TT, int resident)
 {
     const int64_t tiles = (int64_t)(a.nq / TT) * a.n_streams;
-    return a.P * a.d > 128 * kD && tiles <= (int64_t)resident * 64 ? (int)((tiles + resident - 1) / resident) : 1;
+    return a.P * a.d > 128 * kD && tiles <= (int64_t)resident * 256 ? (int)((tiles + resident - 1) / resident) : 1;
 }
 
+template <int D, int G, int BITS, int NTA, int NW>
+static hipError_t launch_k_waves(const QuantArgs &a, hipStream_t s)
+{
+    const size_t lds = table_lds_bytes<D>(a.P) + NW * (size_t)kWkWave<D>, mx = table_lds_bytes<D>(D == 256 && NW > 4 ? 128 : 256) + NW * (size_t)kWkWave<D>;
+    constexpr int kMin = NW * G / 64;   // a wave owns whole groups: at least one group per wave
+    const int round = one_round(a, 64, 256);
+    return launch_tiled<quantize_k_wave_kernel<D, G, BITS, NTA, NW>, 64 * NW>(a, 64, lds, mx, s, round > kMin ? round : kMin, kMin);
+}
+
+// Waves per workgroup: as many as registers allow per CU (three per SIMD, two for 64-token groups of 256 channels) once the table
+// leaves room for one workgroup only (beyond 128 patterns; 64 of 256 channels, whose table beyond 128 leaves room for four waves).
+// Four waves there were one per SIMD: 256 streams x 8192 vectors at 256 patterns 489 -> 300 us (eight waves 318), at 160 301 -> 262 (282), in
+// 32-token groups 328 -> 280 (310); 96 channels, 256 x 4096 at 200 patterns 146 -> 104 (120); 256 channels, 128 x 4096 at 128
+// patterns 196 -> 140, in 32-token groups 201 -> 128.  A job of at most four groups per CU takes four waves, each a group (64
+// groups of 8 x 1024 vectors, 256 patterns: 21 us, in six workgroups of twelve waves 26).
 template <int D, int G, int BITS>
 static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
 {
-    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)kWkWave<D>, mx = table_lds_bytes<D>(256) + 4 * (size_t)kWkWave<D>;
-    constexpr int kMin = G / 16;   // a wave owns whole groups: at least four groups per workgroup
+    const bool few = (int64_t)(a.nq / G) * a.n_streams <= 1024;
     if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
-        const int round = one_round(a, 64, 256);
-        return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
-    } else if constexpr (G == 64) {   // pairs keep three waves per SIMD; the whole group takes two, which pays above 128 patterns
-        if (a.P > 32) {
-            const int round = one_round(a, 64, 256);
-            return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 4>>(a, 64, lds, mx, s, round > kMin ? round : kMin);
-        }
-        return launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, kMin);
+        if (a.P > 64 && a.P <= 128 && !few) return launch_k_waves<D, G, BITS, 2, 8>(a, s);
+        return launch_k_waves<D, G, BITS, 2, 4>(a, s);
+    } else if constexpr (G == 64) {   // the whole group per table pass; pairs up to 32 patterns
+        if (a.P > 128 && !few) return launch_k_waves<D, G, BITS, 4, 12>(a, s);
+        return a.P > 32 ? launch_k_waves<D, G, BITS, 4, 4>(a, s) : launch_k_waves<D, G, BITS, 2, 4>(a, s);
     } else {                          // 32-token groups gain from pairs only once the table is large
-        return a.P >= 128 ? launch_tiled<quantize_k_wave_kernel<D, G, BITS, 2>>(a, 64, lds, mx, s, kMin)
-                          : launch_tiled<quantize_k_wave_kernel<D, G, BITS, 1>>(a, 64, lds, mx, s, kMin);
+        if (a.P > 128 && !few) return launch_k_waves<D, G, BITS, 2, 12>(a, s);
+        return a.P >= 128 ? launch_k_waves<D, G, BITS, 2, 4>(a, s) : launch_k_waves<D, G, BITS, 1, 4>(a, s);
     }
 }
 
@@ -1226,7 +1240,12 @@ static hipError_t launch_k_bits(const QuantArgs &a, hipStream_t s)
     }
     const size_t lds = table_lds_bytes<D>(a.P), mx = table_lds_bytes<D>(256);
     const int round = one_round(a, 128, 256);
-    if constexpr (D != 256) {
+    if constexpr (D == 256) {
+        if (a.P > 64 && a.P <= 128) {
+            constexpr size_t two = 2 * (size_t)kGroupLds<D, 1>;
+            return launch_tiled<quantize_k_group_kernel<D, BITS, 2, 1>, 1024>(a, 128, lds + two, table_lds_bytes<D>(128) + two, s, round);
+        }
+    } else {
         if (a.P > 128) {
             constexpr size_t four = 4 * (size_t)kGroupLds<D, 2>, two = 2 * (size_t)kGroupLds<D, 1>;
             if (round >= 4 || tiles_per_wg(a.nq / 128, a.n_streams) >= 4)
@@ -1260,15 +1279,25 @@ hipError_t launch_quantize_k(const QuantArgs &a_in, hipStream_t s)
     return a.d == kD ? launch_k_of<kD>(a, s) : a.d == 96 ? launch_k_of<96>(a, s) : launch_k_of<256>(a, s);
 }
 
+template <int D, int BITS, int NG, int NT, int NW>
+static hipError_t launch_v_waves(const QuantArgs &a, hipStream_t s)
+{
+    constexpr size_t kWaves = NW * (size_t)VStaging<D, BITS, NG>::kBytes;
+    return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, table_lds_bytes<D>(a.P) + kWaves, table_lds_bytes<D>(256) + kWaves, s,
+                                                                       one_round(a, 64, D == 256 ? 256 : 512), NW / 4 * NT);
+}
+
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
 {
-    const size_t lds = table_lds_bytes<D>(a.P) + 4 * (size_t)VStaging<D, BITS, NG>::kBytes, mx = table_lds_bytes<D>(256) + 4 * (size_t)VStaging<D, BITS, NG>::kBytes;
-    const int round = one_round(a, 64, 512);
-    if constexpr (D != 256) {   // two blocks per table pass (three waves per SIMD instead of four) pay from 128 patterns on
-        if (a.P >= 128) return launch_tiled<quantize_v_kernel<D, BITS, NG, 2>>(a, 64, lds, mx, s, round);
+    if constexpr (D != 256) {   // two blocks per table pass pay from 128 patterns on
+        if (a.P > 128) return launch_v_waves<D, BITS, NG, 2, 8>(a, s);
+        if (a.P == 128) return launch_v_waves<D, BITS, NG, 2, 4>(a, s);
+    } else {
+        if (a.P > 128) return launch_v_waves<D, BITS, NG, 1, 8>(a, s);
+        if (a.P > 64) return launch_v_waves<D, BITS, NG, 1, 12>(a, s);
     }
-    return launch_tiled<quantize_v_kernel<D, BITS, NG, 1>>(a, 64, lds, mx, s, round);
+    return launch_v_waves<D, BITS, NG, 1, 4>(a, s);
 }
 
 template <int D, int BITS>
