@@ -34,6 +34,7 @@
 #include "pk_internal.h"
 #include "pk_decode_fields.h"
 #include "pk_decode_tail.h"
+#include "pk_lanes.h"
 
 namespace pk {
 
@@ -41,13 +42,31 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// Two bit planes of 32 channels -> sixteen operand registers, register V with channels 2V (low half) and 2V + 1: the pairs in which
+// scales and queries lie in memory.  (Even channels in one half of the registers and odd ones in the other take two byte permutes
+// less here, and sixteen more per K group to pair its scales in that way.)
+__device__ __forceinline__ void planes_to_operand(uint32_t p0, uint32_t p1, uint32_t *out)
+{
+    const uint32_t even = bfi(0x55555555u, p0, p1 << 1), odd = bfi(0x55555555u, p0 >> 1, p1);   // 2-bit fields of the even and odd channels
+    fields_to_operand(__builtin_amdgcn_perm(odd, even, 0x05040100u), out);
+    fields_to_operand(__builtin_amdgcn_perm(odd, even, 0x07060302u), out + 8);
+}
+
 struct GroupOperand {
-    uint32_t Bq[16];   // q[h][c] * s[g][c] * 2^(8-pos) rounded to fp16, operand order
+    uint32_t Bq[16];   // q[h][c] * s[g][c] * 2^(8-pos) rounded to fp16, channels 2V and 2V + 1 in register V
     uint32_t Bl[16];   // what that rounding dropped (the product of two fp16 numbers has 22 significant bits), as fp16;
                        // formed and used only for groups whose scales are large enough for it to matter (lo_on)
     float qz;          // scale * log2(e) * q_h . z[g]
     bool lo_on;        // wave-uniform
 };
+
+// total over the four rows of a column
+template <class OP>
+__device__ __forceinline__ float over_rows(float v, OP op)
+{
+    const float one[1] = {v};
+    return fold_rows<1>(one, op);
+}
 
 // sum over the 64 lanes (row shifts, then the two row broadcasts of the wave), returned wave-uniform
 __device__ __forceinline__ float wave_sum(float v)
@@ -184,8 +203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         float qmax = 0.f;
 #pragma unroll
         for (int i = 0; i < 32; ++i) qmax = fmaxf(qmax, fabsf((float)qh[i]));
-        qmax = fmaxf(qmax, __shfl_xor(qmax, 16));
-        qmax = fmaxf(qmax, __shfl_xor(qmax, 32));
+        qmax = over_rows(qmax, MaxF());
         if (qmax > 0.f) {
             int e;
             (void)frexpf(qmax, &e);          // qmax = m * 2^e, m in [0.5, 1)
@@ -203,67 +221,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         float qq = 0.f;
 #pragma unroll
         for (int i = 0; i < 32; ++i) qq = fmaf((float)qh[i], (float)qh[i], qq);
-        qq += __shfl_xor(qq, 16);
-        qq += __shfl_xor(qq, 32);                                     // |lam q|^2 of the column's head
+        qq = over_rows(qq, AddF());                                   // |lam q|^2 of the column's head
         const float per_head = a.softmax_scale * a.softmax_scale / (lam * lam) * qq * (1.f / kD);
         float worst = per_head;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) worst = fmaxf(worst, __shfl_xor(worst, off));
+        worst = row_max(worst);
         worst = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, worst)));
         lo_threshold = worst > 0.f ? 2.04f / worst : INFINITY;       // (6e-4 / 4.2e-4)^2
     }
-    uint32_t qn[16], qp[16];   // natural channel order; operand order with the field scale folded in
+    uint32_t qn[16], qp[16];   // channel pairs; the same with the field scale of the operand register folded in
 #pragma unroll
     for (int i = 0; i < 16; ++i) qn[i] = pack2(qh[2 * i], qh[2 * i + 1]);
 #pragma unroll
     for (int V = 0; V < 16; ++V) {
-        const int v = V & 7, odd = V >> 3;
-        const _Float16 c = (_Float16)(float)(1 << (8 - fpos(v)));
-        qp[V] = pack2(qh[e_lo(v) + odd] * c, qh[e_lo(v) + 16 + odd] * c);
+        const _Float16 c = (_Float16)(float)(1 << (8 - fpos(V & 7)));
+        qp[V] = pack2(qh[2 * V] * c, qh[2 * V + 1] * c);
     }
-
-    // ---- QM[p][n] = scale*log2e * q_h . M_K[p], one 16-pattern tile per wave and round
-    for (int tp = wave; tp * 16 < P; tp += 4) {
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        const int p = tp * 16 + n;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            uint4 av = make_uint4(0, 0, 0, 0);
-            if (p < P) av = *reinterpret_cast<const uint4 *>(MK + (int64_t)p * kD + 32 * kb + 8 * s);
-            acc = mfma16(reinterpret_cast<const uint32_t *>(&av), &qn[4 * s], acc);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int pr = tp * 16 + 4 * kb + i;
-            if (pr < P) QMs[pr * 16 + n] = acc[i] * sc2;
-        }
-    }
-    for (int i = lane; i < R * WS; i += 64) Ws[wave * R * WS + i] = 0ull;
-    // With two K groups per block, or the extra operands of 4-bit codes, the registers that q in natural order
-    // would hold for the rest of the kernel are needed elsewhere (the kernel is at its 256-register limit and
-    // spilled): it waits in LDS instead (identical in the four waves; [piece][lane]).
-    constexpr bool Q_LDS = G32 || BITS == 4;
-    __shared__ uint4 qn_s[Q_LDS ? 4 : 1][64];
-    if (Q_LDS && wave == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qn_s[i][lane] = make_uint4(qn[4 * i], qn[4 * i + 1], qn[4 * i + 2], qn[4 * i + 3]);
-    }
-    __syncthreads();
 
     // ---- this wave's run of 64-token blocks
     const int n_blocks = (t_end - t_begin) >> 6;
     const int per = (n_blocks + 3) >> 2;
     const int b0 = wave * per, b1 = min(n_blocks, b0 + per);
-
-    // Online softmax state per column.  Scores are formed relative to m_run (the reference enters the
-    // matrix-core accumulator), so the exponentials need no subtraction; the reference is raised only
-    // when a block exceeds it.
-    float m_run = 0.f, l_run = 0.f, pzacc = 0.f;
-    bool started = false;
-    floatx4 O[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) O[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    GroupOperand ga, gb;   // gb: second K group of a block, only when G == 32
 
     // Base pointers (wave-uniform) such that base + offset(logical token) is the token's place: for contiguous
     // streams the stream's start, fixed; for a paged cache the start of the page part that holds the block,
@@ -313,53 +290,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         }
         if (COMP) gr.own = *reinterpret_cast<const uint32_t *>(kscale + (uint32_t)grp * kD * 2 + lane * 4);
     };
-    auto build_group = [&](const GroupRaw &gr, GroupOperand &go) {
-        _Float16 sh[32];
-        float acc = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const half2v *hv = reinterpret_cast<const half2v *>(&gr.s[i]);
-            const uint32_t *zu = reinterpret_cast<const uint32_t *>(&gr.z[i]);
-            uint4 qv;
-            if (G32 || BITS == 4)
-                qv = qn_s[i][lane];
-            else
-                qv = make_uint4(qn[4 * i], qn[4 * i + 1], qn[4 * i + 2], qn[4 * i + 3]);
-            const uint32_t qw[4] = {qv.x, qv.y, qv.z, qv.w};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                sh[8 * i + 2 * k] = hv[k][0];
-                sh[8 * i + 2 * k + 1] = hv[k][1];
-                acc = dot2(qw[k], zu[k], acc);
-            }
-        }
-#pragma unroll
-        for (int V = 0; V < 16; ++V) {
-            const int v = V & 7, odd = V >> 3;
-            go.Bq[V] = pk_mul(qp[V], pack2(sh[e_lo(v) + odd], sh[e_lo(v) + 16 + odd]));
-        }
-        // The fp16 rounding of q * s (2^-12 relative per channel) leaves a score error of about
-        // softmax_scale * 4.2e-4 * sqrt(sum_c q_c^2 s_c^2); where the group's scales make that matter (large-magnitude
-        // channels: outliers over long groups, a RoPE sub-space), the dropped part of every product is formed too
-        // and contracted in a second pass over the same code operand.  The test uses |q|^2 / d for q_c^2.
-        go.lo_on = false;
-        if (COMP) {
-            const float s2 = wave_sum(dot2(gr.own, gr.own, 0.f));
-            go.lo_on = s2 > lo_threshold;
-            if (go.lo_on) {
-#pragma unroll
-                for (int V = 0; V < 16; ++V) {
-                    const int v = V & 7, odd = V >> 3;
-                    go.Bl[V] = product_error(qp[V], pack2(sh[e_lo(v) + odd], sh[e_lo(v) + 16 + odd]), go.Bq[V]);
-                }
-            }
-        }
-        acc += __shfl_xor(acc, 16);
-        acc += __shfl_xor(acc, 32);
-        go.qz = acc * sc2;
-    };
-
-
     // K-side inputs of a block: plane words of this lane's 4 token rows, pattern indices of the tokens whose scores
     // it keeps (16, or its half of the unit: 8)
     uint32_t kw[4][BITS];
@@ -394,15 +324,95 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         }
     };
 
+    // the first block's inputs, in flight while the table of q . M_K is formed
+    GroupRaw first;
     if (b0 < b1) {
         const int tb = t_begin + (b0 << 6);
         load_k(tb);
-        GroupRaw gr;
-        load_group_raw(tb >> lgG, gr);
-        build_group(gr, ga);
+        load_group_raw(tb >> lgG, first);
+    }
+
+    // ---- QM[p][n] = scale*log2e * q_h . M_K[p], one 16-pattern tile per wave and round
+    for (int tp = wave; tp * 16 < P; tp += 4) {
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int p = tp * 16 + n;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            uint4 av = make_uint4(0, 0, 0, 0);
+            if (p < P) av = *reinterpret_cast<const uint4 *>(MK + (int64_t)p * kD + 32 * kb + 8 * s);
+            acc = mfma16(reinterpret_cast<const uint32_t *>(&av), &qn[4 * s], acc);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pr = tp * 16 + 4 * kb + i;
+            if (pr < P) QMs[pr * 16 + n] = acc[i] * sc2;
+        }
+    }
+    for (int i = lane; i < R * WS; i += 64) Ws[wave * R * WS + i] = 0ull;
+    // With two K groups per block, or the extra operands of 4-bit codes, the registers that q in natural order
+    // would hold for the rest of the kernel are needed elsewhere (the kernel is at its 256-register limit and
+    // spilled): it waits in LDS instead (identical in the four waves; [piece][lane]).
+    constexpr bool Q_LDS = G32 || BITS == 4;
+    __shared__ uint4 qn_s[Q_LDS ? 4 : 1][64];
+    if (Q_LDS && wave == 0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qn_s[i][lane] = make_uint4(qn[4 * i], qn[4 * i + 1], qn[4 * i + 2], qn[4 * i + 3]);
+    }
+    __syncthreads();
+
+    // Online softmax state per column.  Scores are formed relative to m_run (the reference enters the
+    // matrix-core accumulator), so the exponentials need no subtraction; the reference is raised only
+    // when a block exceeds it.
+    float m_run = 0.f, l_run = 0.f, pzacc = 0.f;
+    bool started = false;
+    floatx4 O[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) O[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    GroupOperand ga, gb;   // gb: second K group of a block, only when G == 32
+
+    auto build_group = [&](const GroupRaw &gr, GroupOperand &go) {
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t su[4] = {gr.s[i].x, gr.s[i].y, gr.s[i].z, gr.s[i].w}, zu[4] = {gr.z[i].x, gr.z[i].y, gr.z[i].z, gr.z[i].w};
+            uint4 qv;
+            if (G32 || BITS == 4)
+                qv = qn_s[i][lane];
+            else
+                qv = make_uint4(qn[4 * i], qn[4 * i + 1], qn[4 * i + 2], qn[4 * i + 3]);
+            const uint32_t qw[4] = {qv.x, qv.y, qv.z, qv.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                acc = dot2(qw[k], zu[k], acc);
+                go.Bq[4 * i + k] = pk_mul(qp[4 * i + k], su[k]);
+            }
+        }
+        // The fp16 rounding of q * s (2^-12 relative per channel) leaves a score error of about
+        // softmax_scale * 4.2e-4 * sqrt(sum_c q_c^2 s_c^2); where the group's scales make that matter (large-magnitude
+        // channels: outliers over long groups, a RoPE sub-space), the dropped part of every product is formed too
+        // and contracted in a second pass over the same code operand.  The test uses |q|^2 / d for q_c^2.
+        go.lo_on = false;
+        if (COMP) {
+            const float s2 = wave_sum(dot2(gr.own, gr.own, 0.f));
+            go.lo_on = s2 > lo_threshold;
+            if (go.lo_on) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t su[4] = {gr.s[i].x, gr.s[i].y, gr.s[i].z, gr.s[i].w};
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) go.Bl[4 * i + k] = product_error(qp[4 * i + k], su[k], go.Bq[4 * i + k]);
+                }
+            }
+        }
+        go.qz = over_rows(acc, AddF()) * sc2;
+    };
+
+
+    if (b0 < b1) {
+        build_group(first, ga);
         if (G32) {
-            load_group_raw((tb >> lgG) + 1, gr);
-            build_group(gr, gb);
+            load_group_raw(((t_begin + (b0 << 6)) >> lgG) + 1, first);
+            build_group(first, gb);
         }
     }
 
@@ -416,6 +426,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         const _Float16 c_hi = (_Float16)(float)(1 << (8 - fpos(HALF ? V + 4 : V)));
         cfield[V] = second ? pack2(c_hi, c_hi) : pack2(c_lo, c_lo);
     }
+
+    // places inside the dynamic LDS: QMs[index][n]; Ws[wave][hcol][index]
+    const uint32_t mass_row = (uint32_t)(P * 64 + (wave * R + hcol) * WS * 8);
+    auto qm_of = [&](uint32_t ids, int i) { return *reinterpret_cast<const float *>(dyn_smem + byte_address<64>(ids, i, n * 4)); };
 
     for (int b = b0; b < b1; ++b) {
         const int tb = t_begin + (b << 6);
@@ -475,8 +489,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             uint32_t A16[16];
-            fields_to_operand(bfi(0x55555555u, kw[x][0], kw[x][1] << 1), A16);
-            fields_to_operand(bfi(0x55555555u, kw[x][0] >> 1, kw[x][1]), A16 + 8);
+            planes_to_operand(kw[x][0], kw[x][1], A16);
             floatx4 d = {d0, d0, d0, d0}, d2 = {d02, d02, d02, d02};
 #pragma unroll
             for (int s = 0; s < 4; ++s) d = mfma16(&A16[4 * s], &ga.Bq[4 * s], d);
@@ -490,8 +503,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
             }
             if (BITS == 4) {
                 uint32_t H16[16];
-                fields_to_operand(bfi(0x55555555u, kw[x][BITS - 2], kw[x][BITS - 1] << 1), H16);
-                fields_to_operand(bfi(0x55555555u, kw[x][BITS - 2] >> 1, kw[x][BITS - 1]), H16 + 8);
+                planes_to_operand(kw[x][BITS - 2], kw[x][BITS - 1], H16);
                 floatx4 e = {0.f, 0.f, 0.f, 0.f}, e2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) e = mfma16(&H16[4 * s], &ga.Bq[4 * s], e);
@@ -514,16 +526,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
                     // lanes n < 8 take tile x - 2 (tokens 4(x-2) + i of the unit), lanes n >= 8 tile x (tokens 8 + 4(x-2) + i)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const uint32_t sel = (__float_as_uint(dfirst[x - 2][i]) & m_first) | (__float_as_uint(d[i]) & m_second);
-                        const int id = (kidw[x - 2] >> (8 * i)) & 255;
-                        S[4 * (x - 2) + i] = fmaf(__uint_as_float(sel), c1, QMs[id * 16 + n]);
+                        const uint32_t sel = bfi(m_second, __float_as_uint(d[i]), __float_as_uint(dfirst[x - 2][i]));
+                        S[4 * (x - 2) + i] = fmaf(__uint_as_float(sel), c1, qm_of(kidw[x - 2], i));
                     }
                 }
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int id = (kidw[x] >> (8 * i)) & 255;
-                    S[4 * x + i] = fmaf(d[i], c1, QMs[id * 16 + n]);
+                    S[4 * x + i] = fmaf(d[i], c1, qm_of(kidw[x], i));
                 }
             }
         }
@@ -546,8 +556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         for (int k = 2; k < NTK; k += 2) bmax = fmaxf(fmaxf(bmax, S[k]), S[k + 1]);
         if (!started || __ballot(bmax > 0.f) != 0ull) {
             if (HALF) bmax = fmaxf(bmax, __shfl_xor(bmax, 8));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+            bmax = over_rows(bmax, MaxF());
             const float delta = started ? fmaxf(bmax, 0.f) : bmax;
             const float alpha = started ? __builtin_amdgcn_exp2f(-delta) : 0.f;
             l_run *= alpha;
@@ -580,7 +589,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         if (hcol < R) {
 #pragma unroll
             for (int k = 0; k < NTK; ++k)
-                atomicAdd(&Ws[(wave * R + hcol) * WS + ((vidw[k >> 2] >> (8 * (k & 3))) & 255)],
+                atomicAdd(reinterpret_cast<unsigned long long *>(dyn_smem + byte_address<8>(vidw[k >> 2], k & 3, mass_row)),
                           (unsigned long long)(uint32_t)(pr[k] * kWUnit));   // pr <= 1: no overflow; truncation loses < 2^-31
         }
 
@@ -639,10 +648,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void d
         l_run += __shfl_xor(l_run, 8);
         pzacc += __shfl_xor(pzacc, 8);
     }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-    pzacc += __shfl_xor(pzacc, 16);
-    pzacc += __shfl_xor(pzacc, 32);
+    l_run = over_rows(l_run, AddF());
+    pzacc = over_rows(pzacc, AddF());
     if (kb == 0) {
         stat_m[wave][n] = m_run;
         stat_l[wave][n] = l_run;

@@ -61,6 +61,14 @@ __device__ __forceinline__ float row_sum(float v)
     v += __builtin_bit_cast(float, dpp<0x140>(bits_of(v)));
     return v;
 }
+__device__ __forceinline__ float row_max(float v)
+{
+    const MaxF op;
+    v = op(v, __builtin_bit_cast(float, dpp<0xb1>(bits_of(v))));
+    v = op(v, __builtin_bit_cast(float, dpp<0x4e>(bits_of(v))));
+    v = op(v, __builtin_bit_cast(float, dpp<0x141>(bits_of(v))));
+    return op(v, __builtin_bit_cast(float, dpp<0x140>(bits_of(v))));
+}
 
 // Reduction of N values (1, 2 or 4) over the four rows: row kb gets the total of value kb % N.  Rows are combined as neighbours first.
 template <int N, class OP>

@@ -889,7 +889,7 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
         // lane n ^ 8: a rotation of the row; n ^ 4: n ^ 7 (mirrored half row), then ^ 3; n ^ 2, n ^ 1: inside quads
         const uint32_t partner = s == 0 ? dpp<0x128>(x) : s == 1 ? dpp<0x1b>(dpp<0x141>(x)) : s == 2 ? dpp<0x4e>(x) : dpp<0xb1>(x);
         const uint32_t t = partner & c.keep[s];
-        x = (x & c.keep[s]) | __builtin_amdgcn_alignbit(t, t, c.sh[s]);
+        x = __builtin_amdgcn_bitop3_b32(x, c.keep[s], __builtin_amdgcn_alignbit(t, t, c.sh[s]), 0xea);   // (x & keep) | rotated: the fast three-input form
     }
     return x;
 }
