@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes as C
 import operator
 import os
+import struct
 from dataclasses import dataclass, replace
 
 import torch
@@ -51,6 +52,12 @@ class _State(C.Structure):
     _fields_ = [("t_quant", C.c_int32), ("t_tail", C.c_int32), ("tail_start", C.c_int32)]
 
 
+# The calls of a serving loop hand the configuration and the cache over as bytes in the structures' layout, packed in one operation: a
+# ctypes structure filled field by field, and a pointer object per tensor, took longer than a short call's kernels.
+_pack_config = struct.Struct("@12ifii").pack
+_pack_cache = struct.Struct("@11P").pack
+assert struct.calcsize("@12ifii") == C.sizeof(_Config) and struct.calcsize("@11P") == C.sizeof(_Cache)
+
 ABI_VERSION = 5          # PK_ABI_VERSION of include/patternkv.h this binding's structs are laid out for
 
 _lib.pk_abi_version.restype = C.c_uint32
@@ -66,36 +73,36 @@ _lib.pk_decode_plan.argtypes = [C.POINTER(_Config), C.c_int64, C.c_int64, C.POIN
 _lib.pk_workspace_bytes.restype = C.c_size_t
 _lib.pk_workspace_bytes.argtypes = [C.POINTER(_Config), C.c_int, C.c_int64, C.c_int64]
 _lib.pk_mine_patterns.restype = C.c_int
-_lib.pk_mine_patterns.argtypes = [C.POINTER(_Config), C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32,
+_lib.pk_mine_patterns.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32,
                                   C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t,
                                   C.c_void_p]
 _lib.pk_quantize_append.restype = C.c_int
-_lib.pk_quantize_append.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
+_lib.pk_quantize_append.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
                                     C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p,
                                     C.c_size_t, C.c_void_p]
 _lib.pk_quantize_append_ragged.restype = C.c_int
-_lib.pk_quantize_append_ragged.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p, C.c_void_p,
+_lib.pk_quantize_append_ragged.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p, C.c_void_p,
                                            C.POINTER(C.c_int32), C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                            C.c_size_t, C.c_void_p]
 _lib.pk_decode_attention.restype = C.c_int
-_lib.pk_decode_attention.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State),
-                                     C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
+_lib.pk_decode_attention.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State),
+                                     C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
                                      C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                      C.c_size_t, C.c_void_p]
 _lib.pk_decode_attention_ragged.restype = C.c_int
-_lib.pk_decode_attention_ragged.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
-                                            C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
+_lib.pk_decode_attention_ragged.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
+                                            C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
                                             C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                             C.c_size_t, C.c_void_p]
 _lib.pk_decode_attention_noalloc.restype = C.c_int
-_lib.pk_decode_attention_noalloc.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State),
-                                             C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
+_lib.pk_decode_attention_noalloc.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State),
+                                             C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
                                              C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
 NOALLOC_SCRATCH_BYTES = 32 << 20   # PK_NOALLOC_SCRATCH_BYTES
 _lib.pk_window_pattern.restype = C.c_int
 _lib.pk_window_pattern.argtypes = [C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_int64, C.c_void_p]
 _lib.pk_dequantize.restype = C.c_int
-_lib.pk_dequantize.argtypes = [C.POINTER(_Config), C.POINTER(_Cache), C.POINTER(_State), C.c_void_p,
+_lib.pk_dequantize.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(_State), C.c_void_p,
                                C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
 
 
@@ -140,9 +147,11 @@ class Config:
     n_pages: int = 0
 
     def c(self) -> _Config:
-        # the structure's fields by name, in its order: dataclasses.asdict, which copies recursively, took longer than a short
-        # call's kernels (a step of one token over 1.1k vectors on 8 streams, append and decode: 56 -> 41 us with 26 us of kernels)
+        # the structure's fields by name, in its order
         return _Config(*_config_values(self))
+
+    def packed(self) -> bytes:
+        return _pack_config(*_config_values(self))
 
     @property
     def n_streams(self) -> int:
@@ -159,11 +168,11 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous(), "tensors handed to the library must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def pk_cache_layout(cfg: Config) -> dict:
@@ -188,7 +197,8 @@ def pk_workspace_bytes(cfg: Config, op: int, a: int, b: int = 0) -> int:
 
 
 _ARRAYS = tuple(n for n, _ in _Cache._fields_[:-1])
-assert _Cache._fields_[-1][0] == "page_table"   # (Cache.c fills the structure in this order)
+assert _Cache._fields_[-1][0] == "page_table"   # (Cache.packed takes them in this order)
+_arrays_of = operator.itemgetter(*_ARRAYS)
 
 
 class Cache:
@@ -205,12 +215,15 @@ class Cache:
         if cfg.page_tokens > 0:
             self.page_table = torch.zeros((cfg.n_seq, cfg.t_capacity // cfg.page_tokens), dtype=torch.int32, device=device)
 
+    def packed(self) -> bytes:
+        table = self.page_table
+        if table is not None:
+            assert table.dtype == torch.int32 and table.is_contiguous()
+            assert tuple(table.shape) == (self.cfg.n_seq, self.cfg.t_capacity // self.cfg.page_tokens)
+        return _pack_cache(*[t.data_ptr() for t in _arrays_of(self.buf)], 0 if table is None else table.data_ptr())
+
     def c(self) -> _Cache:
-        if self.page_table is not None:
-            assert self.page_table.dtype == torch.int32 and self.page_table.is_contiguous()
-            assert tuple(self.page_table.shape) == (self.cfg.n_seq, self.cfg.t_capacity // self.cfg.page_tokens)
-        return _Cache(*[self.buf[n].data_ptr() for n in _ARRAYS],   # (the order of the structure's fields)
-                      None if self.page_table is None else self.page_table.data_ptr())
+        return _Cache.from_buffer_copy(self.packed())
 
     @property
     def t_quant(self):
@@ -261,9 +274,9 @@ def pk_mine_patterns(cfg: Config, x: torch.Tensor, iters: int, patterns: torch.T
         patterns = torch.empty((n_sets, cfg.n_patterns, d), dtype=torch.float16, device=x.device)
     if workspace is None:
         workspace = torch.empty(max(pk_workspace_bytes(cfg, OP_MINE, T, n_sets), 16), dtype=torch.uint8, device=x.device)
-    c = cfg.c()
+    c = cfg.packed()
     set_stride = x.stride(0) if n_sets > 1 else T * d
-    st = _lib.pk_mine_patterns(C.byref(c), C.c_void_p(x.data_ptr()), set_stride, n_sets, T, iters,
+    st = _lib.pk_mine_patterns(c, x.data_ptr(), set_stride, n_sets, T, iters,
                                1 if init_given else 0, _ptr(patterns), _ptr(assign), _ptr(inertia),
                                _ptr(workspace), workspace.numel(), _stream())
     _check(st, "pk_mine_patterns")
@@ -279,8 +292,8 @@ def pk_window_pattern(x: torch.Tensor, out: torch.Tensor | None = None):
     if out is None:
         out = torch.empty((n_sets, d), dtype=torch.float16, device=x.device)
     assert out.dtype == torch.float16 and out.shape == (n_sets, d) and out.stride(1) == 1
-    st = _lib.pk_window_pattern(C.c_void_p(x.data_ptr()), x.stride(0) if n_sets > 1 else n * d, n_sets, n, d,
-                                C.c_void_p(out.data_ptr()), out.stride(0) if n_sets > 1 else d, _stream())
+    st = _lib.pk_window_pattern(x.data_ptr(), x.stride(0) if n_sets > 1 else n * d, n_sets, n, d,
+                                out.data_ptr(), out.stride(0) if n_sets > 1 else d, _stream())
     _check(st, "pk_window_pattern")
     return out
 
@@ -306,9 +319,9 @@ def pk_quantize_append(cfg: Config, cache: Cache, k_new: torch.Tensor, v_new: to
 
     ss = stream_stride(k_new)
     assert stream_stride(v_new) == ss
-    cc, kc = cfg.c(), cache.c()
-    st = _lib.pk_quantize_append(C.byref(cc), C.byref(kc), C.byref(cache.state), C.c_void_p(k_new.data_ptr()),
-                                 C.c_void_p(v_new.data_ptr()), n_new, ss, _ptr(patterns_k),
+    cc, kc = cfg.packed(), cache.packed()
+    st = _lib.pk_quantize_append(cc, kc, C.byref(cache.state), k_new.data_ptr(),
+                                 v_new.data_ptr(), n_new, ss, _ptr(patterns_k),
                                  _ptr(patterns_v), _ptr(workspace), 0 if workspace is None else workspace.numel(),
                                  _stream())
     _check(st, "pk_quantize_append")
@@ -329,9 +342,9 @@ def pk_quantize_append_ragged(cfg: Config, cache: Cache, states: list, k_new: to
         workspace = torch.empty(max(pk_workspace_bytes(cfg, OP_APPEND, 0, 0), 16), dtype=torch.uint8, device=k_new.device)
     st_arr = (_State * n_seq)(*[_State(int(s[0]), int(s[1]), int(s[2])) for s in states])
     nn_arr = (C.c_int32 * n_seq)(*[int(n) for n in n_new])
-    cc, kc = cfg.c(), cache.c()
-    st = _lib.pk_quantize_append_ragged(C.byref(cc), C.byref(kc), st_arr, C.c_void_p(k_new.data_ptr()),
-                                        C.c_void_p(v_new.data_ptr()), nn_arr, n_max * d, _ptr(patterns_k), _ptr(patterns_v),
+    cc, kc = cfg.packed(), cache.packed()
+    st = _lib.pk_quantize_append_ragged(cc, kc, st_arr, k_new.data_ptr(),
+                                        v_new.data_ptr(), nn_arr, n_max * d, _ptr(patterns_k), _ptr(patterns_v),
                                         _ptr(seq_states_out), _ptr(workspace), workspace.numel(), _stream())
     _check(st, "pk_quantize_append_ragged")
     for i in range(n_seq):
@@ -350,14 +363,13 @@ def pk_decode_attention(cfg: Config, cache: Cache, q: torch.Tensor, softmax_scal
         a = cache.t_quant + cache.t_tail
         b = 0 if prefix is None else prefix.t_quant + prefix.t_tail
         workspace = torch.empty(max(pk_workspace_bytes(cfg, OP_DECODE, a, b), 16), dtype=torch.uint8, device=q.device)
-    cc, kc = cfg.c(), cache.c()
+    cc, kc = cfg.packed(), cache.packed()
     if prefix is not None:
-        pc, pkc = prefix.cfg.c(), prefix.c()
-        pargs = (C.byref(pc), C.byref(pkc), C.byref(prefix.state))
+        pargs = (prefix.cfg.packed(), prefix.packed(), C.byref(prefix.state))
     else:
         pargs = (None, None, None)
-    st = _lib.pk_decode_attention(C.byref(cc), C.byref(kc), C.byref(cache.state), *pargs, _ptr(q),
-                                  C.c_float(softmax_scale), _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
+    st = _lib.pk_decode_attention(cc, kc, C.byref(cache.state), *pargs, _ptr(q),
+                                  softmax_scale, _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
                                   _ptr(lse), _ptr(workspace), workspace.numel(), _stream())
     _check(st, "pk_decode_attention")
     return out
@@ -369,14 +381,13 @@ def pk_decode_attention_noalloc(cfg: Config, cache: Cache, q: torch.Tensor, soft
     """pk_decode_attention with the partial results in the library's fixed scratch array: nothing is allocated,
     here or in the library, so `out` [n_seq, n_q_heads, d] fp32 must be passed in."""
     assert q.dtype == torch.float16 and out.dtype == torch.float32 and out.shape == q.shape
-    cc, kc = cfg.c(), cache.c()
+    cc, kc = cfg.packed(), cache.packed()
     if prefix is not None:
-        pc, pkc = prefix.cfg.c(), prefix.c()
-        pargs = (C.byref(pc), C.byref(pkc), C.byref(prefix.state))
+        pargs = (prefix.cfg.packed(), prefix.packed(), C.byref(prefix.state))
     else:
         pargs = (None, None, None)
-    st = _lib.pk_decode_attention_noalloc(C.byref(cc), C.byref(kc), C.byref(cache.state), *pargs, _ptr(q),
-                                          C.c_float(softmax_scale), _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
+    st = _lib.pk_decode_attention_noalloc(cc, kc, C.byref(cache.state), *pargs, _ptr(q),
+                                          softmax_scale, _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
                                           _ptr(lse), _stream())
     _check(st, "pk_decode_attention_noalloc")
     return out
@@ -396,15 +407,14 @@ def pk_decode_attention_ragged(cfg: Config, cache: Cache, seq_states: torch.Tens
         b = 0 if prefix is None else prefix.t_quant + prefix.t_tail
         workspace = torch.empty(max(pk_workspace_bytes(cfg, OP_DECODE, bound_t_quant + bound_t_tail, b), 16),
                                 dtype=torch.uint8, device=q.device)
-    cc, kc = cfg.c(), cache.c()
+    cc, kc = cfg.packed(), cache.packed()
     bound = _State(bound_t_quant, bound_t_tail, 0)
     if prefix is not None:
-        pc, pkc = prefix.cfg.c(), prefix.c()
-        pargs = (C.byref(pc), C.byref(pkc), C.byref(prefix.state))
+        pargs = (prefix.cfg.packed(), prefix.packed(), C.byref(prefix.state))
     else:
         pargs = (None, None, None)
-    st = _lib.pk_decode_attention_ragged(C.byref(cc), C.byref(kc), C.byref(bound), _ptr(seq_states), *pargs, _ptr(q),
-                                         C.c_float(softmax_scale), _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
+    st = _lib.pk_decode_attention_ragged(cc, kc, C.byref(bound), _ptr(seq_states), *pargs, _ptr(q),
+                                         softmax_scale, _ptr(patterns_k), _ptr(patterns_v), _ptr(out),
                                          _ptr(lse), _ptr(workspace), workspace.numel(), _stream())
     _check(st, "pk_decode_attention_ragged")
     return out
@@ -417,8 +427,8 @@ def pk_dequantize(cfg: Config, cache: Cache, patterns_k: torch.Tensor, patterns_
     dev = patterns_k.device
     k = torch.empty((cfg.n_streams, t1 - t0, cfg.head_dim), dtype=torch.float32, device=dev)
     v = torch.empty_like(k)
-    cc, kc = cfg.c(), cache.c()
-    st = _lib.pk_dequantize(C.byref(cc), C.byref(kc), C.byref(cache.state), _ptr(patterns_k), _ptr(patterns_v),
+    cc, kc = cfg.packed(), cache.packed()
+    st = _lib.pk_dequantize(cc, kc, C.byref(cache.state), _ptr(patterns_k), _ptr(patterns_v),
                             t0, t1, _ptr(k), _ptr(v), _stream())
     _check(st, "pk_dequantize")
     return k, v
