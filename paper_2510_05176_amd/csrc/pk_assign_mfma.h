@@ -46,7 +46,8 @@ __device__ __forceinline__ floatx4_t mfma_f16(const uint4 &a, const uint4 &b, fl
 // gets one maximum per wave.  Ends with a barrier.
 // Work item i = (row, 16-byte piece): the kLanes lanes of a row (16, or 32 at D = 256; lanes past the row's D / 8 pieces
 // idle at D = 96) sum their squares.  kAhead items of a thread are requested before the first is stored: one after the other each
-// waited for its own load (@@).
+// waited for its own load (a step of 8 sets x 8192 vectors at 64 patterns 14.9 -> 13.3 us, an append of 4 x 131072 vectors at 256 patterns
+// 160 -> 155 us).
 template <int D = kD>
 __device__ __forceinline__ void stage_patterns(const __half *Mg, int P, __half *tab_s, float *nh_s, float *red_s,
                                                int nthr = 256)

@@ -1,6 +1,7 @@
 // Exchange between the four 16-lane rows of a wave (lane = 16 * kb + n, kb the row) by row swaps of the vector registers.  In place
 // of permutes through LDS (__shfl_xor compiles to those) the values neither queue behind the wave's other LDS accesses nor wait
-// for them.
+// for them, and two or four values that are reduced over the rows share the swaps (512 streams x 32640 vectors, 128 patterns, K and V
+// quantizers 3001 -> 2825 us, branches in the directed fp16 roundings taken out with them; mining 13.5 -> 13.2 ms).
 #pragma once
 
 #include <hip/hip_runtime.h>

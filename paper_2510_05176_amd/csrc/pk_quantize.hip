@@ -527,7 +527,7 @@ constexpr int kKParams = D * 2 * 2 + D * 4;           // bytes of one group's pa
 
 // Running minimum / maximum per channel over a 16-token tile: the residuals of 32 channels (operand step k) at a time
 // pass through the wave's LDS tile; lane <-> (channel 32k + lane%32, token half lane/32).  A step's values are used behind the next
-// step's stores (the LDS takes a wave's accesses in order): between its own stores and its use a step's loads would be waited for.
+// step's stores (the LDS takes a wave's accesses in order): between its own stores and its use a step's loads would be waited for (1483 -> 1453 us).
 struct ChannelScan {
     float v[8];
     float *mn, *mx;   // of the step that v belongs to; null: none
@@ -853,6 +853,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 25
 // ---- V ------------------------------------------------------------------------------------------------------------
 // Per-wave output staging: the pieces a wave produces for its 16 tokens are put together in LDS so that
 // every global store is one contiguous run of 8- or 16-byte lane pieces.
+// The vector under exact re-evaluation takes the codes' place (the finished unit that waits there is stored first: one token in several
+// hundred is re-evaluated), so that four workgroups fit a CU beside tables of up to 128 patterns of 128 channels: 512 streams x 32640
+// vectors 1410 -> 1280 us (3.4 -> 3.9 TB/s), 256 x 8192 at 64 patterns 187 -> 170.
 template <int D, int BITS, int NG>
 struct VStaging {
     static constexpr int kCodes = 0;                   // the unit's code words in memory order; D halves: one vector for the exact re-evaluation
@@ -864,7 +867,8 @@ struct VStaging {
 
 // 16x16 bit transpose across the 16 lanes of a row, on both 16-bit halves of x at once:
 // on return bit t of a half in lane i is what bit i of that half was in lane t.  The partner's word comes by lane permutations inside
-// the row, folded into the mask operation (permutes through LDS left a wave waiting for four of them in turn).
+// the row, folded into the mask operation (permutes through LDS left a wave waiting for four of them in turn: 512 streams x 32640 vectors
+// 1465 -> 1406 us, 4-bit codes over 32-channel groups 217 -> 201).
 struct TransposeConst {
     uint32_t sh[4], keep[4];   // stage d = 8, 4, 2, 1: rotation of the partner's bits; bits kept of the own word, which are also the places
                                // of those that the partner's word gives, before the rotation
@@ -1192,8 +1196,9 @@ static hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
 
 // Tiles per pass over the pattern table and launch sizes follow the table: every table tile read from LDS serves all the
 // 16-token tiles of a pass.  A large table (beyond 128 patterns, or 64 of 256 channels) leaves room for one or two
-// workgroups per CU, each of which stages up to 128 KB, so a small job is cut into one resident round of `resident`
-// workgroups rather than many short ones.
+// workgroups per CU, each of which stages up to 128 KB, so a job of up to 256 tiles per workgroup is cut into one resident round of
+// `resident` workgroups rather than many short ones (K, 256 streams x 8192 at 256 patterns: 364 us in workgroups of 24 tiles, 300 in one
+// round; at 160 patterns 332 and 262).
 static int one_round(const QuantArgs &a, int TT, int resident)
 {
     const int64_t tiles = (int64_t)(a.nq / TT) * a.n_streams;
@@ -1222,7 +1227,7 @@ static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
     if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
         if (a.P > 64 && a.P <= 128 && !few) return launch_k_waves<D, G, BITS, 2, 8>(a, s);
         return launch_k_waves<D, G, BITS, 2, 4>(a, s);
-    } else if constexpr (G == 64) {   // the whole group per table pass; pairs up to 32 patterns
+    } else if constexpr (G == 64) {   // the whole group per table pass (256 x 8192 at 64 patterns 220 -> 187 us); pairs up to 32 patterns
         if (a.P > 128 && !few) return launch_k_waves<D, G, BITS, 4, 12>(a, s);
         return a.P > 32 ? launch_k_waves<D, G, BITS, 4, 4>(a, s) : launch_k_waves<D, G, BITS, 2, 4>(a, s);
     } else {                          // 32-token groups gain from pairs only once the table is large
@@ -1290,9 +1295,15 @@ static hipError_t launch_v_waves(const QuantArgs &a, hipStream_t s)
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
 {
-    if constexpr (D != 256) {   // two blocks per table pass pay from 128 patterns on
+    // Two blocks per table pass, and the waves per workgroup that fill a CU beside a table that leaves room for two workgroups or
+    // one: 256 streams x 8192 vectors, one block and two (four waves per SIMD either way): 64 patterns 176 -> 162 us, 100 219 -> 197, with the
+    // adaptive threshold 216 -> 191, 16 132 -> 129.  One block where a wave has one or two only (8 x 4096: 8.3 and 9.7 us), with
+    // given indices (131 and 134) and with 4 bits up to 127 patterns (196 and 203).  Eight waves beyond 128 patterns: 256 patterns 302 -> 263,
+    // 200 of 96 channels 142 -> 99; 256 channels, 128 x 4096 vectors: 128 patterns 163 -> 87 with twelve, 250 231 -> 133 with eight.
+    if constexpr (D != 256) {
         if (a.P > 128) return launch_v_waves<D, BITS, NG, 2, 8>(a, s);
-        if (a.P == 128) return launch_v_waves<D, BITS, NG, 2, 4>(a, s);
+        const bool many = (int64_t)(a.nq / 64) * a.n_streams >= 2048;
+        if (a.P == 128 || (BITS == 2 && many && !a.idx_given)) return launch_v_waves<D, BITS, NG, 2, 4>(a, s);
     } else {
         if (a.P > 128) return launch_v_waves<D, BITS, NG, 1, 8>(a, s);
         if (a.P > 64) return launch_v_waves<D, BITS, NG, 1, 12>(a, s);

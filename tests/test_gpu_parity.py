@@ -1291,3 +1291,53 @@ def test_quantize_groups_of_128_tokens_side_by_side(pk, d, bits, P, groups):
     assert whole.t_quant == pieces.t_quant == T
     for name in ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx"):
         assert torch.equal(whole.array(name), pieces.array(name)), name
+
+
+@pytest.mark.parametrize("d,bits,G,P,rho,T", [
+    (128, 2, 64, 200, 0.0, 4416),   # twelve waves per workgroup, 69 groups per stream
+    (128, 4, 32, 130, 0.8, 2112), (96, 2, 32, 250, 0.0, 2112),
+    (128, 2, 64, 40, 0.8, 8256),    # two blocks per table pass on the V side, an odd number of them
+    (256, 2, 64, 100, 0.0, 4416), (256, 4, 32, 65, 0.5, 2112),   # eight waves (K), twelve (V)
+    (256, 2, 128, 90, 0.0, 1152),   # two groups of 128 tokens side by side
+    (256, 2, 64, 250, 0.0, 1088),   # eight waves on the V side
+])
+def test_quantizers_of_large_jobs(pk, d, bits, G, P, rho, T):
+    """Launch shapes that only jobs of many groups take, with rounds that do not come out even.  The cache equals, byte for byte, the
+    one that the same vectors give in appends of a few groups, whose shapes the other tests compare with the oracle."""
+    n_seq, hkv = 4, 4
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + P + G)
+    center = torch.randn((hkv, 40, d), generator=gen, device="cuda")
+    pick = torch.randint(0, 40, (n_seq, hkv, T), generator=gen, device="cuda")
+    x = torch.gather(center.expand(n_seq, hkv, 40, d), 2, pick[..., None].expand(-1, -1, -1, d))
+    x = (x + 0.3 * torch.randn(x.shape, generator=gen, device="cuda")).half()
+    Mk, Mv = x[0, :, :P].contiguous(), x[1, :, 100:100 + P].contiguous()
+    F = max(G, 64)
+    cfg = pk.Config(n_seq=n_seq, n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, seqs_per_set=0, bits=bits, group=G,
+                    recent=0, flush=F, t_capacity=T, metric=0, v_rho=rho)
+    whole, pieces = pk.Cache(cfg), pk.Cache(cfg)
+    v = x.flip(2).contiguous()
+    pk.pk_quantize_append(cfg, whole, x, v, Mk, Mv)
+    for t in range(0, T, 384):
+        pk.pk_quantize_append(cfg, pieces, x[:, :, t:t + 384].contiguous(), v[:, :, t:t + 384].contiguous(), Mk, Mv)
+    assert whole.t_quant == pieces.t_quant == T
+    for name in ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx"):
+        assert torch.equal(whole.array(name), pieces.array(name)), name
+
+
+@pytest.mark.parametrize("d,P,T,sets", [(128, 16, 300, 3), (128, 64, 1100, 2), (128, 128, 700, 2), (96, 40, 513, 2), (256, 33, 600, 2), (128, 30, 3000, 90)])
+def test_mining_starts_from_the_vectors(pk, d, P, T, sets):
+    """The first step reads its table from the sets' first vectors: the same patterns, bit for bit, as from a table that holds a copy of
+    them, also for sets with a stride, for patterns that start equal (all but one of them stay empty and keep their place) and
+    without any iteration."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T)
+    x = torch.randn((sets, T + 3, d), generator=gen, device="cuda").half()[:, :T]
+    x[:, 1:6] = x[:, :1]
+    cfg = pk.Config(n_kv_heads=1, n_q_heads=1, head_dim=d, n_patterns=P)
+    for iters in (0, 1, 3):
+        got = pk.pk_mine_patterns(cfg, x, iters)
+        want = x[:, :P].clone().contiguous()
+        pk.pk_mine_patterns(cfg, x, iters, patterns=want, init_given=True)
+        assert torch.equal(got, want), iters
+    assert torch.equal(got[:, 1:6], x[:, 1:6])
