@@ -1288,7 +1288,7 @@ template <int D, int BITS, int NG, int NT, int NW>
 static hipError_t launch_v_waves(const QuantArgs &a, hipStream_t s)
 {
     constexpr size_t kWaves = NW * (size_t)VStaging<D, BITS, NG>::kBytes;
-    return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, table_lds_bytes<D>(a.P) + kWaves, table_lds_bytes<D>(256) + kWaves, s,
+    return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, table_lds_bytes<D>(a.P) + kWaves, table_lds_bytes<D>(NW == 12 ? 128 : 256) + kWaves, s,
                                                                        one_round(a, 64, D == 256 ? 256 : 512), NW / 4 * NT);
 }
 
