@@ -7,6 +7,7 @@
 // write the softmax mass per pattern W[p] instead, so that W . M_V is formed once per head here.
 #include "pk_internal.h"
 #include "pk_decode_tail.h"
+#include "pk_lanes.h"
 
 namespace pk {
 
@@ -123,6 +124,98 @@ __global__ __launch_bounds__(128 * NQ) void decode_merge_kernel(DecodeArgs a)
     if (a.lse && c == 0) a.lse[u] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
 }
 
+// The same merge for RB heads of a KV head at a time: every pattern row read serves all of them (a head alone read the whole table,
+// 32 KB at 128 patterns, for 128 outputs).  256 threads; wave w forms the slot weights of head w, then takes every fourth slot and
+// pattern, two channels per lane; the waves' parts are added in a fixed order.  Dynamic LDS: slot weights [slots][RB], masses
+// [prefix, own][P][RB].  Whole merges: 16384 heads in groups of four at 128 patterns 71 -> 33 us, 2048 with a shared prefix at 64 patterns 10.5 -> 7.7, 1024
+// 8.9 -> 7.5, 896 in groups of seven 10.2 -> 8.2; pairs, 512 heads, 7.4 -> 7.0.
+template <int RB>
+__global__ __launch_bounds__(256) void decode_merge_heads_kernel(DecodeArgs a)
+{
+    static_assert(RB <= 4, "a wave per head");
+    extern __shared__ float merge_smem[];
+    __shared__ float M_s[RB], L_s[RB];
+    __shared__ float2 part_s[4][RB][kD / 2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), P = a.P;
+    const int r = a.n_q_heads / a.n_kv_heads, groups = (r + RB - 1) / RB;
+    const int n = blockIdx.x / groups, h0 = (blockIdx.x - n * groups) * RB, nh = min(RB, r - h0);
+    const int seq = n / a.n_kv_heads, head = n - seq * a.n_kv_heads;
+    const int n_packed = a.splits_prefix + a.splits_own;
+    const int64_t base = (int64_t)n * (n_packed + 2);
+    const int n_slots = a.prefix.t_tail > 0 ? n_packed + 2 : a.own.t_tail > 0 ? n_packed + 1 : n_packed;
+    float *weight = merge_smem, *mass = merge_smem + n_slots * RB;
+    if (wave < RB) {
+        const float *ml = a.part_ml + (base * r + h0 + min(wave, nh - 1)) * 2;
+        float M = -INFINITY, L = 0.f;
+        for (int s = lane; s < n_slots; s += 64)
+            if (ml[(int64_t)s * r * 2 + 1] > 0.f) M = fmaxf(M, ml[(int64_t)s * r * 2]);
+        const float m1[1] = {row_max(M)};
+        M = fold_rows<1>(m1, MaxF());
+        for (int s = lane; s < n_slots; s += 64) {
+            const float l = ml[(int64_t)s * r * 2 + 1];
+            const float w = l > 0.f && wave < nh ? exp2f(ml[(int64_t)s * r * 2] - M) : 0.f;
+            weight[s * RB + wave] = w;
+            L = fmaf(l, w, L);
+        }
+        const float l1[1] = {row_sum(L)};
+        L = fold_rows<1>(l1, AddF());
+        if (lane == 0) {
+            M_s[wave] = M;
+            L_s[wave] = L;
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < nh * P; e += 256) {
+        const int h = (e >= P) + (e >= 2 * P) + (e >= 3 * P), p = e - h * P;
+        const float *w = a.part_w + (base * r + h0) * P + e;   // (the heads' masses of a slot lie one after the other)
+        float wp = 0.f, wo = 0.f;
+#pragma unroll 4
+        for (int s = 0; s < a.splits_prefix; ++s) wp = fmaf(w[(int64_t)s * r * P], weight[s * RB + h], wp);
+#pragma unroll 4
+        for (int s = a.splits_prefix; s < n_packed; ++s) wo = fmaf(w[(int64_t)s * r * P], weight[s * RB + h], wo);
+        mass[p * RB + h] = wp;
+        mass[(P + p) * RB + h] = wo;
+    }
+    float2 acc[RB];
+#pragma unroll
+    for (int h = 0; h < RB; ++h) acc[h] = make_float2(0.f, 0.f);
+    for (int s = wave; s < n_slots; s += 4) {
+#pragma unroll
+        for (int h = 0; h < RB; ++h) {
+            const float2 o = *reinterpret_cast<const float2 *>(a.part_o + ((base + s) * r + h0 + min(h, nh - 1)) * kD + 2 * lane);
+            const float w = weight[s * RB + h];
+            acc[h].x = fmaf(o.x, w, acc[h].x);
+            acc[h].y = fmaf(o.y, w, acc[h].y);
+        }
+    }
+    __syncthreads();
+    auto add_patterns = [&](const __half *MV, const float *m) {
+#pragma unroll 4
+        for (int p = wave; p < P; p += 4) {
+            const __half2 v = *reinterpret_cast<const __half2 *>(MV + (int64_t)p * kD + 2 * lane);
+            const float x = __low2float(v), y = __high2float(v);
+#pragma unroll
+            for (int h = 0; h < RB; ++h) {   // (heads past the last one: never stored)
+                acc[h].x = fmaf(m[p * RB + h], x, acc[h].x);
+                acc[h].y = fmaf(m[p * RB + h], y, acc[h].y);
+            }
+        }
+    };
+    if (a.splits_prefix > 0) add_patterns(a.patterns_v + (int64_t)head * P * kD, mass);
+    if (a.splits_own > 0) add_patterns(a.patterns_v + (int64_t)a.sets.set_of(n) * P * kD, mass + P * RB);
+#pragma unroll
+    for (int h = 0; h < RB; ++h) part_s[wave][h][lane] = acc[h];
+    __syncthreads();
+    const int64_t first = (int64_t)seq * a.n_q_heads + head * r + h0;
+    for (int e = tid; e < nh * kD; e += 256) {
+        const int h = e / kD, c = e % kD;
+        const float *p = reinterpret_cast<const float *>(part_s) + h * kD + c;
+        const float sum = (p[0] + p[RB * kD]) + (p[2 * RB * kD] + p[3 * RB * kD]);
+        a.out[first * kD + e] = L_s[h] > 0.f ? sum / L_s[h] : 0.f;
+    }
+    if (a.lse && tid < nh) a.lse[first + tid] = L_s[tid] > 0.f ? (M_s[tid] + log2f(L_s[tid])) * kLn2 : -INFINITY;
+}
+
 // Ragged batch: rank of every sequence by the length of its packed part, longest first (ties by index), by
 // counting; one workgroup, n_seq <= kMaxOrdered.  Workgroups are dispatched in grid order, so starting the long
 // streams first keeps the last round from consisting of a few long ones running alone.
@@ -209,7 +302,15 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
     // four parts per channel when a thread would otherwise walk many slots or patterns alone and the
     // (sequence, head) pairs are too few to fill the chip with 128-thread workgroups; eight when there are hundreds
     // of slots and patterns for a few heads only (config 5: 28 heads, 130 slots, 256 patterns: 17 -> 13 us)
-    if (a.splits_prefix + a.splits_own + a.P >= 256 && a.n_seq * a.n_q_heads <= 256)
+    // heads of a KV head together wherever that leaves a workgroup for every CU
+    const int slots = a.splits_prefix + a.splits_own + 2;
+    if (r > 1 && N * ((r + 3) / 4) >= 256) {
+        const size_t lds = (size_t)(slots + 2 * a.P) * (r == 2 ? 2 : 4) * 4;   // at most 45 KB
+        if (r == 2)
+            hipLaunchKernelGGL(decode_merge_heads_kernel<2>, dim3(N), dim3(256), lds, s, a);
+        else
+            hipLaunchKernelGGL(decode_merge_heads_kernel<4>, dim3(N * ((r + 3) / 4)), dim3(256), lds, s, a);
+    } else if (a.splits_prefix + a.splits_own + a.P >= 256 && a.n_seq * a.n_q_heads <= 256)
         hipLaunchKernelGGL(decode_merge_kernel<8>, dim3(a.n_seq * a.n_q_heads), dim3(1024), 0, s, a);
     else if (a.splits_prefix + a.splits_own + a.P >= 96 && a.n_seq * a.n_q_heads <= 2048)
         hipLaunchKernelGGL(decode_merge_kernel<4>, dim3(a.n_seq * a.n_q_heads), dim3(512), 0, s, a);

@@ -1341,3 +1341,32 @@ def test_mining_starts_from_the_vectors(pk, d, P, T, sets):
         pk.pk_mine_patterns(cfg, x, iters, patterns=want, init_given=True)
         assert torch.equal(got, want), iters
     assert torch.equal(got[:, 1:6], x[:, 1:6])
+
+
+@pytest.mark.parametrize("hkv,r,bits,G,P,prefix", [(2, 2, 2, 64, 24, False), (1, 4, 2, 64, 40, True), (2, 5, 4, 64, 16, False), (1, 7, 2, 128, 130, True)])
+def test_decode_merges_heads_together(pk, hkv, r, bits, G, P, prefix):
+    """The merge that takes the heads of a KV head together (batches of 256 KV heads and more) against the one that takes a head at a
+    time: sequence 0 in a batch of many copies, and alone.  Both add the same partials in binary32, in different orders: 4e-6 of a
+    row's largest value is some thirty roundings.  (Equal split lengths on both sides: the contexts are shorter than one split.)"""
+    copies, T = 260, 300
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(P)
+    k, v = (torch.randn((1, hkv, T, 128), generator=gen, device="cuda").half() for _ in range(2))
+    M = torch.randn((hkv, P, 128), generator=gen, device="cuda").half()
+    q = torch.randn((1, hkv * r, 128), generator=gen, device="cuda").half()
+    got = []
+    for n in (1, copies):
+        cfg = pk.Config(n_seq=n, n_kv_heads=hkv, n_q_heads=hkv * r, n_patterns=P, seqs_per_set=0, bits=bits, group=G, recent=20, flush=128, t_capacity=512)
+        cache, pre = pk.Cache(cfg), None
+        pk.pk_quantize_append(cfg, cache, k.expand(n, -1, -1, -1).contiguous(), v.expand(n, -1, -1, -1).contiguous(), M, M)
+        if prefix:
+            pcfg = pk.Config(n_seq=1, n_kv_heads=hkv, n_q_heads=hkv * r, n_patterns=P, seqs_per_set=0, bits=bits, group=G, recent=20, flush=128, t_capacity=512)
+            pre = pk.Cache(pcfg)
+            pk.pk_quantize_append(pcfg, pre, v, k, M, M)
+        lse = torch.empty((n, hkv * r), dtype=torch.float32, device="cuda")
+        out = pk.pk_decode_attention(cfg, cache, q.expand(n, -1, -1).contiguous(), 128 ** -0.5, M, M, lse=lse, prefix=pre)
+        got.append((out, lse))
+    (one, one_lse), (many, many_lse) = got
+    limit = 4e-6 * one.abs().amax(2, keepdim=True)
+    assert ((many - one).abs() <= limit).all()
+    assert ((many_lse - one_lse).abs() <= 4e-6 * (1 + one_lse.abs())).all()
