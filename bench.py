@@ -66,7 +66,7 @@ WORKLOADS = {
     "cfg4": dict(spec="cfg4"),   # streaming: its own step, see run_streaming()
     "cfg3r": dict(spec="cfg3"),  # config 3's shape with a mix of sequence lengths: ragged prefill + ragged decode, see run_ragged()
 }
-DECODE_KERNELS = "decode_packed_kernel(+decode_tail_kernel+decode_merge_kernel)"
+DECODE_KERNELS = "decode_packed_kernel(+decode_tail_kernel+decode_merge_kernel or decode_merge_heads_kernel)"
 DECODE_KERNELS_OTHER_D = "gen_decode_kernel(+gen_tail_kernel+gen_decode_merge_kernel)"   # head dimensions 96 and 256
 
 

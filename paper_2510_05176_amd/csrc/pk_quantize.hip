@@ -1087,14 +1087,14 @@ __global__ __launch_bounds__(64 * NW) void quantize_v_kernel(QuantArgs a, int ti
                 if (16 * b + 16 <= kAll || n < 8) dst[0] = word;
             } else {
 #pragma unroll
-            for (int w = 0; w < WPU; ++w) {
-                // t_p = (bits p of the 16 codes) << p; low half of x = plane 2w, high half = plane 2w+1
-                const uint32_t t0 = (plane_byte_shifted(cw[2], cw[3], 2 * w) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w);
-                const uint32_t t1 = (plane_byte_shifted(cw[2], cw[3], 2 * w + 1) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w + 1);
-                const uint32_t x = (t0 >> (2 * w)) | (t1 << (15 - 2 * w));
-                const uint32_t word = transpose16(x, tc);
-                if (16 * b + 16 <= kAll || n < 8) dst[w] = word;
-            }
+                for (int w = 0; w < WPU; ++w) {
+                    // t_p = (bits p of the 16 codes) << p; low half of x = plane 2w, high half = plane 2w+1
+                    const uint32_t t0 = (plane_byte_shifted(cw[2], cw[3], 2 * w) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w);
+                    const uint32_t t1 = (plane_byte_shifted(cw[2], cw[3], 2 * w + 1) << 8) | plane_byte_shifted(cw[0], cw[1], 2 * w + 1);
+                    const uint32_t x = (t0 >> (2 * w)) | (t1 << (15 - 2 * w));
+                    const uint32_t word = transpose16(x, tc);
+                    if (16 * b + 16 <= kAll || n < 8) dst[w] = word;
+                }
             }
         }
         wave_lds_sync();
