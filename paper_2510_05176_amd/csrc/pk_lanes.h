@@ -19,23 +19,14 @@ __device__ __forceinline__ rows2 swap32(uint32_t a, uint32_t b) { return __built
 __device__ __forceinline__ uint32_t bits_of(float v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ __forceinline__ uint32_t bits_of(uint32_t v) { return v; }
 
-// minimum and maximum as the instruction forms them (fminf and fmaxf quieten signalling NaN first, an operation more per operand
-// that comes from another lane)
+// Operations the compiler knows: it keeps two wait states between a vector operation's result and the lane swap that reads it, and
+// does not count what inline assembly writes.  (fminf and fmaxf quieten signalling NaN first, an operation more per operand that
+// comes from another lane: K and V quantizers of 512 streams x 32640 vectors 2656 us with the bare instructions, 2665 with these.)
 struct MinF {
-    __device__ __forceinline__ float operator()(float a, float b) const
-    {
-        float r;
-        asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-        return r;
-    }
+    __device__ __forceinline__ float operator()(float a, float b) const { return fminf(a, b); }
 };
 struct MaxF {
-    __device__ __forceinline__ float operator()(float a, float b) const
-    {
-        float r;
-        asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-        return r;
-    }
+    __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
 };
 struct AddF {
     __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
