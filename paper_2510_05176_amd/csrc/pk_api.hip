@@ -286,6 +286,7 @@ namespace {
 // a per-sequence table for everything else.
 struct AppendPlan {
     int64_t nq;            // vectors to quantize per stream (largest of the batch)
+    int64_t n_vectors;     // of all streams together
     int32_t t0, ring_start, n_ring;
     int64_t i0, i1;        // tail copy: logical vectors [i0, i1) (ragged: 0 .. the widest range)
     const int32_t *seq_table;
@@ -313,6 +314,7 @@ pk_status launch_append(const pk_config *cfg, const pk_cache *cache, const Appen
         a.d = cfg->head_dim;
         a.n_streams = N;
         a.nq = (int32_t)p.nq;
+        a.n_vectors = p.n_vectors;
         a.t0 = p.t0;
         a.map = make_map(cfg, cache);
         a.seq_table = p.seq_table;
@@ -388,6 +390,7 @@ pk_status pk_quantize_append(const pk_config *cfg, const pk_cache *cache, pk_sta
 
     AppendPlan p;
     p.nq = nq;
+    p.n_vectors = nq * cfg->n_seq * cfg->n_kv_heads;
     p.t0 = state->t_quant;
     p.ring_start = state->tail_start;
     p.n_ring = state->t_tail;
@@ -436,6 +439,7 @@ pk_status pk_quantize_append_ragged(const pk_config *cfg, const pk_cache *cache,
     std::vector<int32_t> entry((size_t)S * kSeqEntry, 0), after((size_t)S * 3, 0);
     AppendPlan p;
     p.nq = 0;
+    p.n_vectors = 0;
     p.t0 = 0;
     p.ring_start = 0;
     p.n_ring = 0;
@@ -457,6 +461,7 @@ pk_status pk_quantize_append_ragged(const pk_config *cfg, const pk_cache *cache,
         after[(size_t)i * 3 + 1] = (int32_t)(L - nq);
         after[(size_t)i * 3 + 2] = (int32_t)((s.tail_start + nq) % ring);
         if (nq > p.nq) p.nq = nq;
+        p.n_vectors += nq * cfg->n_kv_heads;
         if (e[kSeqI1] - e[kSeqI0] > p.i1) p.i1 = e[kSeqI1] - e[kSeqI0];   // launch width of the tail copy
     }
     hipStream_t hs = static_cast<hipStream_t>(stream);

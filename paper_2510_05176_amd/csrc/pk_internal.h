@@ -156,6 +156,7 @@ struct QuantArgs {
     float v_rho;              // V side: adaptive threshold (0 = off)
     int32_t n_streams;
     int32_t nq;               // vectors to quantize per stream (multiple of G)
+    int64_t n_vectors;        // of all streams together (launch sizing)
     int32_t t0;               // first packed position to write (= t_quant)
     PackedMap map;            // where the packed tokens of a stream live
     uint32_t *codes_k;        // K side

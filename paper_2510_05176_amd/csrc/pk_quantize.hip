@@ -17,6 +17,7 @@
 
 #include "pk_assign_mfma.h"
 #include "pk_quant_arith.h"
+#include "pk_cut.h"
 #include "pk_internal.h"
 
 namespace pk {
@@ -1164,17 +1165,15 @@ static int tiles_per_wg(int n_tiles, int n_streams)
     return t < 1 ? 1 : (t > cap ? cap : t);
 }
 
+// Workgroups of at most `tiles` tiles of one stream each.  max_lds: the most that the instantiation is launched with.
 template <auto KERNEL, int THREADS = 256>
-static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t max_lds, hipStream_t s, int min_tiles = 1, int multiple = 1)
+static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t max_lds, hipStream_t s, int tiles)
 {
-    static LdsOptIn opt_in;   // per kernel instantiation; max_lds: what it needs with a table of 256 patterns
+    static LdsOptIn opt_in;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(KERNEL), opt_in, max_lds);
     if (e != hipSuccess) return e;
-    int tpw = tiles_per_wg(a.nq / TT, a.n_streams);
-    if (tpw < min_tiles) tpw = min_tiles;
-    tpw = (tpw + multiple - 1) / multiple * multiple;   // (whole rounds of the workgroup's waves)
-    const int n_tiles = a.nq / TT;
-    hipLaunchKernelGGL(KERNEL, dim3((n_tiles + tpw - 1) / tpw, a.n_streams), dim3(THREADS), lds, s, a, tpw);
+    const int chunks = (a.nq / TT + tiles - 1) / tiles;
+    hipLaunchKernelGGL(KERNEL, dim3(chunks, a.n_streams), dim3(THREADS), lds, s, a, tiles);
     return hipGetLastError();
 }
 
@@ -1196,23 +1195,35 @@ static hipError_t launch_assign_minmax(const QuantArgs &a, hipStream_t s)
 
 // Tiles per pass over the pattern table and launch sizes follow the table: every table tile read from LDS serves all the
 // 16-token tiles of a pass.  A large table (beyond 128 patterns, or 64 of 256 channels) leaves room for one or two
-// workgroups per CU, each of which stages up to 128 KB, so a job of up to 256 tiles per workgroup is cut into one resident round of
-// `resident` workgroups rather than many short ones (K, 256 streams x 8192 at 256 patterns: 364 us in workgroups of 24 tiles, 300 in one
-// round; at 160 patterns 332 and 262).
-static int one_round(const QuantArgs &a, int TT, int resident)
+// workgroups per CU, each of which stages up to 128 KB: what a launch takes then hangs on how many workgroups every CU gets.
+template <int D>
+static bool large_table(int P)
 {
-    const int64_t tiles = (int64_t)(a.nq / TT) * a.n_streams;
-    return a.P * a.d > 128 * kD && tiles <= (int64_t)resident * 256 ? (int)((tiles + resident - 1) / resident) : 1;
+    return P > (D == 256 ? 64 : 128);
+}
+
+// multiple: tiles that the workgroup takes side by side; waves_per_cu: what registers allow
+static Cut cut_job(const QuantArgs &a, int TT, size_t lds, int waves, int waves_per_cu, int multiple)
+{
+    const Job j = {a.nq / TT, a.n_streams, a.n_vectors / TT, a.seq_table != nullptr, 256.f / TT};
+    return cut_streams(j, (int)(163840 / lds), waves, waves_per_cu, multiple);
 }
 
 template <int D, int G, int BITS, int NTA, int NW>
-static hipError_t launch_k_waves(const QuantArgs &a, hipStream_t s)
-{
-    const size_t lds = table_lds_bytes<D>(a.P) + NW * (size_t)kWkWave<D>, mx = table_lds_bytes<D>(D == 256 && NW > 4 ? 128 : 256) + NW * (size_t)kWkWave<D>;
-    constexpr int kMin = NW * G / 64;   // a wave owns whole groups: at least one group per wave
-    const int round = one_round(a, 64, 256);
-    return launch_tiled<quantize_k_wave_kernel<D, G, BITS, NTA, NW>, 64 * NW>(a, 64, lds, mx, s, round > kMin ? round : kMin, kMin);
-}
+struct KWaves {
+    static constexpr int kMultiple = NW * G / 64 > 0 ? NW * G / 64 : 1;   // a wave owns whole groups: one group per wave at a time
+    static size_t lds(int P) { return table_lds_bytes<D>(P) + NW * (size_t)kWkWave<D>; }
+    static Cut cut(const QuantArgs &a) { return cut_job(a, 64, lds(a.P), NW, D == 256 && G == 64 ? 8 : 12, kMultiple); }
+    static hipError_t launch(const QuantArgs &a, hipStream_t s, int tiles)
+    {
+        return launch_tiled<quantize_k_wave_kernel<D, G, BITS, NTA, NW>, 64 * NW>(a, 64, lds(a.P), lds(D == 256 && NW > 4 ? 128 : 256), s, tiles);
+    }
+    static hipError_t launch(const QuantArgs &a, hipStream_t s)   // small tables
+    {
+        const int t = max(tiles_per_wg(a.nq / 64, a.n_streams), kMultiple);
+        return launch(a, s, (t + kMultiple - 1) / kMultiple * kMultiple);
+    }
+};
 
 // Waves per workgroup: as many as registers allow per CU (three per SIMD, two for 64-token groups of 256 channels) once the table
 // leaves room for one workgroup only (beyond 128 patterns; 64 of 256 channels, whose table beyond 128 leaves room for four waves).
@@ -1225,16 +1236,32 @@ static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
 {
     const bool few = (int64_t)(a.nq / G) * a.n_streams <= 1024;
     if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
-        if (a.P > 64 && a.P <= 128 && !few) return launch_k_waves<D, G, BITS, 2, 8>(a, s);
-        return launch_k_waves<D, G, BITS, 2, 4>(a, s);
+        using Four = KWaves<D, G, BITS, 2, 4>;
+        using Eight = KWaves<D, G, BITS, 2, 8>;
+        if (large_table<D>(a.P) && a.P <= 128 && !few) return Eight::launch(a, s, Eight::cut(a).tiles);
+        return large_table<D>(a.P) ? Four::launch(a, s, Four::cut(a).tiles) : Four::launch(a, s);
     } else if constexpr (G == 64) {   // the whole group per table pass (256 x 8192 at 64 patterns 220 -> 187 us); pairs up to 32 patterns
-        if (a.P > 128 && !few) return launch_k_waves<D, G, BITS, 4, 12>(a, s);
-        return a.P > 32 ? launch_k_waves<D, G, BITS, 4, 4>(a, s) : launch_k_waves<D, G, BITS, 2, 4>(a, s);
+        using Four = KWaves<D, G, BITS, 4, 4>;
+        using Twelve = KWaves<D, G, BITS, 4, 12>;
+        if (large_table<D>(a.P)) return few ? Four::launch(a, s, Four::cut(a).tiles) : Twelve::launch(a, s, Twelve::cut(a).tiles);
+        return a.P > 32 ? Four::launch(a, s) : KWaves<D, G, BITS, 2, 4>::launch(a, s);
     } else {                          // 32-token groups gain from pairs only once the table is large
-        if (a.P > 128 && !few) return launch_k_waves<D, G, BITS, 2, 12>(a, s);
-        return a.P >= 128 ? launch_k_waves<D, G, BITS, 2, 4>(a, s) : launch_k_waves<D, G, BITS, 1, 4>(a, s);
+        using Four = KWaves<D, G, BITS, 2, 4>;
+        using Twelve = KWaves<D, G, BITS, 2, 12>;
+        if (large_table<D>(a.P)) return few ? Four::launch(a, s, Four::cut(a).tiles) : Twelve::launch(a, s, Twelve::cut(a).tiles);
+        return a.P >= 128 ? Four::launch(a, s) : KWaves<D, G, BITS, 1, 4>::launch(a, s);
     }
 }
+
+template <int D, int BITS, int GR, int NT>
+struct KGroups {   // GR groups of 128 tokens side by side
+    static size_t lds(int P) { return table_lds_bytes<D>(P) + GR * (size_t)kGroupLds<D, NT>; }
+    static Cut cut(const QuantArgs &a) { return cut_job(a, 128, lds(a.P), 8 / NT * GR, 16, GR); }
+    static hipError_t launch(const QuantArgs &a, hipStream_t s, int tiles)
+    {
+        return launch_tiled<quantize_k_group_kernel<D, BITS, GR, NT>, 512 / NT * GR>(a, 128, lds(a.P), lds(D == 256 && GR > 1 ? 128 : 256), s, tiles);
+    }
+};
 
 template <int D, int BITS>
 static hipError_t launch_k_bits(const QuantArgs &a, hipStream_t s)
@@ -1243,23 +1270,18 @@ static hipError_t launch_k_bits(const QuantArgs &a, hipStream_t s)
     if constexpr (D != 96) {   // (64 does not divide 96 channels)
         if (a.G == 64) return launch_k_wave<D, 64, BITS>(a, s);
     }
-    const size_t lds = table_lds_bytes<D>(a.P), mx = table_lds_bytes<D>(256);
-    const int round = one_round(a, 128, 256);
+    using One = KGroups<D, BITS, 1, 1>;
+    if (!large_table<D>(a.P)) return One::launch(a, s, tiles_per_wg(a.nq / 128, a.n_streams));
     if constexpr (D == 256) {
-        if (a.P > 64 && a.P <= 128) {
-            constexpr size_t two = 2 * (size_t)kGroupLds<D, 1>;
-            return launch_tiled<quantize_k_group_kernel<D, BITS, 2, 1>, 1024>(a, 128, lds + two, table_lds_bytes<D>(128) + two, s, round);
-        }
-    } else {
-        if (a.P > 128) {
-            constexpr size_t four = 4 * (size_t)kGroupLds<D, 2>, two = 2 * (size_t)kGroupLds<D, 1>;
-            if (round >= 4 || tiles_per_wg(a.nq / 128, a.n_streams) >= 4)
-                return launch_tiled<quantize_k_group_kernel<D, BITS, 4, 2>, 1024>(a, 128, lds + four, mx + four, s, round);
-            return launch_tiled<quantize_k_group_kernel<D, BITS, 2, 1>, 1024>(a, 128, lds + two, mx + two, s, round);
-        }
+        using Two = KGroups<D, BITS, 2, 1>;
+        if (a.P <= 128) return Two::launch(a, s, Two::cut(a).tiles);
+        return One::launch(a, s, One::cut(a).tiles);
+    } else {   // four groups, or two of twice the waves where workgroups are short
+        using Two = KGroups<D, BITS, 2, 1>;
+        using Four = KGroups<D, BITS, 4, 2>;
+        const Cut two = Two::cut(a);
+        return two.tiles >= 4 ? Four::launch(a, s, Four::cut(a).tiles) : Two::launch(a, s, two.tiles);
     }
-    constexpr size_t one = kGroupLds<D, 1>;
-    return launch_tiled<quantize_k_group_kernel<D, BITS, 1, 1>, 512>(a, 128, lds + one, mx + one, s, round);
 }
 
 template <int D>
@@ -1285,12 +1307,15 @@ hipError_t launch_quantize_k(const QuantArgs &a_in, hipStream_t s)
 }
 
 template <int D, int BITS, int NG, int NT, int NW>
-static hipError_t launch_v_waves(const QuantArgs &a, hipStream_t s)
-{
-    constexpr size_t kWaves = NW * (size_t)VStaging<D, BITS, NG>::kBytes;
-    return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, table_lds_bytes<D>(a.P) + kWaves, table_lds_bytes<D>(NW == 12 ? 128 : 256) + kWaves, s,
-                                                                       one_round(a, 64, D == 256 ? 256 : 512), NW / 4 * NT);
-}
+struct VWaves {
+    static constexpr int kMultiple = NW / 4 * NT;   // blocks that the workgroup takes at a time
+    static size_t lds(int P) { return table_lds_bytes<D>(P) + NW * (size_t)VStaging<D, BITS, NG>::kBytes; }
+    static Cut cut(const QuantArgs &a) { return cut_job(a, 64, lds(a.P), NW, D == 256 ? 12 : 16, kMultiple); }
+    static hipError_t launch(const QuantArgs &a, hipStream_t s, int tiles)
+    {
+        return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, lds(a.P), lds(NW == 12 ? 128 : 256), s, tiles);
+    }
+};
 
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
@@ -1301,14 +1326,17 @@ static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
     // given indices (131 and 134) and with 4 bits up to 127 patterns (196 and 203).  Eight waves beyond 128 patterns: 256 patterns 302 -> 263,
     // 200 of 96 channels 142 -> 99; 256 channels, 128 x 4096 vectors: 128 patterns 163 -> 87 with twelve, 250 231 -> 133 with eight.
     if constexpr (D != 256) {
-        if (a.P > 128) return launch_v_waves<D, BITS, NG, 2, 8>(a, s);
+        using Eight = VWaves<D, BITS, NG, 2, 8>;
+        if (large_table<D>(a.P)) return Eight::launch(a, s, Eight::cut(a).tiles);
         const bool many = (int64_t)(a.nq / 64) * a.n_streams >= 2048;
-        if (a.P == 128 || (BITS == 2 && many && !a.idx_given)) return launch_v_waves<D, BITS, NG, 2, 4>(a, s);
+        if (a.P == 128 || (BITS == 2 && many && !a.idx_given)) return VWaves<D, BITS, NG, 2, 4>::launch(a, s, (tiles_per_wg(a.nq / 64, a.n_streams) + 1) / 2 * 2);
     } else {
-        if (a.P > 128) return launch_v_waves<D, BITS, NG, 1, 8>(a, s);
-        if (a.P > 64) return launch_v_waves<D, BITS, NG, 1, 12>(a, s);
+        using Eight = VWaves<D, BITS, NG, 1, 8>;
+        using Twelve = VWaves<D, BITS, NG, 1, 12>;
+        if (a.P > 128) return Eight::launch(a, s, Eight::cut(a).tiles);
+        if (large_table<D>(a.P)) return Twelve::launch(a, s, Twelve::cut(a).tiles);
     }
-    return launch_v_waves<D, BITS, NG, 1, 4>(a, s);
+    return VWaves<D, BITS, NG, 1, 4>::launch(a, s, tiles_per_wg(a.nq / 64, a.n_streams));
 }
 
 template <int D, int BITS>

@@ -1294,15 +1294,15 @@ def test_quantize_groups_of_128_tokens_side_by_side(pk, d, bits, P, groups):
 
 
 @pytest.mark.parametrize("d,bits,G,P,rho,T", [
-    (128, 2, 64, 200, 0.0, 4416),   # twelve waves per workgroup, 69 groups per stream
+    (128, 2, 64, 200, 0.0, 4416),   # 69 groups per stream; eight waves on the V side
     (128, 4, 32, 130, 0.8, 2112), (96, 2, 32, 250, 0.0, 2112),
     (128, 2, 64, 40, 0.8, 8256),    # two blocks per table pass on the V side, an odd number of them
-    (256, 2, 64, 100, 0.0, 4416), (256, 4, 32, 65, 0.5, 2112),   # eight waves (K), twelve (V)
-    (256, 2, 128, 90, 0.0, 1152),   # two groups of 128 tokens side by side
+    (256, 2, 64, 100, 0.0, 4416), (256, 4, 32, 65, 0.5, 2112),
+    (256, 2, 128, 90, 0.0, 1152),   # groups of 128 tokens
     (256, 2, 64, 250, 0.0, 1088),   # eight waves on the V side
 ])
 def test_quantizers_of_large_jobs(pk, d, bits, G, P, rho, T):
-    """Launch shapes that only jobs of many groups take, with rounds that do not come out even.  The cache equals, byte for byte, the
+    """Jobs of many groups on 16 streams, with rounds that do not come out even.  The cache equals, byte for byte, the
     one that the same vectors give in appends of a few groups, whose shapes the other tests compare with the oracle."""
     n_seq, hkv = 4, 4
     gen = torch.Generator(device="cuda")
@@ -1323,6 +1323,54 @@ def test_quantizers_of_large_jobs(pk, d, bits, G, P, rho, T):
     assert whole.t_quant == pieces.t_quant == T
     for name in ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx"):
         assert torch.equal(whole.array(name), pieces.array(name)), name
+
+
+@pytest.mark.parametrize("d,bits,G,P,rho,n_seq,T,ragged", [
+    (128, 2, 64, 250, 0.0, 32, 1600, False),   # K: twelve waves, 25 groups of a stream in three turns of a workgroup; V: eight waves, seven turns
+    (128, 4, 32, 256, 0.0, 32, 1088, False),   # K: twelve waves, 34 groups in three turns
+    (96, 2, 32, 250, 0.5, 32, 1088, False),
+    (128, 2, 128, 200, 0.0, 32, 1152, False),  # K: four groups of 128 tokens side by side, nine in three turns
+    (256, 2, 64, 128, 0.5, 16, 1088, False),   # K: eight waves, two turns and a workgroup with a single group; V: twelve waves, three turns
+    (256, 4, 32, 120, 0.0, 16, 1088, False),
+    (256, 2, 128, 128, 0.0, 32, 1152, False),  # K: two groups of 128 tokens side by side, nine in five turns
+    (256, 2, 64, 250, 0.0, 32, 1088, False),   # K: four waves, five turns; V: eight waves, nine turns
+    (128, 2, 64, 250, 0.0, 24, 1984, True), (128, 4, 32, 160, 0.5, 24, 1984, True), (256, 2, 64, 120, 0.0, 24, 1984, True),
+    (256, 2, 128, 128, 0.0, 24, 1920, True), (128, 2, 128, 250, 0.0, 24, 1920, True),
+])
+def test_quantizers_of_jobs_of_several_rounds(pk, d, bits, G, P, rho, n_seq, T, ragged):
+    """Hundreds of streams with tables of their own, so many that a workgroup's waves take several groups one after the other, also with
+    sequences of very different lengths (one of them empty).  The first, a middle and the last sequence's part of the cache equals, byte
+    for byte, what their vectors give alone, in jobs of eight streams, whose shapes other tests compare with the oracle."""
+    hkv, F = 8, max(G, 64)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + P + G + n_seq)
+    center = torch.randn((n_seq, hkv, P, d), generator=gen, device="cuda")
+    pick = torch.randint(0, P, (n_seq, hkv, T), generator=gen, device="cuda")
+    x = torch.gather(center, 2, pick[..., None].expand(-1, -1, -1, d))
+    x = (x + 0.5 * torch.randn(x.shape, generator=gen, device="cuda")).half()
+    v = x.flip(2).contiguous()
+    Mk = (center + 0.2 * torch.randn(center.shape, generator=gen, device="cuda")).half()
+    Mv = Mk.flip(2).contiguous()
+    kw = dict(n_kv_heads=hkv, n_q_heads=hkv, head_dim=d, n_patterns=P, bits=bits, group=G, recent=0, flush=F, t_capacity=T, v_rho=rho)
+    cfg = pk.Config(n_seq=n_seq, seqs_per_set=1, **kw)
+    whole = pk.Cache(cfg)
+    sets = Mk.view(n_seq * hkv, P, d), Mv.view(n_seq * hkv, P, d)
+    lens = [T] * n_seq
+    if ragged:
+        lens = [T, 0] + [F * (1 + (37 * i) % (T // F)) for i in range(n_seq - 2)]
+        states = [[0, 0, 0] for _ in range(n_seq)]
+        pk.pk_quantize_append_ragged(cfg, whole, states, x, v, lens, *sets)
+        assert [s[0] for s in states] == lens
+    else:
+        pk.pk_quantize_append(cfg, whole, x, v, *sets)
+        assert whole.t_quant == T
+    for i in (0, 1, n_seq // 2, n_seq - 1):
+        one = pk.Cache(pk.Config(n_seq=1, seqs_per_set=0, **kw))
+        if lens[i]:
+            pk.pk_quantize_append(one.cfg, one, x[i:i + 1, :, :lens[i]].contiguous(), v[i:i + 1, :, :lens[i]].contiguous(), Mk[i], Mv[i])
+        part = whole.sequence(i)
+        for name in ("k_codes", "k_scale", "k_zero", "k_idx", "v_codes", "v_scale", "v_zero", "v_idx"):
+            assert torch.equal(part.array(name), one.array(name)), (i, name)
 
 
 @pytest.mark.parametrize("d,P,T,sets", [(128, 16, 300, 3), (128, 64, 1100, 2), (128, 128, 700, 2), (96, 40, 513, 2), (256, 33, 600, 2), (128, 30, 3000, 90)])

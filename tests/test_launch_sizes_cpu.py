@@ -1,0 +1,97 @@
+"""The quantizers' cut of a job into workgroups (large pattern tables), compiled for the host: what a chip of 256 CUs that hands
+workgroups out as places become free would take for it, against the work spread evenly.  No GPU is needed."""
+import heapq
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+DRIVER = """
+#include "pk_cut.h"
+#include <stdio.h>
+int main()
+{
+    int n_tiles, n_streams, ragged, by_lds, waves, waves_per_cu, multiple;
+    long long tiles;
+    while (scanf("%d %d %lld %d %d %d %d %d", &n_tiles, &n_streams, &tiles, &ragged, &by_lds, &waves, &waves_per_cu, &multiple) == 8) {
+        const pk::Cut c = pk::cut_streams({n_tiles, n_streams, tiles, ragged != 0, 4.f}, by_lds, waves, waves_per_cu, multiple);
+        printf("%d %g\\n", c.tiles, c.cost);
+    }
+    return 0;
+}
+"""
+# (workgroups that the LDS holds, waves, waves that registers allow, tiles side by side)
+SHAPES = [(1, 12, 12, 12), (2, 4, 12, 4), (1, 4, 8, 4), (1, 8, 8, 8), (2, 8, 16, 4), (1, 8, 12, 2), (1, 12, 12, 3), (3, 4, 16, 1)]
+STAGING = 4
+
+
+@pytest.fixture(scope="module")
+def cut(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("cut")
+    (d / "driver.cpp").write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2510_05176_amd", "csrc"), str(d / "driver.cpp"),
+                    "-o", str(d / "driver")], check=True)
+
+    def run(jobs):
+        text = "\n".join(" ".join(str(int(v)) for v in j) for j in jobs)
+        lines = subprocess.run([str(d / "driver")], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
+        return [(int(t), float(cost)) for t, cost in (line.split() for line in lines)]
+    return run
+
+
+def _makespan(jobs, places):
+    """Jobs started in order, each as soon as a place is free."""
+    free = [0.0] * places
+    for j in jobs:
+        heapq.heapreplace(free, free[0] + j)
+    return max(free)
+
+
+def _loss(lengths, t, shape):
+    """Time of the cut over that of the same work in equal shares with one workgroup per stream (and one round of a workgroup's waves,
+    which nothing avoids)."""
+    by_lds, waves, waves_per_cu, multiple = shape
+    beside = max(1, min(by_lds, waves_per_cu // waves))
+    chunks = [min(t, n - s) for s in range(0, max(lengths), t) for n in lengths if n > s]
+    took = _makespan([c * beside + STAGING for c in chunks], 256 * beside)
+    return took / (sum(lengths) / 256 + STAGING * -(-len(lengths) // (256 * beside)) + multiple * beside)
+
+
+def test_cut_leaves_no_round_nearly_empty(cut):
+    """Any number of streams and any length: at most 1.5 times the evenly spread work where a CU takes one workgroup, 1.9 times where it takes
+    several (one alone is counted here as slow as among others, which it is not).  One workgroup per CU, computed from the tiles of
+    all streams, takes a second round as long as the first from 257 streams on."""
+    rng = random.Random(3)
+    jobs = [(n, s) for s in (8, 64, 200, 256, 257, 260, 288, 320, 384, 400, 511, 513, 640, 1024, 3000) for n in (1, 2, 5, 16, 33, 64, 128, 500)]
+    jobs += [(rng.randint(1, 600), rng.randint(1, 2000)) for _ in range(60)]
+    for shape in SHAPES:
+        for (n, s), (t, _) in zip(jobs, cut([(n, s, n * s, 0, *shape) for n, s in jobs])):
+            assert t > 0 and t % shape[3] == 0
+            loss = _loss([n] * s, t, shape)
+            assert loss < (1.5 if shape[0] == 1 else 1.9), (shape, n, s, t, loss)
+
+
+def test_cut_of_a_ragged_job_follows_the_tiles_that_exist(cut):
+    """Sequences of very different lengths, one long one among short ones among them: at most 1.7 times the evenly spread work."""
+    rng = random.Random(4)
+    jobs = [[512] + [8] * 15, [512] * 2 + [30] * 30, [128] * 3, [64, 1]]
+    jobs += [[rng.randint(1, hi) for _ in range(rng.randint(2, 40))] for hi in (8, 64, 512, 2000) for _ in range(6)]
+    jobs = [[n for n in j for _ in range(8)] for j in jobs]   # eight heads of a sequence
+    for shape in SHAPES:
+        for j, (t, _) in zip(jobs, cut([(max(j), len(j), sum(j), 1, *shape) for j in jobs])):
+            assert t > 0 and t % shape[3] == 0
+            loss = _loss(j, t, shape)
+            assert loss < 1.7, (shape, max(j), len(j), sum(j), t, loss)
+
+
+def test_cut_of_extreme_jobs(cut):
+    """A single tile, a single stream of millions of vectors, hundreds of thousands of streams."""
+    jobs = [(1, 1, 1, 0), (1, 1, 0, 1), (1 << 17, 1, 1 << 17, 0), (1, 1 << 19, 1 << 19, 0), (1 << 17, 1 << 12, 1 << 29, 0), (1 << 15, 4096, 1 << 15, 1)]
+    for shape in SHAPES:
+        for t, _ in cut([(*j, *shape) for j in jobs]):
+            assert 0 < t < 1 << 20 and t % shape[3] == 0
