@@ -58,4 +58,13 @@ inline Cut cut_streams(const Job &j, int by_lds, int waves, int waves_per_cu, in
     return best;
 }
 
+// V quantizer beside a small table: two blocks per pass over it, four waves per SIMD either way.  Pays from 16 blocks per stream and 2048 in
+// all on (256 streams x 8192 vectors: at 113 patterns 177 -> 165 us, 64 176 -> 162, 16 132 -> 129); below, one is faster (1024 x 320 at 64
+// patterns 25.2 and 25.9, 4096 x 64 26.5 and 31.2, 8 x 4096 at 128 7.7 and 8.2).  Not with given indices (131 and 134); with
+// 4 bits beyond 112 patterns only (256 x 8192 at 120 patterns 203 -> 191, at 64 196 and 203).
+inline bool two_blocks_per_pass(int blocks, int n_streams, int P, int bits, bool idx_given)
+{
+    return !idx_given && blocks >= 16 && (int64_t)blocks * n_streams >= 2048 && (bits == 2 || P > 112);
+}
+
 }  // namespace pk

@@ -1225,31 +1225,32 @@ struct KWaves {
     }
 };
 
-// Waves per workgroup: as many as registers allow per CU (three per SIMD, two for 64-token groups of 256 channels) once the table
-// leaves room for one workgroup only (beyond 128 patterns; 64 of 256 channels, whose table beyond 128 leaves room for four waves).
-// Four waves there were one per SIMD: 256 streams x 8192 vectors at 256 patterns 489 -> 300 us (eight waves 318), at 160 301 -> 262 (282), in
-// 32-token groups 328 -> 280 (310); 96 channels, 256 x 4096 at 200 patterns 146 -> 104 (120); 256 channels, 128 x 4096 at 128
-// patterns 196 -> 140, in 32-token groups 201 -> 128.  A job of at most four groups per CU takes four waves, each a group (64
-// groups of 8 x 1024 vectors, 256 patterns: 21 us, in six workgroups of twelve waves 26).
+// Large tables: four waves per workgroup, or as many as registers allow per CU, whichever cut is modelled to take less.  Twelve (eight
+// with 64-token groups of 256 channels) pay where the table leaves room for one workgroup only, which with four has one wave per SIMD
+// (288 streams x 64 vectors at 256 patterns 25.7 us with twelve, 27.3 with four; x 4096: 169 and 234), not where two of four fit (at
+// 200 patterns 22 and 14, 154 and 152) unless twelve make a whole round (256 streams x 4096: 112 and 119), and not in small jobs, whose
+// workgroups are then too few (8 x 4096 at 256 patterns 26 and 16).
+template <class MANY, class FOUR>
+static hipError_t launch_k_large(const QuantArgs &a, hipStream_t s)
+{
+    const Cut many = MANY::cut(a), four = FOUR::cut(a);
+    return many.cost < four.cost ? MANY::launch(a, s, many.tiles) : FOUR::launch(a, s, four.tiles);
+}
+
 template <int D, int G, int BITS>
 static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
 {
-    const bool few = (int64_t)(a.nq / G) * a.n_streams <= 1024;
     if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
         using Four = KWaves<D, G, BITS, 2, 4>;
-        using Eight = KWaves<D, G, BITS, 2, 8>;
-        if (large_table<D>(a.P) && a.P <= 128 && !few) return Eight::launch(a, s, Eight::cut(a).tiles);
-        return large_table<D>(a.P) ? Four::launch(a, s, Four::cut(a).tiles) : Four::launch(a, s);
+        if (a.P > 128) return Four::launch(a, s, Four::cut(a).tiles);   // (more waves don't fit beside the table)
+        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 2, 8>, Four>(a, s);
+        return Four::launch(a, s);
     } else if constexpr (G == 64) {   // the whole group per table pass (256 x 8192 at 64 patterns 220 -> 187 us); pairs up to 32 patterns
-        using Four = KWaves<D, G, BITS, 4, 4>;
-        using Twelve = KWaves<D, G, BITS, 4, 12>;
-        if (large_table<D>(a.P)) return few ? Four::launch(a, s, Four::cut(a).tiles) : Twelve::launch(a, s, Twelve::cut(a).tiles);
-        return a.P > 32 ? Four::launch(a, s) : KWaves<D, G, BITS, 2, 4>::launch(a, s);
+        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 4, 12>, KWaves<D, G, BITS, 4, 4>>(a, s);
+        return a.P > 32 ? KWaves<D, G, BITS, 4, 4>::launch(a, s) : KWaves<D, G, BITS, 2, 4>::launch(a, s);
     } else {                          // 32-token groups gain from pairs only once the table is large
-        using Four = KWaves<D, G, BITS, 2, 4>;
-        using Twelve = KWaves<D, G, BITS, 2, 12>;
-        if (large_table<D>(a.P)) return few ? Four::launch(a, s, Four::cut(a).tiles) : Twelve::launch(a, s, Twelve::cut(a).tiles);
-        return a.P >= 128 ? Four::launch(a, s) : KWaves<D, G, BITS, 1, 4>::launch(a, s);
+        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 2, 12>, KWaves<D, G, BITS, 2, 4>>(a, s);
+        return a.P >= 128 ? KWaves<D, G, BITS, 2, 4>::launch(a, s) : KWaves<D, G, BITS, 1, 4>::launch(a, s);
     }
 }
 
@@ -1273,9 +1274,13 @@ static hipError_t launch_k_bits(const QuantArgs &a, hipStream_t s)
     using One = KGroups<D, BITS, 1, 1>;
     if (!large_table<D>(a.P)) return One::launch(a, s, tiles_per_wg(a.nq / 128, a.n_streams));
     if constexpr (D == 256) {
-        using Two = KGroups<D, BITS, 2, 1>;
-        if (a.P <= 128) return Two::launch(a, s, Two::cut(a).tiles);
-        return One::launch(a, s, One::cut(a).tiles);
+        const Cut one = One::cut(a);
+        if (a.P <= 128 && a.nq >= 256) {
+            using Two = KGroups<D, BITS, 2, 1>;
+            const Cut two = Two::cut(a);
+            if (two.cost < one.cost) return Two::launch(a, s, two.tiles);
+        }
+        return One::launch(a, s, one.tiles);
     } else {   // four groups, or two of twice the waves where workgroups are short
         using Two = KGroups<D, BITS, 2, 1>;
         using Four = KGroups<D, BITS, 4, 2>;
@@ -1320,23 +1325,34 @@ struct VWaves {
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
 {
-    // Two blocks per table pass, and the waves per workgroup that fill a CU beside a table that leaves room for two workgroups or
-    // one: 256 streams x 8192 vectors, one block and two (four waves per SIMD either way): 64 patterns 176 -> 162 us, 100 219 -> 197, with the
-    // adaptive threshold 216 -> 191, 16 132 -> 129.  One block where a wave has one or two only (8 x 4096: 8.3 and 9.7 us), with
-    // given indices (131 and 134) and with 4 bits up to 127 patterns (196 and 203).  Eight waves beyond 128 patterns: 256 patterns 302 -> 263,
-    // 200 of 96 channels 142 -> 99; 256 channels, 128 x 4096 vectors: 128 patterns 163 -> 87 with twelve, 250 231 -> 133 with eight.
-    if constexpr (D != 256) {
-        using Eight = VWaves<D, BITS, NG, 2, 8>;
-        if (large_table<D>(a.P)) return Eight::launch(a, s, Eight::cut(a).tiles);
-        const bool many = (int64_t)(a.nq / 64) * a.n_streams >= 2048;
-        if (a.P == 128 || (BITS == 2 && many && !a.idx_given)) return VWaves<D, BITS, NG, 2, 4>::launch(a, s, (tiles_per_wg(a.nq / 64, a.n_streams) + 1) / 2 * 2);
-    } else {
-        using Eight = VWaves<D, BITS, NG, 1, 8>;
-        using Twelve = VWaves<D, BITS, NG, 1, 12>;
-        if (a.P > 128) return Eight::launch(a, s, Eight::cut(a).tiles);
-        if (large_table<D>(a.P)) return Twelve::launch(a, s, Twelve::cut(a).tiles);
+    // The waves per workgroup that fill a CU beside a table that leaves room for two workgroups or one: eight (256 streams x 8192 vectors at
+    // 256 patterns 250 -> 222 us, 288 x 1024 at 200 patterns of 256 channels 120 -> 83); up to 128 patterns of 256 channels twelve
+    // or four by their cuts (at 128 patterns 512 x 4096 335 with four, 309 with twelve; 288 x 64 12 and 18).  With eight waves of up to 128
+    // channels two blocks per table pass; where a stream has one or two, they would repeat one (4096 x 64 at 256 patterns 81 -> 66,
+    // 4096 x 128 at 160 76 -> 61).
+    using Plain = VWaves<D, BITS, NG, 1, 4>;
+    const int blocks = a.nq / 64;
+    if (large_table<D>(a.P)) {
+        const Cut plain = Plain::cut(a);
+        if constexpr (D == 256) {
+            if (a.P > 128) {
+                using Eight = VWaves<D, BITS, NG, 1, 8>;
+                return Eight::launch(a, s, Eight::cut(a).tiles);
+            }
+            using Twelve = VWaves<D, BITS, NG, 1, 12>;
+            const Cut twelve = Twelve::cut(a);
+            if (twelve.cost < plain.cost) return Twelve::launch(a, s, twelve.tiles);
+        } else if (blocks > 2) {
+            using Eight = VWaves<D, BITS, NG, 2, 8>;
+            return Eight::launch(a, s, Eight::cut(a).tiles);
+        }
+        return Plain::launch(a, s, plain.tiles);
     }
-    return VWaves<D, BITS, NG, 1, 4>::launch(a, s, tiles_per_wg(a.nq / 64, a.n_streams));
+    const int t = tiles_per_wg(blocks, a.n_streams);
+    if constexpr (D != 256) {
+        if (two_blocks_per_pass(blocks, a.n_streams, a.P, BITS, a.idx_given != 0)) return VWaves<D, BITS, NG, 2, 4>::launch(a, s, (t + 1) / 2 * 2);
+    }
+    return Plain::launch(a, s, t);
 }
 
 template <int D, int BITS>

@@ -14,9 +14,13 @@ DRIVER = """
 #include <stdio.h>
 int main()
 {
-    int n_tiles, n_streams, ragged, by_lds, waves, waves_per_cu, multiple;
+    int n_tiles, n_streams, ragged, by_lds, waves, waves_per_cu, multiple;   // waves 0: two_blocks_per_pass(blocks, streams, patterns, bits, given)
     long long tiles;
     while (scanf("%d %d %lld %d %d %d %d %d", &n_tiles, &n_streams, &tiles, &ragged, &by_lds, &waves, &waves_per_cu, &multiple) == 8) {
+        if (waves == 0) {
+            printf("%d 0\\n", pk::two_blocks_per_pass(n_tiles, n_streams, ragged, by_lds, multiple != 0));
+            continue;
+        }
         const pk::Cut c = pk::cut_streams({n_tiles, n_streams, tiles, ragged != 0, 4.f}, by_lds, waves, waves_per_cu, multiple);
         printf("%d %g\\n", c.tiles, c.cost);
     }
@@ -95,3 +99,25 @@ def test_cut_of_extreme_jobs(cut):
     for shape in SHAPES:
         for t, _ in cut([(*j, *shape) for j in jobs]):
             assert 0 < t < 1 << 20 and t % shape[3] == 0
+
+
+def test_many_waves_need_many_groups(cut):
+    """A flush of one or two blocks over thousands of streams, beside a table that leaves room for two workgroups of four waves: those, and
+    not one of twelve of which ten idle.  Beside a table that leaves room for one workgroup, and in long jobs of a stream per CU, twelve."""
+    four, twelve, alone = (2, 4, 12, 4), (1, 12, 12, 12), (1, 4, 12, 4)
+    for n, s in ((1, 4096), (2, 4096), (4, 2048), (1, 288), (2, 1024)):
+        few, many, single = cut([(n, s, n * s, 0, *shape) for shape in (four, twelve, alone)])
+        assert few[1] < many[1] < single[1], (n, s)
+    few, many = cut([(128, 256, 128 * 256, 0, *shape) for shape in (four, twelve)])
+    assert many[1] < few[1]
+
+
+def test_two_blocks_per_pass_need_blocks(cut):
+    """One or a few blocks per stream, however many streams, never take two per pass (the second would repeat the first); jobs of many
+    blocks do, with no difference between table sizes that are padded to the same number of rows."""
+    def two(blocks, streams, P, bits, given=0):
+        return cut([(blocks, streams, 0, P, bits, 0, 0, given)])[0][0]
+    for P in (1, 64, 112, 113, 120, 127, 128):
+        assert not two(1, 4096, P, 2) and not two(2, 1 << 16, P, 2) and not two(64, 8, P, 2) and not two(128, 256, P, 2, given=1)
+        assert two(128, 256, P, 2) and two(16, 1024, P, 2)
+        assert two(128, 256, P, 4) == two(128, 256, -(-P // 16) * 16, 4)
