@@ -1418,3 +1418,89 @@ def test_decode_merges_heads_together(pk, hkv, r, bits, G, P, prefix):
     limit = 4e-6 * one.abs().amax(2, keepdim=True)
     assert ((many - one).abs() <= limit).all()
     assert ((many_lse - one_lse).abs() <= 4e-6 * (1 + one_lse.abs())).all()
+
+
+def _attention_of_streams(q, streams, scale):
+    """q [S, hkv, r, d] and, per stream in that order, the list of its (K, V) parts -> attention and log-sum-exp in 64 bits."""
+    S, hkv, r, d = q.shape
+    out = torch.zeros((S, hkv, r, d), dtype=torch.float64, device="cuda")
+    lse = torch.full((S, hkv, r), -torch.inf, dtype=torch.float64, device="cuda")
+    for n, parts in enumerate(streams):
+        k, v = (torch.cat([p[i].double() for p in parts]) for i in range(2))
+        if len(k):
+            s = q[n // hkv, n % hkv].double() @ k.T.contiguous() * scale
+            lse[n // hkv, n % hkv] = torch.logsumexp(s, -1)
+            out[n // hkv, n % hkv] = torch.softmax(s, -1) @ v
+    return out, lse
+
+
+@pytest.mark.parametrize("S,hkv,r,bits,G,P,T,prefix,ragged,rho", [
+    (16, 8, 7, 2, 64, 130, 3000, 0, False, 0.0),    # four own splits, two groups of heads
+    (64, 1, 16, 2, 64, 24, 5000, 0, False, 0.8),    # eight own splits, four groups of heads; 256 mass slots per head
+    (64, 2, 5, 2, 64, 33, 2100, 900, False, 0.0),   # own splits and the shared prompt's; a group with one head
+    (32, 8, 2, 4, 64, 40, 2300, 500, False, 0.0),   # pairs of heads
+    (40, 8, 4, 2, 64, 64, 4200, 0, True, 0.0),      # sequences of different lengths, one empty, one with a tail only
+    (64, 2, 8, 2, 64, 20, 2600, 700, True, 0.0),
+    (64, 1, 16, 2, 64, 16, 300, 2200000, False, 0.0),   # more slots than a wave has lanes
+])
+def test_decode_merge_of_different_sequences(pk, S, hkv, r, bits, G, P, T, prefix, ragged, rho):
+    """The merge that takes the heads of a KV head together (256 groups of heads and more): sequences with vectors, queries and tables of
+    their own, several splits, against attention in 64 bits over the reconstructed cache, every row within the bar of 2e-3."""
+    d, F, R = 128, 64, 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S + P + T)
+    rand = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    k, v = (rand(S, hkv, T, d).half() for _ in range(2))
+    Mk, Mv = (rand(S * hkv, P, d).half() for _ in range(2))
+    q = rand(S, hkv * r, d).half()
+    lens = [T] * S
+    if ragged:
+        lens = [T, 0, R + 3] + [1 + (97 * i * i) % T for i in range(S - 3)]
+    kw = dict(n_kv_heads=hkv, n_q_heads=hkv * r, head_dim=d, n_patterns=P, bits=bits, group=G, recent=R, flush=F, v_rho=rho)
+    cfg = pk.Config(n_seq=S, seqs_per_set=1, t_capacity=-(-T // F) * F, **kw)
+    cache, pre = pk.Cache(cfg), None
+    states = [[0, 0, 0] for _ in range(S)]
+    seq_states = torch.zeros((S, 4), dtype=torch.int32, device="cuda")
+    if ragged:
+        pk.pk_quantize_append_ragged(cfg, cache, states, k, v, lens, Mk, Mv, seq_states_out=seq_states)
+    else:
+        pk.pk_quantize_append(cfg, cache, k, v, Mk, Mv)
+        states = [[cache.t_quant, cache.t_tail, cache.tail_start]] * S
+    common = []
+    if prefix:
+        pcfg = pk.Config(n_seq=1, seqs_per_set=0, t_capacity=-(-prefix // F) * F, **kw)
+        pre = pk.Cache(pcfg)
+        pkv = rand(2, 1, hkv, min(prefix, 4096), d).half()
+        pkv = pkv.repeat(1, 1, 1, -(-prefix // pkv.shape[3]), 1)[:, :, :, :prefix].contiguous()
+        # (the shared prompt's tables: the first set of every head)
+        pk.pk_quantize_append(pcfg, pre, pkv[0], pkv[1], Mk[:hkv].contiguous(), Mv[:hkv].contiguous())
+        pd = pk.pk_dequantize(pcfg, pre, Mk[:hkv].contiguous(), Mv[:hkv].contiguous())
+        common = [[(pd[0][h], pd[1][h]), (pkv[0, 0, h, pre.t_quant:], pkv[1, 0, h, pre.t_quant:])] for h in range(hkv)]
+    if prefix > 1 << 20:
+        assert pk.pk_decode_plan(cfg, states[0][0], pre.t_quant)[1] > 66
+    lse = torch.empty((S, hkv * r), dtype=torch.float32, device="cuda")
+    if ragged:
+        got = pk.pk_decode_attention_ragged(cfg, cache, seq_states, max(s[0] for s in states), max(s[1] for s in states), q, d ** -0.5, Mk, Mv,
+                                            lse=lse, prefix=pre)
+    else:
+        got = pk.pk_decode_attention(cfg, cache, q, d ** -0.5, Mk, Mv, lse=lse, prefix=pre)
+    picked = range(S) if prefix <= 1 << 20 else (0, S // 2, S - 1)
+    streams = []
+    for i in picked:
+        part = cache.sequence(i)
+        part.state = pk._State(*states[i])
+        tq = states[i][0]
+        kd, vd = pk.pk_dequantize(part.cfg, part, Mk[i * hkv:(i + 1) * hkv], Mv[i * hkv:(i + 1) * hkv]) if tq else (k[i, :, :0].float(), v[i, :, :0].float())
+        for h in range(hkv):
+            streams.append((common[h] if prefix else []) + [(kd[h], vd[h]), (k[i, h, tq:lens[i]], v[i, h, tq:lens[i]])])
+    rows = torch.tensor(list(picked), device="cuda")
+    want, want_lse = _attention_of_streams(q[rows].view(-1, hkv, r, d), streams, d ** -0.5)
+    want, want_lse = want.view(-1, hkv * r, d), want_lse.view(-1, hkv * r)
+    got, got_lse = got[rows].double(), lse[rows].double()
+    for j, i in enumerate(picked):
+        if lens[i] + prefix == 0:
+            assert torch.all(got[j] == 0) and torch.all(torch.isneginf(got_lse[j]))
+        else:
+            err = (got[j] - want[j]).norm(dim=1) / want[j].norm(dim=1)
+            assert float(err.max()) <= 2e-3, (i, float(err.max()))
+            assert float((got_lse[j] - want_lse[j]).abs().max()) <= 2e-3, i
