@@ -299,10 +299,10 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
             hipLaunchKernelGGL((decode_tail_kernel<8>), grid, dim3(256), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    // four parts per channel when a thread would otherwise walk many slots or patterns alone and the
-    // (sequence, head) pairs are too few to fill the chip with 128-thread workgroups; eight when there are hundreds
-    // of slots and patterns for a few heads only (config 5: 28 heads, 130 slots, 256 patterns: 17 -> 13 us)
-    // heads of a KV head together wherever that leaves a workgroup for every CU
+    // Heads of a KV head together wherever that leaves a workgroup for every CU.  Elsewhere a head at a time: four parts per channel
+    // when a thread would otherwise walk many slots or patterns alone and the (sequence, head) pairs are too few to fill the
+    // chip with 128-thread workgroups; eight when there are hundreds of slots and patterns for a few heads only (28 heads, 130
+    // slots, 256 patterns: 17 -> 13 us).
     const int slots = a.splits_prefix + a.splits_own + 2;
     if (r > 1 && N * ((r + 3) / 4) >= 256) {
         const size_t lds = (size_t)(slots + 2 * a.P) * (r == 2 ? 2 : 4) * 4;   // at most 45 KB

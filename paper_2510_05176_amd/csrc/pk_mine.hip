@@ -82,7 +82,7 @@ typedef _Float16 half2m __attribute__((ext_vector_type(2)));
 typedef short short4m __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4m *lds_short4_ptr;
 
-constexpr bool step_sorts(int D, int NPT, int NW) { return NW <= 8 && (NPT == 16 || (NPT == 8 && D <= 128)); }
+constexpr bool step_sorts(int D, int NPT) { return NPT == 16 || (NPT == 8 && D <= 128); }
 
 template <int D, int NPT, int NW, int NT, int XC>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1 && NPT <= 4 && D <= 128 ? 4 : 2))) void mine_step_kernel(MineArgs a, int chunk, int outputs)
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NT == 1
     constexpr int ST = 16 * NT * NW;     // vectors per sub-tile: NT 16-vector tiles per wave
     __half *idx_s = xs + ST * kXs;       // pattern index of every row of the sub-tile, as an fp16 number
     __shared__ float red_s[NW];
-    constexpr bool kSort = step_sorts(D, NPT, NW);
+    constexpr bool kSort = step_sorts(D, NPT);
     constexpr int kStepUnroll = kSort ? 1 : ST / 32;
     __shared__ int bucket_s[kSort ? NW * NW : 1];   // [bucket][wave]: vectors of the wave's in the bucket (the pattern rows that one wave sums)
 

@@ -612,10 +612,11 @@ __device__ __forceinline__ void k_store_staging(const QuantArgs &a, int64_t tok0
 }
 
 // K, groups of 128 tokens: 8 / NT waves take one group at a time, NT 16-token tiles each.  Every wave reduces its own tokens
-// per channel (scan_channels) and leaves the minima and maxima in its LDS tile; between two barriers a thread per channel
-// combines them and forms the parameters.  A workgroup holds GR groups side by side.  Beyond 128 patterns (up to 128
-// channels) the table leaves room for one workgroup per CU only: sixteen waves cover the barriers' latency, in four groups
-// with two tiles per pass over the table where a workgroup has that many groups to take, else in two.
+// per channel (ChannelScan) and leaves the minima and maxima in its LDS tile; between two barriers a thread per channel
+// combines them and forms the parameters.  A workgroup holds GR groups side by side.  Beyond 128 patterns of up to 128
+// channels the table leaves room for one workgroup per CU only: sixteen waves cover the barriers' latency, in four groups
+// with two tiles per pass over the table where a workgroup has that many groups to take, else in two.  At 256 channels a workgroup has
+// two groups from 65 to 128 patterns where that cut is modelled to take less, else one (beyond 128 there is no room for two).
 // (A residual tile of the whole group in LDS, scanned by columns, took 68 KB at 128 channels beside the table: one workgroup
 // per CU from 128 patterns on, and no room at all at 256 channels.  Appends, K and V: 256 streams x 8192 at 64 patterns 374
 // -> 349 us; 64 streams, 4 bits, 128 patterns 174 -> 150; 4 streams x 131072 at 256 patterns, with the first decode, 220 ->
@@ -899,10 +900,10 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
     return x;
 }
 
-// V: workgroup = 256 threads, blocks of 64 tokens of one stream; wave w owns the 16-token unit w of the
-// block.  NG = channel groups per token (D / Gc).  NT = blocks taken together: the wave assigns its units of
-// NT consecutive blocks in one pass over the pattern table (every table tile read from LDS serves all of
-// them), then quantizes them one after the other.
+// V: workgroup = NW waves (4, 8 or 12), blocks of 64 tokens of one stream; wave w owns the 16-token unit w % 4 of its blocks, and
+// waves 4i .. 4i + 3 take the i-th NT blocks of a round of NW / 4 * NT.  NG = channel groups per token (D / Gc).  NT = blocks taken
+// together: the wave assigns its units of NT consecutive blocks in one pass over the pattern table (every table tile read
+// from LDS serves all of them), then quantizes them one after the other.
 template <int D, int BITS, int NG, int NT, int NW>
 __global__ __launch_bounds__(64 * NW) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
 {
