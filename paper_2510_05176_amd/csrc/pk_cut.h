@@ -58,6 +58,14 @@ inline Cut cut_streams(const Job &j, int by_lds, int waves, int waves_per_cu, in
     return best;
 }
 
+// V quantizer beside a large table of up to 128 channels: eight waves and two blocks per pass over the table, or four waves and one
+// (`plain`), by the modelled time of their cuts.  Two blocks per pass, of which the model knows nothing, are worth a fifteenth.  Few
+// blocks lie better in many small workgroups (eight waves and four, 256 patterns: 8 x 2048 vectors 17.7 and 12.1 us, 128 x 256 18.3
+// and 17.1; at 136 8 x 1024 12.8 and 9.3), many in large ones (128 x 1024 27.7 and 31.0, 512 x 1024 72.5 and 87.6).  Up to three blocks of
+// a stream are four in pairs (1024 x 192 at 144 patterns of 128 channels 13 % slower).  Over 119 timings (8 to 2048 streams of 3
+// to 256 blocks, 136 to 256 patterns) the choice is 0.4 % slower on average than the better of the two, eight waves throughout 12 %.
+inline bool eight_waves(const Cut &eight, const Cut &plain, int blocks) { return blocks > 3 && eight.cost < 1.07f * plain.cost; }
+
 // V quantizer beside a small table: two blocks per pass over it, four waves per SIMD either way.  Pays from 16 blocks per stream and 2048 in
 // all on (256 streams x 8192 vectors: at 113 patterns 177 -> 165 us, 64 176 -> 162, 16 132 -> 129); below, one is faster (1024 x 320 at 64
 // patterns 25.2 and 25.9, 4096 x 64 26.5 and 31.2, 8 x 4096 at 128 7.7 and 8.2).  Not with given indices (131 and 134); with

@@ -1231,8 +1231,9 @@ struct KWaves {
 // (288 streams x 64 vectors at 256 patterns 25.7 us with twelve, 27.3 with four; x 4096: 169 and 234), not where two of four fit (at
 // 200 patterns 22 and 14, 154 and 152) unless twelve make a whole round (256 streams x 4096: 112 and 119), and not in small jobs, whose
 // workgroups are then too few (8 x 4096 at 256 patterns 26 and 16).
+// (The V quantizer's of 256 channels likewise.)
 template <class MANY, class FOUR>
-static hipError_t launch_k_large(const QuantArgs &a, hipStream_t s)
+static hipError_t launch_cheaper(const QuantArgs &a, hipStream_t s)
 {
     const Cut many = MANY::cut(a), four = FOUR::cut(a);
     return many.cost < four.cost ? MANY::launch(a, s, many.tiles) : FOUR::launch(a, s, four.tiles);
@@ -1244,13 +1245,13 @@ static hipError_t launch_k_wave(const QuantArgs &a, hipStream_t s)
     if constexpr (D == 256) {      // (64-token groups: the tiles of a group take 128 registers, so pairs at most)
         using Four = KWaves<D, G, BITS, 2, 4>;
         if (a.P > 128) return Four::launch(a, s, Four::cut(a).tiles);   // (more waves don't fit beside the table)
-        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 2, 8>, Four>(a, s);
+        if (large_table<D>(a.P)) return launch_cheaper<KWaves<D, G, BITS, 2, 8>, Four>(a, s);
         return Four::launch(a, s);
     } else if constexpr (G == 64) {   // the whole group per table pass (256 x 8192 at 64 patterns 220 -> 187 us); pairs up to 32 patterns
-        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 4, 12>, KWaves<D, G, BITS, 4, 4>>(a, s);
+        if (large_table<D>(a.P)) return launch_cheaper<KWaves<D, G, BITS, 4, 12>, KWaves<D, G, BITS, 4, 4>>(a, s);
         return a.P > 32 ? KWaves<D, G, BITS, 4, 4>::launch(a, s) : KWaves<D, G, BITS, 2, 4>::launch(a, s);
     } else {                          // 32-token groups gain from pairs only once the table is large
-        if (large_table<D>(a.P)) return launch_k_large<KWaves<D, G, BITS, 2, 12>, KWaves<D, G, BITS, 2, 4>>(a, s);
+        if (large_table<D>(a.P)) return launch_cheaper<KWaves<D, G, BITS, 2, 12>, KWaves<D, G, BITS, 2, 4>>(a, s);
         return a.P >= 128 ? KWaves<D, G, BITS, 2, 4>::launch(a, s) : KWaves<D, G, BITS, 1, 4>::launch(a, s);
     }
 }
@@ -1326,28 +1327,20 @@ struct VWaves {
 template <int D, int BITS, int NG>
 static hipError_t launch_v_groups(const QuantArgs &a, hipStream_t s)
 {
-    // The waves per workgroup that fill a CU beside a table that leaves room for two workgroups or one: eight (256 streams x 8192 vectors at
-    // 256 patterns 250 -> 222 us, 288 x 1024 at 200 patterns of 256 channels 120 -> 83); up to 128 patterns of 256 channels twelve
-    // or four by their cuts (at 128 patterns 512 x 4096 335 with four, 309 with twelve; 288 x 64 12 and 18).  With eight waves of up to 128
-    // channels two blocks per table pass; where a stream has one or two, they would repeat one (4096 x 64 at 256 patterns 81 -> 66,
-    // 4096 x 128 at 160 76 -> 61).
+    // Beside a table that leaves room for two workgroups or one: the waves per workgroup that fill a CU, or four, whichever cut is modelled
+    // to take less.  Eight (256 streams x 8192 vectors at 256 patterns 222 us, 250 with four; 288 x 1024 at 200 patterns of 256 channels 83
+    // and 120; 8 x 2048 at 136 of 256 17.1 and 15.2); up to 128 patterns of 256 channels twelve (at 128 patterns 512 x 4096 309 and 335; 288 x 64
+    // 18 and 12).  With eight waves of up to 128 channels two blocks per table pass.
     using Plain = VWaves<D, BITS, NG, 1, 4>;
     const int blocks = a.nq / 64;
     if (large_table<D>(a.P)) {
-        const Cut plain = Plain::cut(a);
         if constexpr (D == 256) {
-            if (a.P > 128) {
-                using Eight = VWaves<D, BITS, NG, 1, 8>;
-                return Eight::launch(a, s, Eight::cut(a).tiles);
-            }
-            using Twelve = VWaves<D, BITS, NG, 1, 12>;
-            const Cut twelve = Twelve::cut(a);
-            if (twelve.cost < plain.cost) return Twelve::launch(a, s, twelve.tiles);
-        } else if (blocks > 2) {
+            return a.P > 128 ? launch_cheaper<VWaves<D, BITS, NG, 1, 8>, Plain>(a, s) : launch_cheaper<VWaves<D, BITS, NG, 1, 12>, Plain>(a, s);
+        } else {
             using Eight = VWaves<D, BITS, NG, 2, 8>;
-            return Eight::launch(a, s, Eight::cut(a).tiles);
+            const Cut eight = Eight::cut(a), plain = Plain::cut(a);
+            return eight_waves(eight, plain, blocks) ? Eight::launch(a, s, eight.tiles) : Plain::launch(a, s, plain.tiles);
         }
-        return Plain::launch(a, s, plain.tiles);
     }
     const int t = tiles_per_wg(blocks, a.n_streams);
     if constexpr (D != 256) {

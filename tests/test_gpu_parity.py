@@ -1294,7 +1294,7 @@ def test_quantize_groups_of_128_tokens_side_by_side(pk, d, bits, P, groups):
 
 
 @pytest.mark.parametrize("d,bits,G,P,rho,T", [
-    (128, 2, 64, 200, 0.0, 4416),   # 69 groups per stream; eight waves on the V side
+    (128, 2, 64, 200, 0.0, 4416),   # 69 groups per stream
     (128, 4, 32, 130, 0.8, 2112), (96, 2, 32, 250, 0.0, 2112),
     (128, 2, 64, 40, 0.8, 8256),    # two blocks per table pass on the V side, an odd number of them
     (256, 2, 64, 100, 0.0, 4416), (256, 4, 32, 65, 0.5, 2112),

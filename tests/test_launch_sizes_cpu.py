@@ -15,10 +15,16 @@ DRIVER = """
 int main()
 {
     int n_tiles, n_streams, ragged, by_lds, waves, waves_per_cu, multiple;   // waves 0: two_blocks_per_pass(blocks, streams, patterns, bits, given)
+                                                                             // waves -1: eight_waves, by_lds and multiple workgroups per CU of either
     long long tiles;
     while (scanf("%d %d %lld %d %d %d %d %d", &n_tiles, &n_streams, &tiles, &ragged, &by_lds, &waves, &waves_per_cu, &multiple) == 8) {
         if (waves == 0) {
             printf("%d 0\\n", pk::two_blocks_per_pass(n_tiles, n_streams, ragged, by_lds, multiple != 0));
+            continue;
+        }
+        if (waves == -1) {
+            const pk::Job j = {n_tiles, n_streams, tiles, ragged != 0, 4.f};
+            printf("%d 0\\n", pk::eight_waves(pk::cut_streams(j, by_lds, 8, 16, 4), pk::cut_streams(j, multiple, 4, 16, 1), n_tiles));
             continue;
         }
         const pk::Cut c = pk::cut_streams({n_tiles, n_streams, tiles, ragged != 0, 4.f}, by_lds, waves, waves_per_cu, multiple);
@@ -121,3 +127,16 @@ def test_two_blocks_per_pass_need_blocks(cut):
         assert not two(1, 4096, P, 2) and not two(2, 1 << 16, P, 2) and not two(64, 8, P, 2) and not two(128, 256, P, 2, given=1)
         assert two(128, 256, P, 2) and two(16, 1024, P, 2)
         assert two(128, 256, P, 4) == two(128, 256, -(-P // 16) * 16, 4)
+
+
+@pytest.mark.parametrize("by_lds", [(2, 2), (3, 3)])   # workgroups per CU beside 256 and beside 136 patterns of 128 channels
+def test_eight_waves_need_many_blocks(cut, by_lds):
+    """V beside a large table: jobs whose blocks give every CU at most a workgroup or two of four waves take those (an eight-wave
+    workgroup takes four blocks at least), jobs of many blocks the eight-wave ones; also ragged, by the blocks that exist."""
+    def eight(blocks, streams, tiles=None, ragged=0):
+        return cut([(blocks, streams, tiles or blocks * streams, ragged, by_lds[0], -1, 0, by_lds[1])])[0][0]
+    for blocks, streams in ((4, 8), (16, 8), (32, 8), (64, 8), (4, 32), (16, 32), (4, 128), (1, 4096), (3, 2048)):
+        assert not eight(blocks, streams), (blocks, streams)
+    for blocks, streams in ((64, 128), (256, 8), (4, 512), (128, 256), (2048, 4)):
+        assert eight(blocks, streams), (blocks, streams)
+    assert eight(512, 128, 20000, 1) and not eight(32, 16, 200, 1)
