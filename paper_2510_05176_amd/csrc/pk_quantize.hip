@@ -237,7 +237,7 @@ __device__ __forceinline__ int minmax_nearest(const __half *xrow, const uint32_t
 }
 
 template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void assign_minmax_kernel(QuantArgs a, int tiles_per_wg)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void assign_minmax_kernel(QuantKernelArgs a, int tiles_per_wg)
 {
     constexpr int NC = D / 8;   // 16-byte pieces of a vector
     const int tid = threadIdx.x, lane = tid & 63, ns = blockIdx.y, P = a.P;
@@ -441,7 +441,7 @@ __device__ __forceinline__ PatternTable make_table(const TableLds &sh, int P)
 // B operand of one 16-token tile: vectors i0 .. i0+15 of stream ns (i0 wave-uniform).  A tile without vectors of the ring - nearly
 // all of a long append - takes one scalar address and fixed lane offsets.
 template <int KS>
-__device__ __forceinline__ void load_tile(const QuantArgs &a, int ns, int i0, uint4 (&xb)[KS])
+__device__ __forceinline__ void load_tile(const QuantKernelArgs &a, int ns, int i0, uint4 (&xb)[KS])
 {
     constexpr int D = 32 * KS;
     const int lane = threadIdx.x & 63, n = lane & 15, kb = lane >> 4;
@@ -567,7 +567,7 @@ __device__ __forceinline__ void put_params(float mn, float mx, int bits, int c, 
 
 // Stored parameters of a group, 16-byte pieces by one wave: zero points, then scales
 template <int D>
-__device__ __forceinline__ void store_params(const QuantArgs &a, int64_t group, const uint16_t *pz)
+__device__ __forceinline__ void store_params(const QuantKernelArgs &a, int64_t group, const uint16_t *pz)
 {
     const int lane = threadIdx.x & 63;
     if (D == 256 || lane < D / 4) {
@@ -603,7 +603,7 @@ __device__ __forceinline__ void k_codes8(const float *r, int k, const uint16_t *
 
 // Staging area -> global: the 16 tokens' code words as one contiguous run, then their 16 indices.
 template <int D, int BITS>
-__device__ __forceinline__ void k_store_staging(const QuantArgs &a, int64_t tok0, const uint8_t *stg)
+__device__ __forceinline__ void k_store_staging(const QuantKernelArgs &a, int64_t tok0, const uint8_t *stg)
 {
     constexpr int kBytes = 16 * D * BITS / 8;
     static_assert(kBytes + 16 <= kWkTile, "output staging fits the residual tile");
@@ -625,7 +625,7 @@ template <int D, int NT>
 constexpr int kGroupLds = 8 / NT * kWkTile + kKParams<D>;   // bytes of LDS per group
 
 template <int D, int BITS, int GR, int NT>
-__global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void quantize_k_group_kernel(QuantArgs a, int tiles_per_wg)
+__global__ __launch_bounds__(512 / NT * GR) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4))) void quantize_k_group_kernel(QuantKernelArgs a, int tiles_per_wg)
 {
     constexpr int KS = D / 32, TT = 128, NW = 8 / NT, NTH = 64 * NW;   // waves and threads of a group
     static_assert(2 * D * 4 <= kWkTile, "a wave's minima and maxima fit its tile");
@@ -734,7 +734,7 @@ template <int D>
 constexpr int kWkWave = kWkTile + kKParams<D>;   // bytes of LDS per wave
 
 template <int D, int G, int BITS, int NTA, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 256 && G == 64 ? 2 : 3))) void quantize_k_wave_kernel(QuantArgs a, int tiles_per_wg)
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 256 && G == 64 ? 2 : 3))) void quantize_k_wave_kernel(QuantKernelArgs a, int tiles_per_wg)
 {
     constexpr int NTG = G / 16, KS = D / 32;
     static_assert(G == 32 || G == 64, "a wave holds the group's tiles in registers");
@@ -905,7 +905,7 @@ __device__ __forceinline__ uint32_t transpose16(uint32_t x, const TransposeConst
 // together: the wave assigns its units of NT consecutive blocks in one pass over the pattern table (every table tile read
 // from LDS serves all of them), then quantizes them one after the other.
 template <int D, int BITS, int NG, int NT, int NW>
-__global__ __launch_bounds__(64 * NW) void quantize_v_kernel(QuantArgs a, int tiles_per_wg)
+__global__ __launch_bounds__(64 * NW) void quantize_v_kernel(QuantKernelArgs a, int tiles_per_wg)
 {
     using St = VStaging<D, BITS, NG>;
     constexpr int TT = 64, WPU = BITS / 2, KS = D / 32, BPG = KS / NG;   // BPG = 32-channel blocks per group
