@@ -66,13 +66,27 @@ inline Cut cut_streams(const Job &j, int by_lds, int waves, int waves_per_cu, in
 // to 256 blocks, 136 to 256 patterns) the choice is 0.4 % slower on average than the better of the two, eight waves throughout 12 %.
 inline bool eight_waves(const Cut &eight, const Cut &plain, int blocks) { return blocks > 3 && eight.cost < 1.07f * plain.cost; }
 
-// V quantizer beside a small table: two blocks per pass over it, four waves per SIMD either way.  Pays from 16 blocks per stream and 2048 in
-// all on (256 streams x 8192 vectors: at 113 patterns 177 -> 165 us, 64 176 -> 162, 16 132 -> 129); below, one is faster (1024 x 320 at 64
-// patterns 25.2 and 25.9, 4096 x 64 26.5 and 31.2, 8 x 4096 at 128 7.7 and 8.2).  Not with given indices (131 and 134); with
-// 4 bits beyond 112 patterns only (256 x 8192 at 120 patterns 203 -> 191, at 64 196 and 203).
+inline int tiles_per_wg(int n_tiles, int n_streams)
+{
+    // aim at ~1024 workgroups, each staging the pattern table once for at most 16 tiles; a job of very many
+    // tiles (8 or more resident rounds even then) takes 32 or 64 per workgroup: fewer prologues, and the last,
+    // partly filled round stays a small share (-4 % on the V kernel of config 3, worse on small jobs)
+    const int64_t total = (int64_t)n_tiles * n_streams;
+    const int cap = total >= 64 * 768 * 8 ? 64 : total >= 32 * 768 * 8 ? 32 : 16;
+    const int t = (int)((total + 1023) / 1024);
+    return t < 1 ? 1 : (t > cap ? cap : t);
+}
+
+// V quantizer beside a small table: two blocks per pass over it, four waves per SIMD either way.  A wave takes its unit of all of its
+// workgroup's blocks, so what counts is how many those are: 1024 streams of 2, 4, 6, 8, 10, 14 and 16 blocks take 1.03, 1.02, 1.01, 0.98,
+// 0.98, 0.95 and 0.96 of one block's time at 64 patterns, 1.01, 0.99, 0.97, 0.96, 0.95, 0.95 and 0.94 at 128, 1.03, 1.04, 1.02, 1.00,
+// 1.01, 0.98 and 0.99 at 16; of 3 and 5 blocks, the last of which is searched twice, 1.16 and 1.13.  Likewise 512 streams of twice as
+// many, which workgroups of half a stream share; of 10, in workgroups of five blocks or else six and four, 1.09.  Not with given
+// indices (256 x 8192 vectors 131 and 134 us); with 4 bits beyond 112 patterns only (1024 x 1024 vectors 0.93 at 120 patterns, 1.08 at 64).
 inline bool two_blocks_per_pass(int blocks, int n_streams, int P, int bits, bool idx_given)
 {
-    return !idx_given && blocks >= 16 && (int64_t)blocks * n_streams >= 2048 && (bits == 2 || P > 112);
+    const int own = std::min(tiles_per_wg(blocks, n_streams), blocks), enough = P > 64 ? 6 : P > 32 ? 8 : 12;
+    return !idx_given && own >= enough && (own % 2 == 0 || own >= 16) && (bits == 2 || P > 112);
 }
 
 }  // namespace pk

@@ -1155,17 +1155,6 @@ hipError_t launch_seq_table(const SeqTableArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-static int tiles_per_wg(int n_tiles, int n_streams)
-{
-    // aim at ~1024 workgroups, each staging the pattern table once for at most 16 tiles; a job of very many
-    // tiles (8 or more resident rounds even then) takes 32 or 64 per workgroup: fewer prologues, and the last,
-    // partly filled round stays a small share (-4 % on the V kernel of config 3, worse on small jobs)
-    const int64_t total = (int64_t)n_tiles * n_streams;
-    const int cap = total >= 64 * 768 * 8 ? 64 : total >= 32 * 768 * 8 ? 32 : 16;
-    const int t = (int)((total + 1023) / 1024);
-    return t < 1 ? 1 : (t > cap ? cap : t);
-}
-
 // Workgroups of at most `tiles` tiles of one stream each.  max_lds: the most that the instantiation is launched with.
 template <auto KERNEL, int THREADS = 256>
 static hipError_t launch_tiled(const QuantArgs &a, int TT, size_t lds, size_t max_lds, hipStream_t s, int tiles)

@@ -140,3 +140,14 @@ def test_eight_waves_need_many_blocks(cut, by_lds):
     for blocks, streams in ((64, 128), (256, 8), (4, 512), (128, 256), (2048, 4)):
         assert eight(blocks, streams), (blocks, streams)
     assert eight(512, 128, 20000, 1) and not eight(32, 16, 200, 1)
+
+
+def test_two_blocks_per_pass_share_evenly(cut):
+    """What counts is how many blocks a workgroup has: an odd few leave the last one to be searched twice, few are not worth it, fewer are
+    enough beside larger tables."""
+    def two(blocks, streams, P):
+        return cut([(blocks, streams, 0, P, 2, 0, 0, 0)])[0][0]
+    for P in (40, 64, 100, 128):
+        assert two(8, 2048, P) and two(14, 1024, P) and two(20, 1024, P) and two(16, 512, P) and two(32, 512, P)
+        assert not any(two(b, n, P) for b, n in ((3, 4096), (5, 4096), (9, 1024), (10, 512), (20, 256), (4, 4096), (16, 256)))
+    assert two(6, 1024, 128) and not two(6, 1024, 64) and not two(10, 1024, 16) and two(12, 1024, 16)
