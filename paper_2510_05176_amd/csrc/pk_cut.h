@@ -30,7 +30,7 @@ struct Cut {
 // Ragged appends: the tiles that exist in equal shares, one workgroup that ends last, half a workgroup per stream for the remainders, and
 // half a staging for every workgroup behind its sequence's end.  Counted by the longest sequence they were cut far too coarsely: one
 // prompt of 32k vectors among fifteen of 512, 8 heads, 256 patterns: K 395 us, V 222; 70 and 46 now.
-inline Cut cut_streams(const Job &j, int by_lds, int waves, int waves_per_cu, int multiple)
+inline Cut cut_streams(Job j, int by_lds, int waves, int waves_per_cu, int multiple)
 {
     const int beside = std::max(1, std::min(by_lds, waves_per_cu / waves));
     auto slowness = [](int w) { return w >= 12 ? 1.f : w >= 8 ? 1.08f : 1.54f; };
@@ -58,13 +58,22 @@ inline Cut cut_streams(const Job &j, int by_lds, int waves, int waves_per_cu, in
     return best;
 }
 
-// V quantizer beside a large table of up to 128 channels: eight waves and two blocks per pass over the table, or four waves and one
-// (`plain`), by the modelled time of their cuts.  Two blocks per pass, of which the model knows nothing, are worth a fifteenth.  Few
-// blocks lie better in many small workgroups (eight waves and four, 256 patterns: 8 x 2048 vectors 17.7 and 12.1 us, 128 x 256 18.3
-// and 17.1; at 136 8 x 1024 12.8 and 9.3), many in large ones (128 x 1024 27.7 and 31.0, 512 x 1024 72.5 and 87.6).  Up to three blocks of
-// a stream are four in pairs (1024 x 192 at 144 patterns of 128 channels 13 % slower).  Over 119 timings (8 to 2048 streams of 3
-// to 256 blocks, 136 to 256 patterns) the choice is 0.4 % slower on average than the better of the two, eight waves throughout 12 %.
-inline bool eight_waves(const Cut &eight, const Cut &plain, int blocks) { return blocks > 3 && eight.cost < 1.07f * plain.cost; }
+// V quantizer beside a large table of up to 128 channels: eight waves that take two blocks per pass over the table, or four waves and one
+// (`plain`), by the modelled time of their cuts.  Two blocks per pass take some four fifths of the time per block (264 x 8320 vectors at 256
+// patterns 0.76 of four waves' time, 128 x 4096 at 136 0.93).  Few blocks lie better in many small workgroups (eight waves and four, 256
+// patterns: 8 x 2048 vectors 17.7 and 12.1 us; at 136 8 x 1024 12.8 and 9.3, 96 x 576 1.09 of the time), many in large ones (256
+// patterns: 128 x 1024 27.7 and 31.0 us, 512 x 1024 72.5 and 87.6; 320 x 1024 at 136 of 96 channels 36 and 43).  Up to three blocks of a stream
+// are four in pairs (1024 x 192 at 144 patterns 13 % slower).  Over 119 timings (8 to 2048 streams of 3 to 256 blocks, 136 to 256
+// patterns) the choice is 0.5 % slower on average than the better of the two, eight waves throughout 12 %.
+inline Cut cut_pairs(Job j, int by_lds, int waves, int waves_per_cu, int multiple)
+{
+    constexpr float kTile = 0.8f;
+    j.staging /= kTile;
+    Cut c = cut_streams(j, by_lds, waves, waves_per_cu, multiple);
+    c.cost *= kTile;
+    return c;
+}
+inline bool eight_waves(const Cut &eight, const Cut &plain, int blocks) { return blocks > 3 && eight.cost < plain.cost; }
 
 inline int tiles_per_wg(int n_tiles, int n_streams)
 {
@@ -80,13 +89,17 @@ inline int tiles_per_wg(int n_tiles, int n_streams)
 // V quantizer beside a small table: two blocks per pass over it, four waves per SIMD either way.  A wave takes its unit of all of its
 // workgroup's blocks, so what counts is how many those are: 1024 streams of 2, 4, 6, 8, 10, 14 and 16 blocks take 1.03, 1.02, 1.01, 0.98,
 // 0.98, 0.95 and 0.96 of one block's time at 64 patterns, 1.01, 0.99, 0.97, 0.96, 0.95, 0.95 and 0.94 at 128, 1.03, 1.04, 1.02, 1.00,
-// 1.01, 0.98 and 0.99 at 16; of 3 and 5 blocks, the last of which is searched twice, 1.16 and 1.13.  Likewise 512 streams of twice as
-// many, which workgroups of half a stream share; of 10, in workgroups of five blocks or else six and four, 1.09.  Not with given
-// indices (256 x 8192 vectors 131 and 134 us); with 4 bits beyond 112 patterns only (1024 x 1024 vectors 0.93 at 120 patterns, 1.08 at 64).
+// 1.01, 0.98 and 0.99 at 16; of 3 and 5 blocks, the last of which is searched twice, 1.16 and 1.13.  Workgroups get an even number of blocks
+// for it, which changes their rounds of 1024: 512 streams of 10 blocks, in five and five or six and four, 1.09; 320 of 16, of which fives make
+// more than a round and sixes do not, 0.76.  Not with given indices (256 x 8192 vectors 131 and 134 us); with 4 bits beyond 112
+// patterns only (1024 x 1024 vectors 0.93 at 120 patterns, 1.08 at 64).
 inline bool two_blocks_per_pass(int blocks, int n_streams, int P, int bits, bool idx_given)
 {
-    const int own = std::min(tiles_per_wg(blocks, n_streams), blocks), enough = P > 64 ? 6 : P > 32 ? 8 : 12;
-    return !idx_given && own >= enough && (own % 2 == 0 || own >= 16) && (bits == 2 || P > 112);
+    if (idx_given || (bits == 4 && P <= 112)) return false;
+    const int t = tiles_per_wg(blocks, n_streams), even = (t + 1) / 2 * 2, own = std::min(t, blocks);
+    auto rounds = [&](int tiles) { return ((int64_t)n_streams * ((blocks + tiles - 1) / tiles) + 1023) / 1024; };
+    const int64_t one = rounds(t) * own, two = rounds(even) * ((std::min(even, blocks) + 1) / 2 * 2);
+    return two < 0.9f * one || (own >= (P > 64 ? 6 : P > 32 ? 8 : 12) && two <= 1.06f * one);
 }
 
 }  // namespace pk

@@ -1193,10 +1193,10 @@ static bool large_table(int P)
 }
 
 // multiple: tiles that the workgroup takes side by side; waves_per_cu: what registers allow
-static Cut cut_job(const QuantArgs &a, int TT, size_t lds, int waves, int waves_per_cu, int multiple)
+static Cut cut_job(const QuantArgs &a, int TT, size_t lds, int waves, int waves_per_cu, int multiple, bool pairs = false)
 {
     const Job j = {a.nq / TT, a.n_streams, a.n_vectors / TT, a.seq_table != nullptr, 256.f / TT};
-    return cut_streams(j, (int)(163840 / lds), waves, waves_per_cu, multiple);
+    return (pairs ? cut_pairs : cut_streams)(j, (int)(163840 / lds), waves, waves_per_cu, multiple);
 }
 
 template <int D, int G, int BITS, int NTA, int NW>
@@ -1306,7 +1306,7 @@ template <int D, int BITS, int NG, int NT, int NW>
 struct VWaves {
     static constexpr int kMultiple = NW / 4 * NT;   // blocks that the workgroup takes at a time
     static size_t lds(int P) { return table_lds_bytes<D>(P) + NW * (size_t)VStaging<D, BITS, NG>::kBytes; }
-    static Cut cut(const QuantArgs &a) { return cut_job(a, 64, lds(a.P), NW, D == 256 ? 12 : 16, kMultiple); }
+    static Cut cut(const QuantArgs &a) { return cut_job(a, 64, lds(a.P), NW, D == 256 ? 12 : 16, kMultiple, NT > 1); }
     static hipError_t launch(const QuantArgs &a, hipStream_t s, int tiles)
     {
         return launch_tiled<quantize_v_kernel<D, BITS, NG, NT, NW>, 64 * NW>(a, 64, lds(a.P), lds(NW == 12 ? 128 : 256), s, tiles);

@@ -24,7 +24,7 @@ int main()
         }
         if (waves == -1) {
             const pk::Job j = {n_tiles, n_streams, tiles, ragged != 0, 4.f};
-            printf("%d 0\\n", pk::eight_waves(pk::cut_streams(j, by_lds, 8, 16, 4), pk::cut_streams(j, multiple, 4, 16, 1), n_tiles));
+            printf("%d 0\\n", pk::eight_waves(pk::cut_pairs(j, by_lds, 8, 16, 4), pk::cut_streams(j, multiple, 4, 16, 1), n_tiles));
             continue;
         }
         const pk::Cut c = pk::cut_streams({n_tiles, n_streams, tiles, ragged != 0, 4.f}, by_lds, waves, waves_per_cu, multiple);
@@ -148,6 +148,6 @@ def test_two_blocks_per_pass_share_evenly(cut):
     def two(blocks, streams, P):
         return cut([(blocks, streams, 0, P, 2, 0, 0, 0)])[0][0]
     for P in (40, 64, 100, 128):
-        assert two(8, 2048, P) and two(14, 1024, P) and two(20, 1024, P) and two(16, 512, P) and two(32, 512, P)
+        assert two(8, 2048, P) and two(14, 1024, P) and two(20, 1024, P) and two(16, 512, P) and two(32, 512, P) and two(16, 320, P)
         assert not any(two(b, n, P) for b, n in ((3, 4096), (5, 4096), (9, 1024), (10, 512), (20, 256), (4, 4096), (16, 256)))
     assert two(6, 1024, 128) and not two(6, 1024, 64) and not two(10, 1024, 16) and two(12, 1024, 16)
