@@ -299,12 +299,16 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t s)
             hipLaunchKernelGGL((decode_tail_kernel<8>), grid, dim3(256), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    // Heads of a KV head together wherever that leaves a workgroup for every CU.  Elsewhere a head at a time: four parts per channel
-    // when a thread would otherwise walk many slots or patterns alone and the (sequence, head) pairs are too few to fill the
-    // chip with 128-thread workgroups; eight when there are hundreds of slots and patterns for a few heads only (28 heads, 130
-    // slots, 256 patterns: 17 -> 13 us).
-    const int slots = a.splits_prefix + a.splits_own + 2;
-    if (r > 1 && N * ((r + 3) / 4) >= 256) {
+    // Heads of a KV head together wherever that leaves a workgroup for every CU, but not few heads with several splits' masses over
+    // large tables: those of a group form them one after the other, a head alone beside the others' (512 heads in pairs, 256 patterns, two splits
+    // 9.4 us together and 8.1 alone; 768 in threes 10.8 and 9.0; 1024 in fours at 200 patterns 10.5 and 9.5; 896 in sevens, four splits, 11.2 and 10.6; but 1056
+    // in fours, more than a round alone, 10.5 and 13.5; 1024 in fours with one split 7.7 and 10.2; of eights with two 9.8 and 10.6).  A head
+    // at a time: four parts per channel when a thread would otherwise walk many slots or patterns alone and the (sequence,
+    // head) pairs are too few to fill the chip with 128-thread workgroups; eight when there are hundreds of slots and patterns
+    // for a few heads only (28 heads, 130 slots, 256 patterns: 17 -> 13 us).
+    const int splits = a.splits_prefix + a.splits_own, slots = splits + 2;
+    const bool masses = a.P > 128 && splits * a.P > (r <= 4 ? 256 : 512) && a.n_seq * a.n_q_heads <= 1024;
+    if (r > 1 && N * ((r + 3) / 4) >= 256 && !masses) {
         const size_t lds = (size_t)(slots + 2 * a.P) * (r == 2 ? 2 : 4) * 4;   // at most 45 KB
         if (r == 2)
             hipLaunchKernelGGL(decode_merge_heads_kernel<2>, dim3(N), dim3(256), lds, s, a);

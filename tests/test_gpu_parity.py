@@ -1435,7 +1435,9 @@ def _attention_of_streams(q, streams, scale):
 
 
 @pytest.mark.parametrize("S,hkv,r,bits,G,P,T,prefix,ragged,rho", [
-    (16, 8, 7, 2, 64, 130, 3000, 0, False, 0.0),    # four own splits, two groups of heads
+    (16, 8, 7, 2, 64, 120, 3000, 0, False, 0.0),    # four own splits, two groups of heads
+    (16, 8, 7, 2, 64, 250, 3000, 0, False, 0.0),    # a large table: a head at a time
+    (32, 8, 4, 2, 64, 200, 2100, 900, True, 0.0),
     (64, 1, 16, 2, 64, 24, 5000, 0, False, 0.8),    # eight own splits, four groups of heads; 256 mass slots per head
     (64, 2, 5, 2, 64, 33, 2100, 900, False, 0.0),   # own splits and the shared prompt's; a group with one head
     (32, 8, 2, 4, 64, 40, 2300, 500, False, 0.0),   # pairs of heads
