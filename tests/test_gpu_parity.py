@@ -1296,7 +1296,7 @@ def test_quantize_groups_of_128_tokens_side_by_side(pk, d, bits, P, groups):
 @pytest.mark.parametrize("d,bits,G,P,rho,T", [
     (128, 2, 64, 200, 0.0, 4416),   # 69 groups per stream
     (128, 4, 32, 130, 0.8, 2112), (96, 2, 32, 250, 0.0, 2112),
-    (128, 2, 64, 40, 0.8, 8256),    # two blocks per table pass on the V side, an odd number of them
+    (128, 2, 64, 40, 0.8, 8256),    # a small table: workgroups of three tiles
     (256, 2, 64, 100, 0.0, 4416), (256, 4, 32, 65, 0.5, 2112),
     (256, 2, 128, 90, 0.0, 1152),   # groups of 128 tokens
     (256, 2, 64, 250, 0.0, 1088),   # eight waves on the V side
@@ -1334,6 +1334,8 @@ def test_quantizers_of_large_jobs(pk, d, bits, G, P, rho, T):
     (256, 4, 32, 120, 0.0, 16, 1088, False),
     (256, 2, 128, 128, 0.0, 32, 1152, False),  # K: two groups of 128 tokens side by side, nine in five turns
     (256, 2, 64, 250, 0.0, 32, 1088, False),   # K: four waves, five turns; V: eight waves, nine turns
+    (128, 2, 64, 40, 0.8, 32, 1856, False),    # V: two blocks per table pass, eight per workgroup, five in the last of a stream
+    (128, 4, 32, 120, 0.0, 32, 1856, False), (96, 2, 32, 100, 0.5, 32, 1856, False), (128, 2, 64, 100, 0.0, 40, 1856, True),
     (128, 2, 64, 250, 0.0, 24, 1984, True), (128, 4, 32, 160, 0.5, 24, 1984, True), (256, 2, 64, 120, 0.0, 24, 1984, True),
     (256, 2, 128, 128, 0.0, 24, 1920, True), (128, 2, 128, 250, 0.0, 24, 1920, True),
 ])
