@@ -43,8 +43,8 @@ namespace {
 // vectors, every one of 64 patterns four times 2714 -> 637 us for the append (binary32 ranking 640), of 200 8847 -> 1656
 // (1658), vectors of spread 0.05 at a distance of 3 1317 -> 705 (591) and 4910 -> 1723 (1646).
 // 1.1 vector operations per channel and pattern instead of the 2.1 of ranking in binary32 (a mixed-precision subtraction and
-// half of a three-operand maximum and minimum), bound by their issue: 256 streams x 8192 vectors, 64 patterns 998 -> 565 us a search alone, 600 to 612 in a traced append
-// per search (485 at the issue rate of the packed operations), at 128 patterns a whole append 4.16 -> 2.53 ms, 128 streams
+// half of a three-operand maximum and minimum), bound by their issue: 256 streams x 8192 vectors, 64 patterns 998 -> 565 us
+// per search alone, 600 to 612 in an append (485 at the issue rate of the packed operations), at 128 patterns a whole append 4.16 -> 2.53 ms, 128 streams
 // of 256 channels 3.32 -> 2.33 ms.  (Scalar loads of 32 channels per wait instead of 64: 650 us, and no gain at 256 channels,
 // whose two waves per SIMD did not cover their latency.)
 // Ruling patterns out by the range over a few channels first (the widest over the table) and evaluating the rest in full
